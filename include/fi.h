@@ -233,9 +233,9 @@ fi_status fi_gemm_inject_batch_noalloc(fi_plan* plan, const fi_fault* d_faults, 
                                        uint32_t policy, fi_trial_result* d_results, float* d_c_out,
                                        void* stream);
 
-/* The same campaign restricted to what a fault can reach: for each trial only the output
- * tiles holding the faulted element (ACC, PRODUCT), its output row (A) or its output column
- * (B) are computed; every other element of a trial equals the fault-free result bit for bit
+/* The same campaign restricted to what a fault can reach: for each trial only the faulted
+ * output element (ACC, PRODUCT), its output row (A) or its output column (B) is computed,
+ * rows and columns of many trials gathered into common matrix operands; every other element of a trial equals the fault-free result bit for bit
  * and must not be flagged: the plan counts, when it is created, the elements of the fault-free
  * result its own detector flags (none under FI_BOUND_ROWCOL / FI_BOUND_GLOBAL with gamma at or
  * above the default; possible under FI_BOUND_EXPONENT, where any |C*_ij| >= 2^17 is flagged, or

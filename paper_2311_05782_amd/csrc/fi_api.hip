@@ -11,6 +11,7 @@
 #include <unordered_set>
 #include <vector>
 
+#include "affected.hpp"
 #include "aux_kernels.hpp"
 #include "fi.h"
 #include "gemm_fi.hpp"
@@ -73,14 +74,14 @@ struct fi_plan {
   uint16_t* Bpad = nullptr;
   uint32_t kshift = 0;
   float* c_star = nullptr;           // [M][N]
-  float* s_abs = nullptr;            // [M][N]
+  float* s_abs = nullptr;            // [M][N], allocated like c_star
   float* kra = nullptr;              // [pad(M)]
   float* cb = nullptr;               // [pad(N)]
   float* scratch = nullptr;          // 4 floats + 4 words: maxima, "operand not finite", clean flags
   float t_global = 0.0f;
   uint32_t n_clean_flagged = 0;      // elements of C* the plan's own detector flags
   int cfg = 0;                       // index into kCfg
-  int cfg_affected = 0;              // index into kCfg for the affected-tiles-only campaign
+  int cfg_affected = 0;              // index into kCfg: the tile shape that the affected-only campaign's batch limit counts
   int mcfg = -1;                     // index into kMulti, or -1: every trial through the single-trial kernel
   int prop_cfg = -1;                 // index into kMulti for the next-layer batch, or -1: single-trial kernel
   int group = 32;                    // trials sharing a tile back to back
@@ -153,6 +154,41 @@ GemmArgs base_args(const fi_plan* p, int cfg = -1) {
   a.c_star_bytes = gold_bytes < (1ull << 32) ? (uint32_t)gold_bytes : 0u;
   a.clocks = p->clocks;
   return a;
+}
+
+// The affected-only campaign: every record by the element kernel, then the operand faults' rows
+// and columns.
+template <int DT>
+fi_status launch_affected(const GemmArgs& a, int n_cus, hipStream_t s) {
+  // A piece is one load instruction per row (512 k) up to K = 512, two beyond.  Three pieces in
+  // flight cover the memory latency of a wave that has its CU to itself; from two waves per CU on
+  // they take each other's LDS, and one piece in flight per wave is the better use of it.
+  const unsigned waves = ((unsigned)a.n_trials + fi::kElemTrials - 1) / fi::kElemTrials;
+  const bool wide = a.K > 512, deep = waves <= 2u * (unsigned)n_cus;
+  const int pieces = wide ? (a.K + 1023) / 1024 : 1;
+  const int bufs = pieces < (deep ? 4 : 2) ? pieces : deep ? 4 : 2;
+  const size_t lds = (size_t)2 * fi::kElemTrials * (wide ? 2080 : 1056) * bufs;
+  if (!wide)
+    hipLaunchKernelGGL((fi::affected_element_kernel<DT, 1, 2>), dim3(waves), dim3(64), lds, s, a);
+  else if (deep)
+    hipLaunchKernelGGL((fi::affected_element_kernel<DT, 2, 4>), dim3(waves), dim3(64), lds, s, a);
+  else
+    hipLaunchKernelGGL((fi::affected_element_kernel<DT, 2, 2>), dim3(waves), dim3(64), lds, s, a);
+  FI_HIP(hipGetLastError());
+  // Workgroups per (chunk, item): one per tile of the other operand while that stays within some
+  // 2048 workgroups; beyond, each walks several tiles, and the workgroups that find no item (all of
+  // them in a batch of accumulator faults) stay few.
+  const int64_t items = ((int64_t)a.n_trials + fi::kRowsChunk - 1) / fi::kRowsChunk * fi::kRowsSlots;
+  const int64_t tiles = ((int64_t)(a.M > a.N ? a.M : a.N) + fi::kRowsX - 1) / fi::kRowsX;
+  int64_t per_slot = (tiles * items + 2047) / 2048;
+  if (per_slot > tiles) per_slot = tiles;
+  const int x_slots = (int)((tiles + per_slot - 1) / per_slot);
+  if (a.c_star_bytes != 0)
+    hipLaunchKernelGGL((fi::affected_rows_kernel<DT, false>), dim3((unsigned)(items * x_slots)), dim3(256), 0, s, a, x_slots);
+  else
+    hipLaunchKernelGGL((fi::affected_rows_kernel<DT, true>), dim3((unsigned)(items * x_slots)), dim3(256), 0, s, a, x_slots);
+  FI_HIP(hipGetLastError());
+  return FI_OK;
 }
 
 // C* with the same kernel family the campaign uses (so that a fault-free tile of a trial is
@@ -262,11 +298,12 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   const fi_plan_desc& d = p->d;
   const size_t mn = (size_t)d.M * d.N;
   // C* is padded to whole 256-row tiles plus one tile width (zeros): the next layer's kernel
-  // reads the tile-shaped neighbourhood of its outputs without clamping rows or columns.
+  // reads the tile-shaped neighbourhood of its outputs without clamping rows or columns, and so
+  // does the affected-only campaign with both arrays (what it reads past the sums is not used).
   const size_t mn_pad = golden_elems(d);
   FI_HIP(hipMalloc(&p->c_star, mn_pad * sizeof(float)));
   FI_HIP(hipMemsetAsync(p->c_star + mn, 0, (mn_pad - mn) * sizeof(float), s));
-  FI_HIP(hipMalloc(&p->s_abs, mn * sizeof(float)));
+  FI_HIP(hipMalloc(&p->s_abs, mn_pad * sizeof(float)));
   FI_HIP(hipMalloc(&p->kra, padded(d.M) * sizeof(float)));
   FI_HIP(hipMalloc(&p->cb, padded(d.N) * sizeof(float)));
   FI_HIP(hipMalloc(&p->scratch, 8 * sizeof(float)));
@@ -526,7 +563,7 @@ fi_status fi_plan_create(const fi_plan_desc* desc, const void* d_A, const void* 
   p->d = d;
   p->d.gamma = gamma;
   p->cfg = pick_cfg(d);
-  p->cfg_affected = d.N <= 64 ? 2 : 1;   // small tiles: only the reached part is of interest
+  p->cfg_affected = d.N <= 64 ? 2 : 1;
   p->mcfg = pick_multi(d);
   // Next-layer launches: on problems below 2^35 multiply-adds the 128 x 128 shape with two
   // workgroups per CU measured faster (one's epilogue runs under the other's MFMAs: 0.75 against
@@ -740,18 +777,13 @@ fi_status fi_gemm_inject_batch_affected(fi_plan* plan, const fi_fault* d_faults,
   const uint64_t blocks = slots * n_trials;
   if (blocks >= (1ull << 31)) return fail(FI_UNSUPPORTED, "tiles x trials exceeds 2^31 workgroups; split the batch");
   hipStream_t s = as_stream(stream);
-  const size_t words = (size_t)n_trials * (sizeof(fi_trial_result) / 4);
-  hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)((words + 255) / 256 > 1024 ? 1024 : (words + 255) / 256)),
-                     dim3(256), 0, s, reinterpret_cast<uint32_t*>(d_results), words, 0u);
-  FI_HIP(hipGetLastError());
   a.n_trials = (int)n_trials;
-  a.group = plan->group;
   a.faults = d_faults;
   a.results = d_results;
   a.policy = (int)policy;
   a.product_check = plan->product_check;
-  FI_HIP(launch_gemm(fi::MODE_AFFECTED, (int)plan->d.dtype, plan->cfg_affected, a, (int)blocks, s));
-  return FI_OK;
+  if (plan->d.dtype == FI_BF16) return launch_affected<FI_BF16>(a, plan->n_cus, s);
+  return launch_affected<FI_FP16>(a, plan->n_cus, s);
 }
 
 fi_status fi_activation_round(uint32_t dtype, const float* d_c, uint64_t n, uint16_t* d_h, void* stream) {

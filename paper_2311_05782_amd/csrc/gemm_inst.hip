@@ -29,7 +29,6 @@ hipError_t FI_NAME(launch_single_d, FI_INST_DT, FI_INST_CFG)(int mode, const Gem
   switch (mode) {
     case MODE_CAMPAIGN: return launch_mode<MODE_CAMPAIGN>(a, n_blocks, s);
     case MODE_GOLDEN: return launch_mode<MODE_GOLDEN>(a, n_blocks, s);
-    case MODE_AFFECTED: return launch_mode<MODE_AFFECTED>(a, n_blocks, s);
     case MODE_PROPAGATE: return launch_mode<MODE_PROPAGATE>(a, n_blocks, s);
   }
   return hipErrorInvalidValue;

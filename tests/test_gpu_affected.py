@@ -1,0 +1,77 @@
+"""The affected-only campaign's element and row / column kernels at the sizes where their indexing
+can go wrong, against the full campaign: the records have to be the same bytes (every element is
+accumulated by the same sequence of matrix steps)."""
+import numpy as np
+import pytest
+
+from oracle import pyoracle as orc
+from paper_2311_05782_amd import fi, workloads as wl
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def _faults(desc, n, seed, kinds):
+    parts = [fi.fi_sample_faults(seed + q, 0, n, desc, k, b)
+             for q, (k, b) in enumerate(((fi.KIND_ALL_ACC, 1), (fi.KIND_ALL_PRODUCT, 4), (fi.KIND_ALL_A, 1), (fi.KIND_ALL_B, 2)))]
+    rng = np.random.default_rng(seed)
+    pick = rng.choice([q for q in range(4) if "eprc"[q] in kinds], size=n)
+    f = np.stack(parts)[pick, np.arange(n)]
+    if "x" in kinds:                                    # no fault, and sites outside the problem
+        f["kind"][rng.integers(0, n, n // 8 + 1)] = fi.SITE_NONE
+        f["row"][rng.integers(0, n, n // 8 + 1)] = 10 ** 7
+        f["kind"][rng.integers(0, n, n // 16 + 1)] = 77
+    return f
+
+
+# (M, N, K, k-block), trials, kinds (e element, p product, r A rows, c B columns, x none / invalid)
+@pytest.mark.parametrize("shape,n,kinds", [
+    ((1, 1, 16, 16), 3, "eprcx"),            # one step, one element; fewer trials than a wave takes
+    ((5, 3, 48, 16), 70, "eprc"),            # K below a k-tile
+    ((130, 70, 528, 16), 513, "eprcx"),      # one trial beyond a chunk; K past one 512-wide piece, ragged k-tile
+    ((257, 131, 1040, 16), 1100, "eprcx"),   # K past one 1024-wide piece; N not a multiple of 4
+    ((300, 515, 192, 32), 640, "r"),         # A rows only: ten items in two chunks
+    ((515, 300, 192, 64), 577, "c"),         # B columns only, a ragged last item
+    ((33, 200, 4096, 64), 2500, "ep"),       # several pieces, shallow buffering (more than two waves a CU)
+    ((64, 72, 5120, 64), 90, "eprx"),        # more pieces than buffers
+])
+@pytest.mark.parametrize("fmt", [orc.FP16, orc.BF16])
+def test_affected_records_equal_the_full_campaigns(shape, n, kinds, fmt):
+    import torch
+    M, N, K, kb = shape
+    Aw, Bw = wl.gaussian(M, N, K, fmt, seed=M + K)
+    wide = np.zeros((M, K + 24), np.uint16)             # rows longer than K, the gap full of NaN
+    wide[:] = 0x7FFF
+    wide[:, :K] = Aw
+    for policy, b_layout, check in ((wl.CORRECT_ZERO, 0, fi.PCHECK_NONE), (wl.CORRECT_RECOMPUTE, 1, fi.PCHECK_RANGE_MAX),
+                                    (wl.CORRECT_NONE, 0, fi.PCHECK_BOUND)):
+        bound = (fi.BOUND_ROWCOL, fi.BOUND_GLOBAL, fi.BOUND_EXPONENT)[policy]
+        B = Bw if b_layout == 0 else np.ascontiguousarray(Bw.T)
+        plan = fi.Plan(fi.plan_desc(M, N, K, kb, fmt, b_layout=b_layout, bound_mode=bound, lda=K + 24),
+                       fi.words_to_device(wide), fi.words_to_device(B))
+        plan.set_product_check(check)
+        faults = _faults(plan.desc, n, seed=n + policy, kinds=kinds)
+        want = gu.gpu_campaign(plan, faults, policy)
+        # records 4 bytes off an 8-byte boundary once: no alignment is promised beyond the words'
+        off = 4 if policy == wl.CORRECT_RECOMPUTE else 0
+        buf = torch.full((n * 48 + off,), 0xAB, dtype=torch.uint8, device="cuda")
+        plan.fi_gemm_inject_batch_affected(fi.to_device(faults), n, policy, buf[off:])
+        got = fi.results_to_host(buf[off:])
+        assert got.tobytes() == want.tobytes(), [(t, faults[t], got[t], want[t]) for t in range(n) if got[t] != want[t]][:3]
+        plan.destroy()
+
+
+def test_affected_records_where_the_fault_free_result_spans_4_gib():
+    # C* addressed with 64 bits (rows kernel), one 16-wide step
+    M, N, K, kb, fmt = 65600, 16400, 16, 16, orc.BF16
+    Aw, Bw = wl.gaussian(M, N, K, fmt, seed=9)
+    plan = gu.make_plan(Aw, Bw, kb, fmt)
+    n = 12
+    faults = _faults(plan.desc, n, seed=4, kinds="eprc")
+    faults["kind"][:4] = (fi.SITE_A, fi.SITE_B, fi.SITE_A, fi.SITE_B)
+    faults["row"][:4], faults["col"][:4] = (M - 1, K - 1, 3, 0), (K - 1, N - 1, 7, 16395)
+    want = gu.gpu_campaign(plan, faults, wl.CORRECT_ZERO)
+    d_r = fi.empty_results(n)
+    plan.fi_gemm_inject_batch_affected(fi.to_device(faults), n, wl.CORRECT_ZERO, d_r)
+    assert fi.results_to_host(d_r).tobytes() == want.tobytes()
+    plan.destroy()
