@@ -317,7 +317,7 @@ def main():
         dms = [a.elapsed_time(b) for a, b in dev]
         dbytes = float(batch) * w.M * w.N * 4
         dgbs = dbytes / (sum(dms) / len(dms) * 1e-3) / 1e9
-        out["detector_roofline"] = {"kernel": "detect_correct_kernel<4> (+ a 1-block counter fill)", "bound": "hbm",
+        out["detector_roofline"] = {"kernel": "detect_correct_kernel<4, true, 4> (+ a 1-block counter fill)", "bound": "hbm",
                                     "achieved": round(dgbs, 1), "peak": 8000.0, "unit": "GB/s",
                                     "frac": round(dgbs / 8000.0, 4), "bytes_per_launch": dbytes,
                                     "kernel_ms_avg": round(sum(dms) / len(dms), 4), "batch": batch,

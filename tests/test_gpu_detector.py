@@ -1,0 +1,55 @@
+"""The standalone detector / corrector at the sizes where its walk over the flat outputs can go wrong:
+narrow and odd rows, vectors that span rows and trials, unaligned buffers, several rounds of its
+grid.  Against the definition, element by element, in binary32 (the threshold's three roundings)."""
+import numpy as np
+import pytest
+
+from oracle import pyoracle as orc
+from paper_2311_05782_amd import fi, workloads as wl
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,batch,shift", [
+    (1, 1, 1, 0), (1, 1, 9000, 0), (3, 2, 700, 0), (5, 3, 401, 0),     # N < 4: element by element
+    (1, 5, 1000, 0), (7, 5, 333, 0), (33, 7, 70, 0),                   # vectors over rows and trials
+    (100, 64, 17, 0), (2, 4, 2049, 0), (257, 1028, 3, 0),              # whole vectors in a row
+    (100, 64, 17, 1), (33, 7, 70, 2), (3, 4099, 2, 3),                 # buffers off alignment
+    (1000, 1003, 40, 0), (1000, 1004, 40, 0),                          # more chunks than workgroups
+])
+@pytest.mark.parametrize("bound", [fi.BOUND_ROWCOL, fi.BOUND_GLOBAL])
+def test_detector_equals_its_definition(M, N, batch, shift, bound):
+    import torch
+    Aw, Bw = wl.gaussian(M, N, 64, orc.BF16, seed=M + N)
+    plan = gu.make_plan(Aw, Bw, 32, orc.BF16, bound_mode=bound)
+    kra = torch.from_numpy(plan.buffer_to_host(fi.BUF_KRA)).cuda()
+    cb = torch.from_numpy(plan.buffer_to_host(fi.BUF_CB)).cuda()
+    cstar = torch.from_numpy(plan.buffer_to_host(fi.BUF_C_STAR)).cuda()
+    gamma = np.float32(1 + 2.0 ** -11)
+    T = (kra[:, None] * cb[None, :]) * float(gamma)
+    if bound == fi.BOUND_GLOBAL:
+        T = torch.full_like(T, float(np.float32(np.float32(kra.max().item()) * np.float32(cb.max().item())) * gamma))
+    g = torch.Generator(device="cuda").manual_seed(M * 31 + N)
+    n = batch * M * N
+    src = T.expand(batch, M, N).reshape(-1) * (torch.rand(n, generator=g, device="cuda") * 1.0005)
+    at = torch.randint(0, n, (max(1, n // 50),), generator=g, device="cuda")
+    src[at] = torch.tensor([float("nan"), float("inf"), -3.0e38, 0.0], device="cuda")[torch.arange(len(at), device="cuda") % 4]
+    src[torch.randint(0, n, (max(1, n // 9),), generator=g, device="cuda")] *= -1
+    want = ~(src.view(batch, M, N).abs() <= T)
+    for policy in (wl.CORRECT_NONE, wl.CORRECT_ZERO, wl.CORRECT_RECOMPUTE):
+        c_buf = torch.full((n + 8,), 7.0, device="cuda")
+        f_buf = torch.full((n + 8,), 9, dtype=torch.uint8, device="cuda")
+        c, fl = c_buf[shift:shift + n], f_buf[shift:shift + n]
+        c.copy_(src)
+        cnt = torch.full((batch,), -1, dtype=torch.int32, device="cuda")
+        plan.fi_detect_correct(c, batch, policy, fl, cnt)
+        assert torch.equal(fl.view(batch, M, N) != 0, want)
+        assert torch.equal(cnt, want.sum(dim=(1, 2), dtype=torch.int32))
+        ref = src.view(batch, M, N)
+        if policy != wl.CORRECT_NONE:
+            ref = torch.where(want, cstar.expand(batch, M, N) if policy == wl.CORRECT_RECOMPUTE else torch.zeros((), device="cuda"), ref)
+        assert torch.equal(c.view(torch.int32), ref.reshape(-1).view(torch.int32))
+        assert bool((c_buf[:shift] == 7).all()) and bool((c_buf[shift + n:] == 7).all())     # nothing outside
+        assert bool((f_buf[:shift] == 9).all()) and bool((f_buf[shift + n:] == 9).all())
+    plan.destroy()
