@@ -16,6 +16,7 @@
 #include "fi.h"
 #include "gemm_fi.hpp"
 #include "gemm_fi_multi.hpp"
+#include "gemm_fi_small.hpp"
 #include "tile_cfg.hpp"
 
 namespace {
@@ -85,6 +86,7 @@ struct fi_plan {
   int mcfg = -1;                     // index into kMulti, or -1: every trial through the single-trial kernel
   int prop_cfg = -1;                 // index into kMulti for the next-layer batch, or -1: single-trial kernel
   int group = 32;                    // trials sharing a tile back to back
+  bool auto_cfg = true;              // no fi_plan_tune has chosen a tile configuration
   int device = 0;
   std::vector<BatchScratch> batch;   // per stream, see BatchScratch
   int n_cus = 8;                     // compute units of the device: grid of the persistent kernel
@@ -93,6 +95,12 @@ struct fi_plan {
 };
 
 namespace {
+
+// Where one wave per (trial, 32 x 32 tile) stops paying, in its MFMA steps per SIMD.  Measured against
+// the multi-trial kernel, accumulator faults: 288 steps (4 trials of 512 x 3072 x 768) 22 : 32 us, 220
+// (32 of 3136 x 64 x 576) 20 : 27, 385 (512 of 300 x 203 x 176) 46 : 41, 512 (8 of 1024^3) 33 : 30;
+// batches with operand faults, two launches there, cross at some 800.
+constexpr double kSmallSteps = 320.0;
 
 using fi::GemmArgs;
 
@@ -136,6 +144,17 @@ int pick_cfg(const fi_plan_desc& d) {
   if (d.N <= 64) return 2;
   if (d.M >= 512 && d.N >= 512) return 0;
   return 1;
+}
+
+// Matrix steps per SIMD if every (trial, 32 x 32 tile) were a wave of gemm_fi_small_kernel.
+double small_steps(const fi_plan* p, uint32_t n_trials) {
+  const fi_plan_desc& d = p->d;
+  return (double)n_trials * ((d.M + 31) / 32) * ((d.N + 31) / 32) * (d.K / 16) / (4.0 * p->n_cus);
+}
+
+// Batches that gemm_fi_small_kernel serves, unless the caller has chosen a tile configuration.
+bool use_small(const fi_plan* p, uint32_t n_trials) {
+  return p->auto_cfg && small_steps(p, n_trials) <= kSmallSteps;
 }
 
 GemmArgs base_args(const fi_plan* p, int cfg = -1) {
@@ -452,6 +471,22 @@ fi_status check_batch_args(const fi_plan* plan, const fi_fault* d_faults, uint32
   return FI_OK;
 }
 
+// As many of a workgroup's four waves on trials of one tile as there are trials: they share most.
+template <int DT>
+void launch_small(const GemmArgs& a, hipStream_t s) {
+  const unsigned n = (unsigned)a.n_trials;
+  auto blocks = [&](unsigned tpw) {
+    const unsigned tiles = 4 / tpw;
+    return dim3((n + tpw - 1) / tpw * (unsigned)a.tiles_m * (((unsigned)a.tiles_n + tiles - 1) / tiles));
+  };
+  if (n >= 3)
+    hipLaunchKernelGGL((fi::gemm_fi_small_kernel<DT, 4, false>), blocks(4), dim3(256), 0, s, a);
+  else if (n == 2)
+    hipLaunchKernelGGL((fi::gemm_fi_small_kernel<DT, 2, false>), blocks(2), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((fi::gemm_fi_small_kernel<DT, 1, false>), blocks(1), dim3(256), 0, s, a);
+}
+
 // One campaign batch: record fill, then either the partition kernel and the two launches of
 // the multi-trial kernel (scratch in `ts`), or one launch of the one-trial kernel.
 fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trials, uint32_t policy,
@@ -494,6 +529,13 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
     g->h_out = d_h_out;
     g->policy = (int)policy;
     g->product_check = plan->product_check;
+  }
+  if (use_small(plan, n_trials)) {
+    a.tiles_m = (a.M + 31) / 32;
+    a.tiles_n = (a.N + 31) / 32;
+    if (plan->d.dtype == FI_BF16) launch_small<FI_BF16>(a, s); else launch_small<FI_FP16>(a, s);
+    FI_HIP(hipGetLastError());
+    return FI_OK;
   }
   if (plan->mcfg < 0) {
     FI_HIP(launch_gemm(fi::MODE_CAMPAIGN, (int)plan->d.dtype, plan->cfg, a, (int)blocks, s));
@@ -659,6 +701,7 @@ fi_status fi_plan_tune(fi_plan* plan, int32_t tile_config, int32_t trial_group, 
   if (trial_group > 0) plan->group = trial_group;
   // C* does not depend on the tile shape: every shape feeds each output element the same
   // sequence of 16-wide MFMA steps in ascending k.
+  if (tile_config >= 0) plan->auto_cfg = false;
   if (tile_config >= kNumCfg) {
     plan->mcfg = tile_config - kNumCfg;
     if (kMulti[plan->mcfg].r == 1) plan->prop_cfg = plan->mcfg;
@@ -723,14 +766,18 @@ fi_status fi_plan_describe(const fi_plan* plan, char* h_buf, uint64_t n) {
   if (!h_buf || n == 0) return fail(FI_INVALID_ARG, "h_buf is NULL or n is 0");
   const TileCfg c = kCfg[plan->cfg];
   const char* dt = plan->d.dtype == FI_BF16 ? "bf16" : "fp16";
+  char small[128] = "";
+  if (use_small(plan, 1))
+    snprintf(small, sizeof(small), "; batches of up to %u trials: gemm_fi_small_kernel<%s, one trial per wave, 32x32>",
+             (unsigned)(kSmallSteps / small_steps(plan, 1)), dt);
   if (plan->mcfg >= 0) {
     const MultiCfg m = kMulti[plan->mcfg];
     if (m.r == 1)
-      snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, one trial per item, %dx%d, %d threads, persistent x%d per CU>", dt,
-               m.bm, m.bn, m.wm * m.wn * 64, m.wgs);
+      snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, one trial per item, %dx%d, %d threads, persistent x%d per CU>%s", dt,
+               m.bm, m.bn, m.wm * m.wn * 64, m.wgs, small);
     else
     snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, R=%d, %dx%d, %d threads, persistent x%d per CU> (a second, "
-             "operand-patching instantiation for operand faults)", dt, m.r, m.bm, m.bn, m.wm * m.wn * 64, m.wgs);
+             "operand-patching instantiation for operand faults)%s", dt, m.r, m.bm, m.bn, m.wm * m.wn * 64, m.wgs, small);
   } else {
     snprintf(h_buf, n, "gemm_fi_kernel<%s, %dx%d, %d threads>", dt, c.bm, c.bn, c.wm * c.wn * 64);
   }
@@ -744,7 +791,7 @@ fi_status fi_gemm_inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t
   TrialScratch ts;
   if (plan->mcfg >= 0) {
     BatchScratch* bs = nullptr;
-    st = batch_scratch(plan, as_stream(stream), n_trials, &bs);
+    st = batch_scratch(plan, as_stream(stream), use_small(plan, n_trials) ? 0 : n_trials, &bs);
     if (st != FI_OK) return st;
     ts.perm = bs->perm; ts.counts = bs->perm + bs->cap; ts.desc = bs->desc;
   }
@@ -761,7 +808,7 @@ fi_status fi_gemm_inject_batch_act(fi_plan* plan, const fi_fault* d_faults, uint
     return fail(FI_UNSUPPORTED, "the fused hand-over is not available with tile_config 2; use fi_gemm_inject_batch "
                 "with d_c_out and fi_activation_round");
   BatchScratch* bs = nullptr;
-  st = batch_scratch(plan, as_stream(stream), n_trials, &bs);
+  st = batch_scratch(plan, as_stream(stream), use_small(plan, n_trials) ? 0 : n_trials, &bs);
   if (st != FI_OK) return st;
   TrialScratch ts;
   ts.perm = bs->perm; ts.counts = bs->perm + bs->cap; ts.desc = bs->desc;

@@ -66,6 +66,7 @@ struct GemmArgs {
   // tile width, so that a tile reaching over the edge of a ragged problem reads allocated memory.
   uint32_t c_star_bytes;
   float* c_out;             // campaign: nullable [n_trials][M][N]; golden: [M][N]
+  float* s_out;             // small golden pass: [M][N] magnitude sums
   // Campaign (multi-trial kernel), nullable: [n_trials][M][N] words of the operand format, the
   // corrected output after ReLU and rounding - the next layer's operand, written by the epilogue
   // instead of an FP32 output that a second kernel would read back.
