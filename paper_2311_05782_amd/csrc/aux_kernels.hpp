@@ -21,76 +21,47 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
   for (; i < n; i += step) p[i] = v;
 }
 
-// out[r] = scale * max_k |x_rk| for the rows of a K-contiguous 16-bit matrix:
-// the operand magnitude maxima behind the detector's bound (Sec. VI-A: the
-// result's magnitude is bounded by the operands').  Magnitudes of finite
-// FP16/BF16 numbers order like their low 15 bits.  One wave per row.
+// Plan statistics in one launch: kra_i = fl32(K * max_k |a_ik|) and cb_j = max_k |b_kj| (B stored
+// [N][ldb], k contiguous), both zero padded, with {max kra, max cb} in maxima[0..1] and "an operand is
+// Inf or NaN" in *nonfinite (all three zero before): the operand magnitude maxima behind the detector's
+// bound (Sec. VI-A: the result's magnitude is bounded by the operands').  Magnitudes of finite
+// FP16/BF16 numbers order like their low 15 bits, non-negative floats like their words.  A wave per
+// row, walking the rows of A and then of B with the grid as stride; one atomic per workgroup and
+// maximum.
 template <int DT>
-__global__ void __launch_bounds__(256) row_absmax_kernel(const uint16_t* __restrict__ X, int rows,
-                                                        int K, uint32_t ld, float scale,
-                                                        float* __restrict__ out,
-                                                        uint32_t* __restrict__ nonfinite) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const uint16_t* x = X + (size_t)row * ld;
-  uint32_t m = 0;
-  for (int c = lane; c < K / 8; c += 64) {
-    u32x4_t v = *reinterpret_cast<const u32x4_t*>(x + c * 8);
+__global__ void __launch_bounds__(256) plan_stats_kernel(const uint16_t* __restrict__ A, uint32_t lda, uint32_t M,
+                                                         uint32_t M_pad, const uint16_t* __restrict__ B, uint32_t ldb,
+                                                         uint32_t N, uint32_t N_pad, uint32_t K, float* __restrict__ kra,
+                                                         float* __restrict__ cb, uint32_t* __restrict__ maxima,
+                                                         uint32_t* __restrict__ nonfinite) {
+  __shared__ uint32_t part[2][4];
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t top[2] = {0, 0};
+  for (uint32_t r = blockIdx.x * 4 + wave; r < M_pad + N_pad; r += gridDim.x * 4) {
+    const bool isA = r < M_pad;
+    const uint32_t row = isA ? r : r - M_pad;
+    float out = 0.0f;
+    if (row < (isA ? M : N)) {
+      const uint16_t* x = isA ? A + (size_t)row * lda : B + (size_t)row * ldb;
+      uint32_t m = 0;
+      for (uint32_t c = lane; c < K / 8; c += 64) {
+        u32x4_t v = *reinterpret_cast<const u32x4_t*>(x + c * 8);
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      uint32_t lo = v[d] & 0x7FFFu, hi = (v[d] >> 16) & 0x7FFFu;
-      m = lo > m ? lo : m;
-      m = hi > m ? hi : m;
+        for (int d = 0; d < 4; ++d) m = max(max(m, v[d] & 0x7FFFu), (v[d] >> 16) & 0x7FFFu);
+      }
+      m = wave_max(m);
+      const uint32_t first_nonfinite = (DT == FI_BF16) ? 0x7F80u : 0x7C00u;
+      if (m >= first_nonfinite && lane == 0) atomicOr(nonfinite, 1u);
+      out = __fmul_rn(isA ? (float)K : 1.0f, decode16<DT>(m));
     }
+    if (lane == 0) (isA ? kra : cb)[row] = out;
+    top[isA ? 0 : 1] = max(top[isA ? 0 : 1], __float_as_uint(out));
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    uint32_t w = __shfl_xor(m, o, 64);
-    m = w > m ? w : m;
-  }
-  if (lane == 0) {
-    const uint32_t first_nonfinite = (DT == FI_BF16) ? 0x7F80u : 0x7C00u;
-    if (m >= first_nonfinite) atomicOr(nonfinite, 1u);
-    out[row] = __fmul_rn(scale, decode16<DT>(m));
-  }
-}
-
-// out[0] = max(v[0..n)) for non-negative floats; one workgroup.
-__global__ void __launch_bounds__(1024) max_reduce_kernel(const float* __restrict__ v, int n,
-                                                         float* __restrict__ out) {
-  __shared__ uint32_t part[16];
-  uint32_t m = 0;
-  for (int i = threadIdx.x; i < n; i += 1024) {
-    uint32_t w = __float_as_uint(v[i]);
-    m = w > m ? w : m;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    uint32_t w = __shfl_xor(m, o, 64);
-    m = w > m ? w : m;
-  }
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+  if (lane == 0) { part[0][wave] = top[0]; part[1][wave] = top[1]; }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < 16; ++i) m = part[i] > m ? part[i] : m;
-    out[0] = __uint_as_float(m);
-  }
-}
-
-// out = |in| for FP16/BF16 words (clear the sign bits), 8 words per thread; `in` has rows of
-// ld_in elements of which the first K are copied, `out` is packed [rows][K].  Used once per plan
-// to build the operands of the magnitude-sum GEMM behind the tolerance.
-__global__ void __launch_bounds__(256) abs16_kernel(const uint16_t* __restrict__ in, uint32_t ld_in,
-                                                   uint16_t* __restrict__ out, int rows, int K) {
-  const size_t per_row = (size_t)K / 8, total = per_row * (size_t)rows;
-  size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  const size_t step = (size_t)gridDim.x * 256;
-  for (; i < total; i += step) {
-    const size_t r = i / per_row, c = i % per_row;
-    u32x4_t v = *reinterpret_cast<const u32x4_t*>(in + r * ld_in + c * 8);
-    v &= 0x7FFF7FFFu;
-    *reinterpret_cast<u32x4_t*>(out + r * (size_t)K + c * 8) = v;
+  if (threadIdx.x < 2) {
+    const uint32_t m = max(max(part[threadIdx.x][0], part[threadIdx.x][1]), max(part[threadIdx.x][2], part[threadIdx.x][3]));
+    if (m) atomicMax(maxima + threadIdx.x, m);
   }
 }
 
@@ -332,15 +303,18 @@ __global__ void __launch_bounds__(256) activation_round_kernel(const float* __re
 // 64-wide k-tiles.  Leading zero products leave an accumulator that starts at +0 at +0 exactly,
 // and the real terms keep their grouping into 16-wide MFMA steps (shift is a multiple of 16),
 // so a GEMM over the padded operands equals the unpadded one bit for bit.
+// Sixteen bytes at a time: rows, shift and K are multiples of eight words.
 __global__ void __launch_bounds__(256) pad_front16_kernel(const uint16_t* __restrict__ src, uint32_t ld,
                                                           uint16_t* __restrict__ dst, uint32_t rows, uint32_t K,
                                                           uint32_t shift) {
-  const uint32_t Kp = K + shift;
-  const size_t n = (size_t)rows * Kp;
+  const uint32_t per_row = (K + shift) / 8, front = shift / 8;
+  const size_t n = (size_t)rows * per_row;
   for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
-    const size_t r = e / Kp;
-    const uint32_t c = (uint32_t)(e % Kp);
-    dst[e] = c < shift ? (uint16_t)0 : src[r * ld + (c - shift)];
+    const size_t r = e / per_row;
+    const uint32_t c = (uint32_t)(e - r * per_row);
+    u32x4_t v = {0u, 0u, 0u, 0u};
+    if (c >= front) v = *reinterpret_cast<const u32x4_t*>(src + r * ld + (size_t)(c - front) * 8);
+    *reinterpret_cast<u32x4_t*>(dst + e * 8) = v;
   }
 }
 

@@ -3,6 +3,7 @@
 // anywhere else.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -58,8 +59,8 @@ using fi::MultiCfg;
 // on different streams may be in flight together and must not share this state.
 struct BatchScratch {
   hipStream_t stream = nullptr;
-  uint32_t* perm = nullptr;   // [cap] trial order + 2 counters behind it
-  uint32_t* desc = nullptr;   // [(cap + 16) * kMultiDescWords]
+  uint32_t* perm = nullptr;   // [cap] trial order + 2 counters behind it; start of the allocation
+  uint32_t* desc = nullptr;   // [(cap + 16) * kMultiDescWords], in the same allocation
   uint32_t cap = 0;
 };
 
@@ -68,6 +69,7 @@ struct fi_plan {
   const uint16_t* A = nullptr;
   const uint16_t* B = nullptr;       // effective [N][ldb] K-contiguous matrix
   uint32_t ldb = 0;
+  void* memory = nullptr;            // one allocation for everything below that the plan owns
   uint16_t* Bt = nullptr;            // plan-owned transposed copy (b_layout 1) or NULL
   // K not a multiple of 64: copies of A and B ([M][K + kshift], [N][K + kshift]) with kshift zeros
   // in front of every row, for the kernels that want whole 64-wide k-tiles; else NULL and 0
@@ -101,6 +103,10 @@ namespace {
 // (32 of 3136 x 64 x 576) 20 : 27, 385 (512 of 300 x 203 x 176) 46 : 41, 512 (8 of 1024^3) 33 : 30;
 // batches with operand faults, two launches there, cross at some 800.
 constexpr double kSmallSteps = 320.0;
+// The same for the plan's fault-free pass, which has two results (see compute_golden).
+constexpr double kSmallSums = 768.0;
+// Exponent field >= 144 <=> NOT (|c| <= largest binary32 below 2^17)
+constexpr float kExponentBound = 131071.9921875f;
 
 using fi::GemmArgs;
 
@@ -210,29 +216,55 @@ fi_status launch_affected(const GemmArgs& a, int n_cus, hipStream_t s) {
   return FI_OK;
 }
 
-// C* with the same kernel family the campaign uses (so that a fault-free tile of a trial is
-// bit-identical to it), and S = |A| x |B| on sign-cleared copies of the operands.
-fi_status compute_golden(fi_plan* p, hipStream_t s, const uint16_t* absA, const uint16_t* absB) {
+// C*, the magnitude sums S and the number of elements of C* that the plan's own detector flags, with
+// the campaigns' sequence of matrix steps (so that a fault-free tile of a trial is bit-identical).
+// Up to kSmallSums steps per SIMD one wave per 32 x 32 tile feeds both results from the same
+// fragments, beyond that the 256 x 256 tiles run twice, the second time with the signs cleared.
+// Whole plan creations, waves : tiles: 512 x 3072 x 768 64 : 122 us (24 workgroups of 256 x 256), 2048^3
+// (512 steps) 113 : 188, 4096 x 4096 x 1024 (1024 steps) 207 : 178, 4096^3 496 : 359.
+fi_status compute_golden(fi_plan* p, hipStream_t s) {
   GemmArgs a = base_args(p);
   a.n_trials = 1; a.group = 1;
   a.c_out = p->c_star;
+  a.n_clean = reinterpret_cast<uint32_t*>(p->scratch + 5);
+  a.maxima = p->d.bound_mode == FI_BOUND_GLOBAL ? p->scratch : nullptr;
+  a.t_global = kExponentBound;          // looked at under FI_BOUND_EXPONENT only
+  if (small_steps(p, 1) <= kSmallSums) {
+    a.s_out = p->s_abs;
+    a.tiles_m = (a.M + 31) / 32;
+    a.tiles_n = (a.N + 31) / 32;
+    const dim3 grid((unsigned)a.tiles_m * (((unsigned)a.tiles_n + 3) / 4));
+    if (p->d.dtype == FI_BF16)
+      hipLaunchKernelGGL((fi::gemm_fi_small_kernel<FI_BF16, 1, true>), grid, dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((fi::gemm_fi_small_kernel<FI_FP16, 1, true>), grid, dim3(256), 0, s, a);
+    FI_HIP(hipGetLastError());
+    return FI_OK;
+  }
+  a.word_mask = 0xFFFFFFFFu;
   FI_HIP(launch_gemm(fi::MODE_GOLDEN, (int)p->d.dtype, p->cfg, a, a.tiles_m * a.tiles_n, s));
-  a.A = absA; a.B = absB;
-  a.lda = a.ldb = (uint32_t)p->d.K;     // the copies are packed
+  a.word_mask = 0x7FFF7FFFu;
   a.c_out = p->s_abs;
+  a.n_clean = nullptr;
   FI_HIP(launch_gemm(fi::MODE_GOLDEN, (int)p->d.dtype, p->cfg, a, a.tiles_m * a.tiles_n, s));
   return FI_OK;
 }
 
+// The architecture of a device does not change: asked once per device (the properties take some
+// hundred microseconds).
 fi_status check_device() {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail(FI_STATE, "no HIP device: %s", hipGetErrorString(e));
+  static std::atomic<uint64_t> known{0};               // bit d: device d is a gfx950
+  const uint64_t bit = dev < 64 ? 1ull << dev : 0ull;
+  if (known.load(std::memory_order_relaxed) & bit) return FI_OK;
   hipDeviceProp_t prop;
   e = hipGetDeviceProperties(&prop, dev);
   if (e != hipSuccess) return fail(FI_STATE, "hipGetDeviceProperties: %s", hipGetErrorString(e));
   if (strncmp(prop.gcnArchName, "gfx950", 6) != 0)
     return fail(FI_STATE, "device %d is %s; this library is built for gfx950 only", dev, prop.gcnArchName);
+  known.fetch_or(bit, std::memory_order_relaxed);
   return FI_OK;
 }
 
@@ -272,18 +304,10 @@ fi_status check_plan(const fi_plan* p) {
 }
 
 void free_plan_buffers(fi_plan* p) {
-  if (p->Bt) (void)hipFree(p->Bt);
-  if (p->Apad) (void)hipFree(p->Apad);
-  if (p->Bpad) (void)hipFree(p->Bpad);
-  if (p->c_star) (void)hipFree(p->c_star);
-  if (p->s_abs) (void)hipFree(p->s_abs);
-  if (p->kra) (void)hipFree(p->kra);
-  if (p->cb) (void)hipFree(p->cb);
-  if (p->scratch) (void)hipFree(p->scratch);
-  for (BatchScratch& b : p->batch) {
+  if (p->memory) (void)hipFree(p->memory);
+  p->memory = nullptr;
+  for (BatchScratch& b : p->batch)
     if (b.perm) (void)hipFree(b.perm);
-    if (b.desc) (void)hipFree(b.desc);
-  }
   p->batch.clear();
 }
 
@@ -302,10 +326,10 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
   }
   if (b->cap < n) {
     if (b->perm) (void)hipFree(b->perm);
-    if (b->desc) (void)hipFree(b->desc);
     b->perm = nullptr; b->desc = nullptr; b->cap = 0;
-    FI_HIP(hipMalloc(&b->perm, ((size_t)n + 2) * sizeof(uint32_t)));
-    FI_HIP(hipMalloc(&b->desc, ((size_t)n + 16) * fi::kMultiDescWords * sizeof(uint32_t)));
+    const size_t head = ((size_t)n + 2 + 63) / 64 * 64;   // desc starts 256-byte aligned
+    FI_HIP(hipMalloc(&b->perm, (head + ((size_t)n + 16) * fi::kMultiDescWords) * sizeof(uint32_t)));
+    b->desc = b->perm + head;
     b->cap = n;
   }
   *out = b;
@@ -358,18 +382,38 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   // reads the tile-shaped neighbourhood of its outputs without clamping rows or columns, and so
   // does the affected-only campaign with both arrays (what it reads past the sums is not used).
   const size_t mn_pad = golden_elems(d);
-  FI_HIP(hipMalloc(&p->c_star, mn_pad * sizeof(float)));
-  FI_HIP(hipMemsetAsync(p->c_star + mn, 0, (mn_pad - mn) * sizeof(float), s));
-  FI_HIP(hipMalloc(&p->s_abs, mn_pad * sizeof(float)));
-  FI_HIP(hipMalloc(&p->kra, padded(d.M) * sizeof(float)));
-  FI_HIP(hipMalloc(&p->cb, padded(d.N) * sizeof(float)));
-  FI_HIP(hipMalloc(&p->scratch, 8 * sizeof(float)));
   p->A = static_cast<const uint16_t*>(d_A);
+  p->kshift = d.K % 64 ? 64 - d.K % 64 : 0;
+  const uint32_t kp = d.K + p->kshift;
+  // One allocation: C* with its padding and the scratch words behind it (zeroed together), S, the
+  // statistics, and the operand copies that this problem needs.
+  size_t bytes = 0;
+  auto place = [&](size_t n) {
+    const size_t at = bytes;
+    bytes += (n + 255) / 256 * 256;
+    return at;
+  };
+  const size_t at_c = place((mn_pad + 8) * sizeof(float)), at_s = place(mn_pad * sizeof(float));
+  const size_t at_kra = place(padded(d.M) * sizeof(float)), at_cb = place(padded(d.N) * sizeof(float));
+  const size_t at_bt = place(d.b_layout ? (size_t)d.N * d.K * sizeof(uint16_t) : 0);
+  const size_t at_ap = place(p->kshift ? (size_t)d.M * kp * sizeof(uint16_t) : 0);
+  const size_t at_bp = place(p->kshift ? (size_t)d.N * kp * sizeof(uint16_t) : 0);
+  FI_HIP(hipMalloc(&p->memory, bytes));
+  uint8_t* const base = static_cast<uint8_t*>(p->memory);
+  p->c_star = reinterpret_cast<float*>(base + at_c);
+  p->scratch = p->c_star + mn_pad;
+  p->s_abs = reinterpret_cast<float*>(base + at_s);
+  p->kra = reinterpret_cast<float*>(base + at_kra);
+  p->cb = reinterpret_cast<float*>(base + at_cb);
+  const size_t zeros = mn_pad + 8 - mn;
+  hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)(zeros < 262144 ? (zeros + 255) / 256 : 1024)), dim3(256), 0, s,
+                     reinterpret_cast<uint32_t*>(p->c_star + mn), zeros, 0u);
+  FI_HIP(hipGetLastError());
   if (d.b_layout == 0) {
     p->B = static_cast<const uint16_t*>(d_B);
     p->ldb = (uint32_t)d.ldb;
   } else {
-    FI_HIP(hipMalloc(&p->Bt, (size_t)d.N * d.K * sizeof(uint16_t)));
+    p->Bt = reinterpret_cast<uint16_t*>(base + at_bt);
     dim3 grid((d.N + 31) / 32, (d.K + 31) / 32);
     hipLaunchKernelGGL(fi::transpose16_kernel, grid, dim3(256), 0, s,
                        static_cast<const uint16_t*>(d_B), (uint32_t)d.ldb, p->Bt, d.K, (int)d.K, (int)d.N);
@@ -377,61 +421,31 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
     p->B = p->Bt;
     p->ldb = d.K;
   }
-  if (d.K % 64 != 0) {
-    p->kshift = 64 - d.K % 64;
-    const uint32_t kp = d.K + p->kshift;
-    FI_HIP(hipMalloc(&p->Apad, (size_t)d.M * kp * sizeof(uint16_t)));
-    FI_HIP(hipMalloc(&p->Bpad, (size_t)d.N * kp * sizeof(uint16_t)));
+  if (p->kshift) {
+    p->Apad = reinterpret_cast<uint16_t*>(base + at_ap);
+    p->Bpad = reinterpret_cast<uint16_t*>(base + at_bp);
     hipLaunchKernelGGL(fi::pad_front16_kernel, dim3(1024), dim3(256), 0, s, p->A, (uint32_t)d.lda, p->Apad, d.M, d.K,
                        p->kshift);
     hipLaunchKernelGGL(fi::pad_front16_kernel, dim3(1024), dim3(256), 0, s, p->B, p->ldb, p->Bpad, d.N, d.K,
                        p->kshift);
     FI_HIP(hipGetLastError());
   }
-  // statistics
-  hipLaunchKernelGGL(fi::fill_u32_kernel, dim3(64), dim3(256), 0, s,
-                     reinterpret_cast<uint32_t*>(p->kra), padded(d.M), 0u);
-  hipLaunchKernelGGL(fi::fill_u32_kernel, dim3(64), dim3(256), 0, s,
-                     reinterpret_cast<uint32_t*>(p->cb), padded(d.N), 0u);
-  hipLaunchKernelGGL(fi::fill_u32_kernel, dim3(1), dim3(64), 0, s,
-                     reinterpret_cast<uint32_t*>(p->scratch), (size_t)8, 0u);
-  uint32_t* bad = reinterpret_cast<uint32_t*>(p->scratch + 4);
-  if (d.dtype == FI_FP16) {
-    hipLaunchKernelGGL(fi::row_absmax_kernel<FI_FP16>, dim3((d.M + 3) / 4), dim3(256), 0, s, p->A, (int)d.M,
-                       (int)d.K, (uint32_t)d.lda, (float)d.K, p->kra, bad);
-    hipLaunchKernelGGL(fi::row_absmax_kernel<FI_FP16>, dim3((d.N + 3) / 4), dim3(256), 0, s, p->B, (int)d.N,
-                       (int)d.K, p->ldb, 1.0f, p->cb, bad);
-  } else {
-    hipLaunchKernelGGL(fi::row_absmax_kernel<FI_BF16>, dim3((d.M + 3) / 4), dim3(256), 0, s, p->A, (int)d.M,
-                       (int)d.K, (uint32_t)d.lda, (float)d.K, p->kra, bad);
-    hipLaunchKernelGGL(fi::row_absmax_kernel<FI_BF16>, dim3((d.N + 3) / 4), dim3(256), 0, s, p->B, (int)d.N,
-                       (int)d.K, p->ldb, 1.0f, p->cb, bad);
-  }
+  uint32_t* const words = reinterpret_cast<uint32_t*>(p->scratch);   // maxima, -, -, "not finite", clean flags
+  const uint32_t rows_a = (uint32_t)padded(d.M), rows_b = (uint32_t)padded(d.N);
+  const dim3 stat_grid((rows_a + rows_b) / 4 < 1024 ? (rows_a + rows_b) / 4 : 1024);
+  if (d.dtype == FI_FP16)
+    hipLaunchKernelGGL(fi::plan_stats_kernel<FI_FP16>, stat_grid, dim3(256), 0, s, p->A, (uint32_t)d.lda, d.M, rows_a,
+                       p->B, p->ldb, d.N, rows_b, d.K, p->kra, p->cb, words, words + 4);
+  else
+    hipLaunchKernelGGL(fi::plan_stats_kernel<FI_BF16>, stat_grid, dim3(256), 0, s, p->A, (uint32_t)d.lda, d.M, rows_a,
+                       p->B, p->ldb, d.N, rows_b, d.K, p->kra, p->cb, words, words + 4);
   FI_HIP(hipGetLastError());
-  hipLaunchKernelGGL(fi::max_reduce_kernel, dim3(1), dim3(1024), 0, s, p->kra, (int)d.M, p->scratch + 0);
-  hipLaunchKernelGGL(fi::max_reduce_kernel, dim3(1), dim3(1024), 0, s, p->cb, (int)d.N, p->scratch + 1);
-  FI_HIP(hipGetLastError());
-  // sign-cleared operand copies for the magnitude-sum GEMM; freed once the stream has drained
-  uint16_t *absA = nullptr, *absB = nullptr;
-  const size_t nA = (size_t)d.M * d.K, nB = (size_t)d.N * d.K;
-  hipError_t e1 = hipMalloc(&absA, nA * sizeof(uint16_t));
-  hipError_t e2 = hipMalloc(&absB, nB * sizeof(uint16_t));
-  fi_status st = FI_OK;
-  if (e1 != hipSuccess || e2 != hipSuccess) {
-    st = fail(FI_OOM, "device allocation for the magnitude operands failed");
-  } else {
-    hipLaunchKernelGGL(fi::abs16_kernel, dim3(2048), dim3(256), 0, s, p->A, (uint32_t)d.lda, absA, (int)d.M, (int)d.K);
-    hipLaunchKernelGGL(fi::abs16_kernel, dim3(2048), dim3(256), 0, s, p->B, p->ldb, absB, (int)d.N, (int)d.K);
-    st = compute_golden(p, s, absA, absB);
-  }
-  hipError_t es = hipStreamSynchronize(s);
-  if (absA) (void)hipFree(absA);
-  if (absB) (void)hipFree(absB);
+  fi_status st = compute_golden(p, s);
   if (st != FI_OK) return st;
-  if (es != hipSuccess) return fail(FI_DEVICE, "plan kernels failed: %s", hipGetErrorString(es));
   float host[8];
   FI_HIP(hipMemcpyAsync(host, p->scratch, sizeof(host), hipMemcpyDeviceToHost, s));
-  FI_HIP(hipStreamSynchronize(s));
+  hipError_t es = hipStreamSynchronize(s);
+  if (es != hipSuccess) return fail(FI_DEVICE, "plan kernels failed: %s", hipGetErrorString(es));
   uint32_t badw;
   memcpy(&badw, &host[4], 4);
   if (badw) return fail(FI_INVALID_ARG, "A or B holds an Inf or NaN: the magnitude bound is undefined");
@@ -439,17 +453,11 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   volatile float t = host[0] * host[1];
   t = t * d.gamma;
   p->t_global = t;
-  // Exponent field >= 144 <=> NOT (|c| <= largest binary32 below 2^17)
-  if (d.bound_mode == FI_BOUND_EXPONENT) p->t_global = 131071.9921875f;
+  if (d.bound_mode == FI_BOUND_EXPONENT) p->t_global = kExponentBound;
   // How many elements of the fault-free result the plan's own detector flags (none under the
   // operand-derived bounds with gamma at or above the default; possible under the exponent-only
-  // bound or a caller's smaller gamma).  The affected-tiles-only campaign relies on it being 0.
-  {
-    uint32_t* n_clean = reinterpret_cast<uint32_t*>(p->scratch + 5);
-    FI_HIP(launch_detect(p, p->c_star, 1, FI_CORRECT_NONE, nullptr, n_clean, s));
-    FI_HIP(hipMemcpyAsync(&p->n_clean_flagged, n_clean, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    FI_HIP(hipStreamSynchronize(s));
-  }
+  // bound or a caller's smaller gamma).  The affected-only campaign relies on it being 0.
+  memcpy(&p->n_clean_flagged, &host[5], 4);
   return FI_OK;
 }
 

@@ -67,6 +67,13 @@ struct GemmArgs {
   uint32_t c_star_bytes;
   float* c_out;             // campaign: nullable [n_trials][M][N]; golden: [M][N]
   float* s_out;             // small golden pass: [M][N] magnitude sums
+  // golden pass: what operand words are masked with (all bits, or all but the signs: then c_out
+  // receives the magnitude sums), and where the elements that the plan's own detector flags are
+  // counted (nullable); maxima: {max kra, max cb} on the device, the source of t_global under
+  // FI_BOUND_GLOBAL, which the host does not know yet (else nullptr)
+  uint32_t word_mask;
+  uint32_t* n_clean;
+  const float* maxima;
   // Campaign (multi-trial kernel), nullable: [n_trials][M][N] words of the operand format, the
   // corrected output after ReLU and rounding - the next layer's operand, written by the epilogue
   // instead of an FP32 output that a second kernel would read back.
@@ -248,6 +255,11 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 // |x| with NaN and Inf mapped to +Inf, as an ordered non-negative word.
 __device__ __forceinline__ float finite_or_inf(float d) {
   return (d <= 3.4028234e38f) ? d : __uint_as_float(0x7F800000u);
+}
+
+// The global threshold as a golden pass sees it.
+__device__ __forceinline__ float golden_t_global(const GemmArgs& p) {
+  return p.maxima ? __fmul_rn(__fmul_rn(p.maxima[0], p.maxima[1]), p.gamma) : p.t_global;
 }
 
 // Workgroup id -> (tile, item), item = a trial or a group of trials.  Workgroups are dealt
@@ -484,6 +496,12 @@ __global__ void __launch_bounds__(WM* WN * 64) gemm_fi_kernel(const GemmArgs p) 
     for (int i = 0; i < TM; ++i) f.a[i] = *reinterpret_cast<const u32x4*>(s + a_rd + i * 4096 + slot);
 #pragma unroll
     for (int j = 0; j < TN; ++j) f.b[j] = *reinterpret_cast<const u32x4*>(s + b_rd + j * 4096 + slot);
+    if constexpr (MODE == MODE_GOLDEN) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) f.a[i] &= p.word_mask;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) f.b[j] &= p.word_mask;
+    }
   };
   // One MFMA step; `mid` (the fragment read for the next step) is issued after the first two
   // MFMAs, so it lands under the rest of the burst and is never waited for right after its issue.
@@ -577,15 +595,25 @@ __global__ void __launch_bounds__(WM* WN * 64) gemm_fi_kernel(const GemmArgs p) 
   const int row_base = m0 + wm * WTM + 4 * lhi;       // + 32*i + 8*q + e
   const int col_base = n0 + wn * WTN + l32;           // + 32*j
   if constexpr (MODE == MODE_GOLDEN) {
+    uint32_t n_clean = 0;
+    const float t_all = p.n_clean ? golden_t_global(p) : 0.0f;
     static_for<TM * TN>([&](auto tt) {
       constexpr int i = tt / TN, j = tt % TN;
       const f32x16 t = acc[i][j];
+      const int col = col_base + 32 * j;
+      const float cbj = p.n_clean ? p.cb[col] : 0.0f;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3), col = col_base + 32 * j;
-        if (row < p.M && col < p.N) p.c_out[(size_t)row * p.N + col] = t[v];
+        const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3);
+        const bool in = row < p.M && col < p.N;
+        if (in) p.c_out[(size_t)row * p.N + col] = t[v];
+        if (p.n_clean) {
+          const float th = p.bound_global ? t_all : __fmul_rn(__fmul_rn(p.kra[row], cbj), p.gamma);
+          n_clean += (uint32_t)__builtin_popcountll(__ballot(in && !(fabsf(t[v]) <= th)));
+        }
       }
     });
+    if (n_clean != 0 && lane == 0) atomicAdd(p.n_clean, n_clean);
     return;
   } else {
     uint32_t n_flag = 0;                                 // wave-uniform: popcounts of lane masks

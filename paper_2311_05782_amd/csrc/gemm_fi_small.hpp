@@ -112,9 +112,9 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
 
   // the epilogue's inputs, requested before anything is waited for
   const int row_base = m0 + 4 * lhi, col = n0 + l32;      // rows + 8*q + e; the vectors are zero padded
-  f32x4 kra4[4];
+  f32x4 kra4[4] = {};
   float cbj = 0.0f;
-  if constexpr (!SUMS) {
+  if (works) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) kra4[q] = *reinterpret_cast<const f32x4*>(p.kra + row_base + 8 * q);
     cbj = p.cb[col];
@@ -231,14 +231,21 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
 
   const bool ragged = m0 + 32 > p.M || n0 + 32 > p.N;
   if constexpr (SUMS) {
+    // the elements of the fault-free result that the plan's own detector flags are counted
+    uint32_t n_clean = 0;
+    const float t_all = golden_t_global(p);
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int row = row_base + 8 * (v >> 2) + (v & 3);
-      if (!ragged || (row < p.M && col < p.N)) {
+      const bool in = row < p.M && col < p.N;
+      const float th = p.bound_global ? t_all : __fmul_rn(__fmul_rn(kra4[v >> 2][v & 3], cbj), p.gamma);
+      if (in) {
         p.c_out[(size_t)row * p.N + col] = acc[v];
         p.s_out[(size_t)row * p.N + col] = sum[v];
       }
+      n_clean += (uint32_t)__builtin_popcountll(__ballot(in && !(fabsf(acc[v]) <= th)));
     }
+    if (n_clean != 0 && lane == 0) atomicAdd(p.n_clean, n_clean);
     return;
   } else {
     // ---- detector on every element; those outside the problem (copies of the last row or column)
