@@ -103,6 +103,11 @@ namespace {
 // (32 of 3136 x 64 x 576) 20 : 27, 385 (512 of 300 x 203 x 176) 46 : 41, 512 (8 of 1024^3) 33 : 30;
 // batches with operand faults, two launches there, cross at some 800.
 constexpr double kSmallSteps = 320.0;
+// MFMA steps of one trial up to which its workgroup, on one CU, does not take longer than the launch it
+// saves: 64 trials of 128^3 (128 steps) 8.8 : 10.6 us, of 128 x 128 x 512 13.3 : 11.8; with outputs to
+// store 33 x 59 x 48 (12 steps) 9.4 : 10.7, 128^3 11.6 : 11.1.  Not beyond a trial per CU: 256 of 33 x 59 x
+// 48 7.6 : 10.6, 512 12.0 : 10.5.
+constexpr uint32_t kTrialSteps = 128, kTrialStepsOut = 16;
 // The same for the plan's fault-free pass, which has two results (see compute_golden).
 constexpr double kSmallSums = 768.0;
 // Exponent field >= 144 <=> NOT (|c| <= largest binary32 below 2^17)
@@ -161,6 +166,14 @@ double small_steps(const fi_plan* p, uint32_t n_trials) {
 // Batches that gemm_fi_small_kernel serves, unless the caller has chosen a tile configuration.
 bool use_small(const fi_plan* p, uint32_t n_trials) {
   return p->auto_cfg && small_steps(p, n_trials) <= kSmallSteps;
+}
+
+// Batches that gemm_fi_trial_kernel serves.
+bool use_trial(const fi_plan* p, uint32_t n_trials, bool outputs) {
+  const fi_plan_desc& d = p->d;
+  if (!use_small(p, n_trials) || n_trials > (uint32_t)p->n_cus || d.M > 512 || d.N > 512) return false;
+  const uint32_t tiles = ((d.M + 31) / 32) * ((d.N + 31) / 32);
+  return tiles <= 16 && tiles * (d.K / 16) <= (outputs ? kTrialStepsOut : kTrialSteps);
 }
 
 GemmArgs base_args(const fi_plan* p, int cfg = -1) {
@@ -524,10 +537,6 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
     const uint64_t cus = (uint64_t)(plan->n_cus / 8 * 8) * (uint64_t)mc.wgs;
     mblocks = items < cus ? items : cus;
   }
-  const size_t words = (size_t)n_trials * (sizeof(fi_trial_result) / 4);
-  hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)((words + 255) / 256 > 1024 ? 1024 : (words + 255) / 256)),
-                     dim3(256), 0, s, reinterpret_cast<uint32_t*>(d_results), words, 0u);
-  FI_HIP(hipGetLastError());
   for (GemmArgs* g : {&a, &m}) {
     g->n_trials = (int)n_trials;
     g->group = plan->group;
@@ -538,6 +547,21 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
     g->policy = (int)policy;
     g->product_check = plan->product_check;
   }
+  if (use_trial(plan, n_trials, d_c_out || d_h_out)) {
+    a.tiles_m = (a.M + 31) / 32;
+    a.tiles_n = (a.N + 31) / 32;
+    const size_t lds = (size_t)2 * (a.tiles_m + a.tiles_n) * 32 * 128;
+    if (plan->d.dtype == FI_BF16)
+      hipLaunchKernelGGL((fi::gemm_fi_trial_kernel<FI_BF16>), dim3(n_trials), dim3(1024), lds, s, a);
+    else
+      hipLaunchKernelGGL((fi::gemm_fi_trial_kernel<FI_FP16>), dim3(n_trials), dim3(1024), lds, s, a);
+    FI_HIP(hipGetLastError());
+    return FI_OK;
+  }
+  const size_t words = (size_t)n_trials * (sizeof(fi_trial_result) / 4);
+  hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)((words + 255) / 256 > 1024 ? 1024 : (words + 255) / 256)),
+                     dim3(256), 0, s, reinterpret_cast<uint32_t*>(d_results), words, 0u);
+  FI_HIP(hipGetLastError());
   if (use_small(plan, n_trials)) {
     a.tiles_m = (a.M + 31) / 32;
     a.tiles_n = (a.N + 31) / 32;

@@ -21,12 +21,204 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "fi.h"
 #include "gemm_fi.hpp"
 
 namespace fi {
+
+// A trial's fault (uniform in its wave): its coordinates, the 16-wide step that consumes the faulted
+// operand word (its k is fk) or at whose end the accumulator changes, and a product-term fault's terms.
+struct TrialFault {
+  uint32_t kind, row, col, mask;
+  int event, fk;
+  bool valid;
+  float re, re_err;
+  bool fired;
+  __device__ __forceinline__ bool operand() const { return kind == FI_SITE_A || kind == FI_SITE_B; }
+  __device__ __forceinline__ bool isA() const { return kind == FI_SITE_A; }
+  // the fault reaches an element of the 32 x 32 tile at (m0, n0)
+  __device__ __forceinline__ bool reaches(int m0, int n0) const {
+    const bool in_rows = (int)row >= m0 && (int)row < m0 + 32, in_cols = (int)col >= n0 && (int)col < n0 + 32;
+    return kind == FI_SITE_NONE ? false : kind == FI_SITE_A ? in_rows : kind == FI_SITE_B ? in_cols : in_rows && in_cols;
+  }
+};
+
+__device__ __forceinline__ TrialFault decode_fault(const GemmArgs& p, int trial) {
+  const fi_fault f = p.faults[trial];
+  TrialFault t;
+  t.kind = f.kind; t.row = f.row; t.col = f.col; t.mask = f.xor_mask;
+  t.valid = true; t.event = -1; t.fk = 0; t.re = t.re_err = 0.0f; t.fired = false;
+  if (f.kind == FI_SITE_ACC) {
+    t.valid = f.row < (uint32_t)p.M && f.col < (uint32_t)p.N && f.kblock < (uint32_t)(p.K / p.kb);
+    t.event = (int)((f.kblock + 1) * (uint32_t)p.kb) / 16 - 1;
+  } else if (f.kind == FI_SITE_PRODUCT) {
+    t.valid = f.row < (uint32_t)p.M && f.col < (uint32_t)p.N && f.kblock < (uint32_t)p.K;
+    t.fk = (int)f.kblock;
+  } else if (f.kind == FI_SITE_A) {
+    t.valid = f.row < (uint32_t)p.M && f.col < (uint32_t)p.K;
+    t.fk = (int)f.col;
+  } else if (f.kind == FI_SITE_B) {
+    t.valid = f.row < (uint32_t)p.K && f.col < (uint32_t)p.N;
+    t.fk = (int)f.row;
+  } else {
+    t.valid = f.kind == FI_SITE_NONE;
+  }
+  if (f.kind != FI_SITE_ACC) t.event = t.fk / 16;
+  if (!t.valid) t.kind = FI_SITE_NONE;
+  if (t.kind == FI_SITE_NONE) t.event = -1;
+  return t;
+}
+
+// The terms of a product-term fault, by a wave that owns its element.
+template <int DT>
+__device__ __forceinline__ void fetch_product_terms(TrialFault& t, const GemmArgs& p) {
+  product_fault_terms<DT>(p.A[(size_t)t.row * p.lda + t.fk], p.B[(size_t)t.col * p.ldb + t.fk], t.mask, p.product_check,
+                          t.re, t.re_err, t.fired);
+}
+
+// One 16-wide step at whose operands or end the fault strikes, in a tile that it reaches.
+template <int DT>
+__device__ __forceinline__ f32x16 faulty_step(const TrialFault& t, u32x4 a, u32x4 b, f32x16 acc, int m0, int n0, int lane,
+                                              uint32_t& before, uint32_t& after) {
+  if (t.operand()) {
+    // the lane that holds the word (row or column l % 32, k half l / 32), two words per register
+    const int l = (int)((t.isA() ? t.row - (uint32_t)m0 : t.col - (uint32_t)n0) & 31u) + 32 * ((t.fk >> 3) & 1);
+    const uint32_t x = lane == l ? (t.mask & 0xFFFFu) << (16 * (t.fk & 1)) : 0u;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t xr = r == ((t.fk & 7) >> 1) ? x : 0u;
+      a[r] ^= t.isA() ? xr : 0u;
+      b[r] ^= t.isA() ? 0u : xr;
+    }
+    return mfma_32x32x16<DT>(a, b, acc);
+  }
+  acc = mfma_32x32x16<DT>(a, b, acc);
+  const int ri = (int)t.row - m0, rj = (int)t.col - n0;   // inside the tile
+  const int sel_v = 4 * (ri >> 3) + (ri & 3), sel_lane = rj + 32 * ((ri >> 2) & 1);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const uint32_t word = __float_as_uint(acc[v]);
+    const uint32_t nw = t.kind == FI_SITE_PRODUCT ? __float_as_uint(write_back(acc[v], t.re, t.re_err)) : (word ^ t.mask);
+    before = v == sel_v ? word : before;                  // meaningful in lane sel_lane
+    after = v == sel_v ? nw : after;
+    acc[v] = __uint_as_float((v == sel_v && lane == sel_lane) ? nw : word);
+  }
+  return acc;
+}
+
+// Counts of what a fault changed in one tile that it reaches: one element, one row (it lies in one
+// register and half-wave) or one column (gathered into lanes 0 .. 31, row k to lane k).  Counters are
+// uniform, maxima per lane.
+struct TileDeviation {
+  uint32_t n_bit, n_pre, n_post, n_bT, n_btau;
+  float mx_pre, mx_post;
+};
+__device__ __forceinline__ TileDeviation tile_deviation(const TrialFault& t, const GemmArgs& p, const f32x16& acc,
+                                                        const f32x16& T, int m0, int n0, int lane) {
+  const int l32 = lane & 31, lhi = lane >> 5, col = n0 + l32;
+  float c = acc[0], th = T[0];
+  int row, cc_col;
+  bool act;
+  if (t.kind != FI_SITE_B) {
+    const int ri = ((int)t.row - m0) & 31;
+    const int sel_v = 4 * (ri >> 3) + (ri & 3), sel_hi = (ri >> 2) & 1;
+#pragma unroll
+    for (int v = 1; v < 16; ++v) {
+      c = v == sel_v ? acc[v] : c;
+      th = v == sel_v ? T[v] : th;
+    }
+    row = (int)t.row;
+    cc_col = min(col, p.N - 1);
+    act = lhi == sel_hi && col < p.N && (t.isA() || col == (int)t.col);
+  } else {
+    const int sel = (int)t.col - n0;
+    int x = 0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int word = (int)__float_as_uint(acc[v]);
+      const int k0 = 8 * (v >> 2) + (v & 3);
+      // read with all lanes active, outside the selects
+      const int lo = __builtin_amdgcn_readlane(word, sel), hi = __builtin_amdgcn_readlane(word, sel + 32);
+      x = lane == k0 ? lo : x;
+      x = lane == k0 + 4 ? hi : x;
+    }
+    c = __uint_as_float((uint32_t)x);
+    act = lane < 32 && m0 + lane < p.M;
+    row = min(m0 + l32, p.M - 1);
+    cc_col = (int)t.col;
+    th = p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(p.kra[row], p.cb[t.col]), p.gamma);
+  }
+  const size_t idx = (size_t)row * (size_t)p.N + (size_t)cc_col;
+  const float cs = p.c_star[idx], tau = p.s_abs[idx] * 0.000244140625f;   // 2^-12, exact scaling
+  const bool flag = !(fabsf(c) <= th);
+  float fixed = c;
+  if (flag && p.policy == FI_CORRECT_ZERO) fixed = 0.0f;
+  if (flag && p.policy == FI_CORRECT_RECOMPUTE) fixed = cs;
+  const float dpre = finite_or_inf(fabsf(c - cs)), dpost = finite_or_inf(fabsf(fixed - cs));
+  const float band = fmaxf(2.0f * tau, th * 0.015625f), mag = fabsf(c);
+  const uint64_t am = __ballot(act), changed = __ballot(__float_as_uint(c) != __float_as_uint(cs)) & am;
+  TileDeviation d;
+  d.n_bit = (uint32_t)__builtin_popcountll(changed);
+  d.n_pre = (uint32_t)__builtin_popcountll(__ballot(!(dpre <= tau)) & am);
+  d.n_post = (uint32_t)__builtin_popcountll(__ballot(!(dpost <= tau)) & am);
+  d.n_bT = (uint32_t)__builtin_popcountll(changed & __ballot(mag <= 3.4028234e38f) & __ballot(fabsf(mag - th) <= band));
+  d.n_btau = (uint32_t)__builtin_popcountll(changed & __ballot(tau > 0.0f) & __ballot(dpre >= 0.5f * tau) &
+                                            __ballot(dpre <= 2.0f * tau));
+  d.mx_pre = act ? dpre : 0.0f;
+  d.mx_post = act ? dpost : 0.0f;
+  return d;
+}
+
+// Detector on a tile's elements (those outside the problem, copies of the last row or column, get
+// T = +Inf and the value 0) and its outputs, corrected where flagged, in FP32 or in the operand
+// format.  Returns the number of flagged elements (uniform).
+template <int DT>
+__device__ __forceinline__ uint32_t detect_tile(const GemmArgs& p, f32x16& acc, f32x16& T, const f32x4* kra4, float cbj,
+                                                int trial, int m0, int n0, int lane) {
+  const int row_base = m0 + 4 * (lane >> 5), col = n0 + (lane & 31);
+  const bool ragged = m0 + 32 > p.M || n0 + 32 > p.N;
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    T[v] = p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(kra4[v >> 2][v & 3], cbj), p.gamma);
+  if (ragged) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const bool in = row_base + 8 * (v >> 2) + (v & 3) < p.M && col < p.N;
+      T[v] = in ? T[v] : __builtin_inff();
+      acc[v] = in ? acc[v] : 0.0f;
+    }
+  }
+  uint64_t any = 0;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) any |= __ballot(!(fabsf(acc[v]) <= T[v]));
+  uint32_t n_flag = 0;
+  if (any != 0) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) n_flag += (uint32_t)__builtin_popcountll(__ballot(!(fabsf(acc[v]) <= T[v])));
+  }
+  if (p.c_out || p.h_out) {
+    f32x16 out = acc;
+    if (any != 0 && p.policy != FI_CORRECT_NONE) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (!(fabsf(out[v]) <= T[v]))
+          out[v] = p.policy == FI_CORRECT_ZERO ? 0.0f : p.c_star[(size_t)(row_base + 8 * (v >> 2) + (v & 3)) * p.N + col];
+    }
+    const size_t out0 = (size_t)trial * (size_t)p.M * (size_t)p.N + col;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int row = row_base + 8 * (v >> 2) + (v & 3);
+      if (!ragged || (row < p.M && col < p.N)) {
+        if (p.c_out) __builtin_nontemporal_store(out[v], p.c_out + out0 + (size_t)row * p.N);
+        if (p.h_out) __builtin_nontemporal_store((uint16_t)relu_round16<DT>(out[v]), p.h_out + out0 + (size_t)row * p.N);
+      }
+    }
+  }
+  return n_flag;
+}
 
 // SUMS: the plan's fault-free pass; C* to p.c_out and the magnitude sums, from the same fragments
 // with the sign bits cleared, to p.s_out.  Else a campaign (p.tiles_m, p.tiles_n in 32 x 32 tiles).
@@ -58,57 +250,17 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
   };
   clock(0);
 
-  // ---- this wave's fault (all uniform)
-  uint32_t fkind = FI_SITE_NONE, frow = 0, fcol = 0, fmask = 0;
-  int event = -1;                                         // step that consumes a faulted word, or ends at an accumulator fault
-  int fk = 0;
-  bool owns = false;                                      // the fault reaches an element of this tile
-  float re = 0.0f, re_err = 0.0f;
-  bool fired = false;
+  // ---- this wave's fault
+  TrialFault f = {};
+  f.kind = FI_SITE_NONE; f.event = -1;
+  bool owns = false;                                      // it reaches an element of this tile
   if constexpr (!SUMS) {
-    const fi_fault f = p.faults[trial];
-    fkind = f.kind; frow = f.row; fcol = f.col; fmask = f.xor_mask;
-    bool valid = true;
-    if (fkind == FI_SITE_ACC) valid = frow < (uint32_t)p.M && fcol < (uint32_t)p.N && f.kblock < (uint32_t)(p.K / p.kb);
-    else if (fkind == FI_SITE_PRODUCT) valid = frow < (uint32_t)p.M && fcol < (uint32_t)p.N && f.kblock < (uint32_t)p.K;
-    else if (fkind == FI_SITE_A) valid = frow < (uint32_t)p.M && fcol < (uint32_t)p.K;
-    else if (fkind == FI_SITE_B) valid = frow < (uint32_t)p.K && fcol < (uint32_t)p.N;
-    else if (fkind != FI_SITE_NONE) valid = false;
-    if (!valid) {
-      if (works && m0 == 0 && n0 == 0 && lane == 0) p.results[trial].status = 1;
-      fkind = FI_SITE_NONE;
-    }
-    const bool in_rows = (int)frow >= m0 && (int)frow < m0 + 32, in_cols = (int)fcol >= n0 && (int)fcol < n0 + 32;
-    if (fkind == FI_SITE_ACC) {
-      owns = in_rows && in_cols;
-      event = (int)((f.kblock + 1) * (uint32_t)p.kb) / 16 - 1;
-    } else if (fkind == FI_SITE_PRODUCT) {
-      owns = in_rows && in_cols;
-      fk = (int)f.kblock;
-      event = fk / 16;
-      if (owns)
-        product_fault_terms<DT>(p.A[(size_t)frow * p.lda + fk], p.B[(size_t)fcol * p.ldb + fk], fmask, p.product_check,
-                                re, re_err, fired);
-    } else if (fkind == FI_SITE_A) {
-      owns = in_rows;
-      fk = (int)fcol;
-      event = fk / 16;
-    } else if (fkind == FI_SITE_B) {
-      owns = in_cols;
-      fk = (int)frow;
-      event = fk / 16;
-    }
-    owns = owns && works;
-    if (!owns) event = -1;
+    f = decode_fault(p, trial);
+    owns = works && f.reaches(m0, n0);
+    if (!f.valid && works && m0 == 0 && n0 == 0 && lane == 0) p.results[trial].status = 1;
+    if (owns && f.kind == FI_SITE_PRODUCT) fetch_product_terms<DT>(f, p);
   }
-  const bool operand = fkind == FI_SITE_A || fkind == FI_SITE_B, isA = fkind == FI_SITE_A;
-  // an operand fault's word: the lane that holds it and the XOR in the fragment's register sel_w
-  const int sel_w = (fk & 7) >> 1;
-  const uint32_t x_mine = operand && lane == (int)((isA ? frow - (uint32_t)m0 : fcol - (uint32_t)n0) & 31u) + 32 * ((fk >> 3) & 1)
-                              ? (fmask & 0xFFFFu) << (16 * (fk & 1)) : 0u;
-  // the faulted element's row inside the tile as register and half-wave
-  const int ri = (int)(frow - (uint32_t)m0) & 31;
-  const int sel_v = 4 * (ri >> 3) + (ri & 3), sel_hi = (ri >> 2) & 1;
+  const int event = owns ? f.event : -1;
 
   // the epilogue's inputs, requested before anything is waited for
   const int row_base = m0 + 4 * lhi, col = n0 + l32;      // rows + 8*q + e; the vectors are zero padded
@@ -196,40 +348,17 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
 #pragma unroll 1
       for (int u = 0; u < min(4, n_steps - g); ++u) {
         u32x4 a = fragment(a_rd, u), b = fragment(b_rd, u);
-        const bool here = !SUMS && g + u == event;
-        if (here && operand) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const uint32_t x = r == sel_w ? x_mine : 0u;
-            a[r] ^= isA ? x : 0u;
-            b[r] ^= isA ? 0u : x;
-          }
-        }
-        acc = mfma_32x32x16<DT>(a, b, acc);
-        if constexpr (SUMS) sum = mfma_32x32x16<DT>(a & 0x7FFF7FFFu, b & 0x7FFF7FFFu, sum);
-        if (here && !operand) {
-          const bool product = fkind == FI_SITE_PRODUCT;
-          const bool mine = lhi == sel_hi && col == (int)fcol;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const uint32_t word = __float_as_uint(acc[v]);
-            const uint32_t nw = product ? __float_as_uint(write_back(acc[v], re, re_err)) : (word ^ fmask);
-            before = v == sel_v ? word : before;
-            after = v == sel_v ? nw : after;
-            acc[v] = __uint_as_float((v == sel_v && mine) ? nw : word);
-          }
+        if (!SUMS && g + u == event) {
+          acc = faulty_step<DT>(f, a, b, acc, m0, n0, lane, before, after);
+        } else {
+          acc = mfma_32x32x16<DT>(a, b, acc);
+          if constexpr (SUMS) sum = mfma_32x32x16<DT>(a & 0x7FFF7FFFu, b & 0x7FFF7FFFu, sum);
         }
       }
     }
   }
   if (!works) return;
-  if (!SUMS && event >= 0 && !operand && lhi == sel_hi && col == (int)fcol) {
-    p.results[trial].site_word_before = before;
-    p.results[trial].site_word_after = after;
-    if (fired) p.results[trial].product_flag = 1;
-  }
 
-  const bool ragged = m0 + 32 > p.M || n0 + 32 > p.N;
   if constexpr (SUMS) {
     // the elements of the fault-free result that the plan's own detector flags are counted
     uint32_t n_clean = 0;
@@ -248,120 +377,180 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
     if (n_clean != 0 && lane == 0) atomicAdd(p.n_clean, n_clean);
     return;
   } else {
-    // ---- detector on every element; those outside the problem (copies of the last row or column)
-    // get T = +Inf and the value 0: never flagged, stored or counted
     f32x16 T;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const float th = p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(kra4[v >> 2][v & 3], cbj), p.gamma);
-      T[v] = th;
-    }
-    if (ragged) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const bool in = row_base + 8 * (v >> 2) + (v & 3) < p.M && col < p.N;
-        T[v] = in ? T[v] : __builtin_inff();
-        acc[v] = in ? acc[v] : 0.0f;
-      }
-    }
-    uint64_t any = 0;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) any |= __ballot(!(fabsf(acc[v]) <= T[v]));
+    const uint32_t n_flag = detect_tile<DT>(p, acc, T, kra4, cbj, trial, m0, n0, lane);
     fi_trial_result* const r = p.results + trial;
-    if (any != 0) {
-      uint32_t n_flag = 0;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) n_flag += (uint32_t)__builtin_popcountll(__ballot(!(fabsf(acc[v]) <= T[v])));
-      if (lane == 0) atomicAdd(&r->n_flagged, n_flag);
-    }
-    // ---- outputs: corrected where flagged, in FP32 or handed on in the operand format
-    if (p.c_out || p.h_out) {
-      f32x16 out = acc;
-      if (any != 0 && p.policy != FI_CORRECT_NONE) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (!(fabsf(out[v]) <= T[v]))
-            out[v] = p.policy == FI_CORRECT_ZERO ? 0.0f : p.c_star[(size_t)(row_base + 8 * (v >> 2) + (v & 3)) * p.N + col];
-      }
-      const size_t out0 = (size_t)trial * (size_t)p.M * (size_t)p.N + col;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = row_base + 8 * (v >> 2) + (v & 3);
-        if (!ragged || (row < p.M && col < p.N)) {
-          if (p.c_out) __builtin_nontemporal_store(out[v], p.c_out + out0 + (size_t)row * p.N);
-          if (p.h_out) __builtin_nontemporal_store((uint16_t)relu_round16<DT>(out[v]), p.h_out + out0 + (size_t)row * p.N);
+    if (n_flag != 0 && lane == 0) atomicAdd(&r->n_flagged, n_flag);
+    if (owns) {
+      const TileDeviation d = tile_deviation(f, p, acc, T, m0, n0, lane);
+      // non-negative floats (and +Inf) order like their words
+      const uint32_t mp = wave_max(__float_as_uint(d.mx_pre)), mq = wave_max(__float_as_uint(d.mx_post));
+      if (lane == 0) {
+        if (d.n_bit) atomicAdd(&r->n_bitdiff, d.n_bit);
+        if (d.n_pre) atomicAdd(&r->n_dev_pre, d.n_pre);
+        if (d.n_post) atomicAdd(&r->n_dev_post, d.n_post);
+        if (d.n_bT) atomicAdd(&r->n_border_T, d.n_bT);
+        if (d.n_btau) atomicAdd(&r->n_border_tau, d.n_btau);
+        if (mp) atomicMax(reinterpret_cast<uint32_t*>(&r->max_dev_pre), mp);
+        if (mq) atomicMax(reinterpret_cast<uint32_t*>(&r->max_dev_post), mq);
+        // the faulted operand word, once per trial
+        if (f.operand() && (f.isA() ? n0 == 0 : m0 == 0)) {
+          const uint32_t word = f.isA() ? p.A[(size_t)f.row * p.lda + f.col] : p.B[(size_t)f.col * p.ldb + f.row];
+          r->site_word_before = word;
+          r->site_word_after = word ^ (f.mask & 0xFFFFu);
         }
       }
-    }
-    // ---- deviation from the fault-free result, where the fault reaches: one element, one row (it
-    // lies in one register and half-wave) or one column (gathered into lanes 0 .. 31, row k to lane k)
-    if (!owns) {
-      clock(2);
-      return;
-    }
-    float c = acc[0], th = T[0];
-    int row, cc_col;
-    bool act;
-    if (fkind != FI_SITE_B) {
-#pragma unroll
-      for (int v = 1; v < 16; ++v) {
-        c = v == sel_v ? acc[v] : c;
-        th = v == sel_v ? T[v] : th;
-      }
-      row = (int)frow;
-      cc_col = min(col, p.N - 1);
-      act = lhi == sel_hi && col < p.N && (isA || col == (int)fcol);
-    } else {
-      const int sel = (int)fcol - n0;
-      int x = 0;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int word = (int)__float_as_uint(acc[v]);
-        const int k0 = 8 * (v >> 2) + (v & 3);
-        // read with all lanes active, outside the selects
-        const int lo = __builtin_amdgcn_readlane(word, sel), hi = __builtin_amdgcn_readlane(word, sel + 32);
-        x = lane == k0 ? lo : x;
-        x = lane == k0 + 4 ? hi : x;
-      }
-      c = __uint_as_float((uint32_t)x);
-      act = lane < 32 && m0 + lane < p.M;
-      row = min(m0 + l32, p.M - 1);
-      cc_col = (int)fcol;
-      th = p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(p.kra[row], p.cb[fcol]), p.gamma);
-    }
-    const size_t idx = (size_t)row * (size_t)p.N + (size_t)cc_col;
-    const float cs = p.c_star[idx], tau = p.s_abs[idx] * 0.000244140625f;   // 2^-12, exact scaling
-    const bool flag = !(fabsf(c) <= th);
-    float fixed = c;
-    if (flag && p.policy == FI_CORRECT_ZERO) fixed = 0.0f;
-    if (flag && p.policy == FI_CORRECT_RECOMPUTE) fixed = cs;
-    const float dpre = finite_or_inf(fabsf(c - cs)), dpost = finite_or_inf(fabsf(fixed - cs));
-    const float band = fmaxf(2.0f * tau, th * 0.015625f), mag = fabsf(c);
-    const uint64_t am = __ballot(act), changed = __ballot(__float_as_uint(c) != __float_as_uint(cs)) & am;
-    const uint32_t n_bit = (uint32_t)__builtin_popcountll(changed);
-    const uint32_t n_pre = (uint32_t)__builtin_popcountll(__ballot(!(dpre <= tau)) & am);
-    const uint32_t n_post = (uint32_t)__builtin_popcountll(__ballot(!(dpost <= tau)) & am);
-    const uint32_t n_bT = (uint32_t)__builtin_popcountll(changed & __ballot(mag <= 3.4028234e38f) & __ballot(fabsf(mag - th) <= band));
-    const uint32_t n_btau = (uint32_t)__builtin_popcountll(changed & __ballot(tau > 0.0f) & __ballot(dpre >= 0.5f * tau) &
-                                                           __ballot(dpre <= 2.0f * tau));
-    // non-negative floats (and +Inf) order like their words
-    const uint32_t mp = wave_max(act ? __float_as_uint(dpre) : 0u), mq = wave_max(act ? __float_as_uint(dpost) : 0u);
-    if (lane == 0) {
-      if (n_bit) atomicAdd(&r->n_bitdiff, n_bit);
-      if (n_pre) atomicAdd(&r->n_dev_pre, n_pre);
-      if (n_post) atomicAdd(&r->n_dev_post, n_post);
-      if (n_bT) atomicAdd(&r->n_border_T, n_bT);
-      if (n_btau) atomicAdd(&r->n_border_tau, n_btau);
-      if (mp) atomicMax(reinterpret_cast<uint32_t*>(&r->max_dev_pre), mp);
-      if (mq) atomicMax(reinterpret_cast<uint32_t*>(&r->max_dev_post), mq);
-      // the faulted operand word, once per trial
-      if (operand && (isA ? n0 == 0 : m0 == 0)) {
-        const uint32_t word = isA ? p.A[(size_t)frow * p.lda + fcol] : p.B[(size_t)fcol * p.ldb + frow];
-        r->site_word_before = word;
-        r->site_word_after = word ^ (fmask & 0xFFFFu);
+      if (!f.operand() && lane == ((int)f.col - n0) + 32 * ((((int)f.row - m0) >> 2) & 1)) {
+        r->site_word_before = before;
+        r->site_word_after = after;
+        if (f.fired) r->product_flag = 1;
       }
     }
     clock(2);
+  }
+}
+
+// The smallest problems: one workgroup of 16 waves per trial, a wave for each of its (up to 16) 32 x 32
+// tiles, all rows of A and B staged per k-tile.  A trial's record is put together in LDS and written
+// once, so the call is this one launch: no records to clear, no atomics.  The host's launches are the
+// bound there: 64 trials on 128^3 8.8 us against 10.6 us for fill and gemm_fi_small_kernel.  (Five tiles
+// per wave, for problems up to 300 x 256, spilled 200 registers and took 49 us against 11.)
+template <int DT>
+__global__ void __launch_bounds__(1024) gemm_fi_trial_kernel(const GemmArgs p) {
+  constexpr int BK = 64, LOADS = 5;                       // 8-row groups per wave: (tiles_m + tiles_n) * 4 <= 68
+  extern __shared__ __attribute__((aligned(16))) uint8_t tsmem[];   // two stages
+  __shared__ uint32_t part[16][8];
+  __shared__ uint32_t site[3];                            // word before, after, product check fired
+  typedef __attribute__((address_space(3))) void lds_void;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, lhi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int trial = (int)blockIdx.x;
+  const int n_tiles = p.tiles_m * p.tiles_n, rows = 32 * (p.tiles_m + p.tiles_n), stage_bytes = rows * 128;
+  if (p.clocks && trial == 0 && threadIdx.x == 0) {       // see GemmArgs::clocks
+    p.clocks[0] = __builtin_readcyclecounter();
+    p.clocks[1] = __builtin_amdgcn_s_memrealtime();
+  }
+  if (threadIdx.x < 3) site[threadIdx.x] = 0;
+  TrialFault f = decode_fault(p, trial);
+
+  // ---- staging: wave w loads row groups w, w + 16, ...
+  const int lrow = lane >> 3, lslot = lane & 7;
+  const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(p.A), 0, (int)(uint32_t)(((size_t)(p.M - 1) * p.lda + (size_t)p.K) * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_b = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(p.B), 0, (int)(uint32_t)(((size_t)(p.N - 1) * p.ldb + (size_t)p.K) * 2), 0x00020000);
+  const int groups = rows / 8, groups_a = p.tiles_m * 4;
+  uint32_t goff[LOADS];
+  static_for<LOADS>([&](auto cc) {
+    constexpr int c = cc;
+    const int g = c * 16 + wave, r = g * 8 + lrow;        // row inside the stage
+    const uint32_t chunk = (uint32_t)((lslot ^ lds_swizzle(r)) * 8);
+    goff[c] = g < groups_a ? ((uint32_t)min(r, p.M - 1) * p.lda + chunk) * 2u
+                           : ((uint32_t)min(r - 32 * p.tiles_m, p.N - 1) * p.ldb + chunk) * 2u;
+  });
+  auto issue_tile = [&](int kt, int stage) __attribute__((always_inline)) {
+    const int k0 = kt * BK;
+    const bool whole = k0 + BK <= p.K;                    // uniform
+    static_for<LOADS>([&](auto cc) {
+      constexpr int c = cc;
+      const int g = c * 16 + wave;                        // uniform
+      if (g < groups) {
+        // in a ragged last tile, chunks past K are fetched from the start of their row and never used
+        const int ch = (lslot ^ lds_swizzle(g * 8 + lrow)) * 8;
+        const uint32_t off = whole ? goff[c] : k0 + ch < p.K ? goff[c] + 2u * (uint32_t)k0 : goff[c] - 2u * (uint32_t)ch;
+        const int soff = whole ? k0 * 2 : 0;
+        uint8_t* const s = tsmem + stage * stage_bytes + g * 1024;
+        if (g < groups_a) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (lds_void*)s, 16, (int)off, soff, 0, 0);
+        else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, (lds_void*)s, 16, (int)off, soff, 0, 0);
+      }
+    });
+  };
+  issue_tile(0, 0);
+
+  const bool works = wave < n_tiles;                      // uniform; the others stage and keep the barriers
+  const int m0 = wave / p.tiles_n * 32, n0 = wave % p.tiles_n * 32;
+  const bool owns = works && f.reaches(m0, n0);
+  if (owns && f.kind == FI_SITE_PRODUCT) fetch_product_terms<DT>(f, p);
+  f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const int nkt = (p.K + BK - 1) / BK, n_steps = p.K / 16;
+  const int sw = lds_swizzle(l32);
+  uint32_t before = 0, after = 0;
+  __builtin_amdgcn_s_waitcnt(0x0F70);                     // vmcnt(0)
+  __syncthreads();
+  for (int kt = 0; kt < nkt; ++kt) {
+    if (kt + 1 < nkt) issue_tile(kt + 1, (kt + 1) & 1);
+    const uint8_t* const s = tsmem + (kt & 1) * stage_bytes;
+    const int g = 4 * kt;
+    if (works) {
+      auto fragment = [&](int row, int u) __attribute__((always_inline)) {
+        return *reinterpret_cast<const u32x4*>(s + row * 128 + (((2 * u + lhi) ^ sw) << 4));
+      };
+      const int ra = m0 + l32, rb = 32 * p.tiles_m + n0 + l32;
+      if (g + 4 <= n_steps && !(owns && (f.event >> 2) == kt)) {
+        static_for<4>([&](auto u) { acc = mfma_32x32x16<DT>(fragment(ra, u), fragment(rb, u), acc); });
+      } else {
+#pragma unroll 1
+        for (int u = 0; u < min(4, n_steps - g); ++u) {
+          const u32x4 a = fragment(ra, u), b = fragment(rb, u);
+          if (owns && g + u == f.event) acc = faulty_step<DT>(f, a, b, acc, m0, n0, lane, before, after);
+          else acc = mfma_32x32x16<DT>(a, b, acc);
+        }
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);                   // vmcnt(0): this wave's loads have landed
+    __syncthreads();
+  }
+
+  // ---- detector, outputs and deviations
+  uint32_t n[6] = {0, 0, 0, 0, 0, 0}, mp = 0, mq = 0;
+  if (works) {
+    f32x4 kra4[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) kra4[q] = *reinterpret_cast<const f32x4*>(p.kra + m0 + 4 * lhi + 8 * q);   // zero padded
+    const float cbj = p.cb[n0 + l32];
+    f32x16 T;
+    n[0] = detect_tile<DT>(p, acc, T, kra4, cbj, trial, m0, n0, lane);
+    if (owns) {
+      const TileDeviation d = tile_deviation(f, p, acc, T, m0, n0, lane);
+      n[1] = d.n_bit; n[2] = d.n_pre; n[3] = d.n_post; n[4] = d.n_bT; n[5] = d.n_btau;
+      mp = wave_max(__float_as_uint(d.mx_pre));           // non-negative floats (and +Inf) order like their words
+      mq = wave_max(__float_as_uint(d.mx_post));
+      if (!f.operand() && lane == ((int)f.col - n0) + 32 * ((((int)f.row - m0) >> 2) & 1)) {
+        site[0] = before;
+        site[1] = after;
+        site[2] = f.fired ? 1u : 0u;
+      }
+    }
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int q = 0; q < 6; ++q) part[wave][q] = n[q];
+    part[wave][6] = mp;
+    part[wave][7] = mq;
+  }
+  __syncthreads();
+  if (threadIdx.x < 8) {
+    uint32_t x = 0;
+    for (int w = 0; w < 16; ++w) x = threadIdx.x < 6 ? x + part[w][threadIdx.x] : max(x, part[w][threadIdx.x]);
+    // n_flagged, n_bitdiff, n_dev_pre, n_dev_post, n_border_T, n_border_tau, the two maxima
+    constexpr uint32_t word_of = 0x54983210u;             // their words in a record, one hex digit each
+    static_assert(offsetof(fi_trial_result, max_dev_pre) == 16 && offsetof(fi_trial_result, n_border_T) == 32, "record layout");
+    reinterpret_cast<uint32_t*>(p.results + trial)[(word_of >> (4 * threadIdx.x)) & 15u] = x;
+  } else if (threadIdx.x == 8) {
+    fi_trial_result* const r = p.results + trial;
+    uint32_t b = site[0], a = site[1];
+    if (f.operand()) {
+      b = f.isA() ? p.A[(size_t)f.row * p.lda + f.col] : p.B[(size_t)f.col * p.ldb + f.row];
+      a = b ^ (f.mask & 0xFFFFu);
+    }
+    r->site_word_before = b;
+    r->site_word_after = a;
+    r->status = f.valid ? 0u : 1u;
+    r->product_flag = site[2];
+  }
+  if (p.clocks && trial == 0 && threadIdx.x == 0) {
+    p.clocks[2] = __builtin_readcyclecounter();
+    p.clocks[3] = __builtin_amdgcn_s_memrealtime();
   }
 }
 

@@ -1,5 +1,5 @@
-"""Batches that run one wave per (trial, 32 x 32 tile), against the multi-trial kernel on the same
-faults: records and outputs have to be the same bytes (the same sequence of matrix steps)."""
+"""Batches that run one wave per (trial, 32 x 32 tile) - on the smallest problems one workgroup per
+trial - against the multi-trial kernel on the same faults: records and outputs have to be the same bytes (the same sequence of matrix steps)."""
 import numpy as np
 import pytest
 
@@ -17,6 +17,8 @@ pytestmark = pytest.mark.gpu
     (64, 96, 64, 32),        # whole tiles, one k-tile
     (65, 129, 208, 16),      # strips of 4, 2 and 1 tiles all ragged; more k-tiles than buffers
     (32, 40, 1008, 16),      # many k-tiles, the last ragged
+    (100, 128, 128, 32),     # one workgroup per trial unless outputs are stored: all 16 waves, 2 k-tiles
+    (512, 20, 80, 16),       # the same, one column of 16 tiles, ragged k-tile
 ])
 @pytest.mark.parametrize("n", [1, 2, 3, 5, 40])        # 1, 2 and 4 trials per workgroup, padded groups
 @pytest.mark.parametrize("fmt", [orc.FP16, orc.BF16])
