@@ -11,7 +11,7 @@
 //   - rows and columns: the faulted rows (columns) of 64 trials are gathered into one operand of
 //     64 rows, multiplied with the whole other operand.
 // Measured: 1024 accumulator faults on 4096^3 16 us (195 us with a 128 x 128 tile around every
-// element), 4096 trials on 512 x 3072 x 768, half of them A faults, 46 us (3990 us with a tile row
+// element), 4096 trials on 512 x 3072 x 768, half of them A faults, 44 us (3990 us with a tile row
 // of 128 rows per operand fault).
 #pragma once
 
@@ -28,6 +28,7 @@ constexpr int kElemTrials = 4;        // trials per wave of the element kernel
 constexpr int kRowsChunk = 512;       // consecutive trials whose operand faults are gathered together
 constexpr int kRowsTrials = 64;       // gathered rows per work item
 constexpr int kRowsX = 128;           // rows of the other operand per work item
+constexpr int kRowsBuf = 2;           // k-tile buffers: a third leaves room for two workgroups per CU, 38 -> 45 us
 // A chunk of trials fills at most this many items of one kind after the other: the A and the B
 // faults are gathered separately, so one more than kRowsChunk / kRowsTrials.
 constexpr int kRowsSlots = kRowsChunk / kRowsTrials + 1;
@@ -245,7 +246,7 @@ __global__ void __launch_bounds__(64, 2) affected_element_kernel(const GemmArgs 
 // item, x slot), walking the x tiles with stride n_x_slots; a workgroup without an item leaves after
 // one look at the chunk's kinds.
 //
-// Bound, of 39 us for 2048 A faults x 3072 columns x K = 768: 25 us the k-tiles' latency and LDS reads
+// Bound, of 37 us for 2048 A faults x 3072 columns x K = 768: 23 us the k-tiles' latency and LDS reads
 // (1.5 KB per MFMA of a wave), 9 us the accounting of every element, 5 us the record updates.  64 x 128
 // by four waves takes 48 KB of LDS, three workgroups per CU cover each other.
 // The lanes of a wave lie along the columns of C in both cases, so that C* and the magnitude sums are
@@ -383,16 +384,24 @@ __device__ __forceinline__ void affected_rows_item(const GemmArgs& p, uint8_t* s
     static_for<2>([&](auto i) {
       acc[i] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     });
-    issue_tile(0, 0);                                     // the tile before has been read: its last barrier is behind us
-    __builtin_amdgcn_s_waitcnt(0x0F70);                   // vmcnt(0)
-    fault_tile(0, 0);
-    __syncthreads();
+    // Tiles kt + 1 .. kt + kRowsBuf - 1 are in flight while tile kt is used; one barrier per k-tile
+    // says that tile kt is there for all and that nobody reads the tile before it any more.
+    for (int kt = 0; kt < min(kRowsBuf - 1, nkt); ++kt) issue_tile(kt, kt);
+    int buf = 0;
     for (int kt = 0; kt < nkt; ++kt) {
-      const int stage = kt & 1;
-      const bool more = kt + 1 < nkt;
-      const int steps = more ? 4 : last_steps;
-      if (more) issue_tile(kt + 1, stage ^ 1);
-      const uint8_t* s = smem + stage * STAGE;
+      constexpr int L = G_G + X_G;                        // loads of a tile by this wave
+      static_assert(kRowsBuf == 2 || kRowsBuf == 3, "waits for one or two tiles in flight");
+      if (kRowsBuf == 3 && kt + 1 < nkt) __builtin_amdgcn_s_waitcnt(0x0F70 | L);   // all but the youngest tile's
+      else __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0)
+      fault_tile(kt, buf);
+      __builtin_amdgcn_s_waitcnt(0xC07F);                 // lgkmcnt(0): the fault is in LDS
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (kt + kRowsBuf - 1 < nkt) issue_tile(kt + kRowsBuf - 1, buf == 0 ? kRowsBuf - 1 : buf - 1);
+      const int steps = kt + 1 < nkt ? 4 : last_steps;
+      const uint8_t* s = smem + buf * STAGE;
+      buf = buf == kRowsBuf - 1 ? 0 : buf + 1;
       Frags fr[2];
       read_frags(fr[0], s, 0);
       static_for<4>([&](auto kk) {
@@ -404,12 +413,10 @@ __device__ __forceinline__ void affected_rows_item(const GemmArgs& p, uint8_t* s
           });
         }
       });
-      if (more) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): this wave's loads have landed
-        fault_tile(kt + 1, stage ^ 1);
-      }
-      __syncthreads();
     }
+    // every wave is done with the last tiles before the next ones (or the maxima) go into the buffers
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
     // ---- detector, corrector and counters
     const int xw = x0 + wx * 64;
     static_for<2>([&](auto ii) {
@@ -577,14 +584,17 @@ __device__ __forceinline__ void affected_rows_item(const GemmArgs& p, uint8_t* s
 template <int DT, bool BIG>
 __global__ void __launch_bounds__(256, 3) affected_rows_kernel(const GemmArgs p, int n_x_slots) {
   constexpr int BT = kRowsTrials;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[2 * (kRowsTrials + kRowsX) * 128];
+  __shared__ __attribute__((aligned(16))) uint8_t smem[kRowsBuf * (kRowsTrials + kRowsX) * 128];
   __shared__ uint32_t cnt[2][8];
   __shared__ __attribute__((aligned(16))) RowsLists list;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int x_slot = (int)(blockIdx.x % (uint32_t)n_x_slots);
   const uint32_t item = blockIdx.x / (uint32_t)n_x_slots;
-  const uint32_t sub = item % kRowsSlots, chunk0 = item / kRowsSlots * kRowsChunk;
+  // The first items of all chunks come first: the workgroups that find none start last and do not
+  // hold up those that do (39 -> 37 us on the 4096 trials above, five ninths of whose items are empty).
+  const uint32_t n_chunks = ((uint32_t)p.n_trials + kRowsChunk - 1) / kRowsChunk;
+  const uint32_t sub = item / n_chunks, chunk0 = item % n_chunks * kRowsChunk;
 
   // ---- which trials: ranks of the chunk's A faults and of its B faults, in list order
   fi_fault f[2];
