@@ -271,7 +271,7 @@ fi_status fi_activation_round(uint32_t dtype, const float* d_c, uint64_t n, uint
  * The caller owns d_a_stack and keeps it unmodified until the work has run.  All 2*M*N*K
  * flops of every trial are executed (one trial per work item; tile configurations 0..2, of
  * which 0 and 1 run as persistent workgroups when K is a multiple of 64, the default chosen
- * by problem size).
+ * by problem size; small batches one wave per 32x32 tile while none has been chosen).
  * Errors: INVALID_ARG (NULLs, n_trials == 0, bad policy, trial_stride too small),
  * UNSUPPORTED (alignment; tiles x trials >= 2^31). */
 fi_status fi_gemm_propagate_batch(fi_plan* plan, const void* d_a_stack, uint64_t trial_stride,
@@ -321,7 +321,7 @@ fi_status fi_sample_faults(uint64_t seed, uint32_t first_trial, uint32_t n_trial
  * words, 8-byte aligned, alive while batches of this plan run.  Workgroup 0 of each persistent
  * campaign kernel then writes {shader-clock counter, 100 MHz counter} when it starts and when it
  * has finished its last item: words 0..3 for the launch over the trials that leave the operands
- * alone, 4..7 for the operand-fault launch, 8..11 for fi_gemm_propagate_batch.  (cycles_end -
+ * alone (on small batches for the one launch over all trials), 4..7 for the operand-fault launch, 8..11 for fi_gemm_propagate_batch.  (cycles_end -
  * cycles_start) / ((ticks_end - ticks_start) / 1e8) is the shader clock that launch sustained.
  *
  * fi_probe_mfma_loop: launches n_workgroups workgroups of 8 waves that do nothing but issue

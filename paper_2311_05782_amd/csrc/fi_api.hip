@@ -108,6 +108,11 @@ constexpr double kSmallSteps = 320.0;
 // store 33 x 59 x 48 (12 steps) 9.4 : 10.7, 128^3 11.6 : 11.1.  Not beyond a trial per CU: 256 of 33 x 59 x
 // 48 7.6 : 10.6, 512 12.0 : 10.5.
 constexpr uint32_t kTrialSteps = 128, kTrialStepsOut = 16;
+// The same for the next layer's batches, whose trials share nothing but B (columns counted in whole
+// strips of four tiles).  Measured against the persistent kernel: 100 steps (32 trials of 300 x 200 x 640)
+// 20 : 25 us, 128 (128 of 128 x 128 x 1024) 22 : 31, 144 (2 of 512 x 768 x 3072) 37 : 51, 200 (64 of the
+// first) 32 : 29, 256 (256 of the second) 35 : 34.
+constexpr double kSmallPropagate = 160.0;
 // The same for the plan's fault-free pass, which has two results (see compute_golden).
 constexpr double kSmallSums = 768.0;
 // Exponent field >= 144 <=> NOT (|c| <= largest binary32 below 2^17)
@@ -248,9 +253,9 @@ fi_status compute_golden(fi_plan* p, hipStream_t s) {
     a.tiles_n = (a.N + 31) / 32;
     const dim3 grid((unsigned)a.tiles_m * (((unsigned)a.tiles_n + 3) / 4));
     if (p->d.dtype == FI_BF16)
-      hipLaunchKernelGGL((fi::gemm_fi_small_kernel<FI_BF16, 1, true>), grid, dim3(256), 0, s, a);
+      hipLaunchKernelGGL((fi::gemm_fi_small_kernel<FI_BF16, 1, fi::SMALL_SUMS>), grid, dim3(256), 0, s, a);
     else
-      hipLaunchKernelGGL((fi::gemm_fi_small_kernel<FI_FP16, 1, true>), grid, dim3(256), 0, s, a);
+      hipLaunchKernelGGL((fi::gemm_fi_small_kernel<FI_FP16, 1, fi::SMALL_SUMS>), grid, dim3(256), 0, s, a);
     FI_HIP(hipGetLastError());
     return FI_OK;
   }
@@ -501,11 +506,11 @@ void launch_small(const GemmArgs& a, hipStream_t s) {
     return dim3((n + tpw - 1) / tpw * (unsigned)a.tiles_m * (((unsigned)a.tiles_n + tiles - 1) / tiles));
   };
   if (n >= 3)
-    hipLaunchKernelGGL((fi::gemm_fi_small_kernel<DT, 4, false>), blocks(4), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((fi::gemm_fi_small_kernel<DT, 4, fi::SMALL_CAMPAIGN>), blocks(4), dim3(256), 0, s, a);
   else if (n == 2)
-    hipLaunchKernelGGL((fi::gemm_fi_small_kernel<DT, 2, false>), blocks(2), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((fi::gemm_fi_small_kernel<DT, 2, fi::SMALL_CAMPAIGN>), blocks(2), dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL((fi::gemm_fi_small_kernel<DT, 1, false>), blocks(1), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((fi::gemm_fi_small_kernel<DT, 1, fi::SMALL_CAMPAIGN>), blocks(1), dim3(256), 0, s, a);
 }
 
 // One campaign batch: record fill, then either the partition kernel and the two launches of
@@ -926,7 +931,9 @@ fi_status fi_gemm_propagate_batch(fi_plan* plan, const void* d_a_stack, uint64_t
                 (unsigned long long)trial_stride);
   GemmArgs a = base_args(plan);
   // C* is addressed with 32 bits; the trials' operands are the caller's, so K must hold whole k-tiles
-  const bool persistent = plan->prop_cfg >= 0 && a.c_star_bytes != 0 && plan->kshift == 0;
+  const double strips = (double)((plan->d.N + 127) / 128 * 4) / ((plan->d.N + 31) / 32);
+  const bool small = plan->auto_cfg && small_steps(plan, n_trials) * strips <= kSmallPropagate;
+  const bool persistent = !small && plan->prop_cfg >= 0 && a.c_star_bytes != 0 && plan->kshift == 0;
   if (persistent) {
     const MultiCfg mc = kMulti[plan->prop_cfg];
     a.tiles_m = (a.M + mc.bm - 1) / mc.bm;
@@ -949,6 +956,17 @@ fi_status fi_gemm_propagate_batch(fi_plan* plan, const void* d_a_stack, uint64_t
   a.results = d_results;
   a.c_out = d_c_out;
   a.policy = (int)policy;
+  if (small) {
+    a.tiles_m = (a.M + 31) / 32;
+    a.tiles_n = (a.N + 31) / 32;
+    const dim3 grid((unsigned)a.tiles_m * (((unsigned)a.tiles_n + 3) / 4) * n_trials);
+    if (plan->d.dtype == FI_BF16)
+      hipLaunchKernelGGL((fi::gemm_fi_small_kernel<FI_BF16, 1, fi::SMALL_PROPAGATE>), grid, dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((fi::gemm_fi_small_kernel<FI_FP16, 1, fi::SMALL_PROPAGATE>), grid, dim3(256), 0, s, a);
+    FI_HIP(hipGetLastError());
+    return FI_OK;
+  }
   if (persistent) {
     // persistent workgroups walking (tile, trial) items
     const MultiCfg mc = kMulti[plan->prop_cfg];

@@ -257,6 +257,32 @@ __device__ __forceinline__ float finite_or_inf(float d) {
   return (d <= 3.4028234e38f) ? d : __uint_as_float(0x7F800000u);
 }
 
+// Counters of the elements one lane has looked at.
+struct Deviations {
+  uint32_t n_flag = 0, n_bit = 0, n_pre = 0, n_post = 0, n_bT = 0, n_btau = 0;
+  float mx_pre = 0.0f, mx_post = 0.0f;
+  __device__ __forceinline__ void account(bool act, float c, float T, float cs, float sabs, int policy) {
+    const float tau = sabs * 0.000244140625f;             // 2^-12, exact scaling
+    const bool flag = !(fabsf(c) <= T);
+    float cc = c;
+    if (flag && policy == FI_CORRECT_ZERO) cc = 0.0f;
+    if (flag && policy == FI_CORRECT_RECOMPUTE) cc = cs;
+    const float dpre = finite_or_inf(fabsf(c - cs));
+    const float dpost = finite_or_inf(fabsf(cc - cs));
+    const bool changed = act && __float_as_uint(c) != __float_as_uint(cs);
+    n_flag += (act && flag) ? 1u : 0u;
+    n_bit += changed ? 1u : 0u;
+    n_pre += (act && !(dpre <= tau)) ? 1u : 0u;
+    n_post += (act && !(dpost <= tau)) ? 1u : 0u;
+    mx_pre = fmaxf(mx_pre, act ? dpre : 0.0f);
+    mx_post = fmaxf(mx_post, act ? dpost : 0.0f);
+    const float band = fmaxf(2.0f * tau, T * 0.015625f);
+    const float mag = fabsf(c);
+    n_bT += (changed && mag <= 3.4028234e38f && fabsf(mag - T) <= band) ? 1u : 0u;
+    n_btau += (changed && tau > 0.0f && dpre >= 0.5f * tau && dpre <= 2.0f * tau) ? 1u : 0u;
+  }
+};
+
 // The global threshold as a golden pass sees it.
 __device__ __forceinline__ float golden_t_global(const GemmArgs& p) {
   return p.maxima ? __fmul_rn(__fmul_rn(p.maxima[0], p.maxima[1]), p.gamma) : p.t_global;

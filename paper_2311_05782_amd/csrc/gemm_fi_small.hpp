@@ -220,10 +220,15 @@ __device__ __forceinline__ uint32_t detect_tile(const GemmArgs& p, f32x16& acc, 
   return n_flag;
 }
 
-// SUMS: the plan's fault-free pass; C* to p.c_out and the magnitude sums, from the same fragments
-// with the sign bits cleared, to p.s_out.  Else a campaign (p.tiles_m, p.tiles_n in 32 x 32 tiles).
-template <int DT, int TPW, bool SUMS>
+// CAMPAIGN: trials with faults.  SUMS: the plan's fault-free pass; C* to p.c_out and the magnitude
+// sums, from the same fragments with the sign bits cleared, to p.s_out.  PROPAGATE: the next layer;
+// trial t multiplies its own A operand, nothing is injected, every element is compared with C*.
+// p.tiles_m and p.tiles_n count 32 x 32 tiles.
+enum { SMALL_CAMPAIGN = 0, SMALL_SUMS = 1, SMALL_PROPAGATE = 2 };
+template <int DT, int TPW, int MODE>
 __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
+  constexpr bool SUMS = MODE == SMALL_SUMS, PROP = MODE == SMALL_PROPAGATE;
+  static_assert(TPW == 1 || MODE == SMALL_CAMPAIGN, "only campaign trials share operands");
   static_assert(TPW == 1 || TPW == 2 || TPW == 4, "four waves: trials x tiles");
   constexpr int TILES = 4 / TPW;                          // neighbouring 32-column tiles
   constexpr int NBUF = TPW == 1 ? 3 : 4;                  // 60, 48 or 32 KB of LDS
@@ -244,6 +249,7 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
   const bool works = blockIdx.x % n_groups * TPW + (uint32_t)(wave % TPW) < n_trials && n0 < p.N;
   auto clock = [&](int at) __attribute__((always_inline)) {   // see GemmArgs::clocks
     if (!SUMS && p.clocks && blockIdx.x == 0 && threadIdx.x == 0) {
+      at += PROP ? 8 : 0;
       p.clocks[at] = __builtin_readcyclecounter();
       p.clocks[at + 1] = __builtin_amdgcn_s_memrealtime();
     }
@@ -254,7 +260,7 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
   TrialFault f = {};
   f.kind = FI_SITE_NONE; f.event = -1;
   bool owns = false;                                      // it reaches an element of this tile
-  if constexpr (!SUMS) {
+  if constexpr (MODE == SMALL_CAMPAIGN) {
     f = decode_fault(p, trial);
     owns = works && f.reaches(m0, n0);
     if (!f.valid && works && m0 == 0 && n0 == 0 && lane == 0) p.results[trial].status = 1;
@@ -276,7 +282,7 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
   // loads row groups w, w + 4, ...; every wave issues G_W loads per k-tile (one group may come twice).
   const int lrow = lane >> 3, lslot = lane & 7;
   const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(p.A), 0, (int)(uint32_t)(((size_t)(p.M - 1) * p.lda + (size_t)p.K) * 2), 0x00020000);
+      const_cast<uint16_t*>(PROP ? p.A + (size_t)trial * p.a_trial_stride : p.A), 0, (int)(uint32_t)(((size_t)(p.M - 1) * p.lda + (size_t)p.K) * 2), 0x00020000);
   const __amdgpu_buffer_rsrc_t rsrc_b = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(p.B), 0, (int)(uint32_t)(((size_t)(p.N - 1) * p.ldb + (size_t)p.K) * 2), 0x00020000);
   static_assert(GROUPS % 4 == 0, "every wave loads its own row groups");
@@ -333,7 +339,7 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
     auto fragment = [&](int rd, int u) __attribute__((always_inline)) {
       return *reinterpret_cast<const u32x4*>(s + rd + (((2 * u + lhi) ^ sw) << 4));
     };
-    if (__builtin_expect(g + 4 <= n_steps && (SUMS || (event >> 2) != kt), 1)) {
+    if (__builtin_expect(g + 4 <= n_steps && (MODE != SMALL_CAMPAIGN || (event >> 2) != kt), 1)) {
       u32x4 a[4], b[4];
       static_for<4>([&](auto uu) {
         a[uu] = fragment(a_rd, uu);
@@ -348,7 +354,7 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
 #pragma unroll 1
       for (int u = 0; u < min(4, n_steps - g); ++u) {
         u32x4 a = fragment(a_rd, u), b = fragment(b_rd, u);
-        if (!SUMS && g + u == event) {
+        if (MODE == SMALL_CAMPAIGN && g + u == event) {
           acc = faulty_step<DT>(f, a, b, acc, m0, n0, lane, before, after);
         } else {
           acc = mfma_32x32x16<DT>(a, b, acc);
@@ -381,6 +387,38 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
     const uint32_t n_flag = detect_tile<DT>(p, acc, T, kra4, cbj, trial, m0, n0, lane);
     fi_trial_result* const r = p.results + trial;
     if (n_flag != 0 && lane == 0) atomicAdd(&r->n_flagged, n_flag);
+    if constexpr (PROP) {
+      // most tiles equal the fault-free result bit for bit (nothing to count, unless a NaN does)
+      float cs[16];
+      bool differs = false;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = row_base + 8 * (v >> 2) + (v & 3);
+        cs[v] = p.c_star[(size_t)min(row, p.M - 1) * p.N + min(col, p.N - 1)];
+        differs |= row < p.M && col < p.N && (__float_as_uint(acc[v]) != __float_as_uint(cs[v]) || acc[v] != acc[v]);
+      }
+      if (__ballot(differs) != 0) {
+        Deviations d;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int row = row_base + 8 * (v >> 2) + (v & 3);
+          const float sa = p.s_abs[(size_t)min(row, p.M - 1) * p.N + min(col, p.N - 1)];
+          d.account(row < p.M && col < p.N, acc[v], T[v], cs[v], sa, p.policy);
+        }
+        const uint32_t n_bit = wave_sum(d.n_bit), n_pre = wave_sum(d.n_pre), n_post = wave_sum(d.n_post);
+        const uint32_t n_bT = wave_sum(d.n_bT), n_btau = wave_sum(d.n_btau);
+        const uint32_t mp = wave_max(__float_as_uint(d.mx_pre)), mq = wave_max(__float_as_uint(d.mx_post));
+        if (lane == 0) {
+          if (n_bit) atomicAdd(&r->n_bitdiff, n_bit);
+          if (n_pre) atomicAdd(&r->n_dev_pre, n_pre);
+          if (n_post) atomicAdd(&r->n_dev_post, n_post);
+          if (n_bT) atomicAdd(&r->n_border_T, n_bT);
+          if (n_btau) atomicAdd(&r->n_border_tau, n_btau);
+          if (mp) atomicMax(reinterpret_cast<uint32_t*>(&r->max_dev_pre), mp);
+          if (mq) atomicMax(reinterpret_cast<uint32_t*>(&r->max_dev_post), mq);
+        }
+      }
+    }
     if (owns) {
       const TileDeviation d = tile_deviation(f, p, acc, T, m0, n0, lane);
       // non-negative floats (and +Inf) order like their words

@@ -55,3 +55,39 @@ def test_small_batches_equal_the_multi_trial_kernel(shape, n, fmt):
             got.append(out)
             plan.destroy()
         assert got[0] == got[1], [i for i, (a, b) in enumerate(zip(*got)) if a != b]
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 16, 16), (33, 140, 80, 16), (64, 128, 128, 64), (65, 31, 576, 64)])
+@pytest.mark.parametrize("n", [1, 3, 9])
+@pytest.mark.parametrize("fmt", [orc.FP16, orc.BF16])
+def test_small_next_layer_batches_equal_the_large_kernels(shape, n, fmt):
+    # every trial its own A operand: equal to the plan's, a few words changed, Inf and NaN among them
+    import torch
+    M, N, K, kb = shape
+    Aw, Bw = wl.gaussian(M, N, K, fmt, seed=M * N + K)
+    rng = np.random.default_rng(n + K)
+    stack = np.repeat(Aw[None], n, axis=0)
+    for t in range(1, n):
+        for _ in range(t):
+            stack[t, rng.integers(M), rng.integers(K)] ^= np.uint16(1 << rng.integers(16))
+    if n > 3:
+        stack[3, M - 1, K - 1] = 0x7FFF                 # NaN in both formats
+        stack[4, 0, 0] = 0x7F80 if fmt == orc.BF16 else 0x7C00
+    d_A, d_B, d_s = fi.words_to_device(Aw), fi.words_to_device(Bw), fi.words_to_device(stack)
+    for policy, bound in ((wl.CORRECT_ZERO, fi.BOUND_ROWCOL), (wl.CORRECT_RECOMPUTE, fi.BOUND_GLOBAL), (wl.CORRECT_NONE, fi.BOUND_EXPONENT)):
+        got = []
+        for cfg in (-1, 1, 2):                          # a wave per tile; persistent (K % 64 == 0); one workgroup per tile
+            plan = fi.Plan(fi.plan_desc(M, N, K, kb, fmt, bound_mode=bound), d_A, d_B)
+            plan.tune(cfg)
+            d_r = fi.empty_results(n)
+            d_c = torch.full((n, M, N), 7.0, device="cuda")
+            plan.fi_gemm_propagate_batch(d_s, M * K, n, policy, d_r, d_c)
+            recs = fi.results_to_host(d_r)
+            plan.fi_gemm_propagate_batch(d_s, 0, n, policy, d_r)          # everybody the plan's own operand
+            got.append((recs.tobytes(), d_c.cpu().numpy().view(np.uint32), fi.results_to_host(d_r).tobytes()))
+            plan.destroy()
+        assert not any(got[0][2][q] for q in range(len(got[0][2]))) or bound == fi.BOUND_EXPONENT
+        for other in got[1:]:
+            assert got[0][0] == other[0] and got[0][2] == other[2]
+            nan = (got[0][1] & 0x7FFFFFFF) > 0x7F800000       # a NaN's payload is not compared
+            assert np.array_equal(np.where(nan, 0, got[0][1]), np.where((other[1] & 0x7FFFFFFF) > 0x7F800000, 0, other[1]))
