@@ -257,6 +257,9 @@ __device__ __forceinline__ float finite_or_inf(float d) {
   return (d <= 3.4028234e38f) ? d : __uint_as_float(0x7F800000u);
 }
 
+// One comparison, as acc != acc is for NaN alone.
+__device__ __forceinline__ bool not_finite(float x) { return __builtin_amdgcn_classf(x, 0x207); }   // NaNs, +-Inf
+
 // Counters of the elements one lane has looked at.
 struct Deviations {
   uint32_t n_flag = 0, n_bit = 0, n_pre = 0, n_post = 0, n_bT = 0, n_btau = 0;

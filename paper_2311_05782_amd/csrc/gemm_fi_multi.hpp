@@ -671,7 +671,8 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       // Every element of the trial's output against the fault-free result.  Two phases per
       // 32 x 32 tile: the fault-free words (requested tiles ahead) are compared bit for bit
       // (most tiles of most trials are untouched by what the previous layer's fault changed: no
-      // counter can move there); only a tile with a differing (or NaN) element runs the full
+      // counter can move there); only a tile with an element that differs or is not finite, or of a
+      // wave that flagged one (corrected, it deviates whatever it was compared with), runs the full
       // accounting, four rows at a time so that it needs few registers.
       uint32_t n_bit = 0, n_pre = 0, n_post = 0, n_bT = 0, n_btau = 0;
       float mx_pre = 0.0f, mx_post = 0.0f;
@@ -688,9 +689,9 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
         for (int v = 0; v < 16; ++v) {
           const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3);
           const bool act = !ragged || (row < p.M && col < p.N);
-          differs |= (act && (__float_as_uint(t[v]) != __float_as_uint(cs[v]) || t[v] != t[v])) ? 1u : 0u;
+          differs |= (act && (__float_as_uint(t[v]) != __float_as_uint(cs[v]) || not_finite(t[v]))) ? 1u : 0u;
         }
-        if (__ballot(differs != 0) != 0) {
+        if (n_flag[0] != 0 || __ballot(differs != 0) != 0) {
           static_for<4>([&](auto qq) {
             constexpr int q = qq;
             __builtin_amdgcn_sched_barrier(0);
@@ -731,8 +732,8 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
         }
       });
       // most trial tiles equal the fault-free result bit for bit: one ballot, nothing to reduce
-      if (__ballot((n_bit | n_pre | n_post) != 0) == 0) return;
       uint32_t mp = __float_as_uint(mx_pre), mq = __float_as_uint(mx_post);   // non-negative: ordered like words
+      if (__ballot((n_bit | n_pre | n_post | mp | mq) != 0) == 0) return;
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) {
         n_bit += __shfl_xor(n_bit, o, 64); n_pre += __shfl_xor(n_pre, o, 64); n_post += __shfl_xor(n_post, o, 64);

@@ -388,14 +388,15 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
     fi_trial_result* const r = p.results + trial;
     if (n_flag != 0 && lane == 0) atomicAdd(&r->n_flagged, n_flag);
     if constexpr (PROP) {
-      // most tiles equal the fault-free result bit for bit (nothing to count, unless a NaN does)
+      // most tiles equal the fault-free result bit for bit and hold nothing that is flagged (a corrected
+      // element deviates whatever it was compared with) or not finite: nothing to count
       float cs[16];
-      bool differs = false;
+      bool differs = n_flag != 0;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = row_base + 8 * (v >> 2) + (v & 3);
         cs[v] = p.c_star[(size_t)min(row, p.M - 1) * p.N + min(col, p.N - 1)];
-        differs |= row < p.M && col < p.N && (__float_as_uint(acc[v]) != __float_as_uint(cs[v]) || acc[v] != acc[v]);
+        differs |= row < p.M && col < p.N && (__float_as_uint(acc[v]) != __float_as_uint(cs[v]) || not_finite(acc[v]));
       }
       if (__ballot(differs) != 0) {
         Deviations d;

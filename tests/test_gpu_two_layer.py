@@ -87,6 +87,62 @@ def test_next_layer_exact_regime_bit_equal(fmt, cfg, shape):
     plan.destroy()
 
 
+@pytest.mark.parametrize("cfg", [None, 0, 1, 2])
+@pytest.mark.parametrize("shape", [(130, 65, 96, 48), (140, 70, 128, 32), (64, 64, 32, 16)])
+def test_next_layer_counts_corrected_elements_that_equal_the_fault_free_result(cfg, shape):
+    # Under the exponent-only bound elements of C* itself can be flagged.  Zeroed, they deviate after
+    # correction although their word equals the fault-free one before it.
+    M, N, K, kb = shape
+    fmt, n = orc.BF16, 5
+    Aw, Bw = wl.small_integers(M, N, K, fmt, seed=M + K, lim=4, step=2)
+    Aw, Bw = Aw.copy(), Bw.copy()
+    big = wl.to_words(np.full(K, 64.0, np.float32), fmt)
+    Aw[[3, M - 1], :], Bw[[7, N - 1], :] = big, big              # |C*| = 4096 K >= 2^17 in four tiles' corners
+    stack = np.stack([Aw.copy() for _ in range(n)])
+    stack[1, 3] = 0                                              # a flagged row gone
+    stack[2, 40] = big                                           # one more
+    stack[3, M - 1, K - 1] ^= 0x8000
+    plan = gu.make_plan(Aw, Bw, kb, fmt, cfg=cfg, bound_mode=fi.BOUND_EXPONENT)
+    p = orc.problem(M, N, K, kb, fmt, bound_mode=orc.BOUND_EXPONENT)
+    for policy in (orc.CORRECT_NONE, orc.CORRECT_ZERO, orc.CORRECT_RECOMPUTE):
+        recs = _stack_gpu(plan, stack, policy)
+        orecs, _ = orc.propagate(p, Aw, Bw, stack, policy, want_outputs=True)
+        for k in ("n_flagged", "n_bitdiff", "n_dev_pre", "n_dev_post"):
+            assert np.array_equal(recs[k], orecs[k]), (policy, k, recs[k], orecs[k])
+        assert np.array_equal(recs["max_dev_pre"], orecs["max_dev_pre"].astype(np.float32))
+        assert np.array_equal(recs["max_dev_post"], orecs["max_dev_post"].astype(np.float32))
+        assert recs["n_flagged"][0] == 4 and recs["n_dev_post"][0] == (4 if policy == orc.CORRECT_ZERO else 0)
+    plan.destroy()
+
+
+@pytest.mark.parametrize("shape", [(70, 65, 96, 48), (70, 65, 128, 32)])
+def test_next_layer_records_do_not_depend_on_the_route_where_the_fault_free_result_overflows(shape):
+    # C* holds Inf and NaN (finite operands, sums beyond binary32): their largest deviation is +Inf in
+    # every trial, equal words or not
+    M, N, K, kb = shape
+    fmt, n = orc.BF16, 3
+    Aw, Bw = wl.gaussian(M, N, K, fmt, seed=K)
+    Aw, Bw = Aw.copy(), Bw.copy()
+    Aw[5, :] = wl.to_words(np.full(K, 2.0 ** 100, np.float32), fmt)
+    Aw[41, 0::2] = Aw[5, 0]
+    Aw[41, 1::2] = Aw[5, 0] | 0x8000
+    Bw[[2, 64], :] = wl.to_words(np.full(K, 2.0 ** 60, np.float32), fmt)
+    stack = np.stack([Aw.copy() for _ in range(n)])
+    stack[1, 69, 0] ^= 0x0100
+    stack[2, 5, 0] ^= 0x8000
+    for policy, bound in ((orc.CORRECT_ZERO, fi.BOUND_ROWCOL), (orc.CORRECT_RECOMPUTE, fi.BOUND_GLOBAL), (orc.CORRECT_ZERO, fi.BOUND_EXPONENT)):
+        got = []
+        for cfg in (None, 0, 1, 2):
+            plan = gu.make_plan(Aw, Bw, kb, fmt, cfg=cfg, bound_mode=bound)
+            c = plan.buffer_to_host(fi.BUF_C_STAR)
+            assert np.isinf(c[5, 2]) and np.isnan(c[41, 64])
+            got.append(_stack_gpu(plan, stack, policy))
+            plan.destroy()
+        assert np.isinf(got[0]["max_dev_pre"]).all()
+        for g in got[1:]:
+            assert g.tobytes() == got[0].tobytes(), (policy, bound, g, got[0])
+
+
 @pytest.mark.parametrize("fmt,cfg", [(orc.FP16, 0), (orc.BF16, 1), (orc.BF16, 2)])
 def test_next_layer_on_perturbed_gaussian_operands_guard_band_rule(fmt, cfg):
     M, N, K, kb = 260, 136, 256, 32
