@@ -230,6 +230,13 @@ struct RowsLists {
   uint32_t trial[kRowsTrials], row[kRowsTrials], k[kRowsTrials], mask[kRowsTrials];
 };
 
+// The row / column kernel compares most elements with kra * (cb * gamma) * 0.97 instead of the three roundings
+// T = fl(fl(kra * cb) * gamma).  The two agree to a few ulps while neither leaves the normal range:
+// every kra and cb that is not 0 at or above this (a product of two stays normal, a 0 makes the
+// limit 0), cb * gamma finite and T below 1.7e38 everywhere.  Plans for which that does not hold take
+// the whole rule for every element.
+constexpr float kTinyFactor = 0x1p-60f;
+
 // v[LANE] = x (uniform): v_writelane_b32 has no builtin.
 template <int LANE>
 __device__ __forceinline__ void set_lane(int& v, int x) {
@@ -239,7 +246,7 @@ __device__ __forceinline__ void set_lane(int& v, int x) {
 // One item, all its x tiles.  ISA: A faults.  BIG: C* spans 4 GiB or more (64-bit addresses).
 template <int DT, bool BIG, bool ISA>
 __device__ __forceinline__ void affected_rows_item(const GemmArgs& p, uint8_t* smem, const RowsLists& list, int n_act,
-                                                   int x_slot, int n_x_slots) {
+                                                   int x_slot, int n_x_slots, bool plain_holds) {
   constexpr int BK = 64, BT = kRowsTrials, BX = kRowsX;
   constexpr int STAGE = (BT + BX) * 128;
   constexpr int G_G = BT / 8 / 4, X_G = BX / 8 / 4;       // 8-row groups staged per wave
@@ -293,7 +300,7 @@ __device__ __forceinline__ void affected_rows_item(const GemmArgs& p, uint8_t* s
   // ISA: counters of trial l32 in lanes 0 .. 31 (from lane masks), the maxima per register (trial)
   // and lane.  Else: lane = trial, everything in its own counters.
   [[maybe_unused]] int n_flag = 0, n_bit = 0, n_pre = 0, n_corr = 0, n_bT = 0, n_btau = 0;
-  [[maybe_unused]] const uint64_t plain_ok = p.t_global < 1.7e38f ? ~0ull : 0ull;   // no threshold exceeds t_global
+  [[maybe_unused]] const uint64_t plain_ok = plain_holds ? ~0ull : 0ull;   // see kTinyFactor
   [[maybe_unused]] float mxp[ISA ? 16 : 1], mxq[ISA ? 16 : 1];
   [[maybe_unused]] Deviations dev;
   const int q_mine = wt * 32 + l32;                       // this lane's trial (ISA: as a counter)
@@ -422,9 +429,9 @@ __device__ __forceinline__ void affected_rows_item(const GemmArgs& p, uint8_t* s
           set_lane<lo + 4>(to, __builtin_popcount((uint32_t)(m >> 32)));
         };
         const uint64_t in_mask = __ballot(in);
-        // Plain: |c| below 0.97 T (T to a few ulps) and 2 tau below T/64, hence below the band around T,
-        // unflagged and finite as long as no threshold overflows: nothing is corrected and the
-        // deviation is the same before and after.
+        // Plain: |c| below 0.97 T (T to a few ulps, see kTinyFactor) and 2 tau below T/64, hence below the
+        // band around T, unflagged and finite: nothing is corrected and the deviation is the same before
+        // and after.
         const float lim_x = p.bound_global ? 0.97f : cb_x * p.gamma * 0.97f;
         static_for<16>([&](auto vv) {
           constexpr int v = vv;
@@ -556,7 +563,7 @@ __device__ __forceinline__ void affected_rows_item(const GemmArgs& p, uint8_t* s
 }
 
 template <int DT, bool BIG>
-__global__ void __launch_bounds__(256, 3) affected_rows_kernel(const GemmArgs p, int n_x_slots) {
+__global__ void __launch_bounds__(256, 3) affected_rows_kernel(const GemmArgs p, int n_x_slots, int plain_holds) {
   constexpr int BT = kRowsTrials;
   __shared__ __attribute__((aligned(16))) uint8_t smem[kRowsBuf * (kRowsTrials + kRowsX) * 128];
   __shared__ uint32_t cnt[2][8];
@@ -619,8 +626,8 @@ __global__ void __launch_bounds__(256, 3) affected_rows_kernel(const GemmArgs p,
     }
   }
   __syncthreads();
-  if (isA) affected_rows_item<DT, BIG, true>(p, smem, list, n_act, x_slot, n_x_slots);
-  else affected_rows_item<DT, BIG, false>(p, smem, list, n_act, x_slot, n_x_slots);
+  if (isA) affected_rows_item<DT, BIG, true>(p, smem, list, n_act, x_slot, n_x_slots, plain_holds != 0);
+  else affected_rows_item<DT, BIG, false>(p, smem, list, n_act, x_slot, n_x_slots, false);
 }
 
 }  // namespace fi

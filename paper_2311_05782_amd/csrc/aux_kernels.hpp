@@ -22,8 +22,8 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
 }
 
 // Plan statistics in one launch: kra_i = fl32(K * max_k |a_ik|) and cb_j = max_k |b_kj| (B stored
-// [N][ldb], k contiguous), both zero padded, with {max kra, max cb} in maxima[0..1] and "an operand is
-// Inf or NaN" in *nonfinite (all three zero before): the operand magnitude maxima behind the detector's
+// [N][ldb], k contiguous), both zero padded, with {max kra, max cb} in maxima[0..1] and, in *found, 1 "an
+// operand is Inf or NaN" and 2 "a kra or cb is neither 0 nor as large as `tiny`" (all three zero before): the operand magnitude maxima behind the detector's
 // bound (Sec. VI-A: the result's magnitude is bounded by the operands').  Magnitudes of finite
 // FP16/BF16 numbers order like their low 15 bits, non-negative floats like their words.  A wave per
 // row, walking the rows of A and then of B with the grid as stride; one atomic per workgroup and
@@ -33,7 +33,7 @@ __global__ void __launch_bounds__(256) plan_stats_kernel(const uint16_t* __restr
                                                          uint32_t M_pad, const uint16_t* __restrict__ B, uint32_t ldb,
                                                          uint32_t N, uint32_t N_pad, uint32_t K, float* __restrict__ kra,
                                                          float* __restrict__ cb, uint32_t* __restrict__ maxima,
-                                                         uint32_t* __restrict__ nonfinite) {
+                                                         uint32_t* __restrict__ found, float tiny) {
   __shared__ uint32_t part[2][4];
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t top[2] = {0, 0};
@@ -51,8 +51,9 @@ __global__ void __launch_bounds__(256) plan_stats_kernel(const uint16_t* __restr
       }
       m = wave_max(m);
       const uint32_t first_nonfinite = (DT == FI_BF16) ? 0x7F80u : 0x7C00u;
-      if (m >= first_nonfinite && lane == 0) atomicOr(nonfinite, 1u);
+      if (m >= first_nonfinite && lane == 0) atomicOr(found, 1u);
       out = __fmul_rn(isA ? (float)K : 1.0f, decode16<DT>(m));
+      if (out > 0.0f && out < tiny && lane == 0) atomicOr(found, 2u);
     }
     if (lane == 0) (isA ? kra : cb)[row] = out;
     top[isA ? 0 : 1] = max(top[isA ? 0 : 1], __float_as_uint(out));

@@ -80,9 +80,10 @@ struct fi_plan {
   float* s_abs = nullptr;            // [M][N], allocated like c_star
   float* kra = nullptr;              // [pad(M)]
   float* cb = nullptr;               // [pad(N)]
-  float* scratch = nullptr;          // 4 floats + 4 words: maxima, "operand not finite", clean flags
+  float* scratch = nullptr;          // 4 floats + 4 words: maxima, what plan_stats_kernel found, clean flags
   float t_global = 0.0f;
   uint32_t n_clean_flagged = 0;      // elements of C* the plan's own detector flags
+  bool plain_ok = false;             // the affected-only campaign's short comparison holds, see fi::kTinyFactor
   int cfg = 0;                       // index into kCfg
   int cfg_affected = 0;              // index into kCfg: the tile shape that the affected-only campaign's batch limit counts
   int mcfg = -1;                     // index into kMulti, or -1: every trial through the single-trial kernel
@@ -202,7 +203,7 @@ GemmArgs base_args(const fi_plan* p, int cfg = -1) {
 // The affected-only campaign: every record by the element kernel, then the operand faults' rows
 // and columns.
 template <int DT>
-fi_status launch_affected(const GemmArgs& a, int n_cus, hipStream_t s) {
+fi_status launch_affected(const GemmArgs& a, int n_cus, bool plain_ok, hipStream_t s) {
   // A piece is one load instruction per row (512 k) up to K = 512, two beyond.  Three pieces in
   // flight cover the memory latency of a wave that has its CU to itself; from two waves per CU on
   // they take each other's LDS, and one piece in flight per wave is the better use of it.
@@ -227,9 +228,9 @@ fi_status launch_affected(const GemmArgs& a, int n_cus, hipStream_t s) {
   if (per_slot > tiles) per_slot = tiles;
   const int x_slots = (int)((tiles + per_slot - 1) / per_slot);
   if (a.c_star_bytes != 0)
-    hipLaunchKernelGGL((fi::affected_rows_kernel<DT, false>), dim3((unsigned)(items * x_slots)), dim3(256), 0, s, a, x_slots);
+    hipLaunchKernelGGL((fi::affected_rows_kernel<DT, false>), dim3((unsigned)(items * x_slots)), dim3(256), 0, s, a, x_slots, (int)plain_ok);
   else
-    hipLaunchKernelGGL((fi::affected_rows_kernel<DT, true>), dim3((unsigned)(items * x_slots)), dim3(256), 0, s, a, x_slots);
+    hipLaunchKernelGGL((fi::affected_rows_kernel<DT, true>), dim3((unsigned)(items * x_slots)), dim3(256), 0, s, a, x_slots, (int)plain_ok);
   FI_HIP(hipGetLastError());
   return FI_OK;
 }
@@ -448,15 +449,15 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
                        p->kshift);
     FI_HIP(hipGetLastError());
   }
-  uint32_t* const words = reinterpret_cast<uint32_t*>(p->scratch);   // maxima, -, -, "not finite", clean flags
+  uint32_t* const words = reinterpret_cast<uint32_t*>(p->scratch);   // maxima, -, -, found, clean flags
   const uint32_t rows_a = (uint32_t)padded(d.M), rows_b = (uint32_t)padded(d.N);
   const dim3 stat_grid((rows_a + rows_b) / 4 < 1024 ? (rows_a + rows_b) / 4 : 1024);
   if (d.dtype == FI_FP16)
     hipLaunchKernelGGL(fi::plan_stats_kernel<FI_FP16>, stat_grid, dim3(256), 0, s, p->A, (uint32_t)d.lda, d.M, rows_a,
-                       p->B, p->ldb, d.N, rows_b, d.K, p->kra, p->cb, words, words + 4);
+                       p->B, p->ldb, d.N, rows_b, d.K, p->kra, p->cb, words, words + 4, fi::kTinyFactor);
   else
     hipLaunchKernelGGL(fi::plan_stats_kernel<FI_BF16>, stat_grid, dim3(256), 0, s, p->A, (uint32_t)d.lda, d.M, rows_a,
-                       p->B, p->ldb, d.N, rows_b, d.K, p->kra, p->cb, words, words + 4);
+                       p->B, p->ldb, d.N, rows_b, d.K, p->kra, p->cb, words, words + 4, fi::kTinyFactor);
   FI_HIP(hipGetLastError());
   fi_status st = compute_golden(p, s);
   if (st != FI_OK) return st;
@@ -466,12 +467,14 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   if (es != hipSuccess) return fail(FI_DEVICE, "plan kernels failed: %s", hipGetErrorString(es));
   uint32_t badw;
   memcpy(&badw, &host[4], 4);
-  if (badw) return fail(FI_INVALID_ARG, "A or B holds an Inf or NaN: the magnitude bound is undefined");
+  if (badw & 1u) return fail(FI_INVALID_ARG, "A or B holds an Inf or NaN: the magnitude bound is undefined");
   // T = fl32(fl32(fl32(K*ra_max) * cb_max) * gamma), one rounding per product
   volatile float t = host[0] * host[1];
   t = t * d.gamma;
   p->t_global = t;
   if (d.bound_mode == FI_BOUND_EXPONENT) p->t_global = kExponentBound;
+  const bool factors_normal = !(badw & 2u) && host[1] * d.gamma <= 3.4028234e38f;
+  p->plain_ok = p->t_global < 1.7e38f && (d.bound_mode != FI_BOUND_ROWCOL || factors_normal);
   // How many elements of the fault-free result the plan's own detector flags (none under the
   // operand-derived bounds with gamma at or above the default; possible under the exponent-only
   // bound or a caller's smaller gamma).  The affected-only campaign relies on it being 0.
@@ -893,8 +896,8 @@ fi_status fi_gemm_inject_batch_affected(fi_plan* plan, const fi_fault* d_faults,
   a.results = d_results;
   a.policy = (int)policy;
   a.product_check = plan->product_check;
-  if (plan->d.dtype == FI_BF16) return launch_affected<FI_BF16>(a, plan->n_cus, s);
-  return launch_affected<FI_FP16>(a, plan->n_cus, s);
+  if (plan->d.dtype == FI_BF16) return launch_affected<FI_BF16>(a, plan->n_cus, plan->plain_ok, s);
+  return launch_affected<FI_FP16>(a, plan->n_cus, plan->plain_ok, s);
 }
 
 fi_status fi_activation_round(uint32_t dtype, const float* d_c, uint64_t n, uint16_t* d_h, void* stream) {

@@ -75,3 +75,29 @@ def test_affected_records_where_the_fault_free_result_spans_4_gib():
     plan.fi_gemm_inject_batch_affected(fi.to_device(faults), n, wl.CORRECT_ZERO, d_r)
     assert fi.results_to_host(d_r).tobytes() == want.tobytes()
     plan.destroy()
+
+
+@pytest.mark.parametrize("K,a,b,gamma,kind,masks", [
+    (64, 2.0 ** -57, 2.0 ** 58, 1e22, fi.SITE_A, (0xF000, 0x7000, 0x3000)),   # cb * gamma beyond binary32, kra * cb * gamma not
+    (16, 1.7265625 * 2.0 ** -77, 1.7265625 * 2.0 ** -77, 300.0, fi.SITE_A, (0x0600, 0x0400, 0x0200)),   # kra * cb: 1.49 -> 1 unit of 2^-149
+    (64, 2.0 ** 20, 2.0 ** 20, 1e20, fi.SITE_A, (0x4000, 0x0080)),
+    (64, 2.0 ** 58, 2.0 ** -57, 1e22, fi.SITE_B, (0xF000, 0x7000, 0x3000)),
+])
+@pytest.mark.parametrize("bound", [fi.BOUND_ROWCOL, fi.BOUND_GLOBAL])
+def test_affected_records_at_extreme_thresholds(K, a, b, gamma, kind, masks, bound):
+    # thresholds whose factors leave the normal range on the way: the flags are those of the three
+    # roundings fl(fl(kra * cb) * gamma), as in the full campaign
+    M, N, fmt = 70, 200, orc.BF16
+    Aw = wl.to_words(np.full((M, K), a, np.float32), fmt)
+    Bw = wl.to_words(np.full((N, K), b, np.float32), fmt)
+    plan = gu.make_plan(Aw, Bw, 16, fmt, bound_mode=bound, gamma=gamma)
+    rows = [(kind, r, c, 0, m) for m in masks for r, c in ((0, 0), (K - 1, K // 2), (5, K - 1))]
+    faults = orc.make_faults(rows)
+    want = gu.gpu_campaign(plan, faults, wl.CORRECT_ZERO)
+    d_r = fi.empty_results(len(faults))
+    plan.fi_gemm_inject_batch_affected(fi.to_device(faults), len(faults), wl.CORRECT_ZERO, d_r)
+    got = fi.results_to_host(d_r)
+    assert got.tobytes() == want.tobytes(), [(faults[t], got[t], want[t]) for t in range(len(faults)) if got[t] != want[t]][:3]
+    if gamma == 1e22:
+        assert (want["n_flagged"] > 0).any()
+    plan.destroy()
