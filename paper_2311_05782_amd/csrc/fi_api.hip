@@ -62,6 +62,7 @@ struct BatchScratch {
   uint32_t* perm = nullptr;   // [cap] trial order + 2 counters behind it; start of the allocation
   uint32_t* desc = nullptr;   // [(cap + 16) * kMultiDescWords], in the same allocation
   uint32_t cap = 0;
+  bool own = false;           // an allocation of its own, else part of the plan's
 };
 
 struct fi_plan {
@@ -91,6 +92,7 @@ struct fi_plan {
   int group = 32;                    // trials sharing a tile back to back
   bool auto_cfg = true;              // no fi_plan_tune has chosen a tile configuration
   int device = 0;
+  uint32_t* first_scratch = nullptr; // for kFirstTrials trials on the first stream that asks
   std::vector<BatchScratch> batch;   // per stream, see BatchScratch
   int n_cus = 8;                     // compute units of the device: grid of the persistent kernel
   int product_check = FI_PCHECK_NONE;
@@ -326,13 +328,20 @@ void free_plan_buffers(fi_plan* p) {
   if (p->memory) (void)hipFree(p->memory);
   p->memory = nullptr;
   for (BatchScratch& b : p->batch)
-    if (b.perm) (void)hipFree(b.perm);
+    if (b.own) (void)hipFree(b.perm);
   p->batch.clear();
 }
 
+// Trials that the scratch inside the plan's own allocation holds (58 KB).
+constexpr uint32_t kFirstTrials = 2048;
+size_t scratch_head(uint32_t n) { return ((size_t)n + 2 + 63) / 64 * 64; }   // words; desc starts 256-byte aligned
+size_t scratch_words(uint32_t n) { return scratch_head(n) + ((size_t)n + 16) * fi::kMultiDescWords; }
+
 // The batch scratch of `stream`, holding at least n trials.  Allocates on the first batch of a
 // stream and when a batch is larger than any before on it (the replaced buffers are freed,
-// which waits for device work that may still read them).
+// which waits for device work that may still read them); not for up to kFirstTrials trials on the plan's
+// first stream.  Batches of the small kernels do not use it but size it all the same: a tile
+// configuration chosen later sends the same batch to the multi-trial kernel, which must not allocate then.
 fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch** out) {
   BatchScratch* b = nullptr;
   for (BatchScratch& x : p->batch)
@@ -342,14 +351,19 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
     p->batch.emplace_back();
     b = &p->batch.back();
     b->stream = stream;
+    if (p->batch.size() == 1) {
+      b->perm = p->first_scratch;
+      b->desc = b->perm + scratch_head(kFirstTrials);
+      b->cap = kFirstTrials;
+    }
   }
   if (b->cap < n) {
-    if (b->perm) (void)hipFree(b->perm);
-    b->perm = nullptr; b->desc = nullptr; b->cap = 0;
-    const size_t head = ((size_t)n + 2 + 63) / 64 * 64;   // desc starts 256-byte aligned
-    FI_HIP(hipMalloc(&b->perm, (head + ((size_t)n + 16) * fi::kMultiDescWords) * sizeof(uint32_t)));
-    b->desc = b->perm + head;
+    if (b->own) (void)hipFree(b->perm);
+    b->perm = nullptr; b->desc = nullptr; b->cap = 0; b->own = false;
+    FI_HIP(hipMalloc(&b->perm, scratch_words(n) * sizeof(uint32_t)));
+    b->desc = b->perm + scratch_head(n);
     b->cap = n;
+    b->own = true;
   }
   *out = b;
   return FI_OK;
@@ -405,7 +419,7 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   p->kshift = d.K % 64 ? 64 - d.K % 64 : 0;
   const uint32_t kp = d.K + p->kshift;
   // One allocation: C* with its padding and the scratch words behind it (zeroed together), S, the
-  // statistics, and the operand copies that this problem needs.
+  // statistics, the operand copies that this problem needs, and a first batch scratch.
   size_t bytes = 0;
   auto place = [&](size_t n) {
     const size_t at = bytes;
@@ -417,6 +431,7 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   const size_t at_bt = place(d.b_layout ? (size_t)d.N * d.K * sizeof(uint16_t) : 0);
   const size_t at_ap = place(p->kshift ? (size_t)d.M * kp * sizeof(uint16_t) : 0);
   const size_t at_bp = place(p->kshift ? (size_t)d.N * kp * sizeof(uint16_t) : 0);
+  const size_t at_scratch = place(scratch_words(kFirstTrials) * sizeof(uint32_t));
   FI_HIP(hipMalloc(&p->memory, bytes));
   uint8_t* const base = static_cast<uint8_t*>(p->memory);
   p->c_star = reinterpret_cast<float*>(base + at_c);
@@ -424,6 +439,7 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   p->s_abs = reinterpret_cast<float*>(base + at_s);
   p->kra = reinterpret_cast<float*>(base + at_kra);
   p->cb = reinterpret_cast<float*>(base + at_cb);
+  p->first_scratch = reinterpret_cast<uint32_t*>(base + at_scratch);
   const size_t zeros = mn_pad + 8 - mn;
   hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)(zeros < 262144 ? (zeros + 255) / 256 : 1024)), dim3(256), 0, s,
                      reinterpret_cast<uint32_t*>(p->c_star + mn), zeros, 0u);
@@ -831,7 +847,7 @@ fi_status fi_gemm_inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t
   TrialScratch ts;
   if (plan->mcfg >= 0) {
     BatchScratch* bs = nullptr;
-    st = batch_scratch(plan, as_stream(stream), use_small(plan, n_trials) ? 0 : n_trials, &bs);
+    st = batch_scratch(plan, as_stream(stream), n_trials, &bs);
     if (st != FI_OK) return st;
     ts.perm = bs->perm; ts.counts = bs->perm + bs->cap; ts.desc = bs->desc;
   }
@@ -848,7 +864,7 @@ fi_status fi_gemm_inject_batch_act(fi_plan* plan, const fi_fault* d_faults, uint
     return fail(FI_UNSUPPORTED, "the fused hand-over is not available with tile_config 2; use fi_gemm_inject_batch "
                 "with d_c_out and fi_activation_round");
   BatchScratch* bs = nullptr;
-  st = batch_scratch(plan, as_stream(stream), use_small(plan, n_trials) ? 0 : n_trials, &bs);
+  st = batch_scratch(plan, as_stream(stream), n_trials, &bs);
   if (st != FI_OK) return st;
   TrialScratch ts;
   ts.perm = bs->perm; ts.counts = bs->perm + bs->cap; ts.desc = bs->desc;

@@ -72,6 +72,44 @@ def test_reserve_then_capture_without_an_eager_call_first():
     plan.destroy()
 
 
+@pytest.mark.parametrize("fused", [False, True])
+def test_a_batch_no_larger_than_any_before_allocates_nothing_whatever_configuration_was_chosen_since(fused):
+    # warm up with the batch, choose a tile configuration, capture the same batch: an allocation
+    # inside the capture would be an error.  200 trials fit the plan's own scratch, 3000 do not.
+    import torch
+    w = wl.tiny()
+    for n in (200, 3000):
+        plan = gu.make_plan(w.A, w.B, w.kb, w.fmt)
+        faults = fi.fi_sample_faults(9, 0, n, plan.desc, fi.KIND_MIX_ACC_A, 1)
+        d_f, d_r = fi.to_device(faults), fi.empty_results(n)
+        d_h = torch.empty((n, w.M, w.N), dtype=torch.int16, device="cuda") if fused else None
+
+        def call(stream=None):
+            if fused:
+                plan.fi_gemm_inject_batch_act(d_f, n, fi.CORRECT_ZERO, d_r, d_h, stream=stream)
+            else:
+                plan.fi_gemm_inject_batch(d_f, n, fi.CORRECT_ZERO, d_r, stream=stream)
+        sides = [torch.cuda.Stream(), torch.cuda.Stream()]
+        for side in sides:
+            call(side)
+        torch.cuda.synchronize()
+        want, want_h = fi.results_to_host(d_r).tobytes(), d_h.clone() if fused else None
+        plan.tune(6)
+        for side in sides:
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.stream(side):
+                with torch.cuda.graph(g, stream=side):
+                    call(torch.cuda.current_stream().cuda_stream)
+            for rep in range(3):
+                d_r.zero_()
+                torch.cuda.synchronize()
+                g.replay()
+                torch.cuda.synchronize()
+                assert fi.results_to_host(d_r).tobytes() == want, (n, rep)
+                assert not fused or torch.equal(d_h, want_h)
+        plan.destroy()
+
+
 @pytest.mark.parametrize("cfg", [0, 1, 2, 3, 4, 5, 6])
 @pytest.mark.parametrize("fmt", [orc.FP16, orc.BF16])
 def test_rows_of_all_maximal_same_sign_products_are_never_flagged(cfg, fmt):
