@@ -265,9 +265,9 @@ __device__ __forceinline__ void affected_rows_item(const GemmArgs& p, uint8_t* s
   const __amdgpu_buffer_rsrc_t rsrc_g = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Gp), 0, (int)g_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Xp), 0, (int)x_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsrc_c = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.c_star), 0, (int)p.c_star_bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rsrc_s = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.s_abs), 0, (int)p.c_star_bytes, 0x00020000);
-  // element (row, col) of C* and of the magnitude sums, as row part + column part in bytes; both
-  // arrays are padded to whole tiles: what lies outside the problem is read but not counted
+  const __amdgpu_buffer_rsrc_t rsrc_s = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.s_abs), 0, (int)((uint32_t)p.M * (uint32_t)p.N * 4u), 0x00020000);
+  // element (row, col) of C* and of the magnitude sums, as row part + column part in bytes.  C* is
+  // padded to whole tiles, loads of the sums past their end give 0: neither is counted
   auto golden = [&](uint32_t row, uint32_t col, float& cs, float& sa) __attribute__((always_inline)) {
     if constexpr (!BIG) {
       const uint32_t at = (row * (uint32_t)p.N + col) * 4u;

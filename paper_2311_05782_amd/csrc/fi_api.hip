@@ -78,7 +78,7 @@ struct fi_plan {
   uint16_t* Bpad = nullptr;
   uint32_t kshift = 0;
   float* c_star = nullptr;           // [M][N]
-  float* s_abs = nullptr;            // [M][N], allocated like c_star
+  float* s_abs = nullptr;            // [M][N]
   float* kra = nullptr;              // [pad(M)]
   float* cb = nullptr;               // [pad(N)]
   float* scratch = nullptr;          // 4 floats + 4 words: maxima, what plan_stats_kernel found, clean flags
@@ -413,7 +413,8 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   const size_t mn = (size_t)d.M * d.N;
   // C* is padded to whole 256-row tiles plus one tile width (zeros): the next layer's kernel
   // reads the tile-shaped neighbourhood of its outputs without clamping rows or columns, and so
-  // does the affected-only campaign with both arrays (what it reads past the sums is not used).
+  // does the affected-only campaign (its loads of the sums end at the last one: for one row of 2^18
+  // columns padding both would take 1 GiB instead of 0.5).
   const size_t mn_pad = golden_elems(d);
   p->A = static_cast<const uint16_t*>(d_A);
   p->kshift = d.K % 64 ? 64 - d.K % 64 : 0;
@@ -426,7 +427,7 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
     bytes += (n + 255) / 256 * 256;
     return at;
   };
-  const size_t at_c = place((mn_pad + 8) * sizeof(float)), at_s = place(mn_pad * sizeof(float));
+  const size_t at_c = place((mn_pad + 8) * sizeof(float)), at_s = place(mn * sizeof(float));
   const size_t at_kra = place(padded(d.M) * sizeof(float)), at_cb = place(padded(d.N) * sizeof(float));
   const size_t at_bt = place(d.b_layout ? (size_t)d.N * d.K * sizeof(uint16_t) : 0);
   const size_t at_ap = place(p->kshift ? (size_t)d.M * kp * sizeof(uint16_t) : 0);

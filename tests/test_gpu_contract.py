@@ -110,6 +110,27 @@ def test_a_batch_no_larger_than_any_before_allocates_nothing_whatever_configurat
         plan.destroy()
 
 
+def test_a_plan_of_few_rows_takes_little_more_than_its_padded_result():
+    # C* is padded to 512 rows; nothing else of the plan is
+    import torch
+    M, N, K = 1, 1 << 18, 16
+    Aw, Bw = wl.small_integers(M, N, K, orc.BF16, seed=1, lim=2, step=1)
+    d_A, d_B = fi.words_to_device(Aw), fi.words_to_device(Bw)
+    gu.make_plan(Aw, Bw[:64], 16, orc.BF16).destroy()              # the library's own state is there
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    plan = fi.Plan(fi.plan_desc(M, N, K, 16, orc.BF16), d_A, d_B)
+    torch.cuda.synchronize()
+    used = before - torch.cuda.mem_get_info()[0]
+    assert used < 1.1 * 512 * N * 4, used
+    # and the affected-only campaign reads no more of the sums than there is
+    faults = orc.make_faults([(orc.SITE_A, 0, 3, 0, 0x8000), (orc.SITE_B, 2, N - 1, 0, 0x8000), (orc.SITE_ACC, 0, N - 1, 0, 1 << 30)])
+    d_r = fi.empty_results(3)
+    plan.fi_gemm_inject_batch_affected(fi.to_device(faults), 3, wl.CORRECT_ZERO, d_r)
+    assert fi.results_to_host(d_r).tobytes() == gu.gpu_campaign(plan, faults, wl.CORRECT_ZERO).tobytes()
+    plan.destroy()
+
+
 @pytest.mark.parametrize("cfg", [0, 1, 2, 3, 4, 5, 6])
 @pytest.mark.parametrize("fmt", [orc.FP16, orc.BF16])
 def test_rows_of_all_maximal_same_sign_products_are_never_flagged(cfg, fmt):
