@@ -297,18 +297,22 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
   auto issue_tile = [&](int kt, int buf) __attribute__((always_inline)) {
     const int k0 = kt * BK;
     uint8_t* const s = smem + buf * STAGE + wave * 1024;
-    static_for<G_W>([&](auto cc) {
-      constexpr int c = cc;
-      const int ch = (lslot ^ lds_swizzle((c * 4 + wave) * 8 + lrow)) * 8;
-      // in a ragged last tile, chunks past K are fetched from the start of their row and never used
-      const bool whole = k0 + BK <= p.K;                  // uniform
-      const uint32_t off = whole ? goff[c] : k0 + ch < p.K ? goff[c] + 2u * (uint32_t)k0 : goff[c] - 2u * (uint32_t)ch;
-      const int soff = whole ? k0 * 2 : 0;
-      if constexpr (c == 0)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (lds_void*)(s + c * 4096), 16, (int)off, soff, 0, 0);
-      else
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, (lds_void*)(s + c * 4096), 16, (int)off, soff, 0, 0);
-    });
+    // Two copies behind a uniform branch: with the lane's and the scalar offset chosen by one condition in
+    // one copy, the scalar one landed in a vector register and every load in a loop over its values.
+    if (k0 + BK <= p.K) {
+      static_for<G_W>([&](auto cc) {
+        constexpr int c = cc;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(c == 0 ? rsrc_a : rsrc_b, (lds_void*)(s + c * 4096), 16, (int)goff[c], k0 * 2, 0, 0);
+      });
+    } else {
+      // a ragged last tile: chunks past K are fetched from the start of their row and never used
+      static_for<G_W>([&](auto cc) {
+        constexpr int c = cc;
+        const int ch = (lslot ^ lds_swizzle((c * 4 + wave) * 8 + lrow)) * 8;
+        const uint32_t off = k0 + ch < p.K ? goff[c] + 2u * (uint32_t)k0 : goff[c] - 2u * (uint32_t)ch;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(c == 0 ? rsrc_a : rsrc_b, (lds_void*)(s + c * 4096), 16, (int)off, 0, 0, 0);
+      });
+    }
   };
   const int nkt = (p.K + BK - 1) / BK, n_steps = p.K / 16;
   for (int kt = 0; kt < min(NBUF - 1, nkt); ++kt) issue_tile(kt, kt);
@@ -327,6 +331,7 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
     if (NBUF == 4 && later == 2) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * G_W & 15) | (2 * G_W >> 4 << 14));
     else if (later >= 1) __builtin_amdgcn_s_waitcnt(0x0F70 | G_W);
     else __builtin_amdgcn_s_waitcnt(0x0F70);
+    __builtin_amdgcn_s_waitcnt(0xC07F);                   // lgkmcnt(0): no read of the tile before is in flight
     // after the barrier the tile is there for all, and nobody reads the tile before it any more
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_s_barrier();
