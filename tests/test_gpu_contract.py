@@ -91,6 +91,7 @@ def test_a_batch_no_larger_than_any_before_allocates_nothing_whatever_configurat
                 plan.fi_gemm_inject_batch(d_f, n, fi.CORRECT_ZERO, d_r, stream=stream)
         sides = [torch.cuda.Stream(), torch.cuda.Stream()]
         for side in sides:
+            torch.cuda.synchronize()                               # both write the same records
             call(side)
         torch.cuda.synchronize()
         want, want_h = fi.results_to_host(d_r).tobytes(), d_h.clone() if fused else None
