@@ -101,20 +101,32 @@ struct fi_plan {
 
 namespace {
 
-// Where one wave per (trial, 32 x 32 tile) stops paying, in its MFMA steps per SIMD.  Measured against
-// the multi-trial kernel, accumulator faults: 288 steps (4 trials of 512 x 3072 x 768) 22 : 32 us, 220
-// (32 of 3136 x 64 x 576) 20 : 27, 385 (512 of 300 x 203 x 176) 46 : 41, 512 (8 of 1024^3) 33 : 30;
-// batches with operand faults, two launches there, cross at some 800.
+// Where one wave per (trial, 32 x 32 tile) stops paying, in its MFMA steps per SIMD: K = 576, 3136 x 64, 46
+// trials (317 steps) 29 : 31 us against the multi-trial kernel.
 constexpr double kSmallSteps = 320.0;
+// With short K a tile's fixed part - first loads, detector, counters - is most of it, which the eight trials
+// of the multi-trial kernel share, on 64 x 64 tiles.  Small while
+//   tiles per SIMD <= first + share * (that kernel's, in units of 32 x 32) + 5 per 1000 trials (partition):
+// `first` is what its two more launches cost, without outputs 15 (K = 64, 1000 x 1003, accumulator faults: 15
+// tiles 23 : 25 us, 27 tiles 30 : 26; K = 128, 1024^2: 22 tiles 31 : 26); its tiles cost 0.4 as much, and more with
+// outputs (K = 16, 2000^2, FP32: 39 tiles 68 : 131 us, 140 tiles 190 : 199).  Chosen on 14149 random batches of up
+// to 320 steps, all kinds and outputs, both kernels timed: the choice costs 0.3 % against the better of the two
+// on average (always small 1.0 %, 3.2 % of the batches over 5 % slower, the worst 2.9 times; now 0.9 % of
+// them).  The host does not know the kinds: with operand faults, two launches there, the lines lie higher.
+constexpr double kSmallTiles = 15.0, kSmallTilesOut = 25.0, kSmallShare = 0.4, kSmallShareC = 0.5, kSmallShareH = 0.75;
 // MFMA steps of one trial up to which its workgroup, on one CU, does not take longer than the launch it
 // saves: 64 trials of 128^3 (128 steps) 8.8 : 10.6 us, of 128 x 128 x 512 13.3 : 11.8; with outputs to
 // store 33 x 59 x 48 (12 steps) 9.4 : 10.7, 128^3 11.6 : 11.1.  Not beyond a trial per CU: 256 of 33 x 59 x
 // 48 7.6 : 10.6, 512 12.0 : 10.5.
 constexpr uint32_t kTrialSteps = 128, kTrialStepsOut = 16;
-// The same for the next layer's batches, whose trials share nothing but B (columns counted in whole
-// strips of four tiles).  Measured against the persistent kernel: 100 steps (32 trials of 300 x 200 x 640)
-// 20 : 25 us, 128 (128 of 128 x 128 x 1024) 22 : 31, 144 (2 of 512 x 768 x 3072) 37 : 51, 200 (64 of the
-// first) 32 : 29, 256 (256 of the second) 35 : 34.
+// The same for the next layer's batches, whose trials share nothing but B: a workgroup per strip of 32 rows x
+// 128 columns, two resident per CU.  Up to 160 steps per SIMD, counted in whole strips, while
+//   rounds of resident workgroups <= first + weight * (the other kernel's tiles, in 128 x 128, per two on a CU).
+// Persistent kernel: first = 1 (K = 768, 512 x 768: 4 trials, 0.8 rounds, 17 : 23 us, 6 trials, 1.1 rounds, 27 : 24), 5
+// where it also stores outputs (K = 576, 64 x 3136, 20 trials: 44 : 49), weight 2 (K = 256, 512^2: 15 trials 15 : 20, 27
+// trials 36 : 23).  One-trial kernel, K not a multiple of 64: 1 and 4 (K = 16, 3648 x 31, 330 trials 348 : 134).  Chosen on
+// 9850 random batches: over 5 % slower than the other kernel 2.4 % of them, 7.3 % without the second line.
+// Not beyond K = 8192, a chain of k-tiles (16 x 16 x 4096 38 : 44, x 16384 127 : 113).
 constexpr double kSmallPropagate = 160.0;
 // The same for the plan's fault-free pass, which has two results (see compute_golden).
 constexpr double kSmallSums = 768.0;
@@ -172,16 +184,34 @@ double small_steps(const fi_plan* p, uint32_t n_trials) {
 }
 
 // Batches that gemm_fi_small_kernel serves, unless the caller has chosen a tile configuration.
-bool use_small(const fi_plan* p, uint32_t n_trials) {
-  return p->auto_cfg && small_steps(p, n_trials) <= kSmallSteps;
+bool use_small(const fi_plan* p, uint32_t n_trials, bool c_out, bool h_out) {
+  const fi_plan_desc& d = p->d;
+  if (!p->auto_cfg || small_steps(p, n_trials) > kSmallSteps) return false;
+  if (n_trials <= 2) return true;                        // they fill a quarter of a group of eight at most
+  const double simds = 4.0 * p->n_cus, n = (double)n_trials;
+  const double tiles = (double)((d.M + 31) / 32) * ((d.N + 31) / 32) * ((n_trials + 3) / 4 * 4) / simds;
+  const double theirs = 4.0 * ((d.M + 63) / 64) * ((d.N + 63) / 64) * ((n_trials + 7) / 8 * 8) / simds;
+  return tiles <= (c_out || h_out ? kSmallTilesOut : kSmallTiles) +
+                      (h_out ? kSmallShareH : c_out ? kSmallShareC : kSmallShare) * theirs + 0.005 * n;
+}
+
+// The same for the next layer; persistent: the other kernel is the persistent one.
+bool use_small_propagate(const fi_plan* p, uint32_t n_trials, bool c_out, bool persistent) {
+  const fi_plan_desc& d = p->d;
+  const double strips = (double)((d.N + 127) / 128 * 4) / ((d.N + 31) / 32);
+  if (!p->auto_cfg || small_steps(p, n_trials) * strips > kSmallPropagate || d.K > 8192) return false;
+  const double rounds = (double)n_trials * ((d.M + 31) / 32) * ((d.N + 127) / 128) / (2.0 * p->n_cus);
+  const int bm = persistent ? kMulti[p->prop_cfg].bm : kCfg[p->cfg].bm, bn = persistent ? kMulti[p->prop_cfg].bn : kCfg[p->cfg].bn;
+  const double theirs = (double)n_trials * ((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * (bm * bn / 16384.0) / (2.0 * p->n_cus);
+  return rounds <= (persistent && c_out ? 5.0 : 1.0) + (persistent ? 2.0 : 4.0) * theirs;
 }
 
 // Batches that gemm_fi_trial_kernel serves.
-bool use_trial(const fi_plan* p, uint32_t n_trials, bool outputs) {
+bool use_trial(const fi_plan* p, uint32_t n_trials, bool c_out, bool h_out) {
   const fi_plan_desc& d = p->d;
-  if (!use_small(p, n_trials) || n_trials > (uint32_t)p->n_cus || d.M > 512 || d.N > 512) return false;
+  if (!use_small(p, n_trials, c_out, h_out) || n_trials > (uint32_t)p->n_cus || d.M > 512 || d.N > 512) return false;
   const uint32_t tiles = ((d.M + 31) / 32) * ((d.N + 31) / 32);
-  return tiles <= 16 && tiles * (d.K / 16) <= (outputs ? kTrialStepsOut : kTrialSteps);
+  return tiles <= 16 && tiles * (d.K / 16) <= (c_out || h_out ? kTrialStepsOut : kTrialSteps);
 }
 
 GemmArgs base_args(const fi_plan* p, int cfg = -1) {
@@ -572,7 +602,7 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
     g->policy = (int)policy;
     g->product_check = plan->product_check;
   }
-  if (use_trial(plan, n_trials, d_c_out || d_h_out)) {
+  if (use_trial(plan, n_trials, d_c_out != nullptr, d_h_out != nullptr)) {
     a.tiles_m = (a.M + 31) / 32;
     a.tiles_n = (a.N + 31) / 32;
     const size_t lds = (size_t)2 * (a.tiles_m + a.tiles_n) * 32 * 128;
@@ -587,7 +617,7 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
   hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)((words + 255) / 256 > 1024 ? 1024 : (words + 255) / 256)),
                      dim3(256), 0, s, reinterpret_cast<uint32_t*>(d_results), words, 0u);
   FI_HIP(hipGetLastError());
-  if (use_small(plan, n_trials)) {
+  if (use_small(plan, n_trials, d_c_out != nullptr, d_h_out != nullptr)) {
     a.tiles_m = (a.M + 31) / 32;
     a.tiles_n = (a.N + 31) / 32;
     if (plan->d.dtype == FI_BF16) launch_small<FI_BF16>(a, s); else launch_small<FI_FP16>(a, s);
@@ -824,8 +854,8 @@ fi_status fi_plan_describe(const fi_plan* plan, char* h_buf, uint64_t n) {
   const TileCfg c = kCfg[plan->cfg];
   const char* dt = plan->d.dtype == FI_BF16 ? "bf16" : "fp16";
   char small[128] = "";
-  if (use_small(plan, 1))
-    snprintf(small, sizeof(small), "; batches of up to %u trials: gemm_fi_small_kernel<%s, one trial per wave, 32x32>",
+  if (use_small(plan, 1, false, false))
+    snprintf(small, sizeof(small), "; small batches, at most %u trials: gemm_fi_small_kernel<%s, one trial per wave, 32x32>",
              (unsigned)(kSmallSteps / small_steps(plan, 1)), dt);
   if (plan->mcfg >= 0) {
     const MultiCfg m = kMulti[plan->mcfg];
@@ -951,9 +981,9 @@ fi_status fi_gemm_propagate_batch(fi_plan* plan, const void* d_a_stack, uint64_t
                 (unsigned long long)trial_stride);
   GemmArgs a = base_args(plan);
   // C* is addressed with 32 bits; the trials' operands are the caller's, so K must hold whole k-tiles
-  const double strips = (double)((plan->d.N + 127) / 128 * 4) / ((plan->d.N + 31) / 32);
-  const bool small = plan->auto_cfg && small_steps(plan, n_trials) * strips <= kSmallPropagate;
-  const bool persistent = !small && plan->prop_cfg >= 0 && a.c_star_bytes != 0 && plan->kshift == 0;
+  bool persistent = plan->prop_cfg >= 0 && a.c_star_bytes != 0 && plan->kshift == 0;
+  const bool small = use_small_propagate(plan, n_trials, d_c_out != nullptr, persistent);
+  persistent = persistent && !small;
   if (persistent) {
     const MultiCfg mc = kMulti[plan->prop_cfg];
     a.tiles_m = (a.M + mc.bm - 1) / mc.bm;
