@@ -113,8 +113,16 @@ __device__ __forceinline__ uint32_t divmod_small(uint32_t x, uint32_t d, float i
 // Measured, one row at a time -> flat: 128 x 3136 x 64 with flags 240 -> 24 us (5.3 TB/s), 100 x 1000 x
 // 1003 without 214 -> 70 us (5.8 TB/s), 16 x 4096 x 4096 without 170 -> 168 us (6.4 TB/s); 8 x 3136 x 64
 // with flags 19 -> 11 us, counter fill included.
-// From one chunk of a workgroup to its next: the grid's span in elements, and the same split.
-struct DetectStep { size_t elems; uint32_t trial, row, col; };
+// Updates of the counters come one after the other, some 5 .. 11 ns each, and bound outputs with many flags.
+// On long rows (`together`) what the waves of a workgroup have flagged in a trial is left in LDS for the last of
+// them to add up: no barrier at the end, where waves that wait for each other cost 10 % of 100 x 1000 x 1003.
+// From one chunk of a workgroup to its next: the grid's span in elements, and that split into trials, rows and
+// columns.
+struct DetectStep { size_t elems; uint32_t trial, row, col, together; };
+// Finished trials' counts that a wave leaves, beside its last one; more are handed over at once.  UNROLL 1 has
+// one chunk per workgroup.
+template <int UNROLL>
+constexpr uint32_t kDetectSlots = UNROLL == 1 ? 0 : 7;
 template <int VEC, bool ROW4, int UNROLL>
 __global__ void __launch_bounds__(256) detect_correct_kernel(
     float* __restrict__ C, uint32_t batch, uint32_t M, uint32_t N, const float* __restrict__ kra,
@@ -122,7 +130,15 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
     const float* __restrict__ c_star, uint8_t* __restrict__ flags, uint32_t* __restrict__ n_flagged,
     const DetectStep step) {
   static_assert(VEC == 4 || (VEC == 1 && !ROW4), "vectors of four or single elements");
-  constexpr uint32_t CHUNK = 256u * VEC * UNROLL;
+  constexpr uint32_t THREADS = 256, WAVES = THREADS / 64, CHUNK = THREADS * VEC * UNROLL;
+  // what the waves have flagged, trial by trial: entries 0 .. slots - 1, then what is left at the end
+  constexpr uint32_t SLOTS = kDetectSlots<UNROLL>;
+  __shared__ uint32_t kept_b[WAVES][SLOTS + 1], kept_n[WAVES][SLOTS + 1], arrived;
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  [[maybe_unused]] uint32_t slots = 0;
+  if (threadIdx.x == 0) arrived = 0;
+  const bool together = n_flagged != nullptr && step.together != 0;
+  bool fresh = together;
   const size_t total = (size_t)batch * M * N;
   const float inv_n = 1.0f / (float)N, inv_m = 1.0f / (float)M;
   // first element of this workgroup's chunk as (trial, row, column)
@@ -146,7 +162,7 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
     const bool one_row = c0 + CHUNK <= N;                 // uniform: the chunk lies in one row
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-      const uint32_t off = (u * 256u + threadIdx.x) * VEC;
+      const uint32_t off = (u * THREADS + threadIdx.x) * VEC;
       uint32_t col = c0 + off, row = r0, b = b0;
       if (!one_row) {
         row += divmod_small(c0 + off, N, inv_n, col);
@@ -177,9 +193,17 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
         v[u][0] = at + off < total ? __builtin_nontemporal_load(C + at + off) : 0.0f;
       }
     }
+    if (fresh) {
+      // arrived is 0 for all (uniform; the loads above are in flight meanwhile)
+      __builtin_amdgcn_s_waitcnt(0xC07F);                 // lgkmcnt(0)
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      fresh = false;
+    }
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-      const uint32_t off = (u * 256u + threadIdx.x) * VEC;
+      const uint32_t off = (u * THREADS + threadIdx.x) * VEC;
       const uint32_t col = col_of[u], row = row_of[u], b = b_of[u];
       uint32_t hit = 0;                                   // a byte per element
       bool any_past = false;
@@ -246,7 +270,15 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
               if (here) left &= ~(1u << (8 * e));
             }
             if (bb != run_b) {
-              if (run_n && (threadIdx.x & 63) == 0) atomicAdd(n_flagged + run_b, run_n);
+              if (run_n) {
+                bool kept = false;
+                if constexpr (SLOTS > 0) {
+                  kept = together && slots < SLOTS;
+                  if (kept && lane == 0) { kept_b[wave][slots] = run_b; kept_n[wave][slots] = run_n; }
+                  slots += kept ? 1u : 0u;
+                }
+                if (!kept && lane == 0) atomicAdd(n_flagged + run_b, run_n);
+              }
               run_b = bb;
               run_n = 0;
             }
@@ -263,7 +295,37 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
     r0 -= carry ? M : 0u;
     b0 += step.trial + carry;
   }
-  if (n_flagged && run_n && (threadIdx.x & 63) == 0) atomicAdd(n_flagged + run_b, run_n);
+  if (n_flagged && !together) {
+    if (run_n && lane == 0) atomicAdd(n_flagged + run_b, run_n);
+  } else if (together) {
+    // bits 0 .. 4: waves that are done; 8 + w: wave w has left something
+    const uint32_t mine = run_n != 0 || slots != 0 ? 256u << wave : 0u;
+    uint32_t before = 0;
+    if (lane == 0) {
+      if (mine) {
+        kept_b[wave][slots] = run_b; kept_n[wave][slots] = run_n;
+        for (uint32_t i = slots + 1; i <= SLOTS; ++i) kept_n[wave][i] = 0;
+      }
+      before = __hip_atomic_fetch_add(&arrived, 1u + mine, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    before = (uint32_t)__builtin_amdgcn_readfirstlane((int)before);
+    const uint32_t left = (before + mine) >> 8;
+    if ((before & 31u) != WAVES - 1u || left == 0) return;
+    // the last wave: entry i of wave w goes with entry i of the first wave that has the same trial there
+    for (uint32_t e = lane; e < (SLOTS + 1) * WAVES; e += 64) {
+      const uint32_t w = e / (SLOTS + 1), i = e % (SLOTS + 1), b = kept_b[w][i];
+      uint32_t n = (left >> w) & 1u ? kept_n[w][i] : 0u;
+      if (n != 0) {
+        bool first = true;
+        for (uint32_t v = 0; v < WAVES; ++v) {
+          const bool same = v != w && ((left >> v) & 1u) && kept_n[v][i] != 0 && kept_b[v][i] == b;
+          n += same ? kept_n[v][i] : 0u;
+          first &= !(same && v < w);
+        }
+        if (first) atomicAdd(n_flagged + b, n);
+      }
+    }
+  }
 }
 
 // Hand-over between two layers: h = RNE_fmt(relu(c)).  relu keeps a NaN and maps negatives

@@ -399,9 +399,16 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
   return FI_OK;
 }
 
-// Two chunks or more per workgroup only beyond 2 x 16384 chunks: 8192 and 32768 workgroups measured
-// within 3 % of it, 2048 up to 20 % slower on rows that no chunk fits.
+// Two chunks or more per workgroup, the same number for all of them, only beyond 16384 chunks: 8192 and 32768
+// workgroups measured within 3 % of it, 2048 up to 20 % slower on rows that no chunk fits, a workgroup
+// per chunk 18 % slower on 100 x 1000 x 1003 (84 : 71 us); neighbouring chunks instead of strided ones 2 %.
 constexpr size_t kDetectGrid = 16384;
+// Rows from which the waves of a workgroup hand over what they have flagged together.  With every element
+// flagged 4 x 4096 x 4096 took 755 us wave by wave and 202 together, 2048 x 2048 191 and 53 (with a
+// workgroup per row, before the flat walk, 392 and 98); with none flagged it costs up to 1 us where many
+// workgroups follow each other on a CU (128 x 3136 x 64 17.3 : 18.4), and short rows gained most from the flat
+// walk anyway (flagged throughout 1241 -> 130 us).
+constexpr uint32_t kDetectTogether = 1024;
 
 // The detector / corrector on [batch][M][N] outputs: whole vectors where the outputs (and flags)
 // are aligned for them and a vector spans two rows at most, else element by element.
@@ -416,13 +423,15 @@ hipError_t launch_detect(const fi_plan* p, float* d_c, uint32_t batch, uint32_t 
   const bool deep = total >= one * 4 * 8 * (size_t)p->n_cus;
   const size_t chunk = one * (deep ? 4 : 1);
   const size_t chunks = (total + chunk - 1) / chunk;
-  const dim3 grid((unsigned)(chunks < kDetectGrid ? chunks : kDetectGrid)), block(256);
+  const size_t rounds = (chunks + kDetectGrid - 1) / kDetectGrid;   // the same for every workgroup, or one less
+  const dim3 grid((unsigned)((chunks + rounds - 1) / rounds)), block(256);
   fi::DetectStep step;
   step.elems = grid.x * chunk;
   const size_t rows = step.elems / d.N;
   step.col = (uint32_t)(step.elems % d.N);
   step.row = (uint32_t)(rows % d.M);
   step.trial = (uint32_t)(rows / d.M);
+  step.together = vec && d.N % 4 == 0 && d.N >= kDetectTogether;
   const int global = d.bound_mode != FI_BOUND_ROWCOL;
 #define FI_DETECT(VEC, ROW4, UNROLL)                                                                               \
   hipLaunchKernelGGL((fi::detect_correct_kernel<VEC, ROW4, UNROLL>), grid, block, 0, s, d_c, batch, d.M, d.N, p->kra, \

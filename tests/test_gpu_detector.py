@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
     (1, 5, 1000, 0), (7, 5, 333, 0), (33, 7, 70, 0),                   # vectors over rows and trials
     (100, 64, 17, 0), (2, 4, 2049, 0), (257, 1028, 3, 0),              # whole vectors in a row
     (100, 64, 17, 1), (33, 7, 70, 2), (3, 4099, 2, 3),                 # buffers off alignment
-    (1000, 1003, 40, 0), (1000, 1004, 40, 0),                          # more chunks than workgroups
+    (1000, 1003, 70, 0), (1000, 1004, 70, 0), (100, 7, 25000, 2),      # more chunks than workgroups
+    (1, 1024, 3, 0), (3, 2052, 40, 0), (1000, 1028, 70, 0), (1, 1028, 65535, 0),   # waves that hand over together
 ])
 @pytest.mark.parametrize("bound", [fi.BOUND_ROWCOL, fi.BOUND_GLOBAL])
 def test_detector_equals_its_definition(M, N, batch, shift, bound):
