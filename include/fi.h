@@ -165,7 +165,8 @@ fi_status fi_plan_buffer(const fi_plan* plan, uint32_t which, const void** d_ptr
  *         alone and the operand-fault trials; the latter run in a second instantiation that
  *         XORs the faulted word in the fragment registers around the faulted trial's MFMAs.
  * While no tile_config has been chosen, batches too small to fill the chip run one wave per
- * (trial, 32x32 tile) instead (every fault kind, any K; fi_plan_describe says up to how many trials).
+ * (trial, 32x32 tile) instead (every fault kind, any K; at most as many trials as fi_plan_describe says, fewer where K is short),
+ * and those of the smallest problems one workgroup per trial.
  * trial_group: -1 keep, else how many trials (groups of R trials) of the same
  * output tile are scheduled next to each other, 1..4096.  Results do not depend on
  * either (every shape accumulates each element in the same order); `stream` is unused. */

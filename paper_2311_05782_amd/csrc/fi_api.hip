@@ -862,10 +862,16 @@ fi_status fi_plan_describe(const fi_plan* plan, char* h_buf, uint64_t n) {
   if (!h_buf || n == 0) return fail(FI_INVALID_ARG, "h_buf is NULL or n is 0");
   const TileCfg c = kCfg[plan->cfg];
   const char* dt = plan->d.dtype == FI_BF16 ? "bf16" : "fp16";
-  char small[128] = "";
-  if (use_small(plan, 1, false, false))
-    snprintf(small, sizeof(small), "; small batches, at most %u trials: gemm_fi_small_kernel<%s, one trial per wave, 32x32>",
-             (unsigned)(kSmallSteps / small_steps(plan, 1)), dt);
+  char small[256] = "";
+  if (use_small(plan, 1, false, false)) {
+    const unsigned most = (unsigned)(kSmallSteps / small_steps(plan, 1)), cus = (unsigned)plan->n_cus;
+    char trial[128] = "";
+    if (use_trial(plan, 1, false, false))
+      snprintf(trial, sizeof(trial), ", without outputs and at most %u trials: gemm_fi_trial_kernel<%s, one workgroup per trial>",
+               most < cus ? most : cus, dt);
+    snprintf(small, sizeof(small), "; small batches, at most %u trials: gemm_fi_small_kernel<%s, one trial per wave, 32x32>%s",
+             most, dt, trial);
+  }
   if (plan->mcfg >= 0) {
     const MultiCfg m = kMulti[plan->mcfg];
     if (m.r == 1)

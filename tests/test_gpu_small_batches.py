@@ -38,6 +38,8 @@ def test_small_batches_equal_the_multi_trial_kernel(shape, n, fmt):
             plan.tune(cfg)
             plan.set_product_check(check)
             assert ("gemm_fi_small_kernel" in plan.describe()) == (cfg < 0)
+            tiles = -(-M // 32) * -(-N // 32)               # one workgroup per trial: a wave per tile, few steps
+            assert ("gemm_fi_trial_kernel" in plan.describe()) == (cfg < 0 and tiles <= 16 and tiles * (K // 16) <= 128)
             faults = _faults(plan.desc, n, seed=7 * n + policy, kinds="eprcx" if n > 5 else "eprc")
             if n <= 2:                                  # every kind comes up
                 faults = np.concatenate([_faults(plan.desc, n, seed=n + policy, kinds=k) for k in "eprc"])
