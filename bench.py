@@ -323,7 +323,7 @@ def main():
                                     "kernel_ms_avg": round(sum(dms) / len(dms), 4), "batch": batch,
                                     "flagged": int(nfl.sum().item())}
         del c
-    # The affected-tiles-only campaign on the same batch: a different product (only what a fault can
+    # The affected-only campaign on the same batch: a different product (only what a fault can
     # reach is computed), reported as trials per second and never against the MFMA roof.
     if extras or args.campaigns:
         for _ in range(2):

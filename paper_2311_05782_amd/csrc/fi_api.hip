@@ -86,7 +86,7 @@ struct fi_plan {
   uint32_t n_clean_flagged = 0;      // elements of C* the plan's own detector flags
   bool plain_ok = false;             // the affected-only campaign's short comparison holds, see fi::kTinyFactor
   int cfg = 0;                       // index into kCfg
-  int cfg_affected = 0;              // index into kCfg: the tile shape that the affected-only campaign's batch limit counts
+  int cfg_affected = 0;              // index into kCfg: the tiles that the affected-only campaign's batch limit counts
   int mcfg = -1;                     // index into kMulti, or -1: every trial through the single-trial kernel
   int prop_cfg = -1;                 // index into kMulti for the next-layer batch, or -1: single-trial kernel
   int group = 32;                    // trials sharing a tile back to back
@@ -947,11 +947,14 @@ fi_status fi_gemm_inject_batch_affected(fi_plan* plan, const fi_fault* d_faults,
   if (policy > FI_CORRECT_RECOMPUTE) return fail(FI_INVALID_ARG, "unknown correction policy %u", policy);
   if (plan->n_clean_flagged != 0)
     return fail(FI_UNSUPPORTED, "the plan's detector flags %u element(s) of the fault-free result itself, which the "
-                "affected-tiles-only campaign would not count; use fi_gemm_inject_batch", plan->n_clean_flagged);
+                "affected-only campaign would not count; use fi_gemm_inject_batch", plan->n_clean_flagged);
+  // The largest batch is what it was when an operand fault took a workgroup per tile of its row or column:
+  // callers split their batches by it.  The kernels here take more.
   GemmArgs a = base_args(plan, plan->cfg_affected);
   const uint64_t slots = (uint64_t)(a.tiles_m > a.tiles_n ? a.tiles_m : a.tiles_n);
-  const uint64_t blocks = slots * n_trials;
-  if (blocks >= (1ull << 31)) return fail(FI_UNSUPPORTED, "tiles x trials exceeds 2^31 workgroups; split the batch");
+  if (slots * n_trials >= (1ull << 31))
+    return fail(FI_UNSUPPORTED, "%llu (a row or column in output tiles) x %u trials exceeds 2^31; split the batch",
+                (unsigned long long)slots, n_trials);
   hipStream_t s = as_stream(stream);
   a.n_trials = (int)n_trials;
   a.faults = d_faults;
