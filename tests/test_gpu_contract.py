@@ -49,11 +49,14 @@ def test_batches_of_one_plan_in_flight_on_two_streams_do_not_share_scratch():
     plan.destroy()
 
 
-def test_reserve_then_capture_without_an_eager_call_first():
+# cfg None: the smallest batches' own kernels; 6: record fill, partition and two multi-trial launches.  3000
+# trials are more than the scratch inside the plan holds: without the reserve the capture would allocate
+@pytest.mark.parametrize("cfg,n", [(None, 200), (6, 200), (6, 3000)])
+def test_reserve_then_capture_without_an_eager_call_first(cfg, n):
     import torch
     w = wl.tiny()
-    plan = gu.make_plan(w.A, w.B, w.kb, w.fmt)
-    n = 200
+    plan = gu.make_plan(w.A, w.B, w.kb, w.fmt, cfg=cfg)
+    assert ("gemm_fi_small_kernel" in plan.describe()) == (cfg is None)
     faults = fi.fi_sample_faults(9, 0, n, plan.desc, fi.KIND_MIX_ACC_A, 1)
     d_f, d_r = fi.to_device(faults), fi.empty_results(n)
     side = torch.cuda.Stream()

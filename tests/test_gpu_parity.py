@@ -409,15 +409,17 @@ def test_exponent_bound_detector_campaign_and_standalone(cfg):
     plan.destroy()
 
 
-def test_campaign_calls_replay_correctly_from_a_hip_graph():
+@pytest.mark.parametrize("cfg", [None, 6])               # the smallest batches' own kernels; the multi-trial launches
+def test_campaign_calls_replay_correctly_from_a_hip_graph(cfg):
     # The library clears records and counters with kernels, not memsets, so its calls can be
     # captured.  Replays are interleaved with eager work and synchronisations and every replay is
     # checked against the eager result.
     import torch
     w = wl.tiny()
-    plan = gu.make_plan(w.A, w.B, w.kb, w.fmt)
+    plan = gu.make_plan(w.A, w.B, w.kb, w.fmt, cfg=cfg)
+    assert ("gemm_fi_small_kernel" in plan.describe()) == (cfg is None)
     n = 256
-    faults = fi.fi_sample_faults(5, 0, n, plan.desc, fi.KIND_ALL_ACC, 1)
+    faults = fi.fi_sample_faults(5, 0, n, plan.desc, fi.KIND_ALL_ACC if cfg is None else fi.KIND_MIX_ACC_A, 1)
     d_f = fi.to_device(faults)
     d_r = fi.empty_results(n)
     d_cls = torch.empty(n, dtype=torch.uint8, device="cuda")
@@ -445,7 +447,7 @@ def test_campaign_calls_replay_correctly_from_a_hip_graph():
         assert np.array_equal(d_cnt.cpu().numpy(), want_cnt), rep
         # a different fault list through the same graph (the list lives in device memory)
         if rep == 1:
-            faults2 = fi.fi_sample_faults(6, 0, n, plan.desc, fi.KIND_ALL_ACC, 1)
+            faults2 = fi.fi_sample_faults(6, 0, n, plan.desc, fi.KIND_ALL_ACC if cfg is None else fi.KIND_MIX_ACC_A, 1)
             d_f.copy_(fi.to_device(faults2))
             plan.fi_gemm_inject_batch(d_f, n, fi.CORRECT_ZERO, d_r)
             plan.fi_classify(d_r, n, d_cls, d_cnt)

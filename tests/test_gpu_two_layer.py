@@ -280,18 +280,24 @@ def test_fused_hand_over_is_refused_where_the_one_trial_kernel_runs():
     plan.destroy()
 
 
-def test_the_chain_replays_correctly_from_a_hip_graph():
+# the small batches' own kernels; the multi-trial kernel and the persistent next layer
+@pytest.mark.parametrize("cfgs", [(None, None), (6, 1)])
+def test_the_chain_replays_correctly_from_a_hip_graph(cfgs):
     # The three calls clear their records with kernels and, once the stream's batch scratch is
     # reserved, allocate nothing, so the whole chain can be captured; replays alternate with eager work and are compared with the eager result.
     import torch
     fmt, kb = orc.BF16, 32
     Xw, W1w, W2w = wl.two_layer_mlp(M=128, D=64, H=192, fmt=fmt, seed=3)
     M, D, H = 128, 64, 192
-    plan1 = gu.make_plan(Xw, W1w, kb, fmt)
+    plan1 = gu.make_plan(Xw, W1w, kb, fmt, cfg=cfgs[0])
     d_hstar = torch.empty((M, H), dtype=torch.int16, device="cuda")
     fi.fi_activation_round(fmt, plan1.buffer_ptr(fi.BUF_C_STAR), M * H, d_hstar)
     torch.cuda.synchronize()
     plan2 = fi.Plan(fi.plan_desc(M, D, H, kb, fmt), d_hstar, fi.words_to_device(W2w))
+    if cfgs[1] is not None:
+        plan2.tune(cfgs[1])
+    for p, c in ((plan1, cfgs[0]), (plan2, cfgs[1])):
+        assert ("gemm_fi_small_kernel" in p.describe()) == (c is None)
     n = 40
     lists = [fi.fi_sample_faults(s, 0, n, plan1.desc, fi.KIND_MIX_ACC_A, 2) for s in (1, 2, 3)]
     d_f = fi.to_device(lists[0])

@@ -50,9 +50,11 @@ def test_noalloc_entry_point_equals_the_allocating_one_on_two_calls_in_a_row(cfg
     plan.destroy()
 
 
-def test_noalloc_entry_point_rejects_batches_beyond_its_scratch():
+@pytest.mark.parametrize("cfg", [None, 6])              # the small kernel, which uses no scratch; the multi-trial kernel
+def test_noalloc_entry_point_rejects_batches_beyond_its_scratch(cfg):
     Aw, Bw = wl.gaussian(64, 64, 64, orc.BF16, seed=1)
-    plan = gu.make_plan(Aw, Bw, 32, orc.BF16)
+    plan = gu.make_plan(Aw, Bw, 32, orc.BF16, cfg=cfg)
+    assert ("gemm_fi_small_kernel" in plan.describe()) == (cfg is None)
     n = 16385
     d_f = fi.to_device(np.zeros(n, fi.FAULT_DTYPE))
     d_r = fi.empty_results(n)
@@ -62,4 +64,21 @@ def test_noalloc_entry_point_rejects_batches_beyond_its_scratch():
     plan.fi_gemm_inject_batch_noalloc(d_f, 16384, wl.CORRECT_ZERO, d_r)      # the largest batch it takes
     recs = fi.results_to_host(d_r)[:16384]
     assert not recs["n_flagged"].any() and not recs["n_bitdiff"].any() and not recs["status"].any()
+    plan.destroy()
+
+
+@pytest.mark.parametrize("n", [16384, 8193])            # the whole scratch; one trial beyond the partition's short form
+def test_largest_batches_through_the_static_scratch_equal_the_allocating_ones(n):
+    M, N, K, kb, fmt = 64, 96, 80, 16, orc.BF16
+    Aw, Bw = wl.gaussian(M, N, K, fmt, seed=3)
+    plan = gu.make_plan(Aw, Bw, kb, fmt, cfg=6)
+    assert "gemm_fi_small_kernel" not in plan.describe()
+    faults = _mixed(plan, n, 21)
+    want = gu.gpu_campaign(plan, faults, wl.CORRECT_RECOMPUTE)
+    assert (want["site_word_before"][n - 64:] != 0).any() and want["n_bitdiff"].any()
+    d_r = fi.empty_results(n)
+    d_r.fill_(0xAB)
+    plan.fi_gemm_inject_batch_noalloc(fi.to_device(faults), n, wl.CORRECT_RECOMPUTE, d_r)
+    got = fi.results_to_host(d_r)
+    assert got.tobytes() == want.tobytes(), [t for t in range(n) if got[t] != want[t]][:5]
     plan.destroy()
