@@ -10,9 +10,9 @@
 //     trial r's element is the diagonal one, register r of lane r;
 //   - rows and columns: the faulted rows (columns) of 64 trials are gathered into one operand of
 //     64 rows, multiplied with the whole other operand.
-// Measured: 1024 accumulator faults on 4096^3 16 us (195 us with a 128 x 128 tile around every
-// element), 4096 trials on 512 x 3072 x 768, half of them A faults, 44 us (3990 us with a tile row
-// of 128 rows per operand fault).
+// Measured, a call among others: 1024 accumulator faults on 4096^3 14 us (195 .. 263 us with a 128 x 128
+// tile around every element), 4096 trials on 512 x 3072 x 768, half of them A faults, 48 us (4195 us with
+// a tile row of 128 rows per operand fault), all B faults 57 us (1088 us).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -220,9 +220,11 @@ __global__ void __launch_bounds__(64, 2) affected_element_kernel(const GemmArgs 
 // item, x slot), walking the x tiles with stride n_x_slots; a workgroup without an item leaves after
 // one look at the chunk's kinds.
 //
-// Bound, of 37 us for 2048 A faults x 3072 columns x K = 768: 23 us the k-tiles' latency and LDS reads
-// (1.5 KB per MFMA of a wave), 9 us the accounting of every element, 5 us the record updates.  64 x 128
-// by four waves takes 48 KB of LDS, three workgroups per CU cover each other.
+// Bound: the k-tiles' latency and LDS reads (1.5 KB per MFMA of a wave), then the accounting of every
+// element and the record updates: 37 us for 2048 A faults x 3072 columns x K = 768, 56 us for 4096 B
+// faults x 512 rows, whose accounting has no short form.  64 x 128 by four waves takes 48 KB of LDS, three
+// workgroups per CU cover each other; the 170 registers that leaves a wave are 10 too few (20 with 64-bit
+// addresses), spilled outside the k-loop.
 // The lanes of a wave lie along the columns of C in both cases, so that C* and the magnitude sums are
 // read in whole lines: A faults feed the MFMA G x X (a register is a trial, a lane an element of its
 // row), B faults X x G (a lane is a trial, its registers the elements of its column).

@@ -111,7 +111,7 @@ __device__ __forceinline__ uint32_t divmod_small(uint32_t x, uint32_t d, float i
 // elements of a lane share their row and their column factors are one aligned vector.
 // VEC == 1: any N and alignment.
 // Measured, one row at a time -> flat: 128 x 3136 x 64 with flags 240 -> 24 us (5.3 TB/s), 100 x 1000 x
-// 1003 without 214 -> 70 us (5.8 TB/s), 16 x 4096 x 4096 without 170 -> 168 us (6.4 TB/s); 8 x 3136 x 64
+// 1003 without 214 -> 70 us (5.8 TB/s), 16 x 4096 x 4096 without 160 us both (6.7 TB/s); 8 x 3136 x 64
 // with flags 19 -> 11 us, counter fill included.
 // Updates of the counters come one after the other, some 5 .. 11 ns each, and bound outputs with many flags.
 // On long rows (`together`) what the waves of a workgroup have flagged in a trial is left in LDS for the last of

@@ -115,7 +115,7 @@ constexpr double kSmallSteps = 320.0;
 // them).  The host does not know the kinds: with operand faults, two launches there, the lines lie higher.
 constexpr double kSmallTiles = 15.0, kSmallTilesOut = 25.0, kSmallShare = 0.4, kSmallShareC = 0.5, kSmallShareH = 0.75;
 // MFMA steps of one trial up to which its workgroup, on one CU, does not take longer than the launch it
-// saves: 64 trials of 128^3 (128 steps) 8.8 : 10.6 us, of 128 x 128 x 512 13.3 : 11.8; with outputs to
+// saves: 64 trials of 128^3 (128 steps) 8.8 : 10.6 us, of 128 x 128 x 512 13.3 : 10.8; with outputs to
 // store 33 x 59 x 48 (12 steps) 9.4 : 10.7, 128^3 11.6 : 11.1.  Not beyond a trial per CU: 256 of 33 x 59 x
 // 48 7.6 : 10.6, 512 12.0 : 10.5.
 constexpr uint32_t kTrialSteps = 128, kTrialStepsOut = 16;

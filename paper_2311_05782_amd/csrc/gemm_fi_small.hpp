@@ -11,10 +11,10 @@
 // k-tiles are loaded NBUF - 1 ahead; on larger batches the LDS (two 1 KB fragments per MFMA, where
 // eight trials per wave read a quarter of one).
 //
-// Measured, record fill included, multi-trial kernel -> this one: 64 trials on 128^3 25 -> 10 us, 24 on
-// 300 x 203 x 176 23 -> 10 us (with operand faults 40 -> 10 us, with outputs 47 -> 11 us), 32 on 3136 x
-// 64 x 576 27 -> 20 us, 16 on 64 x 64 x 4096 63 -> 40 us; without LDS, fragments straight from global
-// memory, the last two took 72 and 62 us (a fragment's 32 rows are 32 cache lines).
+// Measured, record fill included, multi-trial kernel -> this one: 24 trials on 300 x 203 x 176 22 -> 10 us
+// (A faults 27 -> 10 us, with outputs 48 -> 12 us), 32 on 3136 x 64 x 576 27 -> 22 us, 16 on 64 x 64 x
+// 4096 63 -> 32 us (40 us with the loads of a k-tile in loops, see issue_tile); without LDS, fragments
+// straight from global memory, the last two took 72 and 62 us (a fragment's 32 rows are 32 cache lines).
 //
 // The per-element arithmetic is that of gemm_fi_kernel: the same sequence of 16-wide MFMA steps in
 // ascending k, hence bit-identical results.
