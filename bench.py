@@ -27,8 +27,8 @@ MFMA_PEAK_TFLOPS = 2516.6     # 256 CUs x 4096 flop/clk/CU x 2.4 GHz, dense FP16
 # commands.  They describe the kernel sources whose digest is recorded with them and are not
 # reported for any other.
 TRAFFIC = {
-    "sources_sha256": "0d6e462ddb719a3157491fbe4b7151f768292301373c1a17c2fafaf509770011",
-    "fetch_bytes": 2.16826e6 * 2.0 * 1024,
+    "sources_sha256": "cfa618c5c105ecd502d13191bacd037ebdb277cfa0a4105d33b0c1a9994e8a07",
+    "fetch_bytes": 2.16827e6 * 2.0 * 1024,
     "write_bytes": 151.375 * 1.0 * 1024,
 }
 
