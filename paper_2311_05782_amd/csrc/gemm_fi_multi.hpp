@@ -45,6 +45,14 @@ constexpr int kMultiDescWords = 6;   // trial, row, col, event, w0, w1
 // so that they do not displace the operand panels in L2
 constexpr int kStreamStore = 2;
 
+// A 16-byte buffer store.  Where the very next instruction is a vector one that overwrites the data, the last
+// four lanes of a row of sixteen have stored the new value (seen on gfx950 with a v_mov in that place; the
+// compiler keeps the two apart only where the scalar offset is not a register), so the data stay for a moment.
+__device__ __forceinline__ void store_wide(u32x4 q, __amdgpu_buffer_rsrc_t to, int lane_off, int scalar_off) {
+  __builtin_amdgcn_raw_buffer_store_b128(q, to, lane_off, scalar_off, kStreamStore);
+  asm volatile("s_nop 1" ::"v"(q) : "memory");
+}
+
 // VAR: which part of the work this instantiation takes.
 enum { VAR_PLAIN = 0, VAR_OPERAND = 1, VAR_PROPAGATE = 2 };
 
@@ -599,8 +607,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
 #pragma unroll
                       for (int ps = 0; ps < 2; ++ps) {
                         const u32x4 q = *reinterpret_cast<const u32x4*>(scr + (8 * ps + (ln >> 3)) * 128 + (ln & 7) * 16);
-                        __builtin_amdgcn_raw_buffer_store_b128(
-                            q, rs, voff, (int)((tile_off + (uint32_t)(16 * half + 8 * ps) * (uint32_t)p.N) * 4u), kStreamStore);
+                        store_wide(q, rs, voff, (int)((tile_off + (uint32_t)(16 * half + 8 * ps) * (uint32_t)p.N) * 4u));
                       }
                     }
                   } else {
@@ -627,8 +634,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
 #pragma unroll
                     for (int ps = 0; ps < 2; ++ps) {
                       const u32x4 q = *reinterpret_cast<const u32x4*>(scr + (16 * ps + (ln >> 2)) * 64 + (ln & 3) * 16);
-                      __builtin_amdgcn_raw_buffer_store_b128(
-                          q, rs, voff, (int)((tile_off + (uint32_t)(16 * ps) * (uint32_t)p.N) * 2u), kStreamStore);
+                      store_wide(q, rs, voff, (int)((tile_off + (uint32_t)(16 * ps) * (uint32_t)p.N) * 2u));
                     }
                   } else {
 #pragma unroll
