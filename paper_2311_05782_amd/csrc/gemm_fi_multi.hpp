@@ -279,6 +279,8 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   // accumulator element, or its fragments hold the faulted operand word), else -1.
   int trial[R], hook_step[R];
   bool has_events = false;                               // some hook_step[r] >= 0
+  // Fields are read with all lanes active, never inside a condition on the lane: where the word has been
+  // spilled, a reload there fetches the active lanes only, and v_readlane takes another's.
   auto desc_field = [&](int r, int field) -> uint32_t {
     return (uint32_t)__builtin_amdgcn_readlane((int)desc_cur, r * kMultiDescWords + field);
   };
@@ -421,7 +423,8 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
     const int wl = isA ? (int)desc_field(r, 1) - cur.m0 - wm * WTM : (int)desc_field(r, 2) - cur.n0 - wn * WTN;
     const int sel_lane = (wl & 31) + 32 * ((k >> 3) & 1);
     const int sel_w = (k & 7) >> 1;
-    const uint32_t x = (lane == sel_lane) ? (desc_field(r, 4) & 0xFFFFu) << (16 * (k & 1)) : 0u;
+    const uint32_t mask = (desc_field(r, 4) & 0xFFFFu) << (16 * (k & 1));
+    const uint32_t x = lane == sel_lane ? mask : 0u;
     // Every register is named statically (a register picked through a run-time index or a
     // pointer to "the A or the B fragment" would move the fragments to scratch memory).
     const uint32_t xa = isA ? x : 0u, xb = isA ? 0u : x;
