@@ -224,9 +224,9 @@ fi_status fi_gemm_inject_batch_act(fi_plan* plan, const fi_fault* d_faults, uint
 
 /* fi_gemm_inject_batch for callers that cannot allocate device memory or synchronise: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments, same kernels, same records and outputs; the trial order, the part counts and the
+ * arguments, same kernels, same records and outputs; the part counts, the work counters and the
  * per-trial descriptors of the batch live in a static device array of the library (about
- * 460 KB per GPU, held until the process ends) instead of plan-owned buffers, so the call
+ * 400 KB per GPU, held until the process ends) instead of plan-owned buffers, so the call
  * allocates nothing and never synchronises.  Limits: n_trials <= 16384 (FI_UNSUPPORTED beyond);
  * every call on a GPU - whatever the plan or stream - uses that GPU's one array, which is
  * rewritten by each call's partition kernel before it is read, so calls that overlap on one

@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(256) pad_front16_kernel(const uint16_t* __rest
 
 // Splits a batch: trials the multi-trial GEMM kernel can take (no fault, an accumulator flip or
 // a product-term fault; out-of-range sites count as "no fault" and get status 1 in their zeroed
-// record) go to the front of perm in list order, all others (operand faults) behind them,
+// record) come first, in list order, all others (operand faults) behind them,
 // ordered by the tile row (A) or tile column (B) of a bm x bn tiling that their fault reaches.
 // counts = {front, back}.  For front position q, desc[6q .. 6q+5] = {trial, row, col, event,
 // w0, w1}: event = -1 for no fault, else the 16-wide MFMA step after which the accumulator
@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(256) pad_front16_kernel(const uint16_t* __rest
 // their site words (the operand word before and after) are written here.  B is [N][ldb], k contiguous.
 // kshift: zeros the GEMM kernel's operand copies carry in front of every row (K not a multiple of
 // 64): every event step moves up by kshift / 16; A, B, K here are the caller's unpadded operands.
-// One workgroup.
+// queue: the work counters of the two launches, cleared.  One workgroup.
 template <int DT>
 __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* __restrict__ f, uint32_t n,
                                                                uint32_t M, uint32_t N, uint32_t K, uint32_t kb,
@@ -402,9 +402,9 @@ __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* 
                                                                const uint16_t* __restrict__ B, uint32_t lda,
                                                                uint32_t ldb, int product_check_mode,
                                                                uint32_t bm, uint32_t bn, uint32_t kshift,
-                                                               uint32_t* __restrict__ perm,
                                                                uint32_t* __restrict__ counts,
                                                                uint32_t* __restrict__ desc,
+                                                               uint32_t* __restrict__ queue, uint32_t queue_words,
                                                                fi_trial_result* __restrict__ results) {
   __shared__ uint32_t total_fast;
   // Operand faults are ordered by the tile row (A) or tile column (B) their fault reaches, so
@@ -427,6 +427,7 @@ __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* 
     return major * kq + kt * kq / n_kt;
   };
   bucket[threadIdx.x] = 0;
+  for (uint32_t i = threadIdx.x; i < queue_words; i += 1024) queue[i] = 0;
   __syncthreads();
   const uint32_t chunk = (n + 1023) / 1024;
   const uint32_t lo = min(threadIdx.x * chunk, n), hi = min(lo + chunk, n);
@@ -543,7 +544,6 @@ __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* 
       d[0] = t; d[1] = x.row; d[2] = x.col; d[3] = ((kk + kshift) / 16) | 0x20000000u; d[4] = m16; d[5] = x.kind;
       results[t].site_word_before = w0;
       results[t].site_word_after = w0 ^ m16;
-      perm[n_fast + pos] = t;
       return;
     }
     uint32_t* d = desc + (size_t)q * 6;
@@ -560,7 +560,6 @@ __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* 
       d[3] = 0xFFFFFFFFu; d[4] = 0; d[5] = 0;
     }
     if (k == 3) results[t].status = 1;
-    perm[q] = t;
   };
   if (local) {
     const unsigned long long below = (1ull << lane) - 1ull;

@@ -5,6 +5,7 @@
 
 #include <atomic>
 #include <cstdarg>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -54,13 +55,12 @@ using fi::MultiCfg;
 
 }  // namespace
 
-// Trial order and descriptors of one batch of the multi-trial kernel.  One set per stream a
+// Counts and descriptors of one batch of the multi-trial kernel.  One set per stream a
 // plan's batches have been enqueued on: batches on the same stream follow each other, batches
 // on different streams may be in flight together and must not share this state.
 struct BatchScratch {
   hipStream_t stream = nullptr;
-  uint32_t* perm = nullptr;   // [cap] trial order + 2 counters behind it; start of the allocation
-  uint32_t* desc = nullptr;   // [(cap + 16) * kMultiDescWords], in the same allocation
+  uint32_t* words = nullptr;  // [scratch_words(cap)], see TrialScratch
   uint32_t cap = 0;
   bool own = false;           // an allocation of its own, else part of the plan's
 };
@@ -358,15 +358,16 @@ void free_plan_buffers(fi_plan* p) {
   if (p->memory) (void)hipFree(p->memory);
   p->memory = nullptr;
   for (BatchScratch& b : p->batch)
-    if (b.own) (void)hipFree(b.perm);
+    if (b.own) (void)hipFree(b.words);
   p->batch.clear();
 }
 
 // Trials that the scratch inside the plan's own allocation holds (8 KB).  Not more: an allocation that it
 // takes past 2 MiB costs 27 us more to make and give back (a layer of 1010 x 161 x 272 with 58 KB 75 -> 102 us).
 constexpr uint32_t kFirstTrials = 256;
-size_t scratch_head(uint32_t n) { return ((size_t)n + 2 + 63) / 64 * 64; }   // words; desc starts 256-byte aligned
-size_t scratch_words(uint32_t n) { return scratch_head(n) + ((size_t)n + 16) * fi::kMultiDescWords; }
+// words: part counts, work counters, descriptors, each 256-byte aligned
+constexpr size_t kScratchQueue = 64, kScratchDesc = kScratchQueue + 2 * fi::kQueueWords;
+constexpr size_t scratch_words(uint32_t n) { return kScratchDesc + ((size_t)n + 16) * fi::kMultiDescWords; }
 
 // The batch scratch of `stream`, holding at least n trials.  Allocates on the first batch of a
 // stream and when a batch is larger than any before on it (the replaced buffers are freed,
@@ -383,16 +384,14 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
     b = &p->batch.back();
     b->stream = stream;
     if (p->batch.size() == 1) {
-      b->perm = p->first_scratch;
-      b->desc = b->perm + scratch_head(kFirstTrials);
+      b->words = p->first_scratch;
       b->cap = kFirstTrials;
     }
   }
   if (b->cap < n) {
-    if (b->own) (void)hipFree(b->perm);
-    b->perm = nullptr; b->desc = nullptr; b->cap = 0; b->own = false;
-    FI_HIP(hipMalloc(&b->perm, scratch_words(n) * sizeof(uint32_t)));
-    b->desc = b->perm + scratch_head(n);
+    if (b->own) (void)hipFree(b->words);
+    b->words = nullptr; b->cap = 0; b->own = false;
+    FI_HIP(hipMalloc(&b->words, scratch_words(n) * sizeof(uint32_t)));
     b->cap = n;
     b->own = true;
   }
@@ -539,12 +538,14 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   return FI_OK;
 }
 
-// Where one batch of the multi-trial kernel keeps its trial order, the two part counts and the
+// Where one batch of the multi-trial kernel keeps its two part counts, its work counters and the
 // per-trial descriptors; all of it is rewritten by the partition kernel of every batch.
 struct TrialScratch {
-  uint32_t* perm = nullptr;     // [n_trials]
   uint32_t* counts = nullptr;   // [2]
+  uint32_t* queue = nullptr;    // [2 * kQueueWords]
   uint32_t* desc = nullptr;     // [(n_trials + 16) * kMultiDescWords]
+  explicit TrialScratch(uint32_t* words) : counts(words), queue(words + kScratchQueue), desc(words + kScratchDesc) {}
+  TrialScratch() = default;
 };
 
 fi_status check_batch_args(const fi_plan* plan, const fi_fault* d_faults, uint32_t n_trials, uint32_t policy,
@@ -644,23 +645,24 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
   if (plan->d.dtype == FI_BF16)
     hipLaunchKernelGGL(fi::partition_trials_kernel<FI_BF16>, dim3(1), dim3(1024), 0, s, d_faults, n_trials,
                        plan->d.M, plan->d.N, plan->d.K, plan->d.k_block, a.A, a.B, a.lda, a.ldb, plan->product_check,
-                       (uint32_t)mc.bm, (uint32_t)mc.bn, plan->kshift, ts.perm, ts.counts, ts.desc, d_results);
+                       (uint32_t)mc.bm, (uint32_t)mc.bn, plan->kshift, ts.counts, ts.desc, ts.queue,
+                       2u * fi::kQueueWords, d_results);
   else
     hipLaunchKernelGGL(fi::partition_trials_kernel<FI_FP16>, dim3(1), dim3(1024), 0, s, d_faults, n_trials,
                        plan->d.M, plan->d.N, plan->d.K, plan->d.k_block, a.A, a.B, a.lda, a.ldb, plan->product_check,
-                       (uint32_t)mc.bm, (uint32_t)mc.bn, plan->kshift, ts.perm, ts.counts, ts.desc, d_results);
+                       (uint32_t)mc.bm, (uint32_t)mc.bn, plan->kshift, ts.counts, ts.desc, ts.queue,
+                       2u * fi::kQueueWords, d_results);
   FI_HIP(hipGetLastError());
-  m.perm = ts.perm;
   m.part_counts = ts.counts;
   m.desc = ts.desc;
+  if (m.K >= 128) m.queue = ts.queue;
   FI_HIP(launch_multi((int)plan->d.dtype, plan->mcfg, m, (int)mblocks, s));
   return FI_OK;
 }
 
 // ---- scratch of fi_gemm_inject_batch_noalloc: one array per GPU, held until the process ends.
 constexpr uint32_t kNoAllocMaxTrials = 16384;
-constexpr size_t kNoAllocPermWords = (((size_t)kNoAllocMaxTrials + 2 + 63) / 64) * 64;   // desc starts 256-byte aligned
-constexpr size_t kNoAllocWords = kNoAllocPermWords + ((size_t)kNoAllocMaxTrials + 16) * fi::kMultiDescWords;
+constexpr size_t kNoAllocWords = scratch_words(kNoAllocMaxTrials);
 static __device__ __align__(256) uint32_t scratch[kNoAllocWords];
 
 // The array's address on each device (the name above is only a host-side handle for the
@@ -896,7 +898,7 @@ fi_status fi_gemm_inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t
     BatchScratch* bs = nullptr;
     st = batch_scratch(plan, as_stream(stream), n_trials, &bs);
     if (st != FI_OK) return st;
-    ts.perm = bs->perm; ts.counts = bs->perm + bs->cap; ts.desc = bs->desc;
+    ts = TrialScratch(bs->words);
   }
   return inject_batch(plan, d_faults, n_trials, policy, d_results, d_c_out, as_stream(stream), ts);
 }
@@ -913,8 +915,7 @@ fi_status fi_gemm_inject_batch_act(fi_plan* plan, const fi_fault* d_faults, uint
   BatchScratch* bs = nullptr;
   st = batch_scratch(plan, as_stream(stream), n_trials, &bs);
   if (st != FI_OK) return st;
-  TrialScratch ts;
-  ts.perm = bs->perm; ts.counts = bs->perm + bs->cap; ts.desc = bs->desc;
+  const TrialScratch ts(bs->words);
   return inject_batch(plan, d_faults, n_trials, policy, d_results, nullptr, as_stream(stream), ts,
                       static_cast<uint16_t*>(d_h_out));
 }
@@ -932,10 +933,7 @@ fi_status fi_gemm_inject_batch_noalloc(fi_plan* plan, const fi_fault* d_faults, 
     base = g_scratch_ptr[plan->device];
   }
   if (!base) return fail(FI_STATE, "the static scratch of device %d was not resolved at plan creation", plan->device);
-  TrialScratch ts;
-  ts.perm = base;
-  ts.counts = base + kNoAllocMaxTrials;          // the two words behind the trial order
-  ts.desc = base + kNoAllocPermWords;
+  const TrialScratch ts(base);
   return inject_batch(plan, d_faults, n_trials, policy, d_results, d_c_out, as_stream(stream), ts);
 }
 
@@ -1038,6 +1036,9 @@ fi_status fi_gemm_propagate_batch(fi_plan* plan, const void* d_a_stack, uint64_t
   }
   if (persistent) {
     // persistent workgroups walking (tile, trial) items
+    static_assert(offsetof(fi_trial_result, site_word_after) == offsetof(fi_trial_result, site_word_before) + 4,
+                  "the word behind the first counter counts the workgroups that are done");
+    if (n_trials >= (uint32_t)fi::kQueueXcds && plan->d.K >= 128) a.queue = &d_results->site_word_before;
     const MultiCfg mc = kMulti[plan->prop_cfg];
     const uint64_t cus = (uint64_t)(plan->n_cus / 8 * 8) * (uint64_t)mc.wgs;
     FI_HIP(launch_prop((int)plan->d.dtype, plan->prop_cfg, a, (int)(blocks < cus ? blocks : cus), s));

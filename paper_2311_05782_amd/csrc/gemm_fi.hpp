@@ -81,12 +81,15 @@ struct GemmArgs {
   int policy;
   int product_check;        // FI_PCHECK_* applied to the erroneous product of PRODUCT faults
   // For the multi-trial kernel: the batch split in two parts (trials that leave the operands
-  // alone, operand-fault trials): part_counts = {c0, c1}, perm = the trial order, desc = 6 words
-  // per trial in that order, see gemm_fi_multi.hpp.
-  const uint32_t* perm;
+  // alone, operand-fault trials): part_counts = {c0, c1}, desc = 6 words per trial, part after
+  // part, see gemm_fi_multi.hpp.
   const uint32_t* part_counts;
   const uint32_t* desc;
   uint64_t a_trial_stride;  // PROPAGATE: trial t reads A + t * a_trial_stride (elements)
+  // Multi-trial kernel, nullable (then its workgroups walk their items with the grid as stride): what
+  // the workgroups of an XCD have taken of its slice of the work list, kQueueStride words per XCD; zero at
+  // the start.  The operand-fault launch has a set of its own behind the first.
+  uint32_t* queue;
   // Measurement aid, nullable: workgroup 0 of the persistent kernel writes the shader-clock
   // counter and the constant-rate (100 MHz) counter when it starts and when it has finished its
   // last item - {cycles, ticks, cycles, ticks} at clocks + 4 * VAR - from which the host derives

@@ -53,6 +53,54 @@ __device__ __forceinline__ void store_wide(u32x4 q, __amdgpu_buffer_rsrc_t to, i
   asm volatile("s_nop 1" ::"v"(q) : "memory");
 }
 
+// Items per workgroup from which a workgroup looks for work in other XCDs' slices at the end (a look takes two
+// round trips to memory).
+constexpr uint32_t kStealItems = 64;
+// Work counters of a launch: one per XCD, 64 bytes apart.
+constexpr int kQueueXcds = 8, kQueueStride = 16, kQueueWords = kQueueXcds * kQueueStride;
+// The next layer's batches own no scratch: their counters are the site words, which that entry point leaves
+// 0, of the first records; the last workgroup clears them again.
+constexpr int kPropQueueStride = sizeof(fi_trial_result) / 4;
+
+// x / d for any 32-bit x, in a multiplication and one correction: m = floor((2^32 - 1) / d) puts
+// the product's high word at the quotient or one below.
+struct Divisor {
+  uint32_t d, m;
+  __device__ __forceinline__ explicit Divisor(uint32_t by) : d(by), m(0xFFFFFFFFu / by) {}
+  __device__ __forceinline__ uint32_t divide(uint32_t x, uint32_t& rem) const {
+    uint32_t q = __umulhi(x, m);
+    rem = x - q * d;
+    if (rem >= d) { rem -= d; ++q; }
+    return q;
+  }
+};
+// The work list of work_of_index for a workgroup that looks at many entries: what does not change from
+// one to the next is formed once, and tiles come as tile row and column.
+struct WorkList {
+  uint32_t per, full, cut;
+  Divisor g, g2, tiles, tn;
+  __device__ __forceinline__ WorkList(int tiles_m, int tiles_n, int n_items, int group)
+      : per((uint32_t)tiles_m * (uint32_t)tiles_n * (uint32_t)n_items >> 3),
+        full((uint32_t)n_items / (uint32_t)min(group, n_items) * (uint32_t)min(group, n_items)),
+        cut(full * (uint32_t)tiles_m * (uint32_t)tiles_n),
+        g((uint32_t)min(group, n_items)),
+        g2(max((uint32_t)n_items - full, 1u)),
+        tiles((uint32_t)tiles_m * (uint32_t)tiles_n),
+        tn((uint32_t)tiles_n) {}
+  __device__ __forceinline__ void at(uint32_t w, uint32_t& tile_m, uint32_t& tile_n, uint32_t& item) const {
+    const uint32_t L = w < per * 8u ? (w & 7u) * per + (w >> 3) : w;
+    uint32_t tile, in_group;
+    if (L < cut) {
+      const uint32_t set = tiles.divide(g.divide(L, in_group), tile);
+      item = set * g.d + in_group;
+    } else {
+      tile = g2.divide(L - cut, in_group);
+      item = full + in_group;
+    }
+    tile_m = tn.divide(tile, tile_n);
+  }
+};
+
 // VAR: which part of the work this instantiation takes.
 enum { VAR_PLAIN = 0, VAR_OPERAND = 1, VAR_PROPAGATE = 2 };
 
@@ -77,18 +125,18 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   // The threshold inputs of the whole wave tile sit in registers during the epilogue (else they
   // are loaded tile by tile: 8 tiles' worth would spill).
   constexpr bool HAVE_T = TM * TN <= 4;
-  // Large wave tiles leave few registers: the next item is located (its staging offsets
-  // computed, its descriptors requested) just before the current item's last k-tile instead of
-  // a whole item ahead, and golden values are fetched in the epilogue instead of up front.
-  constexpr bool LATE_NEXT = TM * TN >= 4;
+  // Large wave tiles leave few registers: golden values are fetched in the epilogue instead of up front.
   constexpr bool PRE_GOLDEN = R >= 4;
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is a multiple of the 32x32 MFMA");
   static_assert((BM / 8) % NW == 0 && (BN / 8) % NW == 0, "row groups divide among the waves");
   static_assert(R * TM * TN * 16 <= 128, "accumulators fit half the register file");
-  static_assert(2 * STAGE <= 160 * 1024, "two stages fit the 160 KB LDS");
+  static_assert(2 * STAGE + 16 <= 160 * 1024, "two stages fit the 160 KB LDS");
   static_assert(R * kMultiDescWords <= 64, "a group's descriptors fit one word per lane");
 
-  __shared__ __attribute__((aligned(16))) uint8_t smem[2 * STAGE];
+  // One array for everything: beside a second one the compiler takes the fragment reads to depend on the
+  // staging loads and puts a wait for them in front of every read (4096^3 33 % slower).
+  __shared__ __attribute__((aligned(16))) uint8_t smem[2 * STAGE + 16];
+  uint32_t* const next_item = reinterpret_cast<uint32_t*>(smem + 2 * STAGE);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -121,11 +169,13 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   };
   Item cur, nxt;                                         // the current item and the one after it
   int stage = 0;                                         // LDS stage of the current k-tile
+  const WorkList list(p.tiles_m, p.tiles_n, n_groups, p.group);
   auto locate = [&](uint32_t w, Item& it) {
-    int tile;
-    work_of_index(w, n_work, p.tiles_m * p.tiles_n, n_groups, p.group, tile, it.grp);
-    it.m0 = (tile / p.tiles_n) * BM;
-    it.n0 = (tile % p.tiles_n) * BN;
+    uint32_t tm, tn, grp;
+    list.at(w, tm, tn, grp);
+    it.grp = (int)grp;
+    it.m0 = (int)tm * BM;
+    it.n0 = (int)tn * BN;
     it.a_base = PROP ? (size_t)it.grp * (size_t)p.a_trial_stride : 0;
 #pragma unroll
     for (int c = 0; c < A_G; ++c) {
@@ -196,6 +246,40 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, (lds_void*)(sB + c * 1024), 16, (int)(off * 2u), kb0, 0, 0);
     }
   };
+  // ---- which item comes next.  Two workgroups on a CU do not run at the same rate (the older wave goes
+  // first where both could issue), and neither do two XCDs, so a workgroup takes its items as it needs
+  // them, the first two excepted.  Wave 0 asks in front of an epilogue (`request`), by the first barrier of
+  // the item behind it the answer has come and goes to the other waves (`publish`), and all read it in front of
+  // that item's last k-tile (`locate_next`): hence two k-tiles or more, and an item is taken one item ahead, not more.
+  const bool dynamic = p.queue != nullptr && n_work > 2 * gridDim.x;   // the grid is then a multiple of kQueueXcds
+  uint32_t* const queue = p.queue + (OPS ? kQueueWords : 0);
+  constexpr int QS = PROP ? kPropQueueStride : kQueueStride;
+  uint32_t ticket = blockIdx.x / kQueueXcds - gridDim.x / kQueueXcds;  // position() of it: blockIdx.x + gridDim.x
+  auto request = [&]() __attribute__((always_inline)) {
+    if (dynamic && tid == 0)
+      ticket = __hip_atomic_fetch_add(queue + (blockIdx.x % kQueueXcds) * QS, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  // position in the work list of the t-th item that is taken from XCD x's slice
+  auto position = [&](uint32_t x, uint32_t t) -> uint32_t { return 2 * gridDim.x + t * kQueueXcds + x; };
+  auto publish = [&]() __attribute__((always_inline)) {
+    if (!dynamic || wave != 0) return;
+    uint32_t w = position(blockIdx.x % kQueueXcds, (uint32_t)__builtin_amdgcn_readfirstlane((int)ticket));
+    // Its own slice is used up: take from the one with the most left, if the launch is a long one.  The
+    // counters only grow, so this ends, at the latest when none has anything left.
+    while (__builtin_expect(w >= n_work && n_work / kStealItems >= gridDim.x, 0)) {
+      const uint32_t taken = __hip_atomic_load(queue + (lane % kQueueXcds) * QS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t at = position((uint32_t)lane % kQueueXcds, taken);
+      const uint32_t left = at < n_work ? n_work - at : 0u;
+      const uint32_t most = wave_max(left);
+      if (most == 0) break;
+      const uint32_t x = (uint32_t)__builtin_ctzll(__ballot(left == most)) % kQueueXcds;
+      uint32_t t = 0;
+      if (lane == 0) t = __hip_atomic_fetch_add(queue + x * QS, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      w = position(x, (uint32_t)__builtin_amdgcn_readfirstlane((int)t));
+    }
+    if (lane == 0) *next_item = w;
+  };
+
   // A group's R descriptors, one word per lane; fields are picked out with v_readlane.
   auto load_desc = [&](int grp) -> uint32_t {
     if constexpr (PROP) return lane == 0 ? (uint32_t)grp : lane == 3 ? 0xFFFFFFFFu : 0u;   // {trial, -, -, no event}
@@ -275,10 +359,10 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   // ---- state of the current item
   uint32_t desc_cur, desc_nxt = 0;                       // lane-distributed descriptor words
   int n_act = 0;                                         // trials in this group
-  // hook_step[r]: the MFMA step of trial r's event if this wave takes part in it (it owns the
-  // accumulator element, or its fragments hold the faulted operand word), else -1.
-  int trial[R], hook_step[R];
-  bool has_events = false;                               // some hook_step[r] >= 0
+  // Bit r: this wave takes part in trial r's event (it owns the accumulator element, or its
+  // fragments hold the faulted operand word).
+  uint32_t owned = 0;
+  int hook_step[R];                                      // items with events: the MFMA step of trial r's, or -1
   // Fields are read with all lanes active, never inside a condition on the lane: where the word has been
   // spilled, a reload there fetches the active lanes only, and v_readlane takes another's.
   auto desc_field = [&](int r, int field) -> uint32_t {
@@ -302,64 +386,33 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
 
   auto decode = [&]() {
     n_act = min(R, n_fast - cur.grp * R);
-    has_events = false;
+    owned = 0;
     if constexpr (!PROP) {
       // Nearly every item holds no event of this wave.  One lane-parallel test over the R
-      // descriptors settles that (a few shuffles and compares, one ballot) instead of R
-      // scalar decodes of some 45 instructions each.  Lane l looks at the descriptor of trial
-      // l / 6, whose words sit in lanes 6 * (l / 6) .. + 5 of desc_cur (recomputed per item: two
-      // registers held across the k-loop would not fit the 128 x 64 shape).
-      const int d_trial = lane / kMultiDescWords, d_base = d_trial * kMultiDescWords;
-      const int row = __shfl((int)desc_cur, d_base + 1, 64), col = __shfl((int)desc_cur, d_base + 2, 64);
-      const int ev = __shfl((int)desc_cur, d_base + 3, 64);
-      const int li = row - cur.m0, lj = col - cur.n0;
-      bool hit;
-      if (OPS && ((ev >> 29) & 1)) {
-        const bool isA = __shfl((int)desc_cur, d_base + 5, 64) == FI_SITE_A;
-        const int wl = isA ? li - wm * WTM : lj - wn * WTN;
-        hit = wl >= 0 && wl < (isA ? WTM : WTN);          // inside the wave's rows / columns of this tile
-      } else {
-        const int wi = li - wm * WTM, wj = lj - wn * WTN;
-        hit = wi >= 0 && wi < WTM && wj >= 0 && wj < WTN;
+      // descriptors settles that: lane 6 r looks at trial r, whose words lie in lanes 6 r .. 6 r + 5
+      // and come down lane by lane (ds_bpermute took twice as long).  Groups are padded to R with
+      // entries without an event.
+      auto down = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_update_dpp(0, x, 0x130, 0xf, 0xf, true); };   // wave_shl:1
+      const int row = down((int)desc_cur), col = down(row), ev = down(col);
+      const int li = row - cur.m0 - wm * WTM, lj = col - cur.n0 - wn * WTN;
+      const bool in_row = (uint32_t)li < (uint32_t)WTM, in_col = (uint32_t)lj < (uint32_t)WTN;
+      bool hit = in_row && in_col;                        // this wave owns the element
+      if constexpr (OPS) {
+        const bool isA = down(down(ev)) == FI_SITE_A;     // this wave's rows / columns of the tile hold the word
+        hit = ((ev >> 29) & 1) ? (isA ? in_row : in_col) : hit;
       }
-      if (__ballot(hit && ev >= 0 && d_trial < n_act && lane < R * kMultiDescWords) == 0) {
+      const unsigned long long hits = __ballot(hit && ev >= 0);
+      static_for<R>([&](auto rr) { owned |= (uint32_t)(hits >> (rr * kMultiDescWords)) & 1u ? 1u << rr : 0u; });
+    }
+    if constexpr (PRE_GOLDEN) {
+      if (owned != 0) {
         static_for<R>([&](auto rr) {
-          trial[rr] = (int)desc_field(rr, 0);
-          hook_step[rr] = -1;
+          constexpr int r = rr;
+          const bool op_b = OPS && ((desc_field(r, 3) >> 29) & 1u) && desc_field(r, 5) != FI_SITE_A;
+          if (((owned >> r) & 1u) && !op_b) prefetch_row_golden(rr);
         });
-        return;
       }
     }
-    static_for<R>([&](auto rr) {
-      constexpr int r = rr;
-      trial[r] = (int)desc_field(r, 0);
-      hook_step[r] = -1;
-      const int ev = PROP ? -1 : (int)desc_field(r, 3);
-      const int hs = ev & 0xFFFF;
-      if (r < n_act && ev >= 0) {
-        const int li = (int)desc_field(r, 1) - cur.m0, lj = (int)desc_field(r, 2) - cur.n0;
-        if (OPS && ((ev >> 29) & 1)) {
-          // A: row i = desc row, every tile of that tile row differs; B: column j = desc col.
-          const bool isA = desc_field(r, 5) == FI_SITE_A;
-          const int l = isA ? li : lj;
-          if (l >= 0 && l < (isA ? BM : BN)) {
-            const int wl = isA ? l - wm * WTM : l - wn * WTN;
-            if (wl >= 0 && wl < (isA ? WTM : WTN)) {
-              hook_step[r] = hs;
-              has_events = true;
-              if (isA) prefetch_row_golden(rr);
-            }
-          }
-        } else if (li >= 0 && li < BM && lj >= 0 && lj < BN) {
-          const int wi = li - wm * WTM, wj = lj - wn * WTN;
-          if (wi >= 0 && wi < WTM && wj >= 0 && wj < WTN) {
-            hook_step[r] = hs;
-            has_events = true;
-            prefetch_row_golden(rr);
-          }
-        }
-      }
-    });
   };
 
   // Accumulator flip of trial r (this wave owns its site); once per trial in the whole grid.
@@ -367,7 +420,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
     constexpr int r = rr;
     const int wi = (int)desc_field(r, 1) - cur.m0 - wm * WTM, wj = (int)desc_field(r, 2) - cur.n0 - wn * WTN;
     const bool product = ((desc_field(r, 3) >> 30) & 1u) != 0;      // else an XOR of the word
-    const uint32_t w0 = desc_field(r, 4), w1 = desc_field(r, 5);
+    const uint32_t trial = desc_field(r, 0), w0 = desc_field(r, 4), w1 = desc_field(r, 5);
     const float re = __uint_as_float(w0), re_err = __uint_as_float(w1);
     const int ri = wi & 31, rj = wj & 31;
     const int sel_t = (wi >> 5) * TN + (wj >> 5);
@@ -391,8 +444,8 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       }
     });
     if (lane == sel_lane) {
-      p.results[trial[r]].site_word_before = before;
-      p.results[trial[r]].site_word_after = after;
+      p.results[trial].site_word_before = before;
+      p.results[trial].site_word_after = after;
     }
     // Leave nothing of this rare path in flight: the compiler places its waits statically, and
     // memory traffic pending here would make every iteration of the main loop wait for it.
@@ -481,10 +534,36 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
 #pragma unroll
     for (int j = 0; j < TN; ++j) cbj[j] = p.cb[min(col_base + 32 * j, p.N - 1)];
   };
+  // PROP: golden values.  They come through buffer loads: the lane's part of the address is one 32-bit
+  // offset for the whole item, the tile's and row's part is scalar - no vector address arithmetic, no
+  // address registers per load.  The allocation is padded to whole tiles, so rows and columns beyond a
+  // ragged problem read allocated memory (such elements are never compared).
+  // The threshold inputs and the first GOLD_EARLY tiles are requested in front of an item's last k-tile,
+  // under whose matrix steps they arrive (`prepare_epilogue`), where the wave has the registers.
+  constexpr int GOLD_EARLY = PROP && TM * TN <= 4 ? 2 : 0;
+  constexpr int GOLD_BUFS = PROP ? 3 : 1;
+  [[maybe_unused]] f32x16 gold[GOLD_BUFS];
+  auto tile_offset = [&](auto tt) __attribute__((always_inline)) -> uint32_t {        // bytes
+    constexpr int i = tt / TN, j = tt % TN;
+    return (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)((((uint32_t)(cur.m0 + wm * WTM + 32 * i) * (uint32_t)p.N) + (uint32_t)(cur.n0 + wn * WTN + 32 * j)) * 4u));
+  };
+  auto load_golden = [&](auto tt, f32x16& dst) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rsrc_gold =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.c_star), 0, (int)p.c_star_bytes, 0x00020000);
+    const int gold_lane = (4 * lhi * p.N + l32) * 4;                  // bytes
+    const uint32_t tile_off = tile_offset(tt);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const uint32_t row_off = (uint32_t)(8 * (v >> 2) + (v & 3)) * (uint32_t)p.N * 4u;
+      dst[v] = __uint_as_float(
+          __builtin_amdgcn_raw_buffer_load_b32(rsrc_gold, gold_lane, (int)(tile_off + row_off), 0));
+    }
+  };
   auto epilogue = [&]() {
     // Larger wave tiles have no registers for the threshold inputs while the k-loop runs: they
     // are fetched here, all at once (one memory round trip for the whole item, not one per tile).
-    if constexpr (HAVE_T && !EARLY_T) fetch_threshold_inputs();
+    if constexpr (HAVE_T && !EARLY_T && GOLD_EARLY == 0) fetch_threshold_inputs();
     const int m0 = cur.m0, n0 = cur.n0;
     const int row_base = m0 + wm * WTM + 4 * lhi;       // + 32*i + 8*q + e
     const int col_base = n0 + wn * WTN + l32;           // + 32*j
@@ -493,16 +572,24 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       constexpr int i = tt / TN, j = tt % TN;
       const int col = col_base + 32 * j;
       f32x16 T;
-      const float cb_here = HAVE_T ? cbj[j] : p.cb[min(col, p.N - 1)];
+      if (p.bound_global) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4 kra_here =
-            HAVE_T ? kra4[i][q] : *reinterpret_cast<const f32x4*>(p.kra + row_base + 32 * i + 8 * q);
+        for (int v = 0; v < 16; ++v) T[v] = p.t_global;
+      } else {
+        const float cb_here = HAVE_T ? cbj[j] : p.cb[min(col, p.N - 1)];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int row = row_base + 32 * i + 8 * q + e;
-          const float t = p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(kra_here[e], cb_here), p.gamma);
-          T[4 * q + e] = (row < p.M && col < p.N) ? t : __builtin_inff();
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 kra_here =
+              HAVE_T ? kra4[i][q] : *reinterpret_cast<const f32x4*>(p.kra + row_base + 32 * i + 8 * q);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) T[4 * q + e] = __fmul_rn(__fmul_rn(kra_here[e], cb_here), p.gamma);
+        }
+      }
+      if (ragged) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3);
+          T[v] = (row < p.M && col < p.N) ? T[v] : __builtin_inff();
         }
       }
       return T;
@@ -519,34 +606,14 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
         acc[r][i][j] = a;
       });
     }
-    // Detector (and corrector, when outputs are wanted) on every element of every trial.  Without
-    // outputs the common case costs one compare and one scalar OR per element: lane masks of
-    // the flags are merged, and only a trial-tile with any flag set is counted exactly.
-    // PROP: the fault-free words of this wave's 32 x 32 tiles travel kGoldAhead tiles ahead of
-    // their use; the first ones are requested here, before the detector pass.
-    constexpr int kGoldAhead = 2;
-    [[maybe_unused]] f32x16 cs_buf[PROP ? kGoldAhead + 1 : 1];
-    // They come through buffer loads: the lane's part of the address is one 32-bit offset for the
-    // whole item, the tile's and row's part is scalar - no vector address arithmetic, no address
-    // registers per load.  The allocation is padded to whole tiles, so rows and columns beyond a
-    // ragged problem read allocated memory (such elements are never compared).
-    const __amdgpu_buffer_rsrc_t rsrc_gold =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.c_star), 0, (int)p.c_star_bytes, 0x00020000);
-    const int gold_lane = (4 * lhi * p.N + l32) * 4;                  // bytes
-    auto load_golden = [&](auto tt, f32x16& dst) __attribute__((always_inline)) {
-      constexpr int i = tt / TN, j = tt % TN;
-      const uint32_t tile_off = __builtin_amdgcn_readfirstlane(
-          (int)((((uint32_t)(m0 + wm * WTM + 32 * i) * (uint32_t)p.N) + (uint32_t)(n0 + wn * WTN + 32 * j)) * 4u));
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const uint32_t row_off = (uint32_t)(8 * (v >> 2) + (v & 3)) * (uint32_t)p.N * 4u;
-        dst[v] = __uint_as_float(
-            __builtin_amdgcn_raw_buffer_load_b32(rsrc_gold, gold_lane, (int)(tile_off + row_off), 0));
-      }
-    };
+    // Detector (and corrector, when outputs are wanted) on every element of every trial.  In the common
+    // case the trials' elements are compared together (half an instruction each and a compare per R), and
+    // only where some flag is set trial by trial and counted.
+    // PROP: the fault-free words of this wave's 32 x 32 tiles are requested tiles ahead of their use, the
+    // next ones here, before the detector pass.
     if constexpr (PROP) {
-      static_for<kGoldAhead>([&](auto tt) {
-        if constexpr (tt < TM * TN) load_golden(tt, cs_buf[tt]);
+      static_for<GOLD_BUFS - 1>([&](auto tt) {
+        if constexpr (tt >= GOLD_EARLY && tt < TM * TN) load_golden(tt, gold[tt]);
       });
     }
     uint32_t n_flag[R];
@@ -567,20 +634,38 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
         constexpr int i = tt / TN, j = tt % TN;
         const f32x16 T = thresholds(tt);
         const int col = col_base + 32 * j;
+        // Every trial's element against the threshold they share: of the largest magnitude of the R the
+        // excess over T (a difference has the sign that the comparison says, subnormals being kept), of
+        // which again the largest.  v_maximum3_f32 takes two values an instruction, and a NaN outweighs
+        // all.  16 compares and scalar ORs in the place of the second maximum wait for each other.
+        float excess = -__builtin_inff();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          float top = fabsf(acc[0][i][j][v]);
+          static_for<R>([&](auto rr) {
+            constexpr int r = rr;
+            if constexpr (r > 0) top = __builtin_elementwise_maximum(top, fabsf(acc[r][i][j][v]));
+          });
+          excess = __builtin_elementwise_maximum(excess, __fsub_rn(top, T[v]));
+        }
+        const uint64_t some = __ballot(!(excess <= 0.0f));
+        if (!OUT && some == 0) return;
         static_for<R>([&](auto rr) {
           constexpr int r = rr;
           if (r < n_act) {
             const f32x16 t = acc[r][i][j];
             uint64_t any = 0;
+            if (some != 0) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) any |= __ballot(!(fabsf(t[v]) <= T[v]));
+              for (int v = 0; v < 16; ++v) any |= __ballot(!(fabsf(t[v]) <= T[v]));
+            }
             if (any != 0) {
 #pragma unroll
               for (int v = 0; v < 16; ++v)
                 n_flag[r] += (uint32_t)__builtin_popcountll(__ballot(!(fabsf(t[v]) <= T[v])));
             }
             if constexpr (OUT) {
-              const size_t out0 = (size_t)trial[r] * (size_t)p.M * (size_t)p.N;
+              const size_t out0 = (size_t)desc_field(r, 0) * (size_t)p.M * (size_t)p.N;
               // Nearly every trial-tile: nothing flagged, no ragged edge.  The values go out as
               // they are, through buffer stores whose address is a per-item lane offset plus a
               // scalar (trial, tile, row) offset: no vector arithmetic, no branch per element.
@@ -649,21 +734,26 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
                     }
                   }
                 }
-              } else
+              } else {
+                // Rows and columns formed here, not carried here from the top of the kernel in registers
+                // that the k-loop does not have (the empty asm statement).
+                int row0 = row_base + 32 * i, col0 = col;
+                asm volatile("" : "+v"(row0), "+v"(col0));
 #pragma unroll
-              for (int v = 0; v < 16; ++v) {
-                const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3);
-                float cc = t[v];
-                if (!(fabsf(cc) <= T[v])) {
-                  if (p.policy == FI_CORRECT_ZERO) cc = 0.0f;
-                  else if (p.policy == FI_CORRECT_RECOMPUTE) cc = p.c_star[(size_t)row * p.N + col];
-                }
-                if (row < p.M && col < p.N) {
-                  const size_t at = out0 + (size_t)row * p.N + col;
-                  if (p.c_out) p.c_out[at] = cc;
-                  // the hand-over between two layers fused into this epilogue: relu keeps a NaN
-                  // and maps negatives and -0 to +0, then the integer round-to-format
-                  if (p.h_out) p.h_out[at] = (uint16_t)round16<DT>((cc > 0.0f || cc != cc) ? cc : 0.0f);
+                for (int v = 0; v < 16; ++v) {
+                  const int row = row0 + 8 * (v >> 2) + (v & 3);
+                  float cc = t[v];
+                  if (!(fabsf(cc) <= T[v])) {
+                    if (p.policy == FI_CORRECT_ZERO) cc = 0.0f;
+                    else if (p.policy == FI_CORRECT_RECOMPUTE) cc = p.c_star[(size_t)row * p.N + col0];
+                  }
+                  if (row < p.M && col0 < p.N) {
+                    const size_t at = out0 + (size_t)row * p.N + col0;
+                    if (p.c_out) p.c_out[at] = cc;
+                    // the hand-over between two layers fused into this epilogue: relu keeps a NaN
+                    // and maps negatives and -0 to +0, then the integer round-to-format
+                    if (p.h_out) p.h_out[at] = (uint16_t)round16<DT>((cc > 0.0f || cc != cc) ? cc : 0.0f);
+                  }
                 }
               }
             }
@@ -674,7 +764,10 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
     if (p.c_out || p.h_out) detect(std::true_type{}); else detect(std::false_type{});
     static_for<R>([&](auto rr) {
       constexpr int r = rr;
-      if (r < n_act && n_flag[r] != 0 && lane == 0) atomicAdd(&p.results[trial[r]].n_flagged, n_flag[r]);
+      if (r < n_act && n_flag[r] != 0) {
+        uint32_t* const to = &p.results[desc_field(r, 0)].n_flagged;
+        if (lane == 0) atomicAdd(to, n_flag[r]);
+      }
     });
     if constexpr (PROP) {
       // Every element of the trial's output against the fault-free result.  Two phases per
@@ -686,40 +779,55 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       uint32_t n_bit = 0, n_pre = 0, n_post = 0, n_bT = 0, n_btau = 0;
       float mx_pre = 0.0f, mx_post = 0.0f;
       static_for<TM * TN>([&](auto tt) {
-        constexpr int i = tt / TN, j = tt % TN, cb = tt % (kGoldAhead + 1);
+        constexpr int i = tt / TN, j = tt % TN, ahead = tt + GOLD_BUFS - 1;
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (tt + kGoldAhead < TM * TN)
-          load_golden(std::integral_constant<int, tt + kGoldAhead>{}, cs_buf[(tt + kGoldAhead) % (kGoldAhead + 1)]);
+        if constexpr (ahead < TM * TN) load_golden(std::integral_constant<int, ahead>{}, gold[ahead % GOLD_BUFS]);
         const f32x16 t = acc[0][i][j];
-        const f32x16 cs = cs_buf[cb];
+        const f32x16 cs = gold[tt % GOLD_BUFS];
         const int col = col_base + 32 * j;
-        uint32_t differs = 0;
+        // words that differ, four rows at a time, and the largest magnitude (a NaN outweighs all): no
+        // branch per element
+        uint32_t differs[4] = {0, 0, 0, 0};
+        float top = 0.0f;
+        if (!ragged) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3);
-          const bool act = !ragged || (row < p.M && col < p.N);
-          differs |= (act && (__float_as_uint(t[v]) != __float_as_uint(cs[v]) || not_finite(t[v]))) ? 1u : 0u;
+          for (int v = 0; v < 16; ++v) differs[v >> 2] |= __float_as_uint(t[v]) ^ __float_as_uint(cs[v]);
+        } else {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3);
+            const uint32_t mask = row < p.M && col < p.N ? 0xFFFFFFFFu : 0u;
+            differs[v >> 2] |= (__float_as_uint(t[v]) ^ __float_as_uint(cs[v])) & mask;
+          }
         }
-        if (n_flag[0] != 0 || __ballot(differs != 0) != 0) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) top = __builtin_elementwise_maximum(top, fabsf(t[v]));
+        const bool whole = n_flag[0] != 0 || __ballot(!(top <= 3.4028234e38f)) != 0;   // uniform
+        if (whole || __ballot((differs[0] | differs[1] | differs[2] | differs[3]) != 0) != 0) {
+          // the magnitude sums: beyond the last row 0, beyond a row's end the next row's (not counted)
+          const __amdgpu_buffer_rsrc_t rsrc_sums = __builtin_amdgcn_make_buffer_rsrc(
+              const_cast<float*>(p.s_abs), 0, (int)((uint32_t)p.M * (uint32_t)p.N * 4u), 0x00020000);
+          const uint32_t sums_off = tile_offset(tt);
           static_for<4>([&](auto qq) {
             constexpr int q = qq;
+            if (!whole && __ballot(differs[q] != 0) == 0) return;
             __builtin_amdgcn_sched_barrier(0);
             const int row0 = row_base + 32 * i + 8 * q;
             const f32x4 kra_q = HAVE_T ? kra4[i][q] : *reinterpret_cast<const f32x4*>(p.kra + row0);
             const float cb_j = HAVE_T ? cbj[j] : p.cb[min(col, p.N - 1)];
-            float sa[4];
+            float sums[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              sa[e] = p.s_abs[(size_t)min(row0 + e, p.M - 1) * p.N + min(col, p.N - 1)];
+              sums[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                  rsrc_sums, (4 * lhi * p.N + l32) * 4, (int)(sums_off + (uint32_t)(8 * q + e) * (uint32_t)p.N * 4u), 0));
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              constexpr int dummy = 0; (void)dummy;
               const int v = 4 * q + e;
               const bool act = row0 + e < p.M && col < p.N;
               const float c = t[v], cse = cs[v];
               const float Tv = !act ? __builtin_inff()
                                     : p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(kra_q[e], cb_j), p.gamma);
-              const float tau = sa[e] * 0.000244140625f;        // 2^-12, exact scaling
+              const float tau = sums[e] * 0.000244140625f;      // 2^-12, exact scaling
               const bool flag = !(fabsf(c) <= Tv);
               float cc = c;
               if (flag && p.policy == FI_CORRECT_ZERO) cc = 0.0f;
@@ -750,8 +858,8 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
         const uint32_t a = __shfl_xor(mp, o, 64), b = __shfl_xor(mq, o, 64);
         mp = a > mp ? a : mp; mq = b > mq ? b : mq;
       }
+      fi_trial_result* const res = p.results + cur.grp;  // an item is a trial
       if (lane == 0) {
-        fi_trial_result* res = p.results + trial[0];
         if (n_bit) atomicAdd(&res->n_bitdiff, n_bit);
         if (n_pre) atomicAdd(&res->n_dev_pre, n_pre);
         if (n_post) atomicAdd(&res->n_dev_post, n_post);
@@ -766,8 +874,6 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
     // the wave owning the element, or the waves holding its output row (A) / column (B).
     // Counts are sums of lane masks (ballot + popcount: no cross-lane traffic); the two maxima
     // of all trials are reduced together at the end, so the shuffles' latencies overlap.
-    uint32_t owned = 0;
-    static_for<R>([&](auto rr) { owned |= hook_step[rr] >= 0 ? 1u << rr : 0u; });
     if (owned == 0) return;
     float mxp[R], mxq[R];                                   // per lane: largest deviation before / after correction
     static_for<R>([&](auto rr) { mxp[rr] = 0.0f; mxq[rr] = 0.0f; });
@@ -791,10 +897,21 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
         }
       });
     }
+    // Loads of threshold factors from here on are new ones to the compiler: it kept those of the detector
+    // pass in registers for this rare path (565 spills with the 64 x 128 wave tile).
+    const float* kra_here = p.kra;
+    asm volatile("" : "+s"(kra_here));
+    // The threshold factors of the faulted rows, likewise.
+    float row_kra[R];
+    static_for<R>([&](auto rr) {
+      constexpr int r = rr;
+      const bool op_b = OPS && ((desc_field(r, 3) >> 29) & 1u) && desc_field(r, 5) == FI_SITE_B;
+      row_kra[r] = ((owned >> r) & 1u) && !op_b ? kra_here[desc_field(r, 1)] : 0.0f;
+    });
     static_for<R>([&](auto rr) {
       constexpr int r = rr;
       if ((owned >> r) & 1u) {
-        fi_trial_result* res = p.results + trial[r];
+        fi_trial_result* res = p.results + desc_field(r, 0);
         const int site_row = (int)desc_field(r, 1), site_col = (int)desc_field(r, 2);
         // what the fault can reach: the element, or (OPS) its output row (A) / column (B)
         const bool op = OPS && ((desc_field(r, 3) >> 29) & 1u);
@@ -831,15 +948,13 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
           static_for<TM * TN>([&](auto tt) {
             constexpr int i = tt / TN, j = tt % TN;
             if (i == (wr >> 5)) {
-              const f32x16 T = thresholds(tt);
               const f32x16 t = acc[r][i][j];
-              float c = t[0], Tv = T[0];
+              float c = t[0];
 #pragma unroll
-              for (int v = 1; v < 16; ++v) {
-                c = (v == sel_v) ? t[v] : c;
-                Tv = (v == sel_v) ? T[v] : Tv;
-              }
+              for (int v = 1; v < 16; ++v) c = (v == sel_v) ? t[v] : c;
               const int col = col_base + 32 * j;
+              const float cb_here = HAVE_T ? cbj[j] : p.cb[min(col, p.N - 1)];
+              const float Tv = p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(row_kra[r], cb_here), p.gamma);
               float cs = 0.0f, sabs = 0.0f;
               if constexpr (PRE_GOLDEN) {
                 cs = cs_pre[r][j];
@@ -883,23 +998,30 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
           // One column, wave tiles of 8 accumulator tiles (no registers to spare for the gather):
           // the lanes holding the column read their rows' golden values; the other lanes read
           // their own columns of the same rows (same cache lines) and count nothing.
+          const int wc = site_col - n0 - wn * WTN;            // 0 .. WTN-1: this wave holds the column
+          const float cb_c = p.cb[site_col];
           static_for<TM * TN>([&](auto tt) {
             constexpr int i = tt / TN, j = tt % TN;
-            const f32x16 T = thresholds(tt);
-            const f32x16 t = acc[r][i][j];
-            const int col = col_base + 32 * j;
-            float cs[16], sa[16];
+            if (j == (wc >> 5)) {
+              const f32x16 t = acc[r][i][j];
+              const int col = col_base + 32 * j;
+              f32x4 kra_q[4];                                 // padded array: no guards
+              float cs[16], sa[16];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3);
-              const size_t idx = (size_t)min(row, p.M - 1) * p.N + min(col, p.N - 1);
-              cs[v] = p.c_star[idx];
-              sa[v] = p.s_abs[idx];
-            }
+              for (int q = 0; q < 4; ++q) kra_q[q] = *reinterpret_cast<const f32x4*>(kra_here + row_base + 32 * i + 8 * q);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3);
-              account(col == site_col && row < p.M, t[v], T[v], cs[v], sa[v]);
+              for (int v = 0; v < 16; ++v) {
+                const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3);
+                const size_t idx = (size_t)min(row, p.M - 1) * p.N + min(col, p.N - 1);
+                cs[v] = p.c_star[idx];
+                sa[v] = p.s_abs[idx];
+              }
+#pragma unroll
+              for (int v = 0; v < 16; ++v) {
+                const int row = row_base + 32 * i + 8 * (v >> 2) + (v & 3);
+                const float Tv = p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(kra_q[v >> 2][v & 3], cb_c), p.gamma);
+                account(col == site_col && row < p.M, t[v], Tv, cs[v], sa[v]);
+              }
             }
           });
         }
@@ -924,8 +1046,9 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
     }
     static_for<R>([&](auto rr) {
       constexpr int r = rr;
-      if (((owned >> r) & 1u) && lane == 0) {
-        fi_trial_result* res = p.results + trial[r];
+      if ((owned >> r) & 1u) {
+        fi_trial_result* const res = p.results + desc_field(r, 0);
+        if (lane != 0) return;
         if (mxp[r] > 0.0f) atomicMax(reinterpret_cast<uint32_t*>(&res->max_dev_pre), __float_as_uint(mxp[r]));
         if (mxq[r] > 0.0f) atomicMax(reinterpret_cast<uint32_t*>(&res->max_dev_post), __float_as_uint(mxq[r]));
       }
@@ -936,20 +1059,31 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   locate(w_cur, cur);
   desc_cur = load_desc(cur.grp);
   issue_tile(cur, 0, 0);
-  uint32_t w_nxt = w_cur + gridDim.x;
-  bool has_next = w_nxt < n_work;
+  bool has_next = false;
   auto locate_next = [&]() __attribute__((always_inline)) {
+    const uint32_t w_nxt = dynamic ? (uint32_t)__builtin_amdgcn_readfirstlane((int)*next_item) : w_cur + gridDim.x;
+    has_next = w_nxt < n_work;
+    w_cur = w_nxt;
     if (has_next) {
       locate(w_nxt, nxt);
       desc_nxt = load_desc(nxt.grp);
     }
   };
-  if constexpr (!LATE_NEXT) locate_next();
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
   __syncthreads();
   Frags f0, f1;
   read_frags(f0, smem, 0);
   const int nkt = p.K / BK;
+
+  auto prepare_epilogue = [&]() __attribute__((always_inline)) {
+    if constexpr (PROP) {
+      if (has_next) request();                             // the epilogue waits for loads of its own, in order
+      if constexpr (GOLD_EARLY > 0) {
+        fetch_threshold_inputs();
+        static_for<GOLD_EARLY>([&](auto tt) { load_golden(tt, gold[tt]); });
+      }
+    }
+  };
 
   // ---- items.  Within one: double-buffered LDS, one barrier per k-tile.  The barrier sits
   // before the last of the four MFMA steps of a tile: by then a wave holds the tile's last
@@ -979,6 +1113,9 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       constexpr int SC = decltype(stage_c)::value;
       if constexpr (SC >= 0) stage = SC;
       const bool last = LM == 2 ? kt == nkt - 1 : LM == 1;
+      if constexpr (LM == 2) {
+        if (last) locate_next();
+      }
       const bool more = !last || has_next;                // a tile follows in the other stage
       if constexpr (EV) {
         // Nothing of the rare paths stays in flight across the tile prefetch: the compiler
@@ -1027,7 +1164,10 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       step(f0, 4 * kt + 2, std::false_type{}, s2{}, [&]() { read_frags(f1, s, 3); });
       // Every fragment of this stage is in registers (the barrier's fence waits for the reads);
       // once all waves are here the next tile has landed and this stage may be overwritten.
-      if (more) __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): this wave's loads have landed
+      // vmcnt(0): this wave's loads have landed.  Also where no tile follows: the epilogue then finds nothing
+      // that the compiler would have to wait for, the answer of `request` included.
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      if constexpr (FIRST && LM == 0) publish();
       __syncthreads();
       step(f1, 4 * kt + 3, std::false_type{}, s3{}, [&]() { if (more) read_frags(f0, s_other, 0); });
       stage ^= 1;
@@ -1040,10 +1180,11 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
     using mid_tile = std::integral_constant<int, 0>;
     using last_tile = std::integral_constant<int, 1>;
     using any_tile = std::integral_constant<int, 2>;
-    if (PROP || !has_events) {
+    if (PROP || owned == 0) {
       // Nearly every wave of nearly every item: no event check anywhere.
       if (nkt == 1) {
-        if constexpr (LATE_NEXT) locate_next();
+        locate_next();
+        prepare_epilogue();
         k_tile(no{}, yes{}, last_tile{}, dyn{}, 0);
       } else if ((nkt & 1) == 0 && stage == 0) {
         // an even number of k-tiles: every item starts in stage 0 and the stages alternate statically
@@ -1056,12 +1197,14 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
           }
           k_tile(no{}, no{}, mid_tile{}, st0{}, nkt - 2);
         }
-        if constexpr (LATE_NEXT) locate_next();
+        locate_next();
+        prepare_epilogue();
         k_tile(no{}, no{}, last_tile{}, st1{}, nkt - 1);
       } else {
         k_tile(no{}, yes{}, mid_tile{}, dyn{}, 0);
         for (int kt = 1; kt + 1 < nkt; ++kt) k_tile(no{}, no{}, mid_tile{}, dyn{}, kt);
-        if constexpr (LATE_NEXT) locate_next();
+        locate_next();
+        prepare_epilogue();
         k_tile(no{}, no{}, last_tile{}, dyn{}, nkt - 1);
       }
     } else if constexpr (!PROP) {
@@ -1073,7 +1216,8 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       // ones.  These copies keep to the running LDS stage, find out at run time whether a k-tile
       // is the item's last, and the accumulators are cleared up front: rare path, and every copy
       // of a k-tile costs code.
-      if constexpr (LATE_NEXT) locate_next();
+      publish();
+      static_for<R>([&](auto rr) { hook_step[rr] = ((owned >> rr) & 1u) ? (int)(desc_field(rr, 3) & 0xFFFFu) : -1; });
       static_for<R * TM * TN>([&](auto t) {
         acc[t / (TM * TN)][(t / TN) % TM][t % TN] =
             f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -1092,14 +1236,22 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       }
     }
 
+    if (!PROP && has_next) request();                    // under the epilogue
     epilogue();
     if (!has_next) break;                                // uniform: every wave leaves here
     cur = nxt;
     desc_cur = desc_nxt;
-    w_cur = w_nxt;
-    w_nxt = w_cur + gridDim.x;
-    has_next = w_nxt < n_work;
-    if constexpr (!LATE_NEXT) locate_next();
+  }
+  if constexpr (PROP) {
+    // the last workgroup to come here leaves the site words at 0: nobody asks any more
+    if (dynamic && tid == 0) {
+      const uint32_t done = __hip_atomic_fetch_add(queue + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (done == gridDim.x - 1u) {
+        for (int x = 0; x < kQueueXcds; ++x)
+          __hip_atomic_store(queue + x * QS, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(queue + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
   }
   if (p.clocks && blockIdx.x == 0 && tid == 0) {
     p.clocks[4 * VAR + 2] = __builtin_readcyclecounter();
