@@ -206,6 +206,21 @@ bool use_small_propagate(const fi_plan* p, uint32_t n_trials, bool c_out, bool p
   return rounds <= (persistent && c_out ? 5.0 : 1.0) + (persistent ? 2.0 : 4.0) * theirs;
 }
 
+// Tile shape of a next-layer batch.  Below 2^35 multiply-adds the plan has the 128 x 128 shape, two workgroups
+// per CU, one's epilogue under the other's MFMAs.  256 x 256 tiles read a third less from LDS per MFMA and half
+// as much from L2, but nothing hides an item's epilogue, so they take long items in whole rounds
+// that fill nine tenths of the chip: 256 : 128, K = 3072, 512 x 768, 256 trials (6 rounds) 590 : 658 us, K = 4096, 1024^2, 32
+// trials 254 : 268; K = 1024, 1024^2, 128 trials 347 : 314; K = 3072, 512 x 768, 64 trials (1.5 rounds) 177 : 145; K = 4096,
+// 256^2, 256 trials (1 round) 186 : 177.
+constexpr uint32_t kPropLongK = 3072;
+int pick_prop(const fi_plan* p, uint32_t n_trials) {
+  const fi_plan_desc& d = p->d;
+  if (!p->auto_cfg || d.K < kPropLongK || d.M % 256 != 0 || d.N % 256 != 0) return p->prop_cfg;
+  const uint64_t items = (uint64_t)(d.M / 256) * (d.N / 256) * n_trials, cus = (uint64_t)p->n_cus;
+  const uint64_t rounds = (items + cus - 1) / cus;
+  return rounds >= 2 && 10 * items >= 9 * rounds * cus ? fi::kMultiOneTrial[0] : p->prop_cfg;
+}
+
 // Batches that gemm_fi_trial_kernel serves.
 bool use_trial(const fi_plan* p, uint32_t n_trials, bool c_out, bool h_out) {
   const fi_plan_desc& d = p->d;
@@ -1001,8 +1016,9 @@ fi_status fi_gemm_propagate_batch(fi_plan* plan, const void* d_a_stack, uint64_t
   bool persistent = plan->prop_cfg >= 0 && a.c_star_bytes != 0 && plan->kshift == 0;
   const bool small = use_small_propagate(plan, n_trials, d_c_out != nullptr, persistent);
   persistent = persistent && !small;
+  const int prop_cfg = pick_prop(plan, n_trials);
   if (persistent) {
-    const MultiCfg mc = kMulti[plan->prop_cfg];
+    const MultiCfg mc = kMulti[prop_cfg];
     a.tiles_m = (a.M + mc.bm - 1) / mc.bm;
     a.tiles_n = (a.N + mc.bn - 1) / mc.bn;
   }
@@ -1039,9 +1055,9 @@ fi_status fi_gemm_propagate_batch(fi_plan* plan, const void* d_a_stack, uint64_t
     static_assert(offsetof(fi_trial_result, site_word_after) == offsetof(fi_trial_result, site_word_before) + 4,
                   "the word behind the first counter counts the workgroups that are done");
     if (n_trials >= (uint32_t)fi::kQueueXcds && plan->d.K >= 128) a.queue = &d_results->site_word_before;
-    const MultiCfg mc = kMulti[plan->prop_cfg];
+    const MultiCfg mc = kMulti[prop_cfg];
     const uint64_t cus = (uint64_t)(plan->n_cus / 8 * 8) * (uint64_t)mc.wgs;
-    FI_HIP(launch_prop((int)plan->d.dtype, plan->prop_cfg, a, (int)(blocks < cus ? blocks : cus), s));
+    FI_HIP(launch_prop((int)plan->d.dtype, prop_cfg, a, (int)(blocks < cus ? blocks : cus), s));
     return FI_OK;
   }
   FI_HIP(launch_gemm(fi::MODE_PROPAGATE, (int)plan->d.dtype, plan->cfg, a, (int)blocks, s));
