@@ -522,12 +522,13 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   }
   uint32_t* const words = reinterpret_cast<uint32_t*>(p->scratch);   // maxima, -, -, found, clean flags
   const uint32_t rows_a = (uint32_t)padded(d.M), rows_b = (uint32_t)padded(d.N);
-  const dim3 stat_grid((rows_a + rows_b) / 4 < 1024 ? (rows_a + rows_b) / 4 : 1024);
+  const uint32_t stat_blocks = (rows_a + rows_b) / fi::kStatWaves;     // a multiple of 32: rows are padded to 512
+  const dim3 stat_grid(stat_blocks < (uint32_t)p->n_cus ? stat_blocks : (uint32_t)p->n_cus), stat_block(fi::kStatWaves * 64);
   if (d.dtype == FI_FP16)
-    hipLaunchKernelGGL(fi::plan_stats_kernel<FI_FP16>, stat_grid, dim3(256), 0, s, p->A, (uint32_t)d.lda, d.M, rows_a,
+    hipLaunchKernelGGL(fi::plan_stats_kernel<FI_FP16>, stat_grid, stat_block, 0, s, p->A, (uint32_t)d.lda, d.M, rows_a,
                        p->B, p->ldb, d.N, rows_b, d.K, p->kra, p->cb, words, words + 4, fi::kTinyFactor);
   else
-    hipLaunchKernelGGL(fi::plan_stats_kernel<FI_BF16>, stat_grid, dim3(256), 0, s, p->A, (uint32_t)d.lda, d.M, rows_a,
+    hipLaunchKernelGGL(fi::plan_stats_kernel<FI_BF16>, stat_grid, stat_block, 0, s, p->A, (uint32_t)d.lda, d.M, rows_a,
                        p->B, p->ldb, d.N, rows_b, d.K, p->kra, p->cb, words, words + 4, fi::kTinyFactor);
   FI_HIP(hipGetLastError());
   fi_status st = compute_golden(p, s);
