@@ -269,6 +269,35 @@ def test_fused_hand_over_equals_campaign_then_activation_round(fmt, cfg, shape):
     plan.destroy()
 
 
+@pytest.mark.parametrize("fmt,scale", [(orc.BF16, 1.0), (orc.BF16, 1e-20), (orc.BF16, 1e18), (orc.FP16, 1.0),
+                                       (orc.FP16, 2.0 ** -11), (orc.FP16, 2.0 ** -15), (orc.FP16, 90.0)])
+def test_fused_hand_over_rounds_as_the_oracle_over_the_formats_ranges(fmt, scale):
+    # whole tiles, 16 bytes per lane: the conversion instructions.  Outputs from the subnormals of the
+    # formats to beyond their largest value, negative ones and zeros among them.
+    import torch
+    M, N, K = 512, 512, 16
+    Aw, Bw = wl.gaussian(M, N, K, fmt, seed=5)
+    f32 = lambda w: torch.from_numpy(w.view(np.int16).copy()).view(torch.float16 if fmt == orc.FP16 else torch.bfloat16).float()
+    words = lambda x: (x * scale).to(torch.float16 if fmt == orc.FP16 else torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
+    Aw, Bw = words(f32(Aw)), words(f32(Bw))
+    Aw[7] = 0
+    plan = gu.make_plan(Aw, Bw, 16, fmt, cfg=6)
+    n = 2
+    d_f, d_r = fi.to_device(np.zeros(n, fi.FAULT_DTYPE)), fi.empty_results(n)
+    d_c = torch.empty((n, M, N), dtype=torch.float32, device="cuda")
+    d_h = torch.full((n, M, N), 0x5555, dtype=torch.int16, device="cuda")
+    plan.fi_gemm_inject_batch(d_f, n, orc.CORRECT_NONE, d_r, d_c)
+    plan.fi_gemm_inject_batch_act(d_f, n, orc.CORRECT_NONE, d_r, d_h)
+    c, h = d_c.cpu().numpy().reshape(-1), d_h.cpu().numpy().view(np.uint16).reshape(-1)
+    want = orc.activation_round(c, fmt)
+    assert np.array_equal(h, want), int((h != want).sum())
+    tops = np.abs(c[c != 0])
+    limits = {2.0 ** -11: (0, 2.0 ** -14), 2.0 ** -15: (0, 2.0 ** -24), 1e-20: (0, 2.0 ** -126), 90.0: (65504, np.inf)}
+    lo, hi = limits.get(scale, (0, np.inf))
+    assert ((tops > lo) & (tops < hi)).any() and (c < 0).any() and (c == 0).any()
+    plan.destroy()
+
+
 def test_fused_hand_over_is_refused_where_the_one_trial_kernel_runs():
     Aw, Bw = wl.gaussian(64, 64, 96, orc.BF16, seed=5)
     plan = gu.make_plan(Aw, Bw, 32, orc.BF16, cfg=2)             # 256 x 64 tiles: the one-trial kernel
