@@ -152,7 +152,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   const int wm = wave / WN, wn = wave % WN;
   const int l32 = lane & 31, lhi = lane >> 5;
 
-  // ---- work list: n_tiles x ceil(n_fast / R) items, walked with the grid as stride
+  // ---- work list: n_tiles x ceil(n_fast / R) items
   // OPS: the second part of the batch; its descriptors follow the first part's, padded to 8.
   const int n_fast = PROP ? p.n_trials : (int)p.part_counts[OPS ? 1 : 0];
   const uint32_t* const desc =
