@@ -54,3 +54,25 @@ def test_detector_equals_its_definition(M, N, batch, shift, bound):
         assert bool((c_buf[:shift] == 7).all()) and bool((c_buf[shift + n:] == 7).all())     # nothing outside
         assert bool((f_buf[:shift] == 9).all()) and bool((f_buf[shift + n:] == 9).all())
     plan.destroy()
+
+
+@pytest.mark.parametrize("cfg", [-1, 2, 3, 6])          # element by element; through the largest excess over T
+def test_fused_detector_tells_subnormal_values_from_a_subnormal_threshold(cfg):
+    # ra = cb = 2^-70, K = 128: T = 2^-133 * (1 + 2^-11) = 65568 units of 2^-149.  The fault writes its mask into an
+    # accumulator of +0, whose value is then that many units: flagged from 65569 on.
+    M, N, K = 64, 64, 128
+    word = np.uint16((127 - 70) << 7)                    # BF16 2^-70
+    A, B = np.zeros((M, K), np.uint16), np.zeros((N, K), np.uint16)
+    A[:, 0], B[:, 1] = word, word                        # every product 0
+    plan = fi.Plan(fi.plan_desc(M, N, K, 32, fi.BF16), fi.words_to_device(A), fi.words_to_device(B))
+    plan.tune(cfg)
+    masks = [1, 0x10000, 0x1001F, 0x10020, 0x10021, 0x10022, 0x80010020, 0x80010021, 0x20000, 0x7F800000, 0x7FC00000]
+    faults = np.zeros(len(masks), fi.FAULT_DTYPE)
+    faults["kind"], faults["row"], faults["col"], faults["kblock"] = fi.SITE_ACC, 5, 40, 3
+    faults["xor_mask"] = masks
+    d_r = fi.empty_results(len(masks))
+    plan.fi_gemm_inject_batch(fi.to_device(faults), len(masks), fi.CORRECT_ZERO, d_r)
+    r = fi.results_to_host(d_r)
+    want = [int((m & 0x7FFFFFFF) > 0x10020) for m in masks]
+    assert r["n_flagged"].tolist() == want and r["n_bitdiff"].tolist() == [1] * len(masks)
+    plan.destroy()
