@@ -45,6 +45,7 @@
 // v_mfma_f32_32x32x16 steps in ascending k, hence bit-identical fault-free results.
 #pragma once
 
+#include "clamped.hpp"
 #include "gemm_fi.hpp"
 
 namespace fi {
@@ -815,10 +816,10 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
         for (int v = 0; v < 16; ++v) top = __builtin_elementwise_maximum(top, fabsf(t[v]));
         const bool whole = n_flag[0] != 0 || __ballot(!(top <= 3.4028234e38f)) != 0;   // uniform
         if (whole || __ballot((differs[0] | differs[1] | differs[2] | differs[3]) != 0) != 0) {
-          // the magnitude sums: beyond the last row 0, beyond a row's end the next row's (not counted)
+          // The magnitude sums are not padded: rows and columns beyond the problem read the last ones (not
+          // counted), in the lane's part of the address.
           const __amdgpu_buffer_rsrc_t rsrc_sums = __builtin_amdgcn_make_buffer_rsrc(
               const_cast<float*>(p.s_abs), 0, (int)((uint32_t)p.M * (uint32_t)p.N * 4u), 0x00020000);
-          const uint32_t sums_off = tile_offset(tt);
           static_for<4>([&](auto qq) {
             constexpr int q = qq;
             if (!whole && __ballot(differs[q] != 0) == 0) return;
@@ -830,7 +831,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
 #pragma unroll
             for (int e = 0; e < 4; ++e)
               sums[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                  rsrc_sums, (4 * lhi * p.N + l32) * 4, (int)(sums_off + (uint32_t)(8 * q + e) * (uint32_t)p.N * 4u), 0));
+                  rsrc_sums, (int)clamped_word_offset(row0 + e, col, p.M, p.N), 0, 0));
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const int v = 4 * q + e;

@@ -177,6 +177,38 @@ def test_next_layer_on_perturbed_gaussian_operands_guard_band_rule(fmt, cfg):
     plan.destroy()
 
 
+@pytest.mark.parametrize("M,N,K,cfg", [(1, 1 << 20, 128, None), (1, 1 << 20, 64, 0), (5, 1 << 18, 128, 1), (257, 4096, 64, 1),
+                                       (259, 4100, 128, 0)])
+def test_next_layer_of_few_rows_and_many_columns_does_not_depend_on_the_route(M, N, K, cfg):
+    # most rows of the tiles lie beyond the problem, megabytes beyond the magnitude sums; a trial that is
+    # flagged throughout, one that changes the last row alone, one that changes nothing
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(N)
+    a = torch.randn(M, K, generator=g, device="cuda").half()
+    b = torch.randn(N, K, generator=g, device="cuda").half()
+    n = 3
+    stack = a.expand(n, M, K).clone()
+    stack[0, M - 1, K - 1] += 1
+    stack[1, :, 0] = float("inf")
+    one = fi.Plan(fi.plan_desc(M, N, K, 32, fi.FP16), a, b)
+    one.tune(2)
+    want = _records_of(one, stack, n)
+    one.destroy()
+    plan = fi.Plan(fi.plan_desc(M, N, K, 32, fi.FP16), a, b)
+    if cfg is not None:
+        plan.tune(cfg)
+    got = _records_of(plan, stack, n)
+    plan.destroy()
+    assert got.tobytes() == want.tobytes(), (got, want)
+    assert N // 2 < got["n_bitdiff"][0] <= N and got["n_flagged"][1] == M * N and got["n_bitdiff"][2] == 0
+
+
+def _records_of(plan, stack, n):
+    d_r = fi.empty_results(n)
+    plan.fi_gemm_propagate_batch(stack, stack[0].numel(), n, orc.CORRECT_ZERO, d_r)
+    return fi.results_to_host(d_r)
+
+
 @pytest.mark.parametrize("fmt", [orc.FP16, orc.BF16])
 def test_two_layers_end_to_end_against_the_oracle_chain(fmt):
     # layer 1: campaign with materialised corrected outputs -> ReLU + rounding -> layer 2 on the
