@@ -1021,14 +1021,17 @@ fi_status fi_gemm_propagate_batch(fi_plan* plan, const void* d_a_stack, uint64_t
   bool persistent = plan->prop_cfg >= 0 && a.c_star_bytes != 0 && plan->kshift == 0;
   const bool small = use_small_propagate(plan, n_trials, d_c_out != nullptr, persistent);
   persistent = persistent && !small;
-  const int prop_cfg = pick_prop(plan, n_trials);
-  if (persistent) {
+  auto tile = [&](int prop_cfg) {
     const MultiCfg mc = kMulti[prop_cfg];
     a.tiles_m = (a.M + mc.bm - 1) / mc.bm;
     a.tiles_n = (a.N + mc.bn - 1) / mc.bn;
-  }
-  const uint64_t blocks = (uint64_t)a.tiles_m * a.tiles_n * n_trials;
+    return (uint64_t)a.tiles_m * a.tiles_n * n_trials;
+  };
+  // The largest batch is that of the plan's own tile shape, whichever shape serves this one.
+  uint64_t blocks = persistent ? tile(plan->prop_cfg) : (uint64_t)a.tiles_m * a.tiles_n * n_trials;
   if (blocks >= (1ull << 31)) return fail(FI_UNSUPPORTED, "tiles x trials exceeds 2^31 workgroups; split the batch");
+  const int prop_cfg = pick_prop(plan, n_trials);
+  if (persistent) blocks = tile(prop_cfg);
   hipStream_t s = as_stream(stream);
   const size_t words = (size_t)n_trials * (sizeof(fi_trial_result) / 4);
   hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)((words + 255) / 256 > 1024 ? 1024 : (words + 255) / 256)),

@@ -49,6 +49,21 @@ def test_batches_of_one_plan_in_flight_on_two_streams_do_not_share_scratch():
     plan.destroy()
 
 
+def test_the_largest_next_layer_batch_does_not_depend_on_the_tiles_that_serve_it():
+    # 256 x 256 x 3072: four tiles of the plan's 128 x 128 shape, one of the 256 x 256 shape that long-K batches take
+    import torch
+    n = 1 << 29
+    a = torch.zeros((256, 3072), dtype=torch.float16, device="cuda")
+    plan = fi.Plan(fi.plan_desc(256, 256, 3072, 32, fi.FP16), a, a)
+    d_r = fi.empty_results(n)                                # 26 GB: refused before anything is enqueued
+    with pytest.raises(fi.FiError, match="2\\^31 workgroups") as e:
+        plan.fi_gemm_propagate_batch(a, 0, n, wl.CORRECT_ZERO, d_r)
+    assert e.value.status == fi.UNSUPPORTED
+    plan.destroy()
+    del d_r
+    torch.cuda.empty_cache()
+
+
 # cfg None: the smallest batches' own kernels; 6: record fill, partition and two multi-trial launches.  3000
 # trials are more than the scratch inside the plan holds: without the reserve the capture would allocate
 @pytest.mark.parametrize("cfg,n", [(None, 200), (6, 200), (6, 3000)])
