@@ -126,9 +126,12 @@ constexpr uint32_t kTrialSteps = 128, kTrialStepsOut = 16;
 // where it also stores outputs (K = 576, 64 x 3136, 20 trials: 44 : 49), weight 2 (K = 256, 512^2: 15 trials 15 : 20, 27
 // trials 36 : 23).  One-trial kernel, K not a multiple of 64: 1 and 4 (K = 16, 3648 x 31, 330 trials 348 : 134).  Chosen on
 // 9850 random batches: over 5 % slower than the other kernel 2.4 % of them, 7.3 % without the second line.
-// Against the persistent kernel from K = 384 on and without outputs the line is 0.8 and 1: its items have lost most of what
-// they cost between two k-loops.  Of 700 random batches small by the line above 92 are not by this one, 1.29x faster (K = 448, 283
-// x 401, 33 trials 31 : 19 us; K = 768, 203 x 623, 15 trials 24 : 19), two of them over 4 % slower (K = 384, 40 x 27, 513 trials 22 : 25).
+// Against the persistent kernel without outputs the line is 0.8 and 1 from K = 640 on: its items have lost most of what
+// they cost between two k-loops.  From K = 384 on it is 0.8 and 1.25, while that kernel takes one round: where a wave's
+// elements all differ (a B fault in the layer before) it waits sixteen times for magnitude sums, which a short k-loop does
+// not outweigh (K = 384, 57 x 61, 521 trials in a second round 31 : 45 us).  Of 11146 random batches small by the line above 2862
+// are not by this one: with one row changed in each trial, every row, or one row of Inf they are 1.35, 1.54 and 1.21x faster,
+// 0.1, 4.5 and 2.9 % of them over 4 % slower (K = 768, 203 x 623, 15 trials, one row 24 : 19 us).
 // Not beyond K = 8192, a chain of k-tiles (16 x 16 x 4096 38 : 44, x 16384 127 : 113).
 constexpr double kSmallPropagate = 160.0;
 // The same for the plan's fault-free pass, which has two results (see compute_golden).
@@ -206,7 +209,8 @@ bool use_small_propagate(const fi_plan* p, uint32_t n_trials, bool c_out, bool p
   const double rounds = (double)n_trials * ((d.M + 31) / 32) * ((d.N + 127) / 128) / (2.0 * p->n_cus);
   const int bm = persistent ? kMulti[p->prop_cfg].bm : kCfg[p->cfg].bm, bn = persistent ? kMulti[p->prop_cfg].bn : kCfg[p->cfg].bn;
   const double theirs = (double)n_trials * ((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * (bm * bn / 16384.0) / (2.0 * p->n_cus);
-  if (persistent && !c_out && d.K >= 384) return rounds <= 0.8 + theirs;
+  if (persistent && !c_out && (d.K >= 640 || (d.K >= 384 && theirs <= 1.0)))
+    return rounds <= 0.8 + (d.K >= 640 ? 1.0 : 1.25) * theirs;
   return rounds <= (persistent && c_out ? 5.0 : 1.0) + (persistent ? 2.0 : 4.0) * theirs;
 }
 

@@ -92,3 +92,46 @@ def test_small_next_layer_batches_equal_the_large_kernels(shape, n, fmt):
         for other in got[1:]:
             assert got[0][0] == other[0] and got[0][2] == other[2]
             assert np.array_equal(got[0][1], other[1])        # NaN words too
+
+
+def _side(M, N, K, n, cus):
+    """Which kernel a next-layer batch without outputs goes to while no tile configuration is chosen."""
+    up = lambda v, d: -(-v // d)
+    steps = n * up(M, 32) * up(N, 128) * 4 * (K // 16) / (4.0 * cus)
+    rounds, theirs = n * up(M, 32) * up(N, 128) / (2.0 * cus), n * up(M, 128) * up(N, 128) / (2.0 * cus)
+    line = 0.8 + theirs if K >= 640 else 0.8 + 1.25 * theirs if K >= 384 and theirs <= 1 else 1.0 + 2.0 * theirs
+    if steps <= 160 and rounds <= line:
+        return "small"
+    wide = up(n * (M // 256) * (N // 256), cus) if K >= 3072 and M % 256 == 0 and N % 256 == 0 else 0
+    return "256" if wide >= 2 and 10 * n * (M // 256) * (N // 256) >= 9 * wide * cus else "128"
+
+
+# n for 256 CUs, either side of each line: the first of K = 640 and of K = 384, that one's end where the persistent
+# kernel takes a second round; two rounds of 256 x 256 tiles, nine tenths full and just less, one round
+@pytest.mark.parametrize("M,N,K,n,side", [
+    (300, 200, 640, 29, "small"), (300, 200, 640, 30, "128"), (300, 200, 384, 32, "small"), (300, 200, 384, 33, "128"),
+    (300, 200, 320, 50, "small"), (57, 61, 384, 521, "small"), (57, 61, 640, 521, "128"),
+    (256, 256, 3072, 461, "256"), (256, 256, 3072, 460, "128"), (256, 256, 3072, 256, "128"), (512, 256, 4096, 256, "256"),
+    (256, 256, 3008, 512, "128"), (260, 256, 3072, 300, "128")])
+def test_next_layer_batches_either_side_of_the_lines_between_the_kernels(M, N, K, n, side):
+    import torch
+    assert _side(M, N, K, n, torch.cuda.get_device_properties(0).multi_processor_count) == side
+    g = torch.Generator(device="cuda").manual_seed(n)
+    a, b = torch.randn(M, K, generator=g, device="cuda").bfloat16(), torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    stack = a.expand(n, M, K).clone()
+    for t in range(0, n, 4):                            # a row, every row, a row that is flagged; every fourth trial untouched
+        stack[t, t % M] = stack[t, (t + 1) % M]
+        if t + 2 < n:
+            stack[t + 1, :, t % K] *= 2
+            stack[t + 2, (t + 5) % M, t % K] = float("inf")
+    got = []
+    for cfg in (-1, 2):                                 # the library's choice; one workgroup per tile
+        plan = fi.Plan(fi.plan_desc(M, N, K, 32, fi.BF16), a, b)
+        plan.tune(cfg)
+        d_r = fi.empty_results(n)
+        plan.fi_gemm_propagate_batch(stack, M * K, n, wl.CORRECT_RECOMPUTE, d_r)
+        got.append(fi.results_to_host(d_r))
+        plan.destroy()
+    assert got[0].tobytes() == got[1].tobytes(), [t for t in range(n) if got[0][t] != got[1][t]][:5]
+    assert not got[0]["n_bitdiff"][3::4].any() and (got[0]["n_bitdiff"][1::4][:n // 4 - 1] > M * N // 2).all()
+    assert (got[0]["n_flagged"][2::4] == N).all()
