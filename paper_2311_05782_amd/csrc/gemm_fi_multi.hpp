@@ -146,7 +146,15 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   // One array for everything: beside a second one the compiler takes the fragment reads to depend on the
   // staging loads and puts a wait for them in front of every read (4096^3 33 % slower).
   __shared__ __attribute__((aligned(16))) uint8_t smem[2 * STAGE + 16];
-  uint32_t* const next_item = reinterpret_cast<uint32_t*>(smem + 2 * STAGE);
+  // Its last word: the item behind the next.  The address is formed where it is used (the empty asm statement).
+  // Kept in a vector register over an epilogue, the compiler may form it anew behind a condition on the lane, in
+  // front of the instruction that ends it, where the other waves have no lane active: they then read their
+  // next item from anywhere (seen in one instance of the 256 x 256 shape).
+  auto next_item = [&]() __attribute__((always_inline)) {
+    int at = 2 * STAGE;
+    asm volatile("" : "+s"(at));
+    return reinterpret_cast<uint32_t*>(smem + at);
+  };
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -287,7 +295,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       if (lane == 0) t = __hip_atomic_fetch_add(queue + x * QS, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       w = position(x, (uint32_t)__builtin_amdgcn_readfirstlane((int)t));
     }
-    if (lane == 0) *next_item = w;
+    if (lane == 0) *next_item() = w;
   };
 
   // A group's R descriptors, one word per lane; fields are picked out with v_readlane.
@@ -1090,7 +1098,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   issue_tile(cur, 0, 0);
   bool has_next = false;
   auto locate_next = [&]() __attribute__((always_inline)) {
-    const uint32_t w_nxt = dynamic ? (uint32_t)__builtin_amdgcn_readfirstlane((int)*next_item) : w_cur + gridDim.x;
+    const uint32_t w_nxt = dynamic ? (uint32_t)__builtin_amdgcn_readfirstlane((int)*next_item()) : w_cur + gridDim.x;
     has_next = w_nxt < n_work;
     w_cur = w_nxt;
     if (has_next) {
