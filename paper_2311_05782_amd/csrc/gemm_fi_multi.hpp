@@ -63,6 +63,13 @@ __device__ __forceinline__ void store_wide(u32x4 q, __amdgpu_buffer_rsrc_t to, i
   asm volatile("s_nop 1" ::"v"(q) : "memory");
 }
 
+// Items per workgroup beyond which they come from the counters: the first two never do.  10383 random batches of 2 to 14
+// items per workgroup, the time with fixed shares over the time with counters.  Trials that leave the operands alone, no FP32
+// outputs: 2 .. 4 items 1.01 in the mean, 8 .. 14 items 1.05, one in fifty over 4 % slower.  Items of operand faults are uneven
+// (one with an event takes up to four times as long), and so are those that store FP32 outputs: 2 .. 4 items 1.006 and one in
+// six over 4 % slower, which gains nothing; 4 .. 8 items 1.025 and one in seven, 8 .. 14 items 1.043 and one in thirteen.  B
+// faults, 183 x 648 x 400, 310 trials (2.5 items) 58 : 70 us, 1000 x 1010 x 1008, 80 trials (5 items) 194 : 155.
+constexpr uint32_t kQueueItems = 2, kQueueItemsUneven = 4;
 // Items per workgroup from which a workgroup looks for work in other XCDs' slices at the end (a look takes two
 // round trips to memory).
 constexpr uint32_t kStealItems = 64;
@@ -269,7 +276,10 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   // them, the first two excepted.  Wave 0 asks in front of an epilogue (`request`), by the first barrier of
   // the item behind it the answer has come and goes to the other waves (`publish`), and all read it in front of
   // that item's last k-tile (`locate_next`): hence two k-tiles or more, and an item is taken one item ahead, not more.
-  const bool dynamic = p.queue != nullptr && n_work > 2 * gridDim.x;   // the grid is then a multiple of kQueueXcds
+  // Not with so few items that it has nothing to gain: a CU whose two workgroups both take one item more than
+  // others' is the last (kQueueItems, kQueueItemsUneven).  The grid is a multiple of kQueueXcds where it is true.
+  const uint32_t few = OPS || (!PROP && p.c_out != nullptr) ? kQueueItemsUneven : kQueueItems;
+  const bool dynamic = p.queue != nullptr && n_work > few * gridDim.x;
   uint32_t* const queue = p.queue + (OPS ? kQueueWords : 0);
   constexpr int QS = PROP ? kPropQueueStride : kQueueStride;
   uint32_t ticket = blockIdx.x / kQueueXcds - gridDim.x / kQueueXcds;  // position() of it: blockIdx.x + gridDim.x
