@@ -774,22 +774,24 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
                 // us, now 103 (83 with 1728 rows, all tiles whole); 310 of 183 x 648 x 400 197 and 120.
                 f32x16 out = t;
                 if (any != 0 && p.policy != FI_CORRECT_NONE) {
+                  const bool zero = p.policy == FI_CORRECT_ZERO;
 #pragma unroll
                   for (int v = 0; v < 16; ++v) {
-                    const int row = row0 + 8 * (v >> 2) + (v & 3);
-                    if (!(fabsf(t[v]) <= T[v])) out[v] = p.policy == FI_CORRECT_ZERO ? 0.0f : p.c_star[(size_t)row * p.N + col0];
+                    const int row = min(row0 + 8 * (v >> 2) + (v & 3), p.M - 1);
+                    const float golden = zero ? 0.0f : p.c_star[(size_t)row * p.N + min(col0, p.N - 1)];
+                    out[v] = fabsf(t[v]) <= T[v] ? t[v] : golden;
                   }
                   __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
                 }
-                const size_t at = out0 + (size_t)row0 * p.N + col0;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                  const int down = 8 * (v >> 2) + (v & 3);
-                  if (row0 + down < p.M && col0 < p.N) {
-                    if (p.c_out) p.c_out[at + (size_t)down * p.N] = out[v];
+                  const int row = row0 + 8 * (v >> 2) + (v & 3);
+                  if (row < p.M && col0 < p.N) {
+                    const size_t at = out0 + (size_t)row * p.N + col0;
+                    if (p.c_out) p.c_out[at] = out[v];
                     // the hand-over between two layers fused into this epilogue: relu keeps a NaN
                     // and maps negatives and -0 to +0, then the integer round-to-format
-                    if (p.h_out) p.h_out[at + (size_t)down * p.N] = (uint16_t)relu_round16<DT>(out[v]);
+                    if (p.h_out) p.h_out[at] = (uint16_t)relu_round16<DT>(out[v]);
                   }
                 }
               }
