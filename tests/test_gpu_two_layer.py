@@ -330,6 +330,49 @@ def test_fused_hand_over_rounds_as_the_oracle_over_the_formats_ranges(fmt, scale
     plan.destroy()
 
 
+def _edge_words():
+    """binary32 words next to where rounding to either format turns: ties and their neighbours on every exponent, FP16's
+    grid below 2^-14 and its largest value, and the specials that no rule flags."""
+    at = lambda exps, tops, shift, lows: (np.array(exps, np.uint32)[:, None, None] << 23 | np.array(tops, np.uint32)[:, None] << shift |
+                                          np.array(lows, np.uint32)).reshape(-1)
+    bf16 = at(range(255), (0, 1, 2, 3, 0x3F, 0x40, 0x7E, 0x7F), 16, (0, 1, 0x7FFF, 0x8000, 0x8001, 0xFFFF))
+    fp16 = at(range(100, 145), (0, 1, 2, 0x1FF, 0x200, 0x3FE, 0x3FF), 13, (0, 1, 0xFFF, 0x1000, 0x1001, 0x1FFF))
+    ties = ((np.arange(0, 1024, 7) + 0.5) * 2.0 ** -24).astype(np.float32).view(np.uint32)
+    special = np.array([0.0, np.inf, 65504.0, 65519.9, 65520.0, 3.4028235e38, 1e-45], np.float32).view(np.uint32)
+    words = np.concatenate([bf16, fp16, ties - 1, ties, ties + 1, special])
+    return np.concatenate([words, words[::5] | np.uint32(0x80000000)])
+
+
+@pytest.mark.parametrize("cfg", [3, 6])
+@pytest.mark.parametrize("fmt", [orc.FP16, orc.BF16])
+def test_fused_hand_over_rounds_every_edge_word_as_the_oracle(fmt, cfg):
+    # an accumulator fault after the last step writes the word into an output of +0; the threshold is +Inf
+    import torch
+    tile, K = 64 if cfg == 6 else 128, 128
+    one = wl.to_words(np.ones(tile, np.float32), fmt)
+    A, B = np.zeros((tile, K), np.uint16), np.zeros((tile, K), np.uint16)
+    A[:, 0], B[:, 1] = one, one                                  # every product 0
+    plan = gu.make_plan(A, B, 32, fmt, cfg=cfg, gamma=3e38)
+    words = _edge_words()
+    if cfg == 3:
+        words = words[::4]
+    n = len(words)
+    t = np.arange(n)
+    faults = np.zeros(n, fi.FAULT_DTYPE)
+    faults["kind"], faults["row"], faults["col"], faults["kblock"] = fi.SITE_ACC, t * 7 % tile, t * 3 % tile, 3
+    faults["xor_mask"] = words
+    d_r = fi.empty_results(n)
+    d_h = torch.full((n, tile, tile), 0x5555, dtype=torch.int16, device="cuda")
+    plan.fi_gemm_inject_batch_act(fi.to_device(faults), n, orc.CORRECT_ZERO, d_r, d_h)
+    r, h = fi.results_to_host(d_r), d_h.cpu().numpy().view(np.uint16)
+    assert not r["n_flagged"].any() and np.array_equal(r["site_word_after"], words)
+    got, want = h[t, faults["row"], faults["col"]], orc.activation_round(words.view(np.float32), fmt)
+    assert np.array_equal(got, want), [(hex(words[i]), hex(got[i]), hex(want[i])) for i in np.nonzero(got != want)[0][:5]]
+    h[t, faults["row"], faults["col"]] = 0
+    assert not h.any()
+    plan.destroy()
+
+
 def test_fused_hand_over_is_refused_where_the_one_trial_kernel_runs():
     Aw, Bw = wl.gaussian(64, 64, 96, orc.BF16, seed=5)
     plan = gu.make_plan(Aw, Bw, 32, orc.BF16, cfg=2)             # 256 x 64 tiles: the one-trial kernel
