@@ -266,13 +266,15 @@ fi_status fi_activation_round(uint32_t dtype, const float* d_c, uint64_t n, uint
  * element of every trial passes the plan's detector / corrector and is compared with the
  * plan's fault-free result C* = A x B under the plan's tolerance: d_results[t] holds
  * n_flagged, n_bitdiff, n_dev_pre, n_dev_post, the largest deviations and the guard-band
- * counts over the whole output (site words 0).  Rows of a trial's operand that equal the
+ * counts over the whole output (site words 0: while the work runs those of the first eight
+ * records may hold its work counters, so nobody else writes d_results meanwhile, and it is read
+ * behind the work).  Rows of a trial's operand that equal the
  * plan's A word for word reproduce the rows of C* bit for bit.  A trial's operand may hold
  * Inf or NaN (they propagate as IEEE and are flagged).  d_c_out as in fi_gemm_inject_batch.
  * The caller owns d_a_stack and keeps it unmodified until the work has run.  All 2*M*N*K
  * flops of every trial are executed (one trial per work item; tile configurations 0..2, of
- * which 0 and 1 run as persistent workgroups when K is a multiple of 64, the default chosen
- * by problem size; small batches one wave per 32x32 tile while none has been chosen).
+ * which 0 and 1 run as persistent workgroups when K is a multiple of 64; while none has been
+ * chosen, by problem size and number of trials, small batches one wave per 32x32 tile).
  * Errors: INVALID_ARG (NULLs, n_trials == 0, bad policy, trial_stride too small),
  * UNSUPPORTED (alignment; tiles x trials >= 2^31). */
 fi_status fi_gemm_propagate_batch(fi_plan* plan, const void* d_a_stack, uint64_t trial_stride,

@@ -28,7 +28,7 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
 // FP16/BF16 numbers order like their low 15 bits, non-negative floats like their words.  A wave per
 // row, walking the rows of A and then of B with the grid as stride, four loads in flight.  One atomic per
 // workgroup and maximum: they come one after the other, some 7 ns each, so workgroups of 16 waves, one
-// per CU at most (512 x 3072 x 768 with four waves each, 896 workgroups, 13.0 us, now 5.4; 4096^3 22.6 -> 15).
+// per CU at most (512 x 3072 x 768 with four waves each, 896 workgroups, 13.0 us, now 5.7; 4096^3 22.6 -> 13.8).
 constexpr uint32_t kStatWaves = 16;
 template <int DT>
 __global__ void __launch_bounds__(kStatWaves * 64) plan_stats_kernel(const uint16_t* __restrict__ A, uint32_t lda, uint32_t M,

@@ -217,9 +217,12 @@ bool use_small_propagate(const fi_plan* p, uint32_t n_trials, bool c_out, bool p
 // Tile shape of a next-layer batch.  Below 2^35 multiply-adds the plan has the 128 x 128 shape, two workgroups
 // per CU, one's epilogue under the other's MFMAs.  256 x 256 tiles read a third less from LDS per MFMA and half
 // as much from L2, but nothing hides an item's epilogue, so they take long items in whole rounds
-// that fill nine tenths of the chip: 256 : 128, K = 3072, 512 x 768, 256 trials (6 rounds) 590 : 658 us, K = 4096, 1024^2, 32
-// trials 254 : 268; K = 1024, 1024^2, 128 trials 347 : 314; K = 3072, 512 x 768, 64 trials (1.5 rounds) 177 : 145; K = 4096,
-// 256^2, 256 trials (1 round) 186 : 177.
+// that fill nine tenths of the chip: 256 : 128, K = 3072, 512 x 768, 256 trials (6 rounds) 590 : 661 us, 81 trials (1.9 rounds)
+// 191 : 195, 80 trials 187 : 186, 90 trials (2.1 rounds, a third empty) 264 : 243, 64 trials (1.5) 177 : 145; 256^2, 512 trials 250 : 284; K = 4096,
+// 1024^2, 32 trials 248 : 266, 256^2, 256 trials (1 round) 186 : 177; K = 8192, 256 x 512, 256 trials 491 : 575.  Shorter K gains
+// less and less surely: K = 2048, 512 x 768, 256 trials 423 : 466 but 512^2, 128 trials 149 : 146; K = 1536, 1024^2, 64 trials 211 : 213; K = 1024,
+// 1024^2, 128 trials 347 : 314.  Shapes that are no multiple of 256 lose where the larger tiles pad more (384^2 x 4096, 128 trials
+// 260 : 214) and would gain where they do not (1000^2 x 3072, 64 trials 389 : 450); they stay with the plan's shape.
 constexpr uint32_t kPropLongK = 3072;
 int pick_prop(const fi_plan* p, uint32_t n_trials) {
   const fi_plan_desc& d = p->d;
@@ -618,9 +621,10 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
       m.K = a.K + (int)plan->kshift;
       m.lda = m.ldb = (uint32_t)m.K;
     }
-    // Persistent workgroups, as many per CU as the configuration's register budget admits, each
-    // walking the work list with the grid as stride; a multiple of 8 keeps a workgroup's items
-    // on one XCD.
+    // Persistent workgroups, as many per CU as the configuration's register budget admits.  They
+    // take their items from counters, one per XCD, or walk the work list with the grid as stride
+    // (see gemm_fi_multi_kernel); for both the grid has to be a multiple of 8 where it is not the
+    // work list's length.
     const uint64_t groups = ((uint64_t)n_trials + mc.r - 1) / mc.r;
     const uint64_t items = (uint64_t)m.tiles_m * m.tiles_n * groups;
     if (items >= (1ull << 31)) return fail(FI_UNSUPPORTED, "tiles x trials exceeds 2^31 work items; split the batch");
@@ -757,9 +761,9 @@ fi_status fi_plan_create(const fi_plan_desc* desc, const void* d_A, const void* 
   p->cfg = pick_cfg(d);
   p->cfg_affected = d.N <= 64 ? 2 : 1;
   p->mcfg = pick_multi(d);
-  // Next-layer launches: on problems below 2^35 multiply-adds the 128 x 128 shape with two
-  // workgroups per CU measured faster (one's epilogue runs under the other's MFMAs: 0.75 against
-  // 0.81 ms on 512 x 768 x 3072, 256 trials), above it the 256 x 256 shape (less LDS traffic per flop).
+  // Next-layer launches: on problems below 2^35 multiply-adds the 128 x 128 shape with two workgroups
+  // per CU (one's epilogue runs under the other's MFMAs) but for the batches that pick_prop sends to the
+  // 256 x 256 shape, above it that one always (less LDS traffic per flop).
   p->prop_cfg = (double)d.M * (double)d.N * (double)d.K >= 34359738368.0 ? fi::kMultiOneTrial[0]
                                                                          : fi::kMultiOneTrial[1];
   p->group = 32;

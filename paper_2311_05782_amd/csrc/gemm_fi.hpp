@@ -183,7 +183,8 @@ __device__ __forceinline__ uint32_t relu_round16(float x) {
 // The words of round16(relu(x)) and round16(relu(y)), x's in the low half, for values that are not NaN: as a
 // signed word a negative value is below 0, and the conversion instruction rounds to nearest even (the mode
 // every kernel here runs in, subnormals kept).  Three instructions a pair where relu_round16 takes ten to
-// twenty; the same words on all 2^32 inputs but the NaNs, of either format.
+// twenty; the same words, of either format, as a comparison over all 2^32 inputs but the NaNs showed and the
+// tests repeat next to every turn of the rounding.
 template <int DT>
 __device__ __forceinline__ uint32_t relu_round16_pair(float x, float y) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));

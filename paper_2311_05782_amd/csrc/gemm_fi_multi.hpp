@@ -31,7 +31,7 @@
 // the grid is one or two workgroups per CU and each walks its items with the k-loop running
 // straight through: during the last k-tile of an item the first k-tile of the next item is
 // already loading into the free LDS stage, and its descriptors with it.  Which item comes next a
-// workgroup learns one item ahead, from a counter: taken in turn with the grid as stride, the older
+// workgroup learns one item ahead, in launches of more than a few items each from a counter: taken in turn with the grid as stride, the older
 // workgroup of a CU was done after two thirds of a launch of two per CU (5121 of 7588 us on 512 x 3072 x
 // 768, 4096 trials), the younger one then alone on its CU.
 //
@@ -71,7 +71,9 @@ __device__ __forceinline__ void store_wide(u32x4 q, __amdgpu_buffer_rsrc_t to, i
 // faults, 183 x 648 x 400, 310 trials (2.5 items) 58 : 70 us, 1000 x 1010 x 1008, 80 trials (5 items) 194 : 155.
 constexpr uint32_t kQueueItems = 2, kQueueItemsUneven = 4;
 // Items per workgroup from which a workgroup looks for work in other XCDs' slices at the end (a look takes two
-// round trips to memory).
+// round trips to memory).  With it and without: 1024^3, 2048 trials (128 items) 2662 : 2760 us, 512 x 3072 x 768, 700 trials (66)
+// 1052 : 1083, 4096 mixed trials 6191 : 6378; 256 in its place gains only beyond (2760, 1083, 6369).  From 16 on (1024^3, 1000
+// trials, 62 items 1311 for 1359; 512 x 3072 x 768, 200 trials, 19 items 317 for 322) it would have gained too.
 constexpr uint32_t kStealItems = 64;
 // Work counters of a launch: one per XCD, 64 bytes apart.
 constexpr int kQueueXcds = 8, kQueueStride = 16, kQueueWords = kQueueXcds * kQueueStride;
