@@ -27,9 +27,9 @@ MFMA_PEAK_TFLOPS = 2516.6     # 256 CUs x 4096 flop/clk/CU x 2.4 GHz, dense FP16
 # commands.  They describe the kernel sources whose digest is recorded with them and are not
 # reported for any other.
 TRAFFIC = {
-    "sources_sha256": "a2383a0a263e2dba9c1342a82d65d4a3dd69b7daf6e01e0b9329cadb1eaf3309",
-    "fetch_bytes": 2.194705e6 * 2.0 * 1024,
-    "write_bytes": 8391.531 * 1.0 * 1024,
+    "sources_sha256": "889bb5a79ece638dc539bc3933ee1ea973aa430577dcf6670e8662042355cfc1",
+    "fetch_bytes": 2.218785e6 * 2.0 * 1024,
+    "write_bytes": 8404.969 * 1.0 * 1024,
 }
 
 
