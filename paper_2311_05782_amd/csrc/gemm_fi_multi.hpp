@@ -352,9 +352,13 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   constexpr int LOAD_STRIDE = NLOADS <= 3 * ((NMMA - 2) / 2 + 1) ? 2 : 1;
   constexpr int LOADS_PER_STEP = (NMMA - 2) / LOAD_STRIDE + 1;   // after MFMA 1, 1 + stride, ...
   static_assert(NMMA >= 2 && NLOADS <= 3 * LOADS_PER_STEP, "the loads of a k-tile fit its first three bursts");
-  auto mma_step_mid = [&](const Frags& f, auto first, auto step_in_tile, auto&& mid, auto&& load) __attribute__((always_inline)) {
-    constexpr bool FIRST = decltype(first)::value;
-    constexpr int SIT = decltype(step_in_tile)::value;   // 0 .. 3; loads go with 0 .. 2
+  // The next layer's loads go out a step earlier (FAR, see below): the first of them behind the barrier, in the last
+  // step of the tile before the one whose steps they used to go with, the others in that one's first step.
+  constexpr int FAR_FIRST = NLOADS < NMMA ? NLOADS : NMMA;
+  static_assert(!PROP || NLOADS - FAR_FIRST <= NMMA, "two bursts take the loads of a k-tile");
+  auto mma_step_mid = [&](const Frags& f, auto first, auto step_in_tile, auto far, auto&& mid, auto&& load) __attribute__((always_inline)) {
+    constexpr bool FIRST = decltype(first)::value, FAR = decltype(far)::value;
+    constexpr int SIT = decltype(step_in_tile)::value;   // 0 .. 3; loads go with 0 .. 2, FAR with 3 and 0
     [[maybe_unused]] Frags q = f;
     static_for<NMMA>([&](auto t) {
       constexpr int r = t / (TM * TN), i = (t / TN) % TM, j = t % TN;
@@ -363,8 +367,9 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
         mid();
         __builtin_amdgcn_sched_barrier(0);
       }
-      if constexpr (SIT < 3 && t >= 1 && (t - 1) % LOAD_STRIDE == 0) {
-        constexpr int k = SIT * LOADS_PER_STEP + (t - 1) / LOAD_STRIDE;
+      if constexpr (FAR ? SIT == 3 || SIT == 0 : SIT < 3 && t >= 1 && (t - 1) % LOAD_STRIDE == 0) {
+        constexpr int k = !FAR ? SIT * LOADS_PER_STEP + (t - 1) / LOAD_STRIDE
+                          : SIT == 0 ? FAR_FIRST + t : t < FAR_FIRST ? (int)t : NLOADS;
         if constexpr (k < NLOADS) {
           __builtin_amdgcn_sched_barrier(0);
           load(std::integral_constant<int, k>{});
@@ -1163,14 +1168,16 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
     auto k_tile = [&](auto with_events, auto is_first, auto last_mode, auto stage_c, int kt) __attribute__((always_inline)) {
       constexpr bool EV = decltype(with_events)::value;
       constexpr bool FIRST = decltype(is_first)::value;
-      // last_mode: 0 not the last k-tile, 1 the last, 2 decided at run time (items with events)
+      // last_mode: 0 not the last k-tile, 1 the last, 2 decided at run time (items with events); FAR: 3 at least
+      // two before the end, 4 the last but one, 5 the last
       constexpr int LM = decltype(last_mode)::value;
+      constexpr bool FAR = LM >= 3;
       static_assert(!(EV && FIRST), "items with events clear their accumulators up front");
       // stage_c: 0 or 1 when the LDS stage is known at compile time (the addresses of the
       // fragment reads then fold into immediates), -1 to use the running variable.
       constexpr int SC = decltype(stage_c)::value;
       if constexpr (SC >= 0) stage = SC;
-      const bool last = LM == 2 ? kt == nkt - 1 : LM == 1;
+      const bool last = LM == 2 ? kt == nkt - 1 : LM == 1 || LM == 5;
       if constexpr (LM == 2) {
         if (last) locate_next();
       }
@@ -1192,8 +1199,12 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       const uint8_t* s = smem + stage * STAGE;
       const uint8_t* s_other = smem + (stage ^ 1) * STAGE;
       auto load = [&](auto kk) __attribute__((always_inline)) {
-        if constexpr (SPREAD) {
-          if constexpr (LM == 0) issue_one(cur, kt + 1, stage ^ 1, kk);
+        if constexpr (FAR && kk < FAR_FIRST) {
+          // behind this tile's barrier: its own stage is free for the tile after the next
+          if constexpr (LM == 3) issue_one(cur, kt + 2, stage, kk);
+          else if constexpr (LM == 4) { if (has_next) issue_one(nxt, 0, stage, kk); }
+        } else if constexpr (SPREAD) {
+          if constexpr (LM == 0 || LM == 3 || LM == 4) issue_one(cur, kt + 1, stage ^ 1, kk);
           else if (has_next) issue_one(nxt, 0, stage ^ 1, kk);
         }
       };
@@ -1204,12 +1215,12 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
           if constexpr (OPS) {
             mma_step_ops(f, m, mid);
           } else {
-            mma_step_mid(f, first, sit, mid, load);
+            mma_step_mid(f, first, sit, std::false_type{}, mid, load);
             __builtin_amdgcn_sched_barrier(0);
             if (__builtin_expect(m != 0, 0)) hooks(m);
           }
         } else {
-          mma_step_mid(f, first, sit, mid, load);
+          mma_step_mid(f, first, sit, std::integral_constant<bool, FAR>{}, mid, load);
         }
         __builtin_amdgcn_sched_barrier(0);
       };
@@ -1225,7 +1236,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       // vmcnt(0): this wave's loads have landed.  Also where no tile follows: the epilogue then finds nothing
       // that the compiler would have to wait for, the answer of `request` included.
       __builtin_amdgcn_s_waitcnt(0x0F70);
-      if constexpr (FIRST && LM == 0) publish();
+      if constexpr (FIRST && (LM == 0 || LM == 3)) publish();
       __syncthreads();
       step(f1, 4 * kt + 3, std::false_type{}, s3{}, [&]() { if (more) read_frags(f0, s_other, 0); });
       stage ^= 1;
@@ -1238,7 +1249,32 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
     using mid_tile = std::integral_constant<int, 0>;
     using last_tile = std::integral_constant<int, 1>;
     using any_tile = std::integral_constant<int, 2>;
-    if (PROP || owned == 0) {
+    [[maybe_unused]] bool far = false;
+    if constexpr (PROP) {
+      // FAR: a k-tile's loads have three steps to land in the place of one or two.  Every trial has an operand of its
+      // own, and the 256 x 256 tiles have no second workgroup on the CU that would work meanwhile: 512 x 768 x 3072, 256
+      // trials 573 -> 546 us.  The next item's first tile is asked for in the last but one, hence a tile between that
+      // and the one whose barrier says which item it is.
+      far = nkt >= 4 && (nkt & 1) == 0 && stage == 0;
+      if (far) {
+        using far_mid = std::integral_constant<int, 3>;
+        using far_pre = std::integral_constant<int, 4>;
+        using far_last = std::integral_constant<int, 5>;
+        static_for<FAR_FIRST>([&](auto kk) { issue_one(cur, 1, 1, kk); });
+        k_tile(no{}, yes{}, far_mid{}, st0{}, 0);
+        k_tile(no{}, no{}, far_mid{}, st1{}, 1);
+        for (int kt = 2; kt + 2 < nkt; kt += 2) {
+          k_tile(no{}, no{}, far_mid{}, st0{}, kt);
+          k_tile(no{}, no{}, far_mid{}, st1{}, kt + 1);
+        }
+        locate_next();
+        k_tile(no{}, no{}, far_pre{}, st0{}, nkt - 2);
+        prepare_epilogue();
+        k_tile(no{}, no{}, far_last{}, st1{}, nkt - 1);
+      }
+    }
+    if (far) {
+    } else if (PROP || owned == 0) {
       // Nearly every wave of nearly every item: no event check anywhere.
       if (nkt == 1) {
         locate_next();

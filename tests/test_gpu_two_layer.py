@@ -209,6 +209,31 @@ def _records_of(plan, stack, n):
     return fi.results_to_host(d_r)
 
 
+@pytest.mark.parametrize("cfg", [0, 1])
+@pytest.mark.parametrize("k_tiles", [1, 2, 3, 4, 5, 6, 8])
+@pytest.mark.parametrize("n", [2, 620])
+def test_next_layer_pipeline_depths_equal_the_one_trial_kernel(cfg, k_tiles, n):
+    # the shortest pipelines and one k-tile more or less than each; a trial per workgroup and several, taken from
+    # the counters; every trial on words of its own, so that a tile of another trial or k would show in its counts
+    import torch
+    M, N, K = 256, 264, 64 * k_tiles
+    g = torch.Generator(device="cuda").manual_seed(100 * k_tiles + n)
+    a = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    b = torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    stack = a.expand(n, M, K).clone()
+    t = torch.arange(n, device="cuda")
+    stack[t, t * 7 % M, t * 13 % K] *= 2
+    stack[t[1::3], t[1::3] * 5 % M] = torch.randn(len(t[1::3]), K, generator=g, device="cuda").bfloat16()
+    recs = []
+    for c in (2, cfg):
+        plan = fi.Plan(fi.plan_desc(M, N, K, 32, fi.BF16), a, b)
+        plan.tune(c)
+        recs.append(_records_of(plan, stack, n))
+        plan.destroy()
+    assert recs[0].tobytes() == recs[1].tobytes()
+    assert recs[0]["n_bitdiff"].min() > 0
+
+
 @pytest.mark.parametrize("fmt", [orc.FP16, orc.BF16])
 def test_two_layers_end_to_end_against_the_oracle_chain(fmt):
     # layer 1: campaign with materialised corrected outputs -> ReLU + rounding -> layer 2 on the
