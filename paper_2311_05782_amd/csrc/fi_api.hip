@@ -63,6 +63,8 @@ struct BatchScratch {
   uint32_t* words = nullptr;  // [scratch_words(cap)], see TrialScratch
   uint32_t cap = 0;
   bool own = false;           // an allocation of its own, else part of the plan's
+  uint32_t* parts = nullptr;  // [parts_cap] words for the affected-only campaign, or NULL: only fi_plan_reserve makes them
+  size_t parts_cap = 0;
 };
 
 struct fi_plan {
@@ -258,37 +260,60 @@ GemmArgs base_args(const fi_plan* p, int cfg = -1) {
   return a;
 }
 
-// The affected-only campaign: every record by the element kernel, then the operand faults' rows
-// and columns.
-template <int DT>
-fi_status launch_affected(const GemmArgs& a, int n_cus, bool plain_ok, hipStream_t s) {
-  // A piece is one load instruction per row (512 k) up to K = 512, two beyond.  Three pieces in
-  // flight cover the memory latency of a wave that has its CU to itself; from two waves per CU on
-  // they take each other's LDS, and one piece in flight per wave is the better use of it.
-  const unsigned waves = ((unsigned)a.n_trials + fi::kElemTrials - 1) / fi::kElemTrials;
-  const bool wide = a.K > 512, deep = waves <= 2u * (unsigned)n_cus;
-  const int pieces = wide ? (a.K + 1023) / 1024 : 1;
-  const int bufs = pieces < (deep ? 4 : 2) ? pieces : deep ? 4 : 2;
-  const size_t lds = (size_t)2 * fi::kElemTrials * (wide ? 2080 : 1056) * bufs;
-  if (!wide)
-    hipLaunchKernelGGL((fi::affected_element_kernel<DT, 1, 2>), dim3(waves), dim3(64), lds, s, a);
-  else if (deep)
-    hipLaunchKernelGGL((fi::affected_element_kernel<DT, 2, 4>), dim3(waves), dim3(64), lds, s, a);
-  else
-    hipLaunchKernelGGL((fi::affected_element_kernel<DT, 2, 2>), dim3(waves), dim3(64), lds, s, a);
-  FI_HIP(hipGetLastError());
-  // Workgroups per (chunk, item): one per tile of the other operand while that stays within some
-  // 2048 workgroups; beyond, each walks several tiles, and the workgroups that find no item (all of
-  // them in a batch of accumulator faults) stay few.
-  const int64_t items = ((int64_t)a.n_trials + fi::kRowsChunk - 1) / fi::kRowsChunk * fi::kRowsSlots;
-  const int64_t tiles = ((int64_t)(a.M > a.N ? a.M : a.N) + fi::kRowsX - 1) / fi::kRowsX;
+// Slots from which workgroups leave their counts in scratch.  Added to the record : left, K = 256, A faults: 4 slots
+// (512^2) 3000 trials 16.5 : 15.6 us, 400 trials 14.7 : 14.9; 8 (1000^2) 19.2 : 17.6, 15.4 : 15.7; 16 (2048^2) 26.5 : 21.2,
+// 16.3 : 15.8; 32 (4096^2) 49.4 : 38.9, 18.1 : 16.3, 8 trials 16.2 : 14.2.  The slots are those of the longer side; where
+// the faults lie along the other, of one to four slots, it costs up to half a microsecond (3072 x 512, 400 trials 15.1 : 15.7).
+constexpr uint32_t kPartSlots = 8;
+// Workgroups of the affected-only campaign's row / column kernel per (chunk of trials, item): one per tile of the other
+// operand while that stays within some 2048 workgroups; beyond, each walks several tiles, and the workgroups that
+// find no item (all of them in a batch of accumulator faults) stay few.
+struct RowsGrid { uint32_t items, x_slots; };
+RowsGrid rows_grid(const fi_plan_desc& d, uint32_t n_trials) {
+  const int64_t items = ((int64_t)n_trials + fi::kRowsChunk - 1) / fi::kRowsChunk * fi::kRowsSlots;
+  const int64_t tiles = ((int64_t)(d.M > d.N ? d.M : d.N) + fi::kRowsX - 1) / fi::kRowsX;
   int64_t per_slot = (tiles * items + 2047) / 2048;
   if (per_slot > tiles) per_slot = tiles;
-  const int x_slots = (int)((tiles + per_slot - 1) / per_slot);
+  return {(uint32_t)items, (uint32_t)((tiles + per_slot - 1) / per_slot)};
+}
+// Words of their parts, for this number of trials and any smaller one: x_slots <= min(tiles, 2048 / items + 1).
+size_t parts_words(const fi_plan_desc& d, uint32_t n_trials) {
+  const size_t chunks = ((size_t)n_trials + fi::kRowsChunk - 1) / fi::kRowsChunk;
+  const size_t tiles = ((size_t)(d.M > d.N ? d.M : d.N) + fi::kRowsX - 1) / fi::kRowsX;
+  const size_t bound = 2048 / fi::kRowsSlots + 1 + chunks;   // of chunks * x_slots
+  return (chunks * tiles < bound ? chunks * tiles : bound) * fi::kRowsChunk * fi::kPartWords;
+}
+
+// The affected-only campaign: the operand faults' rows and columns, and every record by the element kernel, which
+// comes last where `parts` holds what the others have counted.
+template <int DT>
+fi_status launch_affected(const GemmArgs& a, const RowsGrid& rows, int n_cus, bool plain_ok, uint32_t* parts, hipStream_t s) {
+  auto elements = [&]() {
+    // A piece is one load instruction per row (512 k) up to K = 512, two beyond.  Three pieces in
+    // flight cover the memory latency of a wave that has its CU to itself; from two waves per CU on
+    // they take each other's LDS, and one piece in flight per wave is the better use of it.
+    const unsigned waves = ((unsigned)a.n_trials + fi::kElemTrials - 1) / fi::kElemTrials;
+    const bool wide = a.K > 512, deep = waves <= 2u * (unsigned)n_cus;
+    const int pieces = wide ? (a.K + 1023) / 1024 : 1;
+    const int bufs = pieces < (deep ? 4 : 2) ? pieces : deep ? 4 : 2;
+    const size_t lds = (size_t)2 * fi::kElemTrials * (wide ? 2080 : 1056) * bufs;
+#define FI_ELEMENTS(IPR, NBUF)                                                                                        \
+  if (parts)                                                                                                         \
+    hipLaunchKernelGGL((fi::affected_element_kernel<DT, IPR, NBUF, true>), dim3(waves), dim3(64), lds, s, a, parts,   \
+                       (int)rows.x_slots);                                                                           \
+  else                                                                                                               \
+    hipLaunchKernelGGL((fi::affected_element_kernel<DT, IPR, NBUF, false>), dim3(waves), dim3(64), lds, s, a, parts, \
+                       (int)rows.x_slots)
+    if (!wide) { FI_ELEMENTS(1, 2); } else if (deep) { FI_ELEMENTS(2, 4); } else { FI_ELEMENTS(2, 2); }
+#undef FI_ELEMENTS
+  };
+  if (!parts) elements();
   if (a.c_star_bytes != 0)
-    hipLaunchKernelGGL((fi::affected_rows_kernel<DT, false>), dim3((unsigned)(items * x_slots)), dim3(256), 0, s, a, x_slots, (int)plain_ok);
+    hipLaunchKernelGGL((fi::affected_rows_kernel<DT, false>), dim3(rows.items * rows.x_slots), dim3(256), 0, s, a, (int)rows.x_slots, (int)plain_ok, parts);
   else
-    hipLaunchKernelGGL((fi::affected_rows_kernel<DT, true>), dim3((unsigned)(items * x_slots)), dim3(256), 0, s, a, x_slots, (int)plain_ok);
+    hipLaunchKernelGGL((fi::affected_rows_kernel<DT, true>), dim3(rows.items * rows.x_slots), dim3(256), 0, s, a, (int)rows.x_slots, (int)plain_ok, parts);
+  FI_HIP(hipGetLastError());
+  if (parts) elements();
   FI_HIP(hipGetLastError());
   return FI_OK;
 }
@@ -383,8 +408,10 @@ fi_status check_plan(const fi_plan* p) {
 void free_plan_buffers(fi_plan* p) {
   if (p->memory) (void)hipFree(p->memory);
   p->memory = nullptr;
-  for (BatchScratch& b : p->batch)
+  for (BatchScratch& b : p->batch) {
     if (b.own) (void)hipFree(b.words);
+    if (b.parts) (void)hipFree(b.parts);
+  }
   p->batch.clear();
 }
 
@@ -849,7 +876,20 @@ fi_status fi_plan_reserve(fi_plan* plan, uint32_t max_trials, void* stream) {
   if (st != FI_OK) return st;
   if (max_trials == 0) return fail(FI_INVALID_ARG, "max_trials is 0");
   BatchScratch* bs = nullptr;
-  return batch_scratch(plan, as_stream(stream), max_trials, &bs);
+  st = batch_scratch(plan, as_stream(stream), max_trials, &bs);
+  if (st != FI_OK) return st;
+  const size_t words = parts_words(plan->d, max_trials);
+  if (bs->parts_cap < words) {
+    if (bs->parts) (void)hipFree(bs->parts);
+    bs->parts = nullptr; bs->parts_cap = 0;
+    if (hipMalloc(&bs->parts, words * sizeof(uint32_t)) == hipSuccess) {
+      bs->parts_cap = words;
+    } else {
+      bs->parts = nullptr;                                // the affected-only campaign does without
+      (void)hipGetLastError();
+    }
+  }
+  return FI_OK;
 }
 
 fi_status fi_plan_set_clock_sink(fi_plan* plan, uint64_t* d_clocks) {
@@ -988,8 +1028,17 @@ fi_status fi_gemm_inject_batch_affected(fi_plan* plan, const fi_fault* d_faults,
   a.results = d_results;
   a.policy = (int)policy;
   a.product_check = plan->product_check;
-  if (plan->d.dtype == FI_BF16) return launch_affected<FI_BF16>(a, plan->n_cus, plan->plain_ok, s);
-  return launch_affected<FI_FP16>(a, plan->n_cus, plan->plain_ok, s);
+  const RowsGrid rows = rows_grid(plan->d, n_trials);
+  // Not under capture: a graph may be replayed beside calls on this stream, and outlive the buffer.
+  uint32_t* parts = nullptr;
+  for (const BatchScratch& b : plan->batch) {
+    if (rows.x_slots < kPartSlots || b.stream != s || b.parts_cap < (size_t)rows.x_slots * n_trials * fi::kPartWords) continue;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+    else if (capture == hipStreamCaptureStatusNone) parts = b.parts;
+  }
+  if (plan->d.dtype == FI_BF16) return launch_affected<FI_BF16>(a, rows, plan->n_cus, plan->plain_ok, parts, s);
+  return launch_affected<FI_FP16>(a, rows, plan->n_cus, plan->plain_ok, parts, s);
 }
 
 fi_status fi_activation_round(uint32_t dtype, const float* d_c, uint64_t n, uint16_t* d_h, void* stream) {

@@ -61,6 +61,47 @@ def test_affected_records_equal_the_full_campaigns(shape, n, kinds, fmt):
         plan.destroy()
 
 
+# Operand faults whose workgroups leave their counts in reserved scratch, to be added up: a slot per tile of 128 and one
+# trial more than an item, a row that lies in one slot of many (the others leave nothing), more slots than lanes that
+# add up in one go, several tiles per slot
+@pytest.mark.parametrize("M,N,n,kinds", [(70, 1025, 65, "r"), (1025, 70, 65, "c"), (1100, 64, 300, "r"), (64, 2100, 130, "erc"),
+                                         (40, 2200, 1500, "eprcx"), (3000, 40, 9000, "rc")])
+def test_affected_records_added_up_from_reserved_scratch(M, N, n, kinds):
+    import torch
+    fmt = orc.BF16
+    Aw, Bw = wl.gaussian(M, N, 64, fmt, seed=M)
+    plan = gu.make_plan(Aw, Bw, 32, fmt)
+    faults = _faults(plan.desc, n, seed=n, kinds=kinds)
+    want = gu.gpu_campaign(plan, faults, wl.CORRECT_ZERO)
+    d_f = fi.to_device(faults)
+
+    def call(m, stream=None):
+        buf = torch.full((m * 48,), 0xAB, dtype=torch.uint8, device="cuda")
+        plan.fi_gemm_inject_batch_affected(d_f, m, wl.CORRECT_ZERO, buf, stream=stream)
+        return buf
+    # nothing reserved; reserved; a smaller batch, whose slots hold the counts of the larger one; a batch beyond
+    # what is reserved; captured, where the scratch is not used
+    few = max(n // 3, 1)
+    got = [fi.results_to_host(call(n))]
+    plan.reserve(few)
+    got += [fi.results_to_host(call(n)), fi.results_to_host(call(few))]
+    plan.reserve(n)
+    got += [fi.results_to_host(call(n)), fi.results_to_host(call(few)), fi.results_to_host(call(n))]
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    plan.reserve(n, side)
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            buf = call(n, torch.cuda.current_stream().cuda_stream)
+    for _ in range(2):
+        buf.fill_(0xFF)
+        g.replay()
+        torch.cuda.synchronize()
+        got.append(fi.results_to_host(buf))
+    for k, r in enumerate(got):
+        assert r.tobytes() == want[:len(r)].tobytes(), (k, [(t, faults[t], r[t], want[t]) for t in range(len(r)) if r[t] != want[t]][:3])
+    plan.destroy()
+
+
 def test_affected_records_where_the_fault_free_result_spans_4_gib():
     # C* addressed with 64 bits (rows kernel), one 16-wide step
     M, N, K, kb, fmt = 65600, 16400, 16, 16, orc.BF16
