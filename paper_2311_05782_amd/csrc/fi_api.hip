@@ -63,8 +63,7 @@ struct BatchScratch {
   uint32_t* words = nullptr;  // [scratch_words(cap)], see TrialScratch
   uint32_t cap = 0;
   bool own = false;           // an allocation of its own, else part of the plan's
-  uint32_t* parts = nullptr;  // [parts_cap] words for the affected-only campaign, or NULL: only fi_plan_reserve makes them
-  size_t parts_cap = 0;
+  size_t parts_cap = 0;       // words behind scratch_words(cap) for the affected-only campaign: only fi_plan_reserve makes them
 };
 
 struct fi_plan {
@@ -95,6 +94,7 @@ struct fi_plan {
   bool auto_cfg = true;              // no fi_plan_tune has chosen a tile configuration
   int device = 0;
   uint32_t* first_scratch = nullptr; // for kFirstTrials trials on the first stream that asks
+  size_t first_parts = 0;            // words of parts behind it, see BatchScratch
   std::vector<BatchScratch> batch;   // per stream, see BatchScratch
   int n_cus = 8;                     // compute units of the device: grid of the persistent kernel
   int product_check = FI_PCHECK_NONE;
@@ -260,11 +260,6 @@ GemmArgs base_args(const fi_plan* p, int cfg = -1) {
   return a;
 }
 
-// Slots from which workgroups leave their counts in scratch.  Added to the record : left, K = 256, A faults: 4 slots
-// (512^2) 3000 trials 16.5 : 15.6 us, 400 trials 14.7 : 14.9; 8 (1000^2) 19.2 : 17.6, 15.4 : 15.7; 16 (2048^2) 26.5 : 21.2,
-// 16.3 : 15.8; 32 (4096^2) 49.4 : 38.9, 18.1 : 16.3, 8 trials 16.2 : 14.2.  The slots are those of the longer side; where
-// the faults lie along the other, of one to four slots, it costs up to half a microsecond (3072 x 512, 400 trials 15.1 : 15.7).
-constexpr uint32_t kPartSlots = 8;
 // Workgroups of the affected-only campaign's row / column kernel per (chunk of trials, item): one per tile of the other
 // operand while that stays within some 2048 workgroups; beyond, each walks several tiles, and the workgroups that
 // find no item (all of them in a batch of accumulator faults) stay few.
@@ -276,14 +271,6 @@ RowsGrid rows_grid(const fi_plan_desc& d, uint32_t n_trials) {
   if (per_slot > tiles) per_slot = tiles;
   return {(uint32_t)items, (uint32_t)((tiles + per_slot - 1) / per_slot)};
 }
-// Words of their parts, for this number of trials and any smaller one: x_slots <= min(tiles, 2048 / items + 1).
-size_t parts_words(const fi_plan_desc& d, uint32_t n_trials) {
-  const size_t chunks = ((size_t)n_trials + fi::kRowsChunk - 1) / fi::kRowsChunk;
-  const size_t tiles = ((size_t)(d.M > d.N ? d.M : d.N) + fi::kRowsX - 1) / fi::kRowsX;
-  const size_t bound = 2048 / fi::kRowsSlots + 1 + chunks;   // of chunks * x_slots
-  return (chunks * tiles < bound ? chunks * tiles : bound) * fi::kRowsChunk * fi::kPartWords;
-}
-
 // The affected-only campaign: the operand faults' rows and columns, and every record by the element kernel, which
 // comes last where `parts` holds what the others have counted.
 template <int DT>
@@ -408,10 +395,8 @@ fi_status check_plan(const fi_plan* p) {
 void free_plan_buffers(fi_plan* p) {
   if (p->memory) (void)hipFree(p->memory);
   p->memory = nullptr;
-  for (BatchScratch& b : p->batch) {
+  for (BatchScratch& b : p->batch)
     if (b.own) (void)hipFree(b.words);
-    if (b.parts) (void)hipFree(b.parts);
-  }
   p->batch.clear();
 }
 
@@ -420,14 +405,29 @@ void free_plan_buffers(fi_plan* p) {
 constexpr uint32_t kFirstTrials = 256;
 // words: part counts, work counters, descriptors, each 256-byte aligned
 constexpr size_t kScratchQueue = 64, kScratchDesc = kScratchQueue + 2 * fi::kQueueWords;
-constexpr size_t scratch_words(uint32_t n) { return kScratchDesc + ((size_t)n + 16) * fi::kMultiDescWords; }
+constexpr size_t scratch_words(uint32_t n) { return (kScratchDesc + ((size_t)n + 16) * fi::kMultiDescWords + 63) / 64 * 64; }
+
+// Slots from which workgroups leave their counts in scratch.  Added to the record : left, K = 256, A faults: 4 slots
+// (512^2) 3000 trials 16.5 : 15.6 us, 400 trials 14.7 : 14.9; 8 (1000^2) 19.2 : 17.6, 15.4 : 15.7; 16 (2048^2) 26.5 : 21.2,
+// 16.3 : 15.8; 32 (4096^2) 49.4 : 38.9, 18.1 : 16.3, 8 trials 16.2 : 14.2.  The slots are those of the longer side; where
+// the faults lie along the other, of one to four slots, it costs up to half a microsecond (3072 x 512, 400 trials 15.1 : 15.7).
+constexpr uint32_t kPartSlots = 8;
+// Words of those workgroups' parts, for this number of trials and any smaller one: x_slots <= min(tiles, 2048 / items + 1).
+size_t parts_words(const fi_plan_desc& d, uint32_t n_trials) {
+  const size_t chunks = ((size_t)n_trials + fi::kRowsChunk - 1) / fi::kRowsChunk;
+  const size_t tiles = ((size_t)(d.M > d.N ? d.M : d.N) + fi::kRowsX - 1) / fi::kRowsX;
+  const size_t bound = 2048 / fi::kRowsSlots + 1 + chunks;   // of chunks * x_slots
+  if (tiles < kPartSlots) return 0;
+  return (chunks * tiles < bound ? chunks * tiles : bound) * (n_trials < fi::kRowsChunk ? n_trials : fi::kRowsChunk) * fi::kPartWords;
+}
 
 // The batch scratch of `stream`, holding at least n trials.  Allocates on the first batch of a
 // stream and when a batch is larger than any before on it (the replaced buffers are freed,
 // which waits for device work that may still read them); not for up to kFirstTrials trials on the plan's
 // first stream.  Batches of the small kernels do not use it but size it all the same: a tile
 // configuration chosen later sends the same batch to the multi-trial kernel, which must not allocate then.
-fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch** out) {
+// want_parts: with the affected-only campaign's parts behind it, if there is memory for them.
+fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch** out, bool want_parts = false) {
   BatchScratch* b = nullptr;
   for (BatchScratch& x : p->batch)
     if (x.stream == stream) b = &x;
@@ -439,13 +439,20 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
     if (p->batch.size() == 1) {
       b->words = p->first_scratch;
       b->cap = kFirstTrials;
+      b->parts_cap = p->first_parts;
     }
   }
-  if (b->cap < n) {
+  const size_t parts = want_parts ? parts_words(p->d, n) : 0;
+  if (b->cap < n || b->parts_cap < parts) {
+    const uint32_t cap = b->cap > n ? b->cap : n;
     if (b->own) (void)hipFree(b->words);
-    b->words = nullptr; b->cap = 0; b->own = false;
-    FI_HIP(hipMalloc(&b->words, scratch_words(n) * sizeof(uint32_t)));
-    b->cap = n;
+    b->words = nullptr; b->cap = 0; b->own = false; b->parts_cap = 0;
+    if (parts != 0) {
+      if (hipMalloc(&b->words, (scratch_words(cap) + parts) * sizeof(uint32_t)) == hipSuccess) b->parts_cap = parts;
+      else { b->words = nullptr; (void)hipGetLastError(); }
+    }
+    if (!b->words) FI_HIP(hipMalloc(&b->words, scratch_words(cap) * sizeof(uint32_t)));
+    b->cap = cap;
     b->own = true;
   }
   *out = b;
@@ -525,6 +532,10 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   const size_t at_ap = place(p->kshift ? (size_t)d.M * kp * sizeof(uint16_t) : 0);
   const size_t at_bp = place(p->kshift ? (size_t)d.N * kp * sizeof(uint16_t) : 0);
   const size_t at_scratch = place(scratch_words(kFirstTrials) * sizeof(uint32_t));
+  // parts as well, unless they take the allocation past 2 MiB
+  p->first_parts = parts_words(d, kFirstTrials);
+  if (bytes <= (2u << 20) && bytes + p->first_parts * sizeof(uint32_t) > (2u << 20)) p->first_parts = 0;
+  place(p->first_parts * sizeof(uint32_t));
   FI_HIP(hipMalloc(&p->memory, bytes));
   uint8_t* const base = static_cast<uint8_t*>(p->memory);
   p->c_star = reinterpret_cast<float*>(base + at_c);
@@ -876,20 +887,7 @@ fi_status fi_plan_reserve(fi_plan* plan, uint32_t max_trials, void* stream) {
   if (st != FI_OK) return st;
   if (max_trials == 0) return fail(FI_INVALID_ARG, "max_trials is 0");
   BatchScratch* bs = nullptr;
-  st = batch_scratch(plan, as_stream(stream), max_trials, &bs);
-  if (st != FI_OK) return st;
-  const size_t words = parts_words(plan->d, max_trials);
-  if (bs->parts_cap < words) {
-    if (bs->parts) (void)hipFree(bs->parts);
-    bs->parts = nullptr; bs->parts_cap = 0;
-    if (hipMalloc(&bs->parts, words * sizeof(uint32_t)) == hipSuccess) {
-      bs->parts_cap = words;
-    } else {
-      bs->parts = nullptr;                                // the affected-only campaign does without
-      (void)hipGetLastError();
-    }
-  }
-  return FI_OK;
+  return batch_scratch(plan, as_stream(stream), max_trials, &bs, true);
 }
 
 fi_status fi_plan_set_clock_sink(fi_plan* plan, uint64_t* d_clocks) {
@@ -1035,7 +1033,7 @@ fi_status fi_gemm_inject_batch_affected(fi_plan* plan, const fi_fault* d_faults,
     if (rows.x_slots < kPartSlots || b.stream != s || b.parts_cap < (size_t)rows.x_slots * n_trials * fi::kPartWords) continue;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
-    else if (capture == hipStreamCaptureStatusNone) parts = b.parts;
+    else if (capture == hipStreamCaptureStatusNone) parts = b.words + scratch_words(b.cap);
   }
   if (plan->d.dtype == FI_BF16) return launch_affected<FI_BF16>(a, rows, plan->n_cus, plan->plain_ok, parts, s);
   return launch_affected<FI_FP16>(a, rows, plan->n_cus, plan->plain_ok, parts, s);
