@@ -629,6 +629,28 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       }
       return T;
     };
+    // The smallest row factor of this lane's rows of each tile row, the column factors: see `detect`.
+    float kra_least[TM], cb_of[TN];
+    static_for<TM>([&](auto ii) {
+      constexpr int i = ii;
+      f32x4 least = {__builtin_inff(), __builtin_inff(), __builtin_inff(), __builtin_inff()};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        f32x4 k4 = HAVE_T ? kra4[i][q] : *reinterpret_cast<const f32x4*>(p.kra + row_base + 32 * i + 8 * q);
+        if (ragged) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) k4[e] = row_base + 32 * i + 8 * q + e < p.M ? k4[e] : __builtin_inff();
+        }
+        least = __builtin_elementwise_minimum(least, k4);
+      }
+      kra_least[i] = __builtin_elementwise_minimum(__builtin_elementwise_minimum(least[0], least[1]),
+                                                   __builtin_elementwise_minimum(least[2], least[3]));
+    });
+    static_for<TN>([&](auto jj) { cb_of[jj] = HAVE_T ? cbj[jj] : p.cb[min(col_base + 32 * jj, p.N - 1)]; });
+    auto least_threshold = [&](auto tt) __attribute__((always_inline)) {
+      return p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(kra_least[tt / TN], cb_of[tt % TN]), p.gamma);
+    };
+    [[maybe_unused]] bool beyond = false;               // a tile of this wave holds a value at or above that (or a NaN)
     if (ragged) {
       static_for<R * TM * TN>([&](auto t) {
         constexpr int r = t / (TM * TN), i = (t / TN) % TM, j = t % TN;
@@ -667,24 +689,38 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       constexpr bool OUT = decltype(with_out)::value;
       static_for<TM * TN>([&](auto tt) {
         constexpr int i = tt / TN, j = tt % TN;
-        const f32x16 T = thresholds(tt);
         const int col = col_base + 32 * j;
-        // Every trial's element against the threshold they share: of the largest magnitude of the R the
-        // excess over T (a difference has the sign that the comparison says, subnormals being kept), of
-        // which again the largest.  v_maximum3_f32 takes two values an instruction, and a NaN outweighs
-        // all.  16 compares and scalar ORs in the place of the second maximum wait for each other.
-        float excess = -__builtin_inff();
+        // The largest magnitude of the lane's 16 x R elements against the smallest of their thresholds: the three
+        // roundings are monotonous, so that is the threshold of the smallest row factor.  v_maximum3_f32 takes two
+        // values an instruction, and a NaN outweighs all.  Less, not equal: of an infinite row factor and a
+        // column of zeros the threshold is a NaN, which the smallest factor does not show.
+        float top = 0.0f;
+        static_for<R>([&](auto rr) {
+          constexpr int r = rr;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float top = fabsf(acc[0][i][j][v]);
-          static_for<R>([&](auto rr) {
-            constexpr int r = rr;
-            if constexpr (r > 0) top = __builtin_elementwise_maximum(top, fabsf(acc[r][i][j][v]));
-          });
-          excess = __builtin_elementwise_maximum(excess, __fsub_rn(top, T[v]));
-        }
-        const uint64_t some = __ballot(!(excess <= 0.0f));
+          for (int v = 0; v < 16; ++v) top = __builtin_elementwise_maximum(top, fabsf(acc[r][i][j][v]));
+        });
+        uint64_t some = __ballot(!(top < least_threshold(tt)));
         if (!OUT && some == 0) return;
+        f32x16 T = {};
+        if (some != 0) {
+          // Row by row: the excess of the largest magnitude over T (a difference has the sign that the comparison
+          // says, subnormals being kept), of which again the largest.
+          beyond = true;
+          T = thresholds(tt);
+          float excess = -__builtin_inff();
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            float high = fabsf(acc[0][i][j][v]);
+            static_for<R>([&](auto rr) {
+              constexpr int r = rr;
+              if constexpr (r > 0) high = __builtin_elementwise_maximum(high, fabsf(acc[r][i][j][v]));
+            });
+            excess = __builtin_elementwise_maximum(excess, __fsub_rn(high, T[v]));
+          }
+          some = __ballot(!(excess <= 0.0f));
+          if (!OUT && some == 0) return;
+        }
         static_for<R>([&](auto rr) {
           constexpr int r = rr;
           if (r < n_act) {
@@ -833,10 +869,8 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
         const f32x16 t = acc[0][i][j];
         const f32x16 cs = gold[tt % GOLD_BUFS];
         const int col = col_base + 32 * j;
-        // words that differ, four rows at a time, and the largest magnitude (a NaN outweighs all): no
-        // branch per element
+        // words that differ, four rows at a time: no branch per element
         uint32_t differs[4] = {0, 0, 0, 0};
-        float top = 0.0f;
         if (!ragged) {
 #pragma unroll
           for (int v = 0; v < 16; ++v) differs[v >> 2] |= __float_as_uint(t[v]) ^ __float_as_uint(cs[v]);
@@ -848,9 +882,13 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
             differs[v >> 2] |= (__float_as_uint(t[v]) ^ __float_as_uint(cs[v])) & mask;
           }
         }
+        // Equal words count where they are not finite or flagged: in the waves that hold such a value, which lies
+        // at or above the smallest threshold.
+        float top = 0.0f;
+        if (beyond) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) top = __builtin_elementwise_maximum(top, fabsf(t[v]));
-        // Equal words count where they are not finite or flagged: in the waves that hold such a value.
+          for (int v = 0; v < 16; ++v) top = __builtin_elementwise_maximum(top, fabsf(t[v]));
+        }
         if (n_flag[0] != 0 || __ballot(!(top <= 3.4028234e38f)) != 0) {
           static_for<4>([&](auto qq) {
             constexpr int q = qq;

@@ -174,6 +174,55 @@ def test_rows_of_all_maximal_same_sign_products_are_never_flagged(cfg, fmt):
     plan.destroy()
 
 
+def _edge_operands(edge, M, N, K):
+    A, B = np.ones((M, K), np.float32), np.full((N, K), 0.5, np.float32)
+    if edge == "zero":                                  # thresholds of 0
+        A[3] = A[M - 1] = 0
+        B[5] = B[N - 1] = 0
+    elif edge == "infinite":                            # row factors of Inf, of a column of zeros a NaN: flagged
+        A[:] = 1e-3
+        A[2] = A[M - 1] = 3.3e38
+        B[:] = 1e-30
+        B[7] = 0
+    return wl.to_words(A, orc.BF16), wl.to_words(B, orc.BF16)
+
+
+# Every element equal to its threshold; rows and columns of zeros; thresholds that are Inf and NaN.  Whole tiles and
+# ragged ones, whose elements beyond the problem have no threshold.
+@pytest.mark.parametrize("edge", ["equal", "zero", "infinite"])
+@pytest.mark.parametrize("M,N", [(128, 128), (70, 100)])
+@pytest.mark.parametrize("cfg", [0, 1, 3, 4, 5, 6, None])
+def test_flags_at_the_edges_of_the_thresholds_equal_the_one_trial_kernels(edge, M, N, cfg):
+    import torch
+    K, n = 128, 700 if cfg is None else 41              # None: the shape that many trials get by themselves
+    Aw, Bw = _edge_operands(edge, M, N, K)
+    faults = np.zeros(n, fi.FAULT_DTYPE)
+    rng = np.random.default_rng(M)
+    faults["kind"] = fi.SITE_ACC
+    faults["row"] = rng.choice([0, 2, 3, M - 1], n)
+    faults["col"] = rng.choice([1, 5, 7, N - 1], n)
+    faults["kblock"] = K // 32 - 1
+    faults["xor_mask"] = 1 << rng.integers(0, 32, n)
+    faults["kind"][::9] = fi.SITE_NONE
+    got = []
+    for c in (2, cfg):
+        plan = gu.make_plan(Aw, Bw, 32, orc.BF16, cfg=c, gamma=1.0)
+        recs, out = gu.gpu_campaign(plan, faults, wl.CORRECT_ZERO, want_c=True)
+        got.append((gu.gpu_campaign(plan, faults, wl.CORRECT_ZERO).tobytes(), recs.tobytes(), out.tobytes()))
+        if c in (0, 1, 2, None):                        # the next layer: flagged and unchanged, flagged and changed
+            stack = fi.words_to_device(Aw).expand(3, M, K).clone()
+            stack[1] += 1
+            d_r = fi.empty_results(3)
+            plan.fi_gemm_propagate_batch(stack, M * K, 3, wl.CORRECT_ZERO, d_r)
+            got[-1] += (fi.results_to_host(d_r).tobytes(),)
+        plan.destroy()
+    assert got[0][:3] == got[1][:3]
+    assert len(got[1]) == 3 or got[0][3] == got[1][3]
+    flagged = np.frombuffer(got[0][1], recs.dtype)["n_flagged"]
+    clean = {"equal": 0, "zero": 0, "infinite": 2}[edge]
+    assert (flagged[::9] == clean).all() and flagged.max() > clean
+
+
 def test_default_slack_for_long_K_matches_the_oracle_and_keeps_clean_trials_masked():
     M, N, K, kb, fmt = 40, 72, 8192, 64, orc.BF16
     a = np.full((M, K), 143.0 / 128.0, np.float32)           # sums that round upwards step after step
