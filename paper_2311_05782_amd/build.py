@@ -21,7 +21,7 @@ HEADERS = ["gemm_fi.hpp", "gemm_fi_multi.hpp", "gemm_fi_small.hpp", "affected.hp
            "tile_cfg.hpp"]
 SOURCES = ["fi_api.hip", "gemm_inst.hip"]
 # (family, dtype, cfg): family 0 = one trial per work item, 1 = R trials per work item
-INSTANCES = ([(1, dt, cfg) for dt in (0, 1) for cfg in (0, 1, 2, 3, 4, 5)] +
+INSTANCES = ([(1, dt, cfg) for dt in (0, 1) for cfg in (0, 1, 2, 3, 4, 5, 6)] +
              [(0, dt, cfg) for dt in (0, 1) for cfg in (0, 1, 2)])
 
 

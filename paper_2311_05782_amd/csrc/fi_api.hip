@@ -158,6 +158,7 @@ hipError_t launch_multi(int dtype, int mcfg, const GemmArgs& a, int n_blocks, hi
   if (dtype == DT && mcfg == MC) return fi::launch_multi_d##DT##_c##MC(a, n_blocks, s)
   FI_CASE(0, 0); FI_CASE(0, 1); FI_CASE(0, 2); FI_CASE(0, 3); FI_CASE(0, 4); FI_CASE(0, 5);
   FI_CASE(1, 0); FI_CASE(1, 1); FI_CASE(1, 2); FI_CASE(1, 3); FI_CASE(1, 4); FI_CASE(1, 5);
+  FI_CASE(0, 6); FI_CASE(1, 6);
 #undef FI_CASE
   return hipErrorInvalidValue;
 }
@@ -232,6 +233,24 @@ int pick_prop(const fi_plan* p, uint32_t n_trials) {
   const uint64_t items = (uint64_t)(d.M / 256) * (d.N / 256) * n_trials, cus = (uint64_t)p->n_cus;
   const uint64_t rounds = (items + cus - 1) / cus;
   return rounds >= 2 && 10 * items >= 9 * rounds * cus ? fi::kMultiOneTrial[0] : p->prop_cfg;
+}
+
+// Items of four trials, both parts of the batch in one launch, in the place of the 64 x 64 shape's eight trials and two
+// launches.  Four share less, eight leave more of the chip without work at the end and take a launch
+// more (some 4 us), so four while
+//   rounds of that shape's resident workgroups * k-tiles <= 100.
+// From 2021 random batches of up to 27 rounds, all kinds and outputs, eight : four in the mean - up to one round 1.28, one to
+// four 1.17, K = 640 and eight to twelve rounds 1.04, K >= 2560 and twelve to 27 rounds 0.96 (512 x 3072 x 768, 4096
+// trials, 384 rounds 6.8 : 7.5 ms).  By this line 1.11 over all of them, 2.9 % over 3 % slower; 1.8 % from the better of the
+// two.  512 x 3072 x 768, 8 trials with outputs 43.9 : 34.7 us, 3136 x 64 x 576, 128 trials with outputs 56.4 : 47.9.  Not
+// for K <= 64, whose items are handed out in turn: operand faults, 142 x 167 x 64, 7802 trials 190 : 294.
+constexpr uint64_t kFourWork = 100;
+bool use_four(const fi_plan* p, uint32_t n_trials) {
+  const fi_plan_desc& d = p->d;
+  if (!p->auto_cfg || p->mcfg != 3 || d.K <= 64) return false;
+  const MultiCfg& m = kMulti[3];
+  const uint64_t items = (uint64_t)((d.M + m.bm - 1) / m.bm) * ((d.N + m.bn - 1) / m.bn) * (((uint64_t)n_trials + m.r - 1) / m.r);
+  return items * ((d.K + 63) / 64) <= kFourWork * (uint64_t)m.wgs * (uint64_t)p->n_cus;
 }
 
 // Batches that gemm_fi_trial_kernel serves.
@@ -647,7 +666,8 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
   GemmArgs a = base_args(plan);
   const uint64_t blocks = (uint64_t)a.tiles_m * a.tiles_n * n_trials;
   if (blocks >= (1ull << 31)) return fail(FI_UNSUPPORTED, "tiles x trials exceeds 2^31 workgroups; split the batch");
-  const MultiCfg mc = kMulti[plan->mcfg >= 0 ? plan->mcfg : 0];
+  const bool four = use_four(plan, n_trials);
+  const MultiCfg mc = four ? fi::kMultiFour : kMulti[plan->mcfg >= 0 ? plan->mcfg : 0];
   GemmArgs m = a;
   uint64_t mblocks = 0;
   if (plan->mcfg >= 0) {
@@ -663,7 +683,7 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
     // take their items from counters, one per XCD, or walk the work list with the grid as stride
     // (see gemm_fi_multi_kernel); for both the grid has to be a multiple of 8 where it is not the
     // work list's length.
-    const uint64_t groups = ((uint64_t)n_trials + mc.r - 1) / mc.r;
+    const uint64_t groups = ((uint64_t)n_trials + mc.r - 1) / mc.r + (four ? 1 : 0);   // either part may end in a partial one
     const uint64_t items = (uint64_t)m.tiles_m * m.tiles_n * groups;
     if (items >= (1ull << 31)) return fail(FI_UNSUPPORTED, "tiles x trials exceeds 2^31 work items; split the batch");
     const uint64_t cus = (uint64_t)(plan->n_cus / 8 * 8) * (uint64_t)mc.wgs;
@@ -722,7 +742,7 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
   m.part_counts = ts.counts;
   m.desc = ts.desc;
   if (m.K >= 128) m.queue = ts.queue;
-  FI_HIP(launch_multi((int)plan->d.dtype, plan->mcfg, m, (int)mblocks, s));
+  FI_HIP(launch_multi((int)plan->d.dtype, four ? fi::kMultiFourInst : plan->mcfg, m, (int)mblocks, s));
   return FI_OK;
 }
 
@@ -946,9 +966,18 @@ fi_status fi_plan_describe(const fi_plan* plan, char* h_buf, uint64_t n) {
     if (m.r == 1)
       snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, one trial per item, %dx%d, %d threads, persistent x%d per CU>%s", dt,
                m.bm, m.bn, m.wm * m.wn * 64, m.wgs, small);
-    else
-    snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, R=%d, %dx%d, %d threads, persistent x%d per CU> (a second, "
-             "operand-patching instantiation for operand faults)%s", dt, m.r, m.bm, m.bn, m.wm * m.wn * 64, m.wgs, small);
+    else {
+      char four[160] = "";
+      if (use_four(plan, 1)) {
+        const uint64_t each = (uint64_t)((plan->d.M + m.bm - 1) / m.bm) * ((plan->d.N + m.bn - 1) / m.bn) * ((plan->d.K + 63) / 64);
+        const uint64_t most = kFourWork * (uint64_t)m.wgs * (uint64_t)plan->n_cus / each * (uint64_t)m.r;
+        const MultiCfg f = fi::kMultiFour;
+        snprintf(four, sizeof(four), "; at most %llu trials: the same with R=%d, x%d per CU, operand faults in the same launch",
+                 (unsigned long long)most, f.r, f.wgs);
+      }
+      snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, R=%d, %dx%d, %d threads, persistent x%d per CU> (a second, "
+               "operand-patching instantiation for operand faults)%s%s", dt, m.r, m.bm, m.bn, m.wm * m.wn * 64, m.wgs, four, small);
+    }
   } else {
     snprintf(h_buf, n, "gemm_fi_kernel<%s, %dx%d, %d threads>", dt, c.bm, c.bn, c.wm * c.wn * 64);
   }

@@ -121,11 +121,14 @@ struct WorkList {
 };
 
 // VAR: which part of the work this instantiation takes.
-enum { VAR_PLAIN = 0, VAR_OPERAND = 1, VAR_PROPAGATE = 2 };
+// VAR_BOTH: both parts of a campaign's batch, one behind the other in one work list.
+enum { VAR_PLAIN = 0, VAR_OPERAND = 1, VAR_PROPAGATE = 2, VAR_BOTH = 3 };
+
 
 template <int DT, int R, int BM, int BN, int WM, int WN, int VAR>
-__global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const GemmArgs p) {
-  constexpr bool OPS = VAR == VAR_OPERAND;
+__global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) gemm_fi_multi_kernel(const GemmArgs p) {
+  constexpr bool BOTH = VAR == VAR_BOTH, OPS = VAR == VAR_OPERAND || BOTH;
+  constexpr int CLOCKS = BOTH ? 0 : 4 * VAR;              // where this launch's counters go
   // PROP: the next layer of a two-layer workload.  Work item = (output tile, trial); trial t
   // stages ITS OWN A operand (A + t * a_trial_stride) and the shared B, no fault is injected,
   // and every output element is compared with the fault-free result.
@@ -171,17 +174,21 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   const int l32 = lane & 31, lhi = lane >> 5;
 
   // ---- work list: n_tiles x ceil(n_fast / R) items
-  // OPS: the second part of the batch; its descriptors follow the first part's, padded to 8.
-  const int n_fast = PROP ? p.n_trials : (int)p.part_counts[OPS ? 1 : 0];
+  // OPS: the second part of the batch; its descriptors follow the first part's, padded to 8.  BOTH: the groups of
+  // that padding hold no trial and are left out.
+  const int n_fast = PROP ? p.n_trials : (int)p.part_counts[OPS && !BOTH ? 1 : 0];
   const uint32_t* const desc =
-      PROP ? nullptr : p.desc + (OPS ? (size_t)((p.part_counts[0] + 7u) & ~7u) * kMultiDescWords : 0);
-  const int n_groups = (n_fast + R - 1) / R;
+      PROP ? nullptr : p.desc + (OPS && !BOTH ? (size_t)((p.part_counts[0] + 7u) & ~7u) * kMultiDescWords : 0);
+  static_assert(!BOTH || 8 % R == 0, "the second part starts at a group");
+  const int n_slow = BOTH ? (int)p.part_counts[1] : 0;
+  const int fast_groups = (n_fast + R - 1) / R, n_groups = fast_groups + (n_slow + R - 1) / R;
+  const int pad_groups = BOTH ? (int)(((uint32_t)n_fast + 7u) & ~7u) / R - fast_groups : 0;
   const uint32_t n_work = (uint32_t)(p.tiles_m * p.tiles_n) * (uint32_t)n_groups;
   uint32_t w_cur = blockIdx.x;
   if (w_cur >= n_work) return;                            // uniform, before any barrier
   if (p.clocks && blockIdx.x == 0 && tid == 0) {
-    p.clocks[4 * VAR + 0] = __builtin_readcyclecounter();
-    p.clocks[4 * VAR + 1] = __builtin_amdgcn_s_memrealtime();
+    p.clocks[CLOCKS + 0] = __builtin_readcyclecounter();
+    p.clocks[CLOCKS + 1] = __builtin_amdgcn_s_memrealtime();
   }
 
   // ---- staging: global -> LDS directly, as in gemm_fi_kernel
@@ -280,9 +287,9 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   // that item's last k-tile (`locate_next`): hence two k-tiles or more, and an item is taken one item ahead, not more.
   // Not with so few items that it has nothing to gain: a CU whose two workgroups both take one item more than
   // others' is the last (kQueueItems, kQueueItemsUneven).  The grid is a multiple of kQueueXcds where it is true.
-  const uint32_t few = OPS || (!PROP && p.c_out != nullptr) ? kQueueItemsUneven : kQueueItems;
+  const uint32_t few = (BOTH ? n_slow != 0 : OPS) || (!PROP && p.c_out != nullptr) ? kQueueItemsUneven : kQueueItems;
   const bool dynamic = p.queue != nullptr && n_work > few * gridDim.x;
-  uint32_t* const queue = p.queue + (OPS ? kQueueWords : 0);
+  uint32_t* const queue = p.queue + (OPS && !BOTH ? kQueueWords : 0);
   constexpr int QS = PROP ? kPropQueueStride : kQueueStride;
   uint32_t ticket = blockIdx.x / kQueueXcds - gridDim.x / kQueueXcds;  // position() of it: blockIdx.x + gridDim.x
   auto request = [&]() __attribute__((always_inline)) {
@@ -319,7 +326,8 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       const __amdgpu_buffer_rsrc_t rs =
           __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(desc), 0, -1, 0x00020000);
       const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(
-          rs, (lane < R * kMultiDescWords ? lane : 0) * 4, grp * (R * kMultiDescWords * 4), 0);
+          rs, (lane < R * kMultiDescWords ? lane : 0) * 4,
+          (BOTH && grp >= fast_groups ? grp + pad_groups : grp) * (R * kMultiDescWords * 4), 0);
       return lane < R * kMultiDescWords ? w : 0u;
     }
   };
@@ -398,6 +406,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   // fragments hold the faulted operand word).
   uint32_t owned = 0;
   int hook_step[R];                                      // items with events: the MFMA step of trial r's, or -1
+  [[maybe_unused]] uint32_t operands = 0;                // BOTH, items with events: bit r: trial r's is an operand fault
   // Fields are read with all lanes active, never inside a condition on the lane: where the word has been
   // spilled, a reload there fetches the active lanes only, and v_readlane takes another's.
   auto desc_field = [&](int r, int field) -> uint32_t {
@@ -420,7 +429,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
   };
 
   auto decode = [&]() {
-    n_act = min(R, n_fast - cur.grp * R);
+    n_act = BOTH && cur.grp >= fast_groups ? min(R, n_slow - (cur.grp - fast_groups) * R) : min(R, n_fast - cur.grp * R);
     owned = 0;
     if constexpr (!PROP) {
       // Nearly every item holds no event of this wave.  One lane-parallel test over the R
@@ -1250,7 +1259,11 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (EV) {
           const uint32_t m = hit_mask(g);
-          if constexpr (OPS) {
+          if constexpr (BOTH) {
+            mma_step_ops(f, m & operands, mid);
+            __builtin_amdgcn_sched_barrier(0);
+            if (__builtin_expect((m & ~operands) != 0, 0)) hooks(m & ~operands);
+          } else if constexpr (OPS) {
             mma_step_ops(f, m, mid);
           } else {
             mma_step_mid(f, first, sit, std::false_type{}, mid, load);
@@ -1350,6 +1363,10 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
       // of a k-tile costs code.
       publish();
       static_for<R>([&](auto rr) { hook_step[rr] = ((owned >> rr) & 1u) ? (int)(desc_field(rr, 3) & 0xFFFFu) : -1; });
+      if constexpr (BOTH) {
+        operands = 0;
+        static_for<R>([&](auto rr) { operands |= ((desc_field(rr, 3) >> 29) & 5u) == 1u ? 1u << rr : 0u; });
+      }
       static_for<R * TM * TN>([&](auto t) {
         acc[t / (TM * TN)][(t / TN) % TM][t % TN] =
             f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -1386,8 +1403,8 @@ __global__ void __launch_bounds__(WM* WN * 64, 2) gemm_fi_multi_kernel(const Gem
     }
   }
   if (p.clocks && blockIdx.x == 0 && tid == 0) {
-    p.clocks[4 * VAR + 2] = __builtin_readcyclecounter();
-    p.clocks[4 * VAR + 3] = __builtin_amdgcn_s_memrealtime();
+    p.clocks[CLOCKS + 2] = __builtin_readcyclecounter();
+    p.clocks[CLOCKS + 3] = __builtin_amdgcn_s_memrealtime();
   }
 }
 

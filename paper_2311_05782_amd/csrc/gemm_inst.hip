@@ -36,6 +36,15 @@ hipError_t FI_NAME(launch_single_d, FI_INST_DT, FI_INST_CFG)(int mode, const Gem
 
 #else
 
+#if FI_INST_CFG == 6
+static_assert(kMultiFourInst == 6, "the instance of kMultiFour");
+hipError_t FI_NAME(launch_multi_d, FI_INST_DT, 6)(const GemmArgs& a, int n_blocks, hipStream_t s) {
+  constexpr MultiCfg c = kMultiFour;
+  hipLaunchKernelGGL((gemm_fi_multi_kernel<FI_INST_DT, c.r, c.bm, c.bn, c.wm, c.wn, VAR_BOTH>), dim3(n_blocks),
+                     dim3(c.wm * c.wn * 64), 0, s, a);
+  return hipGetLastError();
+}
+#else
 // Two launches: the plain instantiation on the first part of the batch (no fault, accumulator
 // flips, product-term faults), the operand-patching one on the second part (operand faults).
 // Each finds its trial count on the device and exits at once if it is zero.
@@ -50,7 +59,7 @@ hipError_t FI_NAME(launch_multi_d, FI_INST_DT, FI_INST_CFG)(const GemmArgs& a, i
   return hipGetLastError();
 }
 
-#if FI_INST_CFG >= 4
+#if FI_INST_CFG == 4 || FI_INST_CFG == 5
 // The next layer of a two-layer workload: one launch, every trial with its own A operand.
 hipError_t FI_NAME(launch_prop_d, FI_INST_DT, FI_INST_CFG)(const GemmArgs& a, int n_blocks, hipStream_t s) {
   constexpr MultiCfg c = kMulti[FI_INST_CFG];
@@ -61,6 +70,7 @@ hipError_t FI_NAME(launch_prop_d, FI_INST_DT, FI_INST_CFG)(const GemmArgs& a, in
 }
 #endif
 
+#endif
 #endif
 
 }  // namespace fi

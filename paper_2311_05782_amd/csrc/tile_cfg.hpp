@@ -36,6 +36,10 @@ constexpr MultiCfg kMulti[] = {
 // two-layer workload (every trial with its own A operand).
 constexpr int kMultiOneTrial[2] = {4, 5};
 constexpr int kNumMulti = sizeof(kMulti) / sizeof(kMulti[0]);
+// Launches of few or short items (see use_four in fi_api.hip): half the trials per item, three workgroups per compute
+// unit, both parts of the batch in one launch.  Not one of fi_plan_tune's configurations.
+constexpr MultiCfg kMultiFour = {4, 64, 64, 2, 2, 3};
+constexpr int kMultiFourInst = kNumMulti;
 
 // mode: MODE_CAMPAIGN .. MODE_PROPAGATE of gemm_fi.hpp.
 #define FI_DECLARE_SINGLE(DT, CFG) \
@@ -49,6 +53,9 @@ FI_DECLARE_SINGLE(1, 0) FI_DECLARE_SINGLE(1, 1) FI_DECLARE_SINGLE(1, 2)
   hipError_t launch_prop_d##DT##_c##MC(const GemmArgs& a, int n_blocks, hipStream_t s);
 FI_DECLARE_MULTI(0, 0) FI_DECLARE_MULTI(0, 1) FI_DECLARE_MULTI(0, 2) FI_DECLARE_MULTI(0, 3) FI_DECLARE_MULTI(0, 4) FI_DECLARE_MULTI(0, 5)
 FI_DECLARE_MULTI(1, 0) FI_DECLARE_MULTI(1, 1) FI_DECLARE_MULTI(1, 2) FI_DECLARE_MULTI(1, 3) FI_DECLARE_MULTI(1, 4) FI_DECLARE_MULTI(1, 5)
+#define FI_DECLARE_FOUR(DT) hipError_t launch_multi_d##DT##_c6(const GemmArgs& a, int n_blocks, hipStream_t s);
+FI_DECLARE_FOUR(0) FI_DECLARE_FOUR(1)
+#undef FI_DECLARE_FOUR
 FI_DECLARE_PROP(0, 4) FI_DECLARE_PROP(0, 5) FI_DECLARE_PROP(1, 4) FI_DECLARE_PROP(1, 5)
 #undef FI_DECLARE_PROP
 #undef FI_DECLARE_SINGLE

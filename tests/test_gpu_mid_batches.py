@@ -1,0 +1,67 @@
+"""Batches between the smallest and the largest: four trials per item, the operand faults behind the other trials in
+one launch.  Against the shapes that fi_plan_tune chooses (one trial per workgroup; eight trials, two launches), byte for
+byte."""
+import numpy as np
+import pytest
+
+from oracle import pyoracle as orc
+from paper_2311_05782_amd import fi, workloads as wl
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def _faults(plan, n, operand):
+    """n faults of which every `operand`-th (0: none, 1: all) is an operand fault, with fault-free and invalid ones."""
+    f = fi.fi_sample_faults(3, 0, n, plan.desc, fi.KIND_ALL_ACC, 2)
+    f[1::3] = fi.fi_sample_faults(4, 0, n, plan.desc, fi.KIND_ALL_PRODUCT, 4)[1::3]
+    f[::7]["kind"] = fi.SITE_NONE
+    f[5::11]["row"] = 10 ** 7
+    if operand:
+        for k, kind in enumerate((fi.KIND_ALL_A, fi.KIND_ALL_B)):
+            f[k * operand::2 * operand] = fi.fi_sample_faults(5 + k, 0, n, plan.desc, kind, 1)[k * operand::2 * operand]
+    return f
+
+
+# (M, N, K, k-block), trials, every how many-th is an operand fault.  The first part ends 1 .. 8 trials into a group of
+# eight, so that the descriptors' padding holds a group of four or none, and either part may be empty; ragged tiles
+# and k-tiles, an odd number of k-tiles, the shortest K; two items per workgroup, several from the counters, and 64 or more, where
+# workgroups look into other XCDs' slices.
+@pytest.mark.parametrize("shape,n,operand", [
+    ((300, 300, 512, 32), 121, 0), ((300, 300, 512, 32), 124, 1), ((300, 300, 512, 32), 127, 5), ((320, 256, 512, 32), 132, 2),
+    ((300, 300, 512, 32), 133, 132), ((129, 515, 464, 16), 125, 3), ((1000, 130, 320, 32), 119, 4),
+    ((250, 1000, 80, 16), 440, 3), ((600, 300, 192, 32), 900, 6), ((70, 60, 128, 32), 50001, 9),
+])
+def test_mid_batches_equal_the_other_shapes(shape, n, operand):
+    import torch
+    M, N, K, kb = shape
+    fmt = orc.FP16 if n % 2 else orc.BF16
+    Aw, Bw = wl.gaussian(M, N, K, fmt, seed=n)
+    plan, eight = gu.make_plan(Aw, Bw, kb, fmt), gu.make_plan(Aw, Bw, kb, fmt, cfg=6)
+    # the library's own line: eight trials of a 64 x 64 tile, two workgroups per compute unit
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert -(-M // 64) * -(-N // 64) * -(-n // 8) * -(-K // 64) <= 100 * 2 * cus and K > 64
+    faults = _faults(plan, n, operand)
+    want = gu.gpu_campaign(eight, faults, wl.CORRECT_RECOMPUTE)
+    for _ in range(2):
+        got = gu.gpu_campaign(plan, faults, wl.CORRECT_RECOMPUTE)
+        assert got.tobytes() == want.tobytes(), [t for t in range(n) if got[t] != want[t]][:5]
+    if n < 1000:
+        one = gu.make_plan(Aw, Bw, kb, fmt, cfg=2)
+        r1, c1 = gu.gpu_campaign(one, faults, wl.CORRECT_ZERO, want_c=True)
+        r4, c4 = gu.gpu_campaign(plan, faults, wl.CORRECT_ZERO, want_c=True)
+        assert r1.tobytes() == r4.tobytes() and c1.tobytes() == c4.tobytes()
+        one.destroy()
+        d_f = fi.to_device(faults)
+        outs = []
+        for p in (plan, eight):
+            d_r, d_h = fi.empty_results(n), torch.zeros((n, M, N), dtype=torch.int16, device="cuda")
+            p.fi_gemm_inject_batch_act(d_f, n, wl.CORRECT_ZERO, d_r, d_h)
+            outs.append((fi.results_to_host(d_r).tobytes(), d_h))
+        assert outs[0][0] == outs[1][0] and torch.equal(outs[0][1], outs[1][1])
+        # the entry point without allocations runs the same kernels
+        d_r = fi.empty_results(n)
+        plan.fi_gemm_inject_batch_noalloc(d_f, n, wl.CORRECT_RECOMPUTE, d_r)
+        assert fi.results_to_host(d_r).tobytes() == want.tobytes()
+    plan.destroy()
+    eight.destroy()
