@@ -85,6 +85,7 @@ struct fi_plan {
   float* scratch = nullptr;          // 4 floats + 4 words: maxima, what plan_stats_kernel found, clean flags
   float t_global = 0.0f;
   uint32_t n_clean_flagged = 0;      // elements of C* the plan's own detector flags
+  bool factors_normal = false;       // see GemmArgs::normal
   bool plain_ok = false;             // the affected-only campaign's short comparison holds, see fi::kTinyFactor
   int cfg = 0;                       // index into kCfg
   int cfg_affected = 0;              // index into kCfg: the tiles that the affected-only campaign's batch limit counts
@@ -272,6 +273,7 @@ GemmArgs base_args(const fi_plan* p, int cfg = -1) {
   a.kra = p->kra; a.cb = p->cb; a.gamma = p->d.gamma;
   a.bound_global = p->d.bound_mode != FI_BOUND_ROWCOL;
   a.t_global = p->t_global;
+  a.normal = p->factors_normal;
   a.c_star = p->c_star; a.s_abs = p->s_abs;
   const size_t gold_bytes = golden_elems(p->d) * sizeof(float);
   a.c_star_bytes = gold_bytes < (1ull << 32) ? (uint32_t)gold_bytes : 0u;
@@ -613,8 +615,8 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   t = t * d.gamma;
   p->t_global = t;
   if (d.bound_mode == FI_BOUND_EXPONENT) p->t_global = kExponentBound;
-  const bool factors_normal = !(badw & 2u) && host[1] * d.gamma <= 3.4028234e38f;
-  p->plain_ok = p->t_global < 1.7e38f && (d.bound_mode != FI_BOUND_ROWCOL || factors_normal);
+  p->factors_normal = !(badw & 2u) && host[1] * d.gamma <= 3.4028234e38f && t < 1.7e38f;
+  p->plain_ok = p->t_global < 1.7e38f && (d.bound_mode != FI_BOUND_ROWCOL || p->factors_normal);
   // How many elements of the fault-free result the plan's own detector flags (none under the
   // operand-derived bounds with gamma at or above the default; possible under the exponent-only
   // bound or a caller's smaller gamma).  The affected-only campaign relies on it being 0.

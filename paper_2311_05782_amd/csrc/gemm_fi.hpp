@@ -60,6 +60,7 @@ struct GemmArgs {
   float gamma;
   int bound_global;         // 1: T = t_global everywhere
   float t_global;
+  int normal;               // no row or column factor, nor a product of them with gamma, leaves the normal range (0 may)
   const float* c_star;      // [M][N] fault-free result  (campaign)
   const float* s_abs;       // [M][N] sum_k |a b|        (campaign)
   // Bytes the c_star allocation spans, or 0.  The plan pads it to whole 256-row tiles plus one

@@ -638,26 +638,46 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) gemm_fi_
       }
       return T;
     };
-    // The smallest row factor of this lane's rows of each tile row, the column factors: see `detect`.
+    // What `detect` compares with.  HAVE_T: a little less than the column's part of the thresholds, where no product on
+    // the way leaves the normal range (then T is at least 1 - 2^-22 times the exact product), else 0, and row factors of
+    // Inf beyond the problem.  Else the smallest row factor of this lane's rows of each tile row.
     float kra_least[TM], cb_of[TN];
+    static_for<TN>([&](auto jj) {
+      constexpr int j = jj;
+      cb_of[j] = HAVE_T ? (p.normal ? cbj[j] * p.gamma * 0.999996185f : 0.0f) : p.cb[min(col_base + 32 * j, p.N - 1)];
+    });
     static_for<TM>([&](auto ii) {
       constexpr int i = ii;
-      f32x4 least = {__builtin_inff(), __builtin_inff(), __builtin_inff(), __builtin_inff()};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        f32x4 k4 = HAVE_T ? kra4[i][q] : *reinterpret_cast<const f32x4*>(p.kra + row_base + 32 * i + 8 * q);
+      kra_least[i] = 0.0f;
+      if constexpr (HAVE_T) {
         if (ragged) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) k4[e] = row_base + 32 * i + 8 * q + e < p.M ? k4[e] : __builtin_inff();
+          for (int v = 0; v < 16; ++v)
+            kra4[i][v >> 2][v & 3] = row_base + 32 * i + 8 * (v >> 2) + (v & 3) < p.M ? kra4[i][v >> 2][v & 3] : __builtin_inff();
         }
-        least = __builtin_elementwise_minimum(least, k4);
+      } else {
+        f32x4 least = {__builtin_inff(), __builtin_inff(), __builtin_inff(), __builtin_inff()};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          f32x4 k4 = *reinterpret_cast<const f32x4*>(p.kra + row_base + 32 * i + 8 * q);
+          if (ragged) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) k4[e] = row_base + 32 * i + 8 * q + e < p.M ? k4[e] : __builtin_inff();
+          }
+          least = __builtin_elementwise_minimum(least, k4);
+        }
+        kra_least[i] = __builtin_elementwise_minimum(__builtin_elementwise_minimum(least[0], least[1]),
+                                                     __builtin_elementwise_minimum(least[2], least[3]));
       }
-      kra_least[i] = __builtin_elementwise_minimum(__builtin_elementwise_minimum(least[0], least[1]),
-                                                   __builtin_elementwise_minimum(least[2], least[3]));
     });
-    static_for<TN>([&](auto jj) { cb_of[jj] = HAVE_T ? cbj[jj] : p.cb[min(col_base + 32 * jj, p.N - 1)]; });
-    auto least_threshold = [&](auto tt) __attribute__((always_inline)) {
-      return p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(kra_least[tt / TN], cb_of[tt % TN]), p.gamma);
+    auto largest = [&](auto tt, int v) __attribute__((always_inline)) {
+      constexpr int i = tt / TN, j = tt % TN;
+      float top = fabsf(acc[0][i][j][v]);
+      static_for<R>([&](auto rr) {
+        constexpr int r = rr;
+        if constexpr (r > 0) top = __builtin_elementwise_maximum(top, fabsf(acc[r][i][j][v]));
+      });
+      return top;
     };
     [[maybe_unused]] bool beyond = false;               // a tile of this wave holds a value at or above that (or a NaN)
     if (ragged) {
@@ -699,17 +719,27 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) gemm_fi_
       static_for<TM * TN>([&](auto tt) {
         constexpr int i = tt / TN, j = tt % TN;
         const int col = col_base + 32 * j;
-        // The largest magnitude of the lane's 16 x R elements against the smallest of their thresholds: the three
-        // roundings are monotonous, so that is the threshold of the smallest row factor.  v_maximum3_f32 takes two
-        // values an instruction, and a NaN outweighs all.  Less, not equal: of an infinite row factor and a
-        // column of zeros the threshold is a NaN, which the smallest factor does not show.
-        float top = 0.0f;
-        static_for<R>([&](auto rr) {
-          constexpr int r = rr;
+        // Nearly always nothing is flagged, which a comparison with a little less than the thresholds shows: the excess
+        // of the largest magnitude of a row's R elements over it in one instruction, of all rows the largest
+        // (v_maximum3_f32 takes two values an instruction, and a NaN outweighs all).  A threshold of 0 or NaN does not
+        // pass.  Without the row factors in registers the three roundings, which are monotonous, of the smallest one.
+        uint64_t some;
+        if (!HAVE_T || p.bound_global) {
+          float top = 0.0f;
+          static_for<R>([&](auto rr) {
+            constexpr int r = rr;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) top = __builtin_elementwise_maximum(top, fabsf(acc[r][i][j][v]));
-        });
-        uint64_t some = __ballot(!(top < least_threshold(tt)));
+            for (int v = 0; v < 16; ++v) top = __builtin_elementwise_maximum(top, fabsf(acc[r][i][j][v]));
+          });
+          const float least = p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(kra_least[i], cb_of[j]), p.gamma);
+          some = __ballot(!(top < least));
+        } else {
+          float excess = -__builtin_inff();
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            excess = __builtin_elementwise_maximum(excess, __fmaf_rn(-kra4[i][v >> 2][v & 3], cb_of[j], largest(tt, v)));
+          some = __ballot(!(excess < 0.0f));
+        }
         if (!OUT && some == 0) return;
         f32x16 T = {};
         if (some != 0) {
@@ -719,14 +749,7 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) gemm_fi_
           T = thresholds(tt);
           float excess = -__builtin_inff();
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            float high = fabsf(acc[0][i][j][v]);
-            static_for<R>([&](auto rr) {
-              constexpr int r = rr;
-              if constexpr (r > 0) high = __builtin_elementwise_maximum(high, fabsf(acc[r][i][j][v]));
-            });
-            excess = __builtin_elementwise_maximum(excess, __fsub_rn(high, T[v]));
-          }
+          for (int v = 0; v < 16; ++v) excess = __builtin_elementwise_maximum(excess, __fsub_rn(largest(tt, v), T[v]));
           some = __ballot(!(excess <= 0.0f));
           if (!OUT && some == 0) return;
         }
@@ -891,8 +914,8 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) gemm_fi_
             differs[v >> 2] |= (__float_as_uint(t[v]) ^ __float_as_uint(cs[v])) & mask;
           }
         }
-        // Equal words count where they are not finite or flagged: in the waves that hold such a value, which lies
-        // at or above the smallest threshold.
+        // Equal words count where they are not finite or flagged: in the waves that hold such a value, which no
+        // comparison has passed.
         float top = 0.0f;
         if (beyond) {
 #pragma unroll
