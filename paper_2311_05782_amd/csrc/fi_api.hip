@@ -107,6 +107,11 @@ namespace {
 // Where one wave per (trial, 32 x 32 tile) stops paying, in its MFMA steps per SIMD: K = 576, 3136 x 64, 46
 // trials (317 steps) 29 : 31 us against the multi-trial kernel.
 constexpr double kSmallSteps = 320.0;
+// Beyond, for K > 64, while steps + 15 * tiles per SIMD <= 550: few long tiles, which it has the registers and the room to
+// hide less of than those of many short ones.  Of 632 random batches of 280 to 1200 steps, this kernel : four trials per
+// item, up to four tiles per SIMD 0.80 at 280 to 550 steps, four to eight tiles 0.84 up to 400, 0.93 up to 550, 1.0 and
+// more beyond; by this line 1.035 over those of more than 320 steps, 1.8 % of them over 5 % slower.
+constexpr double kSmallLong = 550.0, kSmallLongTile = 15.0;
 // With short K a tile's fixed part - first loads, detector, counters - is most of it, which the eight trials
 // of the multi-trial kernel share, on 64 x 64 tiles.  Small while
 //   tiles per SIMD <= first + share * (that kernel's, in units of 32 x 32) + 5 per 1000 trials (partition):
@@ -193,13 +198,20 @@ double small_steps(const fi_plan* p, uint32_t n_trials) {
   return (double)n_trials * ((d.M + 31) / 32) * ((d.N + 31) / 32) * (d.K / 16) / (4.0 * p->n_cus);
 }
 
+// And its tiles per SIMD, four trials to a workgroup.
+double small_tiles(const fi_plan* p, uint32_t n_trials) {
+  const fi_plan_desc& d = p->d;
+  return (double)((d.M + 31) / 32) * ((d.N + 31) / 32) * ((n_trials + 3) / 4 * 4) / (4.0 * p->n_cus);
+}
+
 // Batches that gemm_fi_small_kernel serves, unless the caller has chosen a tile configuration.
 bool use_small(const fi_plan* p, uint32_t n_trials, bool c_out, bool h_out) {
   const fi_plan_desc& d = p->d;
-  if (!p->auto_cfg || small_steps(p, n_trials) > kSmallSteps) return false;
+  const double steps = small_steps(p, n_trials);
+  if (!p->auto_cfg || (steps > kSmallSteps && (d.K <= 64 || steps + kSmallLongTile * small_tiles(p, n_trials) > kSmallLong))) return false;
   if (n_trials <= 2) return true;                        // they fill a quarter of a group of eight at most
   const double simds = 4.0 * p->n_cus, n = (double)n_trials;
-  const double tiles = (double)((d.M + 31) / 32) * ((d.N + 31) / 32) * ((n_trials + 3) / 4 * 4) / simds;
+  const double tiles = small_tiles(p, n_trials);
   const double theirs = 4.0 * ((d.M + 63) / 64) * ((d.N + 63) / 64) * ((n_trials + 7) / 8 * 8) / simds;
   return tiles <= (c_out || h_out ? kSmallTilesOut : kSmallTiles) +
                       (h_out ? kSmallShareH : c_out ? kSmallShareC : kSmallShare) * theirs + 0.005 * n;
@@ -955,7 +967,8 @@ fi_status fi_plan_describe(const fi_plan* plan, char* h_buf, uint64_t n) {
   const char* dt = plan->d.dtype == FI_BF16 ? "bf16" : "fp16";
   char small[256] = "";
   if (use_small(plan, 1, false, false)) {
-    const unsigned most = (unsigned)(kSmallSteps / small_steps(plan, 1)), cus = (unsigned)plan->n_cus;
+    const double each = small_steps(plan, 1), long_each = each + kSmallLongTile * small_tiles(plan, 4) / 4.0;
+    const unsigned most = (unsigned)(plan->d.K > 64 && kSmallLong / long_each > kSmallSteps / each ? kSmallLong / long_each : kSmallSteps / each), cus = (unsigned)plan->n_cus;
     char trial[128] = "";
     if (use_trial(plan, 1, false, false))
       snprintf(trial, sizeof(trial), ", without outputs and at most %u trials: gemm_fi_trial_kernel<%s, one workgroup per trial>",
