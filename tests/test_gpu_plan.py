@@ -44,3 +44,69 @@ def test_plan_buffers_and_clean_flags(M, N, K, kb, b_layout, bound):
     rec = fi.results_to_host(d_r)[0]
     assert int(rec["n_flagged"]) == flagged and int(rec["n_bitdiff"]) == 0
     plan.destroy()
+
+
+def _records(plan, faults):
+    n = len(faults)
+    d_f, d_r, d_a = fi.to_device(faults), fi.empty_results(n), fi.empty_results(n)
+    plan.fi_gemm_inject_batch(d_f, n, fi.CORRECT_RECOMPUTE, d_r)
+    plan.fi_gemm_inject_batch_affected(d_f, n, fi.CORRECT_RECOMPUTE, d_a)
+    return fi.results_to_host(d_r).tobytes() + fi.results_to_host(d_a).tobytes()
+
+
+def _make(M, N, K, seed, scale=1.0, b_layout=0):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    a = (torch.randn(M, K, generator=g, device="cuda") * scale).bfloat16()
+    b = (torch.randn(N, K, generator=g, device="cuda") * scale).bfloat16()
+    return fi.Plan(fi.plan_desc(M, N, K, 16, fi.BF16, b_layout=b_layout), a, b if b_layout == 0 else b.t().contiguous())
+
+
+# Plans over memory that destroyed ones of other sizes and huge results have left; several threads, each with a
+# stream of its own, whose plans take and give such memory at the same time.
+def test_plans_over_the_memory_of_destroyed_ones():
+    import threading
+    import torch
+    shapes = [(512, 1500, 208, 0), (300, 700, 64, 1), (1030, 900, 80, 0), (400, 1100, 128, 1)]
+    kept = [_make(*s[:3], seed=k, b_layout=s[3]) for k, s in enumerate(shapes)]       # none has had another's memory
+    faults = [np.concatenate([fi.fi_sample_faults(9, 0, 40, p.desc, k, 1) for k in (fi.KIND_MIX_ACC_A, fi.KIND_ALL_B, fi.KIND_ALL_PRODUCT)])
+              for p in kept]
+    want = [_records(p, f) for p, f in zip(kept, faults)]
+    wrong = []
+
+    def sweep(worker):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for rep in range(6):
+                k = (worker + rep) % len(shapes)
+                M, N, K, layout = shapes[k]
+                _make(M, N, K, seed=50 + rep, scale=1e15, b_layout=layout).destroy()
+                plan = _make(M, N, K, seed=k, b_layout=layout)
+                if _records(plan, faults[k]) != want[k]:
+                    wrong.append((worker, rep, k))
+                plan.destroy()
+    sweep(0)
+    assert not wrong
+    threads = [threading.Thread(target=sweep, args=(w,)) for w in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    for p in kept:
+        p.destroy()
+
+
+def test_memory_of_destroyed_plans_is_bounded_and_given_back():
+    import torch
+    torch.cuda.synchronize()
+    MB = 1 << 20
+    before = torch.cuda.mem_get_info()[0]
+    for m in range(12):                                     # 10 .. 130 MB each, never the same
+        _make(1024 + 512 * m, 1024 + 256 * m, 16, seed=m).destroy()
+        torch.cuda.empty_cache()
+        assert before - torch.cuda.mem_get_info()[0] <= (256 + 32) * MB, m
+    for m in range(20):                                     # small ones that have no use for it
+        _make(64, 64, 16, seed=m).destroy()
+    torch.cuda.empty_cache()
+    assert before - torch.cuda.mem_get_info()[0] <= 48 * MB
