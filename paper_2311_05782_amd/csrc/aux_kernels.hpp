@@ -405,7 +405,12 @@ __global__ void __launch_bounds__(256) pad_front16_kernel(const uint16_t* __rest
 // kshift: zeros the GEMM kernel's operand copies carry in front of every row (K not a multiple of
 // 64): every event step moves up by kshift / 16; A, B, K here are the caller's unpadded operands.
 // queue: the work counters of the two launches, cleared.  One workgroup.
-template <int DT>
+// LOCAL: steps of 1024 trials that a batch has at most, or (kPartitionSteps) may have, see below.  A batch of one step runs
+// straight through: its time is that of fetching the code, 32 KB with eight steps, 5 KB with one; and it clears the
+// records, a launch less.  Plan and 8 trials with outputs on 512 x 3072 x 768 89.1 -> 83.4 us, raw outputs of 3136 x 64 x
+// 576, 128 trials, detector and hand-over 101.8 -> 98.2.
+constexpr int kPartitionSteps = 8;
+template <int DT, int LOCAL>
 __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* __restrict__ f, uint32_t n,
                                                                uint32_t M, uint32_t N, uint32_t K, uint32_t kb,
                                                                const uint16_t* __restrict__ A,
@@ -438,6 +443,11 @@ __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* 
   };
   bucket[threadIdx.x] = 0;
   for (uint32_t i = threadIdx.x; i < queue_words; i += 1024) queue[i] = 0;
+  if constexpr (LOCAL == 1) {
+    uint32_t* const words = reinterpret_cast<uint32_t*>(results);
+    for (uint32_t i = threadIdx.x; i < n * (uint32_t)(sizeof(fi_trial_result) / 4); i += 1024) words[i] = 0;
+    __builtin_amdgcn_s_waitcnt(0x0F70);                   // vmcnt(0): before any wave writes into a record
+  }
   __syncthreads();
   const uint32_t chunk = (n + 1023) / 1024;
   const uint32_t lo = min(threadIdx.x * chunk, n), hi = min(lo + chunk, n);
@@ -458,8 +468,8 @@ __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* 
   // Positions in the first part follow list order: a table of counts per (step, wave), scanned
   // once, plus the lane's rank among the wave's fast trials of that step.  Longer batches: each
   // thread walks a contiguous chunk, reading it in place.
-  constexpr int kLocal = 8;
-  const bool local = n <= (uint32_t)kLocal * 1024u;
+  constexpr int kLocal = LOCAL;
+  const bool local = LOCAL == 1 || n <= (uint32_t)kLocal * 1024u;
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   __shared__ uint32_t tab[kLocal * 16];
   fi_fault loc[kLocal];
@@ -522,12 +532,19 @@ __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* 
       uint32_t total = scc;                              // long batches: read at lane 15
       if (local) {
         // the (step, wave) table in list order, two entries per lane
-        static_assert(kLocal * 16 == 128, "two table entries per lane");
-        const uint32_t a = tab[2 * lane], b = tab[2 * lane + 1];
-        const uint32_t st = wave_scan(a + b);
-        tab[2 * lane] = st - (a + b);
-        tab[2 * lane + 1] = st - b;
-        total = __shfl(st, 63, 64);
+        static_assert(kLocal == 8 || kLocal == 1, "two table entries per lane, or one for each of 16");
+        if constexpr (kLocal == 1) {
+          const uint32_t a = lane < 16u ? tab[lane] : 0u;
+          const uint32_t st = wave_scan(a);
+          if (lane < 16u) tab[lane] = st - a;
+          total = __shfl(st, 63, 64);
+        } else {
+          const uint32_t a = tab[2 * lane], b = tab[2 * lane + 1];
+          const uint32_t st = wave_scan(a + b);
+          tab[2 * lane] = st - (a + b);
+          tab[2 * lane + 1] = st - b;
+          total = __shfl(st, 63, 64);
+        }
       }
       if (lane == 15u) {
         total_fast = total;

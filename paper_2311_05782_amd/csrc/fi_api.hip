@@ -841,11 +841,15 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
     FI_HIP(hipGetLastError());
     return FI_OK;
   }
-  const size_t words = (size_t)n_trials * (sizeof(fi_trial_result) / 4);
-  hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)((words + 255) / 256 > 1024 ? 1024 : (words + 255) / 256)),
-                     dim3(256), 0, s, reinterpret_cast<uint32_t*>(d_results), words, 0u);
-  FI_HIP(hipGetLastError());
-  if (use_small(plan, n_trials, d_c_out != nullptr, d_h_out != nullptr)) {
+  const bool small = use_small(plan, n_trials, d_c_out != nullptr, d_h_out != nullptr);
+  const bool one_step = !small && plan->mcfg >= 0 && n_trials <= 1024u;   // the partition kernel clears the records
+  if (!one_step) {
+    const size_t words = (size_t)n_trials * (sizeof(fi_trial_result) / 4);
+    hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)((words + 255) / 256 > 1024 ? 1024 : (words + 255) / 256)),
+                       dim3(256), 0, s, reinterpret_cast<uint32_t*>(d_results), words, 0u);
+    FI_HIP(hipGetLastError());
+  }
+  if (small) {
     a.tiles_m = (a.M + 31) / 32;
     a.tiles_n = (a.N + 31) / 32;
     if (plan->d.dtype == FI_BF16) launch_small<FI_BF16>(a, s); else launch_small<FI_FP16>(a, s);
@@ -859,16 +863,16 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
   // R trials at a time share staged operands.  The batch is split on the device into the trials
   // whose fault leaves the operands alone and the operand-fault trials; each part has its own
   // instantiation of the kernel.
-  if (plan->d.dtype == FI_BF16)
-    hipLaunchKernelGGL(fi::partition_trials_kernel<FI_BF16>, dim3(1), dim3(1024), 0, s, d_faults, n_trials,
-                       plan->d.M, plan->d.N, plan->d.K, plan->d.k_block, a.A, a.B, a.lda, a.ldb, plan->product_check,
-                       (uint32_t)mc.bm, (uint32_t)mc.bn, plan->kshift, ts.counts, ts.desc, ts.queue,
-                       2u * fi::kQueueWords, d_results);
-  else
-    hipLaunchKernelGGL(fi::partition_trials_kernel<FI_FP16>, dim3(1), dim3(1024), 0, s, d_faults, n_trials,
-                       plan->d.M, plan->d.N, plan->d.K, plan->d.k_block, a.A, a.B, a.lda, a.ldb, plan->product_check,
-                       (uint32_t)mc.bm, (uint32_t)mc.bn, plan->kshift, ts.counts, ts.desc, ts.queue,
-                       2u * fi::kQueueWords, d_results);
+#define FI_PARTITION(DT, STEPS)                                                                                           \
+  hipLaunchKernelGGL((fi::partition_trials_kernel<DT, STEPS>), dim3(1), dim3(1024), 0, s, d_faults, n_trials, plan->d.M,  \
+                     plan->d.N, plan->d.K, plan->d.k_block, a.A, a.B, a.lda, a.ldb, plan->product_check, (uint32_t)mc.bm, \
+                     (uint32_t)mc.bn, plan->kshift, ts.counts, ts.desc, ts.queue, 2u * fi::kQueueWords, d_results)
+  if (plan->d.dtype == FI_BF16) {
+    if (one_step) FI_PARTITION(FI_BF16, 1); else FI_PARTITION(FI_BF16, fi::kPartitionSteps);
+  } else {
+    if (one_step) FI_PARTITION(FI_FP16, 1); else FI_PARTITION(FI_FP16, fi::kPartitionSteps);
+  }
+#undef FI_PARTITION
   FI_HIP(hipGetLastError());
   m.part_counts = ts.counts;
   m.desc = ts.desc;

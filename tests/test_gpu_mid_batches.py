@@ -25,12 +25,12 @@ def _faults(plan, n, operand):
 
 # (M, N, K, k-block), trials, every how many-th is an operand fault.  The first part ends 1 .. 8 trials into a group of
 # eight, so that the descriptors' padding holds a group of four or none, and either part may be empty; ragged tiles
-# and k-tiles, an odd number of k-tiles, the shortest K; two items per workgroup, several from the counters, and 64 or more, where
+# and k-tiles, an odd number of k-tiles, the shortest K; the longest batch that one step of the partition kernel sees; two items per workgroup, several from the counters, and 64 or more, where
 # workgroups look into other XCDs' slices.
 @pytest.mark.parametrize("shape,n,operand", [
     ((300, 300, 512, 32), 121, 0), ((300, 300, 512, 32), 124, 1), ((300, 300, 512, 32), 127, 5), ((320, 256, 512, 32), 260, 2),
     ((300, 300, 512, 32), 133, 132), ((129, 515, 464, 16), 205, 3), ((1000, 130, 320, 32), 119, 4),
-    ((250, 1000, 80, 16), 440, 3), ((600, 300, 192, 32), 900, 6), ((70, 60, 128, 32), 50001, 9),
+    ((250, 1000, 80, 16), 440, 3), ((600, 300, 192, 32), 900, 6), ((300, 300, 512, 32), 1024, 3), ((300, 300, 512, 32), 1025, 4), ((70, 60, 128, 32), 50001, 9),
 ])
 def test_mid_batches_equal_the_other_shapes(shape, n, operand):
     import torch
@@ -46,8 +46,11 @@ def test_mid_batches_equal_the_other_shapes(shape, n, operand):
     assert -(-M // 64) * -(-N // 64) * -(-n // 8) * -(-K // 64) <= 100 * 2 * cus and K > 64
     faults = _faults(plan, n, operand)
     want = gu.gpu_campaign(eight, faults, wl.CORRECT_RECOMPUTE)
+    d_f = fi.to_device(faults)
     for _ in range(2):
-        got = gu.gpu_campaign(plan, faults, wl.CORRECT_RECOMPUTE)
+        d_r = fi.empty_results(n).fill_(0xFF)           # the records are cleared by the call
+        plan.fi_gemm_inject_batch(d_f, n, wl.CORRECT_RECOMPUTE, d_r)
+        got = fi.results_to_host(d_r)
         assert got.tobytes() == want.tobytes(), [t for t in range(n) if got[t] != want[t]][:5]
     if n < 1000:
         one = gu.make_plan(Aw, Bw, kb, fmt, cfg=2)
@@ -55,7 +58,6 @@ def test_mid_batches_equal_the_other_shapes(shape, n, operand):
         r4, c4 = gu.gpu_campaign(plan, faults, wl.CORRECT_ZERO, want_c=True)
         assert r1.tobytes() == r4.tobytes() and c1.tobytes() == c4.tobytes()
         one.destroy()
-        d_f = fi.to_device(faults)
         outs = []
         for p in (plan, eight):
             d_r, d_h = fi.empty_results(n), torch.zeros((n, M, N), dtype=torch.int16, device="cuda")
