@@ -513,21 +513,13 @@ __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* 
   uint32_t pf = 0;                                       // long batches: fast trials before my chunk
   {
     __shared__ uint32_t wave_tot[16], wave_tot_c[16];
-    auto wave_scan = [&](uint32_t v) -> uint32_t {       // inclusive
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t u = __shfl_up(v, o, 64);
-        v += lane >= (uint32_t)o ? u : 0u;
-      }
-      return v;
-    };
     const uint32_t own = bucket[threadIdx.x], own_c = c;
-    uint32_t incl = wave_scan(own), incl_c = wave_scan(own_c);
+    uint32_t incl = wave_prefix(own), incl_c = wave_prefix(own_c);
     if (lane == 63u) { wave_tot[wave] = incl; wave_tot_c[wave] = incl_c; }
     __syncthreads();
     if (wave == 0) {
       const uint32_t v = lane < 16u ? wave_tot[lane] : 0u, vc = lane < 16u ? wave_tot_c[lane] : 0u;
-      const uint32_t sc = wave_scan(v), scc = wave_scan(vc);
+      const uint32_t sc = wave_prefix(v), scc = wave_prefix(vc);
       if (lane < 16u) { wave_tot[lane] = sc - v; wave_tot_c[lane] = scc - vc; }
       uint32_t total = scc;                              // long batches: read at lane 15
       if (local) {
@@ -535,12 +527,12 @@ __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* 
         static_assert(kLocal == 8 || kLocal == 1, "two table entries per lane, or one for each of 16");
         if constexpr (kLocal == 1) {
           const uint32_t a = lane < 16u ? tab[lane] : 0u;
-          const uint32_t st = wave_scan(a);
+          const uint32_t st = wave_prefix(a);
           if (lane < 16u) tab[lane] = st - a;
           total = __shfl(st, 63, 64);
         } else {
           const uint32_t a = tab[2 * lane], b = tab[2 * lane + 1];
-          const uint32_t st = wave_scan(a + b);
+          const uint32_t st = wave_prefix(a + b);
           tab[2 * lane] = st - (a + b);
           tab[2 * lane + 1] = st - b;
           total = __shfl(st, 63, 64);
@@ -745,10 +737,7 @@ __global__ void __launch_bounds__(1024) classify_kernel(const fi_trial_result* _
       c0 += (k == FI_MASKED); c1 += (k == FI_SDC); c2 += (k == FI_DETECTED);
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    c0 += __shfl_xor(c0, o, 64); c1 += __shfl_xor(c1, o, 64); c2 += __shfl_xor(c2, o, 64);
-  }
+  c0 = wave_sum(c0); c1 = wave_sum(c1); c2 = wave_sum(c2);
   if ((threadIdx.x & 63) == 0) {
     part[0][threadIdx.x >> 6] = c0; part[1][threadIdx.x >> 6] = c1; part[2][threadIdx.x >> 6] = c2;
   }

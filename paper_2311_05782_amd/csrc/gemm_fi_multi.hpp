@@ -984,13 +984,9 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) gemm_fi_
       // most trial tiles equal the fault-free result bit for bit: one ballot, nothing to reduce
       uint32_t mp = __float_as_uint(mx_pre), mq = __float_as_uint(mx_post);   // non-negative: ordered like words
       if (__ballot((n_bit | n_pre | n_post | mp | mq) != 0) == 0) return;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        n_bit += __shfl_xor(n_bit, o, 64); n_pre += __shfl_xor(n_pre, o, 64); n_post += __shfl_xor(n_post, o, 64);
-        n_bT += __shfl_xor(n_bT, o, 64); n_btau += __shfl_xor(n_btau, o, 64);
-        const uint32_t a = __shfl_xor(mp, o, 64), b = __shfl_xor(mq, o, 64);
-        mp = a > mp ? a : mp; mq = b > mq ? b : mq;
-      }
+      n_bit = wave_sum(n_bit); n_pre = wave_sum(n_pre); n_post = wave_sum(n_post);
+      n_bT = wave_sum(n_bT); n_btau = wave_sum(n_btau);
+      mp = wave_max(mp); mq = wave_max(mq);
       fi_trial_result* const res = p.results + cur.grp;  // an item is a trial
       if (lane == 0) {
         if (n_bit) atomicAdd(&res->n_bitdiff, n_bit);
@@ -1170,20 +1166,14 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) gemm_fi_
       }
     });
     // non-negative floats (and +Inf) order like their words
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      static_for<R>([&](auto rr) {
-        mxp[rr] = fmaxf(mxp[rr], __shfl_xor(mxp[rr], o, 64));
-        mxq[rr] = fmaxf(mxq[rr], __shfl_xor(mxq[rr], o, 64));
-      });
-    }
     static_for<R>([&](auto rr) {
       constexpr int r = rr;
       if ((owned >> r) & 1u) {
         fi_trial_result* const res = p.results + desc_field(r, 0);
+        const uint32_t mp = wave_max(__float_as_uint(mxp[r])), mq = wave_max(__float_as_uint(mxq[r]));
         if (lane != 0) return;
-        if (mxp[r] > 0.0f) atomicMax(reinterpret_cast<uint32_t*>(&res->max_dev_pre), __float_as_uint(mxp[r]));
-        if (mxq[r] > 0.0f) atomicMax(reinterpret_cast<uint32_t*>(&res->max_dev_post), __float_as_uint(mxq[r]));
+        if (mp) atomicMax(reinterpret_cast<uint32_t*>(&res->max_dev_pre), mp);
+        if (mq) atomicMax(reinterpret_cast<uint32_t*>(&res->max_dev_post), mq);
       }
     });
   };
