@@ -83,7 +83,9 @@ struct fi_plan {
   float* s_abs = nullptr;            // [M][N]
   float* kra = nullptr;              // [pad(M)]
   float* cb = nullptr;               // [pad(N)]
-  float* scratch = nullptr;          // 4 floats + 4 words: maxima, what plan_stats_kernel found, clean flags
+  float* scratch = nullptr;          // 4 floats + 4 words: maxima, what plan_stats_kernel found, clean flags; GemmArgs::cleared
+  uint32_t epoch = 0;                // the last value that went into that word, by calls on this stream
+  hipStream_t clear_stream = nullptr;
   float t_global = 0.0f;
   uint32_t n_clean_flagged = 0;      // elements of C* the plan's own detector flags
   bool factors_normal = false;       // see GemmArgs::normal
@@ -675,7 +677,7 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
     bytes += (n + 255) / 256 * 256;
     return at;
   };
-  const size_t at_c = place((mn_pad + 8) * sizeof(float)), at_s = place(mn * sizeof(float));
+  const size_t at_c = place((mn_pad + 9) * sizeof(float)), at_s = place(mn * sizeof(float));
   const size_t at_kra = place(padded(d.M) * sizeof(float)), at_cb = place(padded(d.N) * sizeof(float));
   const size_t at_bt = place(d.b_layout ? (size_t)d.N * d.K * sizeof(uint16_t) : 0);
   const size_t at_ap = place(p->kshift ? (size_t)d.M * kp * sizeof(uint16_t) : 0);
@@ -693,7 +695,7 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   p->kra = reinterpret_cast<float*>(base + at_kra);
   p->cb = reinterpret_cast<float*>(base + at_cb);
   p->first_scratch = reinterpret_cast<uint32_t*>(base + at_scratch);
-  const size_t zeros = mn_pad + 8 - mn;
+  const size_t zeros = mn_pad + 9 - mn;
   hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)(zeros < 262144 ? (zeros + 255) / 256 : 1024)), dim3(256), 0, s,
                      reinterpret_cast<uint32_t*>(p->c_star + mn), zeros, 0u);
   FI_HIP(hipGetLastError());
@@ -753,6 +755,26 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   return FI_OK;
 }
 
+// The small kernels clear the records themselves, through a word of the plan: on the first stream that a plan's such
+// batch comes on, whose calls follow each other, outside capture (a graph may be replayed beside them, and with the same epoch
+// each time), and up to kClearTrials, which one workgroup clears in half a microsecond.  Else a launch in front does.
+constexpr uint32_t kClearTrials = 512;
+bool clear_in_kernel(fi_plan* p, uint32_t n_trials, hipStream_t s, GemmArgs* a) {
+  if (n_trials > kClearTrials) return false;
+  if (p->epoch != 0 && p->clear_stream != s) return false;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (capture != hipStreamCaptureStatusNone) return false;
+  if (++p->epoch == 0) ++p->epoch;
+  p->clear_stream = s;
+  a->cleared = reinterpret_cast<uint32_t*>(p->scratch + 8);
+  a->epoch = p->epoch;
+  return true;
+}
+
 // Where one batch of the multi-trial kernel keeps its two part counts, its work counters and the
 // per-trial descriptors; all of it is rewritten by the partition kernel of every batch.
 struct TrialScratch {
@@ -793,7 +815,7 @@ void launch_small(const GemmArgs& a, hipStream_t s) {
 // the multi-trial kernel (scratch in `ts`), or one launch of the one-trial kernel.
 fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trials, uint32_t policy,
                        fi_trial_result* d_results, float* d_c_out, hipStream_t s, const TrialScratch& ts,
-                       uint16_t* d_h_out = nullptr) {
+                       bool may_clear, uint16_t* d_h_out = nullptr) {
   GemmArgs a = base_args(plan);
   const uint64_t blocks = (uint64_t)a.tiles_m * a.tiles_n * n_trials;
   if (blocks >= (1ull << 31)) return fail(FI_UNSUPPORTED, "tiles x trials exceeds 2^31 workgroups; split the batch");
@@ -843,7 +865,7 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
   }
   const bool small = use_small(plan, n_trials, d_c_out != nullptr, d_h_out != nullptr);
   const bool one_step = !small && plan->mcfg >= 0 && n_trials <= 1024u;   // the partition kernel clears the records
-  if (!one_step) {
+  if (!one_step && !(small && may_clear && clear_in_kernel(plan, n_trials, s, &a))) {
     const size_t words = (size_t)n_trials * (sizeof(fi_trial_result) / 4);
     hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)((words + 255) / 256 > 1024 ? 1024 : (words + 255) / 256)),
                        dim3(256), 0, s, reinterpret_cast<uint32_t*>(d_results), words, 0u);
@@ -1130,7 +1152,7 @@ fi_status fi_gemm_inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t
     if (st != FI_OK) return st;
     ts = TrialScratch(bs->words);
   }
-  return inject_batch(plan, d_faults, n_trials, policy, d_results, d_c_out, as_stream(stream), ts);
+  return inject_batch(plan, d_faults, n_trials, policy, d_results, d_c_out, as_stream(stream), ts, true);
 }
 
 fi_status fi_gemm_inject_batch_act(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trials, uint32_t policy,
@@ -1146,7 +1168,7 @@ fi_status fi_gemm_inject_batch_act(fi_plan* plan, const fi_fault* d_faults, uint
   st = batch_scratch(plan, as_stream(stream), n_trials, &bs);
   if (st != FI_OK) return st;
   const TrialScratch ts(bs->words);
-  return inject_batch(plan, d_faults, n_trials, policy, d_results, nullptr, as_stream(stream), ts,
+  return inject_batch(plan, d_faults, n_trials, policy, d_results, nullptr, as_stream(stream), ts, true,
                       static_cast<uint16_t*>(d_h_out));
 }
 
@@ -1164,7 +1186,7 @@ fi_status fi_gemm_inject_batch_noalloc(fi_plan* plan, const fi_fault* d_faults, 
   }
   if (!base) return fail(FI_STATE, "the static scratch of device %d was not resolved at plan creation", plan->device);
   const TrialScratch ts(base);
-  return inject_batch(plan, d_faults, n_trials, policy, d_results, d_c_out, as_stream(stream), ts);
+  return inject_batch(plan, d_faults, n_trials, policy, d_results, d_c_out, as_stream(stream), ts, false);
 }
 
 fi_status fi_gemm_inject_batch_affected(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trials,
@@ -1252,10 +1274,12 @@ fi_status fi_gemm_propagate_batch(fi_plan* plan, const void* d_a_stack, uint64_t
   const int prop_cfg = pick_prop(plan, n_trials);
   if (persistent) blocks = tile(prop_cfg);
   hipStream_t s = as_stream(stream);
-  const size_t words = (size_t)n_trials * (sizeof(fi_trial_result) / 4);
-  hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)((words + 255) / 256 > 1024 ? 1024 : (words + 255) / 256)),
-                     dim3(256), 0, s, reinterpret_cast<uint32_t*>(d_results), words, 0u);
-  FI_HIP(hipGetLastError());
+  if (!(small && clear_in_kernel(plan, n_trials, s, &a))) {
+    const size_t words = (size_t)n_trials * (sizeof(fi_trial_result) / 4);
+    hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((unsigned)((words + 255) / 256 > 1024 ? 1024 : (words + 255) / 256)),
+                       dim3(256), 0, s, reinterpret_cast<uint32_t*>(d_results), words, 0u);
+    FI_HIP(hipGetLastError());
+  }
   a.A = static_cast<const uint16_t*>(d_a_stack);
   a.a_trial_stride = trial_stride;
   a.n_trials = (int)n_trials;

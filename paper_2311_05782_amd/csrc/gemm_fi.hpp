@@ -91,6 +91,10 @@ struct GemmArgs {
   // the workgroups of an XCD have taken of its slice of the work list, kQueueStride words per XCD; zero at
   // the start.  The operand-fault launch has a set of its own behind the first.
   uint32_t* queue;
+  // Small kernels, nullable (then the records are clear): workgroup 0 clears them and writes `epoch`, which the word
+  // has not held before, into `cleared`; nobody else writes into a record before.
+  uint32_t* cleared;
+  uint32_t epoch;
   // Measurement aid, nullable: workgroup 0 of the persistent kernel writes the shader-clock
   // counter and the constant-rate (100 MHz) counter when it starts and when it has finished its
   // last item - {cycles, ticks, cycles, ticks} at clocks + 4 * VAR - from which the host derives

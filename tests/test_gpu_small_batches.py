@@ -135,3 +135,58 @@ def test_next_layer_batches_either_side_of_the_lines_between_the_kernels(M, N, K
     assert got[0].tobytes() == got[1].tobytes(), [t for t in range(n) if got[0][t] != got[1][t]][:5]
     assert not got[0]["n_bitdiff"][3::4].any() and (got[0]["n_bitdiff"][1::4][:n // 4 - 1] > M * N // 2).all()
     assert (got[0]["n_flagged"][2::4] == N).all()
+
+
+# Campaigns and next layers of the small kernels on dirty records: cleared inside the kernel on a plan's first stream and up to
+# 512 trials, by a launch in front on a second stream, beyond, without allocations and under capture.
+@pytest.mark.parametrize("n", [1, 3, 70, 512, 513])
+def test_small_batches_write_whole_records(n):
+    import torch
+    M, N, K, fmt = 200, 130, 96, orc.FP16
+    Aw, Bw = wl.gaussian(M, N, K, fmt, seed=n)
+    one, plan = gu.make_plan(Aw, Bw, 32, fmt, cfg=2), gu.make_plan(Aw, Bw, 32, fmt)
+    faults = fi.fi_sample_faults(1, 0, n, plan.desc, fi.KIND_MIX_ACC_A, 1)
+    faults[2::5] = fi.fi_sample_faults(2, 0, n, plan.desc, fi.KIND_ALL_B, 2)[2::5]
+    faults[3::5] = fi.fi_sample_faults(3, 0, n, plan.desc, fi.KIND_ALL_PRODUCT, 4)[3::5]
+    faults["row"][4::9] = 10 ** 7
+    faults["kind"][6::9] = fi.SITE_NONE
+    want = gu.gpu_campaign(one, faults, wl.CORRECT_ZERO).tobytes()
+    d_f = fi.to_device(faults)
+    stack = fi.words_to_device(Aw).expand(n, M, K).clone()
+    stack[::2, 5] += 3
+    d_r = fi.empty_results(n)
+    one.fi_gemm_propagate_batch(stack, M * K, n, wl.CORRECT_ZERO, d_r)
+    want_next = fi.results_to_host(d_r).tobytes()
+    side = torch.cuda.Stream()
+
+    def both(stream, call=plan.fi_gemm_inject_batch):
+        a, b = fi.empty_results(n).fill_(0xFF), fi.empty_results(n).fill_(0xFF)
+        torch.cuda.synchronize()
+        call(d_f, n, wl.CORRECT_ZERO, a, stream=stream)
+        plan.fi_gemm_propagate_batch(stack, M * K, n, wl.CORRECT_ZERO, b, stream=stream)
+        return a, b
+
+    def check(a, b, what):
+        assert fi.results_to_host(a).tobytes() == want, what
+        assert fi.results_to_host(b).tobytes() == want_next, what
+    for rep in range(3):
+        check(*both(None), ("first stream", rep))
+        check(*both(side), ("second stream", rep))
+        check(*both(None, plan.fi_gemm_inject_batch_noalloc), ("no allocations", rep))
+    g = torch.cuda.CUDAGraph()
+    plan.reserve(n, side)
+    a, b = fi.empty_results(n), fi.empty_results(n)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            s = torch.cuda.current_stream().cuda_stream
+            plan.fi_gemm_inject_batch(d_f, n, wl.CORRECT_ZERO, a, stream=s)
+            plan.fi_gemm_propagate_batch(stack, M * K, n, wl.CORRECT_ZERO, b, stream=s)
+    for rep in range(2):
+        a.fill_(0xFF); b.fill_(0xFF)
+        check(*both(None), ("between replays", rep))
+        g.replay()
+        torch.cuda.synchronize()
+        check(a, b, ("replay", rep))
+    one.destroy()
+    plan.destroy()
