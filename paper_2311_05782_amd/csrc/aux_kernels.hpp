@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
     float* __restrict__ C, uint32_t batch, uint32_t M, uint32_t N, const float* __restrict__ kra,
     const float* __restrict__ cb, float gamma, int bound_global, float t_global, int policy,
     const float* __restrict__ c_star, uint8_t* __restrict__ flags, uint32_t* __restrict__ n_flagged,
-    const DetectStep step) {
+    const DetectStep step, uint32_t* cleared, uint32_t epoch) {
   static_assert(VEC == 4 || (VEC == 1 && !ROW4), "vectors of four or single elements");
   constexpr uint32_t THREADS = 256, WAVES = THREADS / 64, CHUNK = THREADS * VEC * UNROLL;
   // what the waves have flagged, trial by trial: entries 0 .. slots - 1, then what is left at the end
@@ -147,6 +147,27 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   [[maybe_unused]] uint32_t slots = 0;
   if (threadIdx.x == 0) arrived = 0;
+  // Counters that no launch in front has cleared, as the small campaign kernel's records: the first workgroup to be
+  // dispatched clears them, whoever has flagged something looks whether it has (raw outputs of 3136 x 64 x 576, detector
+  // and hand-over 95.8 -> 94.2 us, two trials of 417 x 842 x 144 21.3 -> 19.0).
+  if (cleared != nullptr && blockIdx.x == 0) {
+    for (uint32_t i = threadIdx.x; i < batch; i += THREADS)
+      __hip_atomic_store(n_flagged + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                   // vmcnt(0)
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(cleared, epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  bool waited = cleared == nullptr;
+  auto wait_cleared = [&]() {                             // by whole waves
+    if (waited) return;
+    uint32_t seen;
+    do {
+      seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(cleared, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      __builtin_amdgcn_s_sleep(1);
+    } while (seen != epoch);
+    asm volatile("" ::: "memory");                        // nothing is read that another wave has written
+    waited = true;
+  };
   const bool together = n_flagged != nullptr && step.together != 0;
   bool fresh = together;
   const size_t total = (size_t)batch * M * N;
@@ -287,7 +308,10 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
                   if (kept && lane == 0) { kept_b[wave][slots] = run_b; kept_n[wave][slots] = run_n; }
                   slots += kept ? 1u : 0u;
                 }
-                if (!kept && lane == 0) atomicAdd(n_flagged + run_b, run_n);
+                if (!kept) {
+                  wait_cleared();
+                  if (lane == 0) atomicAdd(n_flagged + run_b, run_n);
+                }
               }
               run_b = bb;
               run_n = 0;
@@ -306,7 +330,10 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
     b0 += step.trial + carry;
   }
   if (n_flagged && !together) {
-    if (run_n && lane == 0) atomicAdd(n_flagged + run_b, run_n);
+    if (run_n) {
+      wait_cleared();
+      if (lane == 0) atomicAdd(n_flagged + run_b, run_n);
+    }
   } else if (together) {
     // bits 0 .. 4: waves that are done; 8 + w: wave w has left something
     const uint32_t mine = run_n != 0 || slots != 0 ? 256u << wave : 0u;
@@ -321,6 +348,7 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
     before = (uint32_t)__builtin_amdgcn_readfirstlane((int)before);
     const uint32_t left = (before + mine) >> 8;
     if ((before & 31u) != WAVES - 1u || left == 0) return;
+    wait_cleared();
     // the last wave: entry i of wave w goes with entry i of the first wave that has the same trial there
     for (uint32_t e = lane; e < (SLOTS + 1) * WAVES; e += 64) {
       const uint32_t w = e / (SLOTS + 1), i = e % (SLOTS + 1), b = kept_b[w][i];

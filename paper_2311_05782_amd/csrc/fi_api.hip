@@ -624,7 +624,7 @@ constexpr uint32_t kDetectTogether = 1024;
 // The detector / corrector on [batch][M][N] outputs: whole vectors where the outputs (and flags)
 // are aligned for them and a vector spans two rows at most, else element by element.
 hipError_t launch_detect(const fi_plan* p, float* d_c, uint32_t batch, uint32_t policy, uint8_t* d_flags,
-                         uint32_t* d_n_flagged, hipStream_t s) {
+                         uint32_t* d_n_flagged, uint32_t* cleared, uint32_t epoch, hipStream_t s) {
   const fi_plan_desc& d = p->d;
   const bool vec = d.N >= 4 && (reinterpret_cast<uintptr_t>(d_c) & 15u) == 0 &&
                    (reinterpret_cast<uintptr_t>(d_flags) & 3u) == 0;
@@ -646,7 +646,7 @@ hipError_t launch_detect(const fi_plan* p, float* d_c, uint32_t batch, uint32_t 
   const int global = d.bound_mode != FI_BOUND_ROWCOL;
 #define FI_DETECT(VEC, ROW4, UNROLL)                                                                               \
   hipLaunchKernelGGL((fi::detect_correct_kernel<VEC, ROW4, UNROLL>), grid, block, 0, s, d_c, batch, d.M, d.N, p->kra, \
-                     p->cb, d.gamma, global, p->t_global, (int)policy, p->c_star, d_flags, d_n_flagged, step)
+                     p->cb, d.gamma, global, p->t_global, (int)policy, p->c_star, d_flags, d_n_flagged, step, cleared, epoch)
   if (!vec) {
     if (deep) FI_DETECT(1, false, 4); else FI_DETECT(1, false, 1);
   } else if (d.N % 4 == 0) {
@@ -755,7 +755,7 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   return FI_OK;
 }
 
-// The small kernels clear the records themselves, through a word of the plan: on the first stream that a plan's such
+// The small kernels clear the records themselves, and the detector its counters, through a word of the plan: on the first stream that a plan's such
 // batch comes on, whose calls follow each other, outside capture (a graph may be replayed beside them, and with the same epoch
 // each time), and up to kClearTrials, which one workgroup clears in half a microsecond.  Else a launch in front does.
 constexpr uint32_t kClearTrials = 512;
@@ -1324,12 +1324,13 @@ fi_status fi_detect_correct(fi_plan* plan, float* d_c, uint32_t batch, uint32_t 
   if (policy > FI_CORRECT_RECOMPUTE) return fail(FI_INVALID_ARG, "unknown correction policy %u", policy);
   hipStream_t s = as_stream(stream);
   const fi_plan_desc& d = plan->d;
-  if (d_n_flagged) {
+  GemmArgs a = {};
+  if (d_n_flagged && !clear_in_kernel(plan, batch, s, &a)) {
     hipLaunchKernelGGL(fi::fill_u32_kernel, dim3((batch + 255) / 256), dim3(256), 0, s, d_n_flagged,
                        (size_t)batch, 0u);
     FI_HIP(hipGetLastError());
   }
-  FI_HIP(launch_detect(plan, d_c, batch, policy, d_flags, d_n_flagged, s));
+  FI_HIP(launch_detect(plan, d_c, batch, policy, d_flags, d_n_flagged, a.cleared, a.epoch, s));
   return FI_OK;
 }
 

@@ -56,6 +56,42 @@ def test_detector_equals_its_definition(M, N, batch, shift, bound):
     plan.destroy()
 
 
+# Counters holding anything: cleared inside the kernel on a plan's first stream and up to 512 trials, by a launch in front
+# on a second stream, beyond and under capture.  Long rows, whose waves hand over together, and short ones.
+@pytest.mark.parametrize("batch,M,N", [(512, 3, 1028), (513, 3, 1028), (300, 40, 33), (1, 500, 700)])
+def test_detector_clears_its_counters(batch, M, N):
+    import torch
+    plan = gu.make_plan(*wl.gaussian(M, N, 64, orc.BF16, seed=N), 32, orc.BF16)
+    c = torch.zeros(batch, M, N, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    hits = torch.rand(batch, M, N, generator=g, device="cuda") < torch.rand(batch, 1, 1, generator=g, device="cuda") ** 4
+    c[hits] = float("inf")
+    want = hits.sum(dim=(1, 2), dtype=torch.int32)
+    cnt = torch.empty(batch, dtype=torch.int32, device="cuda")
+    side = torch.cuda.Stream()
+
+    def check(stream, what):
+        cnt.fill_(-7)
+        torch.cuda.synchronize()
+        plan.fi_detect_correct(c, batch, wl.CORRECT_NONE, None, cnt, stream=stream)
+        torch.cuda.synchronize()
+        assert torch.equal(cnt, want), what
+    graph = torch.cuda.CUDAGraph()
+    for rep in range(2):
+        check(None, ("first stream", rep))
+        check(side, ("second stream", rep))
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            plan.fi_detect_correct(c, batch, wl.CORRECT_NONE, None, cnt, stream=torch.cuda.current_stream().cuda_stream)
+    for rep in range(2):
+        cnt.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(cnt, want), ("replay", rep)
+        check(None, ("between replays", rep))
+    plan.destroy()
+
+
 @pytest.mark.parametrize("cfg", [-1, 2, 3, 6])          # element by element; through the largest excess over T
 def test_fused_detector_tells_subnormal_values_from_a_subnormal_threshold(cfg):
     # ra = cb = 2^-70, K = 128: T = 2^-133 * (1 + 2^-11) = 65568 units of 2^-149.  The fault writes its mask into an
