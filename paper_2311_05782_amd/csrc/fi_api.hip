@@ -236,19 +236,22 @@ bool use_small_propagate(const fi_plan* p, uint32_t n_trials, bool c_out, bool p
 // Tile shape of a next-layer batch.  Below 2^35 multiply-adds the plan has the 128 x 128 shape, two workgroups
 // per CU, one's epilogue under the other's MFMAs.  256 x 256 tiles read a third less from LDS per MFMA and half
 // as much from L2, but nothing hides an item's epilogue, so they take long items in whole rounds
-// that fill nine tenths of the chip: 256 : 128, K = 3072, 512 x 768, 256 trials (6 rounds) 590 : 661 us, 81 trials (1.9 rounds)
-// 191 : 195, 80 trials 187 : 186, 90 trials (2.1 rounds, a third empty) 264 : 243, 64 trials (1.5) 177 : 145; 256^2, 512 trials 250 : 284; K = 4096,
-// 1024^2, 32 trials 248 : 266, 256^2, 256 trials (1 round) 186 : 177; K = 8192, 256 x 512, 256 trials 491 : 575.  Shorter K gains
-// less and less surely: K = 2048, 512 x 768, 256 trials 423 : 466 but 512^2, 128 trials 149 : 146; K = 1536, 1024^2, 64 trials 211 : 213; K = 1024,
-// 1024^2, 128 trials 347 : 314.  Shapes that are no multiple of 256 lose where the larger tiles pad more (384^2 x 4096, 128 trials
-// 260 : 214) and would gain where they do not (1000^2 x 3072, 64 trials 389 : 450); they stay with the plan's shape.
-constexpr uint32_t kPropLongK = 3072;
+// that fill nine tenths of the chip, on shapes that they pad no more.  128 : 256, shapes of 256 to 1024 a side, in the mean of
+// 9 to 12 each, whole tiles (250 to 1010 a side, ragged ones): K = 1024 0.94 .. 0.98; K = 1536 and 2048 two rounds 1.03 (1.01, the
+// least 0.96), three rounds 1.05 (1.04, 0.99), six 1.07 and 1.11 (1.05 and 1.09); K = 2560 two rounds 1.14, six 1.18; K = 3072 1.12
+// (1.11) and 1.17 (1.16).  512 x 768 x 3072, 256 trials (6 rounds) 535 us; 90 trials (2.1 rounds, a third empty) 264 : 243 the
+// other way, 64 trials (1.5) 177 : 145, and 384^2 x 4096, which the larger tiles pad more, 260 : 214.  All of
+// K a multiple of 128: an odd number of k-tiles runs without the early loads, its line is that of before, K >= 3072 and
+// whole tiles.
+constexpr uint32_t kPropLongK = 1536, kPropLongestK = 2560, kPropOddK = 3072;
 int pick_prop(const fi_plan* p, uint32_t n_trials) {
   const fi_plan_desc& d = p->d;
-  if (!p->auto_cfg || d.K < kPropLongK || d.M % 256 != 0 || d.N % 256 != 0) return p->prop_cfg;
-  const uint64_t items = (uint64_t)(d.M / 256) * (d.N / 256) * n_trials, cus = (uint64_t)p->n_cus;
+  const uint32_t tm = (d.M + 255) / 256, tn = (d.N + 255) / 256;
+  if (!p->auto_cfg || d.K < kPropLongK || (d.M + 127) / 128 != 2 * tm || (d.N + 127) / 128 != 2 * tn) return p->prop_cfg;
+  const uint64_t items = (uint64_t)tm * tn * n_trials, cus = (uint64_t)p->n_cus;
   const uint64_t rounds = (items + cus - 1) / cus;
-  return rounds >= 2 && 10 * items >= 9 * rounds * cus ? fi::kMultiOneTrial[0] : p->prop_cfg;
+  if (d.K % 128 != 0 && (d.K < kPropOddK || d.M % 256 != 0 || d.N % 256 != 0)) return p->prop_cfg;
+  return rounds >= (d.K >= kPropLongestK ? 2u : 3u) && 10 * items >= 9 * rounds * cus ? fi::kMultiOneTrial[0] : p->prop_cfg;
 }
 
 // Items of four trials, both parts of the batch in one launch, in the place of the 64 x 64 shape's eight trials and two

@@ -137,6 +137,30 @@ def test_next_layer_batches_either_side_of_the_lines_between_the_kernels(M, N, K
     assert (got[0]["n_flagged"][2::4] == N).all()
 
 
+# Two or three rounds of 256 x 256 tiles on 256 CUs, either side of the lines in K, trials and padding; ragged tiles, which
+# pad no more than the 128 x 128 shape's, and an odd number of k-tiles
+@pytest.mark.parametrize("M,N,K,n", [(256, 256, 1536, 768), (256, 256, 1536, 690), (256, 256, 1408, 768), (250, 248, 2560, 512),
+                                     (250, 248, 2560, 460), (500, 760, 1536, 128), (250, 390, 2560, 256), (256, 256, 1600, 768)])
+def test_next_layer_batches_either_side_of_the_lines_between_the_tile_shapes(M, N, K, n):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    a, b = torch.randn(M, K, generator=g, device="cuda").bfloat16(), torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    stack = a.expand(n, M, K).clone()
+    t = torch.arange(0, n, 3, device="cuda")
+    stack[t, t * 7 % M, t * 13 % K] *= 3
+    stack[t[::5], t[::5] * 5 % M, 0] = float("inf")
+    got = []
+    for cfg in (-1, 0, 1):
+        plan = fi.Plan(fi.plan_desc(M, N, K, 32, fi.BF16), a, b)
+        plan.tune(cfg)
+        d_r = fi.empty_results(n)
+        plan.fi_gemm_propagate_batch(stack, M * K, n, wl.CORRECT_RECOMPUTE, d_r)
+        got.append(fi.results_to_host(d_r))
+        plan.destroy()
+    assert got[0].tobytes() == got[1].tobytes() == got[2].tobytes()
+    assert (got[0]["n_bitdiff"][::3] > 0).all() and not got[0]["n_bitdiff"][1::3].any()
+
+
 # Campaigns and next layers of the small kernels on dirty records: cleared inside the kernel on a plan's first stream and up to
 # 512 trials, by a launch in front on a second stream, beyond, without allocations and under capture.
 @pytest.mark.parametrize("n", [1, 3, 70, 512, 513])
