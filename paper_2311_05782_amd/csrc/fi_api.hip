@@ -1132,7 +1132,7 @@ fi_status fi_plan_describe(const fi_plan* plan, char* h_buf, uint64_t n) {
         const uint64_t each = (uint64_t)((plan->d.M + m.bm - 1) / m.bm) * ((plan->d.N + m.bn - 1) / m.bn) * ((plan->d.K + 63) / 64);
         const uint64_t most = kFourWork * (uint64_t)m.wgs * (uint64_t)plan->n_cus / each * (uint64_t)m.r;
         const MultiCfg f = fi::kMultiFour;
-        snprintf(four, sizeof(four), "; at most %llu trials: the same with R=%d, x%d per CU, operand faults in the same launch",
+        snprintf(four, sizeof(four), "; at most %llu trials: gemm_fi_four_kernel<R=%d, x%d per CU, operand faults in the same launch>",
                  (unsigned long long)most, f.r, f.wgs);
       }
       snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, R=%d, %dx%d, %d threads, persistent x%d per CU> (a second, "

@@ -124,9 +124,13 @@ struct WorkList {
 // VAR_BOTH: both parts of a campaign's batch, one behind the other in one work list.
 enum { VAR_PLAIN = 0, VAR_OPERAND = 1, VAR_PROPAGATE = 2, VAR_BOTH = 3 };
 
+// The four-trial instances go by a name of their own (see gemm_inst.hip).
+#ifndef FI_MULTI_KERNEL
+#define FI_MULTI_KERNEL gemm_fi_multi_kernel
+#endif
 
 template <int DT, int R, int BM, int BN, int WM, int WN, int VAR>
-__global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) gemm_fi_multi_kernel(const GemmArgs p) {
+__global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) FI_MULTI_KERNEL(const GemmArgs p) {
   constexpr bool BOTH = VAR == VAR_BOTH, OPS = VAR == VAR_OPERAND || BOTH;
   constexpr int CLOCKS = BOTH ? 0 : 4 * VAR;              // where this launch's counters go
   // PROP: the next layer of a two-layer workload.  Work item = (output tile, trial); trial t

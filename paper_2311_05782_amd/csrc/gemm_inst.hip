@@ -1,12 +1,17 @@
 // One translation unit per (kernel family, operand format, tile configuration): compiled with
-//   -DFI_INST_FAMILY=0|1   0: gemm_fi_kernel (one trial per work item), 1: gemm_fi_multi_kernel
+//   -DFI_INST_FAMILY=0|1   0: gemm_fi_kernel (one trial per work item), 1: gemm_fi_multi_kernel, gemm_fi_four_kernel
 //   -DFI_INST_DT=0|1       FI_FP16 / FI_BF16
-//   -DFI_INST_CFG=0..2     index into kCfg / kMulti
+//   -DFI_INST_CFG=0..6     index into kCfg / kMulti; 6 (kMultiFourInst): kMultiFour
 // and exporting the launcher tile_cfg.hpp declares for that triple.
 #include <hip/hip_runtime.h>
 
 #include "tile_cfg.hpp"
 #include "gemm_fi.hpp"
+#if FI_INST_FAMILY == 1 && FI_INST_CFG == 6
+// kMultiFour takes accumulator and operand faults in one launch, at three workgroups per CU: a name that tells its
+// launches from the two of the other configurations in a profile.
+#define FI_MULTI_KERNEL gemm_fi_four_kernel
+#endif
 #include "gemm_fi_multi.hpp"
 
 #define FI_CAT3(a, b, c, d) a##b##c##d
@@ -40,7 +45,7 @@ hipError_t FI_NAME(launch_single_d, FI_INST_DT, FI_INST_CFG)(int mode, const Gem
 static_assert(kMultiFourInst == 6, "the instance of kMultiFour");
 hipError_t FI_NAME(launch_multi_d, FI_INST_DT, 6)(const GemmArgs& a, int n_blocks, hipStream_t s) {
   constexpr MultiCfg c = kMultiFour;
-  hipLaunchKernelGGL((gemm_fi_multi_kernel<FI_INST_DT, c.r, c.bm, c.bn, c.wm, c.wn, VAR_BOTH>), dim3(n_blocks),
+  hipLaunchKernelGGL((gemm_fi_four_kernel<FI_INST_DT, c.r, c.bm, c.bn, c.wm, c.wn, VAR_BOTH>), dim3(n_blocks),
                      dim3(c.wm * c.wn * 64), 0, s, a);
   return hipGetLastError();
 }
