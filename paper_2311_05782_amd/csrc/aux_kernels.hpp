@@ -155,7 +155,7 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
       __hip_atomic_store(n_flagged + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_s_waitcnt(0x0F70);                   // vmcnt(0)
     __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(cleared, epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) __hip_atomic_fetch_max(cleared, epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   }
   bool waited = cleared == nullptr;
   auto wait_cleared = [&]() {                             // by whole waves
@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
     do {
       seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(cleared, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
       __builtin_amdgcn_s_sleep(1);
-    } while (seen != epoch);
+    } while (seen < epoch);
     asm volatile("" ::: "memory");                        // nothing is read that another wave has written
     waited = true;
   };

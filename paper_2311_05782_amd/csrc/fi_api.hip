@@ -758,12 +758,16 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
   return FI_OK;
 }
 
+// One handle for the streams of all host threads: what calls on it have in flight need not follow each other, so nothing
+// but what a multi-trial batch cannot do without is kept by it.
+bool shared_handle(hipStream_t s) { return s == hipStreamPerThread; }
+
 // The small kernels clear the records themselves, and the detector its counters, through a word of the plan: on the first stream that a plan's such
 // batch comes on, whose calls follow each other, outside capture (a graph may be replayed beside them, and with the same epoch
 // each time), and up to kClearTrials, which one workgroup clears in half a microsecond.  Else a launch in front does.
 constexpr uint32_t kClearTrials = 512;
 bool clear_in_kernel(fi_plan* p, uint32_t n_trials, hipStream_t s, GemmArgs* a) {
-  if (n_trials > kClearTrials) return false;
+  if (n_trials > kClearTrials || shared_handle(s) || p->epoch == 0xFFFFFFFFu) return false;
   if (p->epoch != 0 && p->clear_stream != s) return false;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
@@ -771,7 +775,7 @@ bool clear_in_kernel(fi_plan* p, uint32_t n_trials, hipStream_t s, GemmArgs* a) 
     return false;
   }
   if (capture != hipStreamCaptureStatusNone) return false;
-  if (++p->epoch == 0) ++p->epoch;
+  ++p->epoch;
   p->clear_stream = s;
   a->cleared = reinterpret_cast<uint32_t*>(p->scratch + 8);
   a->epoch = p->epoch;
@@ -1219,7 +1223,7 @@ fi_status fi_gemm_inject_batch_affected(fi_plan* plan, const fi_fault* d_faults,
   // Not under capture: a graph may be replayed beside calls on this stream, and outlive the buffer.
   uint32_t* parts = nullptr;
   for (const BatchScratch& b : plan->batch) {
-    if (rows.x_slots < kPartSlots || b.stream != s || b.parts_cap < (size_t)rows.x_slots * n_trials * fi::kPartWords) continue;
+    if (rows.x_slots < kPartSlots || shared_handle(s) || b.stream != s || b.parts_cap < (size_t)rows.x_slots * n_trials * fi::kPartWords) continue;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
     else if (capture == hipStreamCaptureStatusNone) parts = b.words + scratch_words(b.cap);

@@ -260,7 +260,7 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
   // part of the time: 24 product-term trials on 300 x 203 x 176, with classes and histogram, 16.3 -> 14.0 us).  The first
   // workgroup to be dispatched waits for nobody, so every wait for it ends.  A wave that owns a fault looks at the word now
   // and needs it behind its k-loop, the others (thousands, and one word) only when they have something to write.
-  [[maybe_unused]] uint32_t seen = 0;
+  [[maybe_unused]] uint32_t seen = 0;                     // not looked at
   const bool clearing = !SUMS && p.cleared != nullptr;    // uniform in the launch
   if (clearing) {
     if (blockIdx.x == 0) {
@@ -269,14 +269,13 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
         __hip_atomic_store(words + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0)
       __syncthreads();
-      if (threadIdx.x == 0) __hip_atomic_store(p.cleared, p.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      if (threadIdx.x == 0) __hip_atomic_fetch_max(p.cleared, p.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
-    seen = ~p.epoch;                                      // not looked at
   }
   // In front of every write into a record.
   auto wait_cleared = [&]() __attribute__((always_inline)) {
     if (!clearing) return;
-    while ((uint32_t)__builtin_amdgcn_readfirstlane((int)seen) != p.epoch) {
+    while ((uint32_t)__builtin_amdgcn_readfirstlane((int)seen) < p.epoch) {
       seen = __hip_atomic_load(p.cleared, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __builtin_amdgcn_s_sleep(1);
     }

@@ -214,3 +214,40 @@ def test_small_batches_write_whole_records(n):
         check(a, b, ("replay", rep))
     one.destroy()
     plan.destroy()
+
+
+# The handle of the streams of all host threads (hipStreamPerThread): calls on it, one after the other on the host, may run
+# at the same time, and so share nothing that the plan keeps for a stream.
+def test_one_handle_for_the_streams_of_all_threads():
+    import threading
+    import torch
+    PER_THREAD = 2
+    M, N, K, fmt, n, reps = 1100, 130, 96, orc.FP16, 24, 40
+    Aw, Bw = wl.gaussian(M, N, K, fmt, seed=9)
+    plan = gu.make_plan(Aw, Bw, 32, fmt)
+    faults = [fi.fi_sample_faults(t + 1, 0, n, plan.desc, kind, 1) for t, kind in enumerate((fi.KIND_ALL_ACC, fi.KIND_ALL_B))]
+    want = [gu.gpu_campaign(plan, f, wl.CORRECT_ZERO).tobytes() for f in faults]
+    plan.destroy()
+    plan = gu.make_plan(Aw, Bw, 32, fmt)                   # its first stream is the one below
+    plan.reserve(n, PER_THREAD)
+    d_f = [fi.to_device(f) for f in faults]
+    out = [[fi.empty_results(n).fill_(0xFF) for _ in range(2 * reps)] for _ in range(2)]
+    torch.cuda.synchronize()
+    lock = threading.Lock()
+
+    def calls(t):
+        torch.cuda.set_device(0)
+        for rep in range(reps):
+            with lock:
+                plan.fi_gemm_inject_batch(d_f[t], n, wl.CORRECT_ZERO, out[t][2 * rep], stream=PER_THREAD)
+                plan.fi_gemm_inject_batch_affected(d_f[t], n, wl.CORRECT_ZERO, out[t][2 * rep + 1], stream=PER_THREAD)
+    threads = [threading.Thread(target=calls, args=(t,)) for t in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for t in range(2):
+        for i, r in enumerate(out[t]):
+            assert fi.results_to_host(r).tobytes() == want[t], (t, i)
+    plan.destroy()
