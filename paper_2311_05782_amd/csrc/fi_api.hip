@@ -546,8 +546,11 @@ fi_status read_back(const uint32_t* d_words, uint32_t* out, hipStream_t s) {
   return e == hipSuccess ? FI_OK : fail(FI_DEVICE, "plan kernels failed: %s", hipGetErrorString(e));
 }
 
-void free_plan_buffers(fi_plan* p) {
-  if (p->memory) pool_give(p->device, p->memory, p->memory_bytes);
+// idle: the plan's device has been waited for.  Where that failed (a thread captures in the global mode, say) the memory
+// serves no other plan.
+void free_plan_buffers(fi_plan* p, bool idle) {
+  if (p->memory && idle) pool_give(p->device, p->memory, p->memory_bytes);
+  else if (p->memory) (void)hipFree(p->memory);
   p->memory = nullptr;
   for (BatchScratch& b : p->batch)
     if (b.own) (void)hipFree(b.words);
@@ -994,14 +997,13 @@ fi_status fi_plan_create(const fi_plan_desc* desc, const void* d_A, const void* 
     p->n_cus = 8;
   st = build_plan(p, d_A, d_B, as_stream(stream));
   if (st != FI_OK) {
-    (void)hipStreamSynchronize(as_stream(stream));
-    free_plan_buffers(p);
+    free_plan_buffers(p, hipStreamSynchronize(as_stream(stream)) == hipSuccess);
     delete p;
     return st;
   }
   st = resolve_static_scratch(p->device);
   if (st != FI_OK) {
-    free_plan_buffers(p);
+    free_plan_buffers(p, true);                           // its creation has read back from the stream
     delete p;
     return st;
   }
@@ -1020,8 +1022,12 @@ fi_status fi_plan_destroy(fi_plan* plan) {
     std::lock_guard<std::mutex> lock(g_live_mu);
     g_live.erase(plan);
   }
-  (void)hipDeviceSynchronize();   // work that still reads the plan's buffers
-  free_plan_buffers(plan);
+  // work that still reads the plan's buffers, on the plan's device, which need not be the current one
+  int current = plan->device;
+  (void)hipGetDevice(&current);
+  if (current != plan->device) (void)hipSetDevice(plan->device);
+  free_plan_buffers(plan, hipDeviceSynchronize() == hipSuccess);
+  if (current != plan->device) (void)hipSetDevice(current);
   delete plan;
   return FI_OK;
 }

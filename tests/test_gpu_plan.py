@@ -110,3 +110,28 @@ def test_memory_of_destroyed_plans_is_bounded_and_given_back():
         _make(64, 64, 16, seed=m).destroy()
     torch.cuda.empty_cache()
     assert before - torch.cuda.mem_get_info()[0] <= 48 * MB
+
+
+# A plan of another device than the current one: destroyed behind work that still reads it, its memory at once a new plan's.
+@pytest.mark.parametrize("rep", range(3))
+def test_plans_of_another_device_than_the_current_one(rep):
+    import torch
+    if torch.cuda.device_count() < 2:
+        pytest.skip("one GPU")
+    with torch.cuda.device(1):
+        other = _make(512, 1500, 208, seed=rep, scale=1e15)
+        plan = _make(512, 1500, 208, seed=7)
+        faults = fi.fi_sample_faults(9, 0, 2000, plan.desc, fi.KIND_MIX_ACC_A, 1)
+        d_f, d_r, d_s = fi.to_device(faults), fi.empty_results(2000), fi.empty_results(2000)
+        plan.fi_gemm_inject_batch(d_f, 2000, fi.CORRECT_ZERO, d_r)
+        torch.cuda.synchronize()
+        want = fi.results_to_host(d_r).tobytes()
+        plan.fi_gemm_inject_batch(d_f, 2000, fi.CORRECT_ZERO, d_s)
+    with torch.cuda.device(0):
+        plan.destroy()
+        assert torch.cuda.current_device() == 0
+    with torch.cuda.device(1):
+        _make(512, 1500, 208, seed=rep, scale=1e15).destroy()
+        torch.cuda.synchronize()
+        assert fi.results_to_host(d_s).tobytes() == want
+        other.destroy()
