@@ -180,7 +180,9 @@ fi_status fi_plan_tune(fi_plan* plan, int32_t tile_config, int32_t trial_group, 
  * fi_gemm_inject_batch with n_trials <= max_trials on that stream neither allocates nor
  * synchronises (a caller about to capture the calls into a HIP graph wants this), and holds room for what the workgroups
  * of fi_gemm_inject_batch_affected count (32 bytes per trial and 128 rows or columns, some 4 MB at most up to 100000
- * trials), which that call does without where there is none, a little slower, and under capture.
+ * trials), which that call does without where there is none, a little slower, and under capture.  The trial-order scratch
+ * itself is replaced only where max_trials is larger than any batch or reservation before on that stream: a graph captured
+ * with it may be replayed until then.
  * Errors: INVALID_ARG (max_trials == 0), OOM, STATE (more than 64 streams). */
 fi_status fi_plan_reserve(fi_plan* plan, uint32_t max_trials, void* stream);
 

@@ -63,7 +63,11 @@ struct BatchScratch {
   uint32_t* words = nullptr;  // [scratch_words(cap)], see TrialScratch
   uint32_t cap = 0;
   bool own = false;           // an allocation of its own, else part of the plan's
-  size_t parts_cap = 0;       // words behind scratch_words(cap) for the affected-only campaign: only fi_plan_reserve makes them
+  // For the affected-only campaign, in words; only fi_plan_reserve makes them: behind scratch_words(cap) in the same allocation
+  // where that is made with them, else an allocation of their own, as a graph may hold the addresses of the words.
+  uint32_t* parts = nullptr;
+  size_t parts_cap = 0;
+  bool parts_own = false;
 };
 
 struct fi_plan {
@@ -552,8 +556,10 @@ void free_plan_buffers(fi_plan* p, bool idle) {
   if (p->memory && idle) pool_give(p->device, p->memory, p->memory_bytes);
   else if (p->memory) (void)hipFree(p->memory);
   p->memory = nullptr;
-  for (BatchScratch& b : p->batch)
+  for (BatchScratch& b : p->batch) {
     if (b.own) (void)hipFree(b.words);
+    if (b.parts_own) (void)hipFree(b.parts);
+  }
   p->batch.clear();
 }
 
@@ -578,12 +584,26 @@ size_t parts_words(const fi_plan_desc& d, uint32_t n_trials) {
   return (chunks * tiles < bound ? chunks * tiles : bound) * (n_trials < fi::kRowsChunk ? n_trials : fi::kRowsChunk) * fi::kPartWords;
 }
 
+// What only makes a call faster is allocated without a word to captures of other threads, which a plain allocation would
+// break, and not at all where `s` itself is capturing.
+struct BesideCaptures {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  BesideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~BesideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // The batch scratch of `stream`, holding at least n trials.  Allocates on the first batch of a
 // stream and when a batch is larger than any before on it (the replaced buffers are freed,
-// which waits for device work that may still read them); not for up to kFirstTrials trials on the plan's
-// first stream.  Batches of the small kernels do not use it but size it all the same: a tile
+// which waits for device work that may still read them), and replaces them then alone; not for up to kFirstTrials trials on the
+// plan's first stream.  Batches of the small kernels do not use it but size it all the same: a tile
 // configuration chosen later sends the same batch to the multi-trial kernel, which must not allocate then.
-// want_parts: with the affected-only campaign's parts behind it, if there is memory for them.
+// want_parts: with the affected-only campaign's parts, if there is memory for them.
 fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch** out, bool want_parts = false) {
   BatchScratch* b = nullptr;
   for (BatchScratch& x : p->batch)
@@ -596,21 +616,42 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
     if (p->batch.size() == 1) {
       b->words = p->first_scratch;
       b->cap = kFirstTrials;
+      b->parts = b->words + scratch_words(kFirstTrials);
       b->parts_cap = p->first_parts;
     }
   }
   const size_t parts = want_parts ? parts_words(p->d, n) : 0;
-  if (b->cap < n || b->parts_cap < parts) {
-    const uint32_t cap = b->cap > n ? b->cap : n;
-    if (b->own) (void)hipFree(b->words);
-    b->words = nullptr; b->cap = 0; b->own = false; b->parts_cap = 0;
-    if (parts != 0) {
-      if (hipMalloc(&b->words, (scratch_words(cap) + parts) * sizeof(uint32_t)) == hipSuccess) b->parts_cap = parts;
-      else { b->words = nullptr; (void)hipGetLastError(); }
+  if (b->cap < n) {
+    if (b->own) {
+      if (b->parts == b->words + scratch_words(b->cap)) { b->parts = nullptr; b->parts_cap = 0; }   // in that allocation
+      (void)hipFree(b->words);
     }
-    if (!b->words) FI_HIP(hipMalloc(&b->words, scratch_words(cap) * sizeof(uint32_t)));
-    b->cap = cap;
+    b->words = nullptr; b->cap = 0; b->own = false;
+    if (b->parts_cap < parts) {
+      if (hipMalloc(&b->words, (scratch_words(n) + parts) * sizeof(uint32_t)) == hipSuccess) {
+        if (b->parts_own) (void)hipFree(b->parts);
+        b->parts = b->words + scratch_words(n);
+        b->parts_cap = parts;
+        b->parts_own = false;
+      } else {
+        b->words = nullptr;
+        (void)hipGetLastError();
+      }
+    }
+    if (!b->words) FI_HIP(hipMalloc(&b->words, scratch_words(n) * sizeof(uint32_t)));
+    b->cap = n;
     b->own = true;
+  } else if (b->parts_cap < parts && !capturing(stream)) {
+    const BesideCaptures beside;
+    uint32_t* more = nullptr;
+    if (hipMalloc(&more, parts * sizeof(uint32_t)) == hipSuccess) {
+      if (b->parts_own) (void)hipFree(b->parts);
+      b->parts = more;
+      b->parts_cap = parts;
+      b->parts_own = true;
+    } else {
+      (void)hipGetLastError();
+    }
   }
   *out = b;
   return FI_OK;
@@ -772,12 +813,7 @@ constexpr uint32_t kClearTrials = 512;
 bool clear_in_kernel(fi_plan* p, uint32_t n_trials, hipStream_t s, GemmArgs* a) {
   if (n_trials > kClearTrials || shared_handle(s) || p->epoch == 0xFFFFFFFFu) return false;
   if (p->epoch != 0 && p->clear_stream != s) return false;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  if (capture != hipStreamCaptureStatusNone) return false;
+  if (capturing(s)) return false;
   ++p->epoch;
   p->clear_stream = s;
   a->cleared = reinterpret_cast<uint32_t*>(p->scratch + 8);
@@ -1230,9 +1266,7 @@ fi_status fi_gemm_inject_batch_affected(fi_plan* plan, const fi_fault* d_faults,
   uint32_t* parts = nullptr;
   for (const BatchScratch& b : plan->batch) {
     if (rows.x_slots < kPartSlots || shared_handle(s) || b.stream != s || b.parts_cap < (size_t)rows.x_slots * n_trials * fi::kPartWords) continue;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
-    else if (capture == hipStreamCaptureStatusNone) parts = b.words + scratch_words(b.cap);
+    if (!capturing(s)) parts = b.parts;
   }
   if (plan->d.dtype == FI_BF16) return launch_affected<FI_BF16>(a, rows, plan->n_cus, plan->plain_ok, parts, s);
   return launch_affected<FI_FP16>(a, rows, plan->n_cus, plan->plain_ok, parts, s);

@@ -292,3 +292,39 @@ def test_operands_ending_at_the_end_of_their_allocation_short_K():
         s = gu.compare_records(recs, ora, faults, exact_words=True)
         assert not s["mismatches"], s["mismatches"]
         plan.destroy()
+
+
+# A graph holds the scratch of its batch: a later reserve for as many trials or fewer leaves it, and gives the affected-only
+# campaign its room elsewhere (1152 columns: nine tiles of 128, from eight on it has a use for it).
+@pytest.mark.parametrize("n,first", [(100, False), (2000, False), (2000, True)])
+def test_a_reserve_after_the_capture_leaves_what_the_graph_holds(n, first):
+    import torch
+    Aw, Bw = wl.gaussian(130, 1152, 128, orc.BF16, seed=n)
+    plan = gu.make_plan(Aw, Bw, 32, orc.BF16, cfg=6)
+    faults = fi.fi_sample_faults(9, 0, n, plan.desc, fi.KIND_MIX_ACC_A, 1)
+    d_f, d_r, d_a = fi.to_device(faults), fi.empty_results(n), fi.empty_results(n)
+    side = torch.cuda.Stream()
+    if not first:
+        plan.fi_gemm_inject_batch(d_f, n, fi.CORRECT_ZERO, d_r)
+        torch.cuda.synchronize()
+    plan.fi_gemm_inject_batch(d_f, n, fi.CORRECT_ZERO, d_r, stream=side)
+    torch.cuda.synchronize()
+    want = fi.results_to_host(d_r).tobytes()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            plan.fi_gemm_inject_batch(d_f, n, fi.CORRECT_ZERO, d_r, stream=torch.cuda.current_stream().cuda_stream)
+    plan.reserve(n // 2, side)
+    plan.reserve(n, side)
+    for rep in range(3):
+        other = [torch.full((1 << k,), -1, dtype=torch.int32, device="cuda") for k in range(10, 20)]   # of the sizes of such scratch
+        d_r.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert fi.results_to_host(d_r).tobytes() == want, rep
+        assert all(bool((x == -1).all()) for x in other), rep
+        plan.fi_gemm_inject_batch_affected(d_f, n, fi.CORRECT_ZERO, d_a, stream=side)
+        torch.cuda.synchronize()
+        assert fi.results_to_host(d_a).tobytes() == want, rep
+    plan.destroy()

@@ -1,0 +1,59 @@
+"""The host code of plans - scratch, memory of destroyed plans, devices - over a stand-in for the HIP runtime."""
+import pytest
+
+import host_double
+
+
+# A graph holds the addresses of the scratch that its batch was captured with.  512 x 3072: 24 tiles of 128 along the longer
+# side, so the affected-only campaign has a use for parts.
+@pytest.mark.parametrize("stream,n", [("SIDE", 8), ("SIDE", 2000), ("None", 2000)])
+def test_reserve_leaves_the_scratch_of_a_batch_no_smaller(tmp_path, stream, n):
+    host_double.run("""
+    stream, n = %s, %d
+    plan = create(512, 3072, 768)
+    L.fi_plan_tune(plan, 6, -1, None)
+    inject(plan, 1, OTHER if stream else None)          # a plan's first stream has scratch inside the plan
+    assert inject(plan, n, stream) == 0
+    held = scratch_of_last_batch()
+    for m in (n, max(1, n // 4), n - 1):
+        assert reserve(plan, m, stream) == 0
+        assert all(D.double_is_live(w) for w in held), m
+    D.double_capacity(D.double_in_use())                # nor where there is no memory left
+    assert reserve(plan, n, stream) == 0 and inject(plan, n, stream) == 0
+    assert scratch_of_last_batch() == held
+    """ % (stream, n), tmp_path)
+
+
+# What only makes a call faster breaks no capture: a reserve no larger than a batch before allocated nothing before there
+# were parts.
+@pytest.mark.parametrize("captures", ["SIDE", "OTHER"])
+def test_reserve_of_what_is_there_under_capture(tmp_path, captures):
+    host_double.run("""
+    plan = create(512, 3072, 768)
+    inject(plan, 1, OTHER)
+    assert inject(plan, 2000, SIDE) == 0
+    D.double_capture(%s, 1)
+    D.double_forget()
+    assert reserve(plan, 2000, SIDE) == 0 and reserve(plan, 300, SIDE) == 0
+    assert D.double_unsafe_calls() == 0
+    assert affected(plan, 2000, SIDE) == 0
+    assert parts_used() == %s                           # another stream's capture does not keep it from them
+    """ % (captures, captures == "OTHER"), tmp_path)
+
+
+def test_parts_come_with_a_reserve_after_the_batch(tmp_path):
+    host_double.run("""
+    plan = create(512, 3072, 768)
+    inject(plan, 1, OTHER)
+    assert inject(plan, 4096, SIDE) == 0 and affected(plan, 4096, SIDE) == 0
+    assert not parts_used()
+    blocks = D.double_blocks()
+    for n in (8, 4096, 500, 4096):                      # the smaller parts go when the larger ones come
+        assert reserve(plan, n, SIDE) == 0
+        assert D.double_blocks() == blocks + 1
+        D.double_forget()
+        assert affected(plan, n, SIDE) == 0
+        assert parts_used(), n
+    L.fi_plan_destroy(plan)
+    assert D.double_blocks() == 1                       # the plan's own memory, kept for the next
+    """, tmp_path)
