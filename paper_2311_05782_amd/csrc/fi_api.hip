@@ -603,7 +603,8 @@ bool capturing(hipStream_t s) {
 // which waits for device work that may still read them), and replaces them then alone; not for up to kFirstTrials trials on the
 // plan's first stream.  Batches of the small kernels do not use it but size it all the same: a tile
 // configuration chosen later sends the same batch to the multi-trial kernel, which must not allocate then.
-// want_parts: with the affected-only campaign's parts, if there is memory for them.
+// want_parts: with the affected-only campaign's parts, if there is memory for them; once there they stay, also where a
+// larger batch replaces the scratch.
 fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch** out, bool want_parts = false) {
   BatchScratch* b = nullptr;
   for (BatchScratch& x : p->batch)
@@ -620,10 +621,13 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
       b->parts_cap = p->first_parts;
     }
   }
-  const size_t parts = want_parts ? parts_words(p->d, n) : 0;
+  size_t parts = want_parts ? parts_words(p->d, n) : 0;
   if (b->cap < n) {
     if (b->own) {
-      if (b->parts == b->words + scratch_words(b->cap)) { b->parts = nullptr; b->parts_cap = 0; }   // in that allocation
+      if (b->parts == b->words + scratch_words(b->cap)) {   // in that allocation: what was reserved stays so
+        if (parts < b->parts_cap) parts = b->parts_cap;
+        b->parts = nullptr; b->parts_cap = 0;
+      }
       (void)hipFree(b->words);
     }
     b->words = nullptr; b->cap = 0; b->own = false;

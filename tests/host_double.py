@@ -1,8 +1,10 @@
 """The library over tests/hip_runtime_double.cpp: its host code without a GPU.  In a process of its own, as the stand-in takes
 the place of the HIP runtime there: `run(body)` runs the lines of `body` with the names below in a child."""
+import functools
 import os
 import subprocess
 import sys
+import tempfile
 import textwrap
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -54,10 +56,16 @@ def parts_used():
 """
 
 
-def run(body, tmp_path):
-    double = os.path.join(str(tmp_path), "hip_runtime_double.so")
+@functools.lru_cache(None)
+def _double():
+    folder = tempfile.TemporaryDirectory()
+    path = os.path.join(folder.name, "hip_runtime_double.so")
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-w", "-I", "/opt/rocm/include",
-                    os.path.join(HERE, "hip_runtime_double.cpp"), "-o", double], check=True)
-    code = PRELUDE % dict(root=ROOT, double=double) + textwrap.dedent(body)
+                    os.path.join(HERE, "hip_runtime_double.cpp"), "-o", path], check=True)
+    return folder, path
+
+
+def run(body):
+    code = PRELUDE % dict(root=ROOT, double=_double()[1]) + textwrap.dedent(body)
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert r.returncode == 0, r.stdout

@@ -7,7 +7,7 @@ import host_double
 # A graph holds the addresses of the scratch that its batch was captured with.  512 x 3072: 24 tiles of 128 along the longer
 # side, so the affected-only campaign has a use for parts.
 @pytest.mark.parametrize("stream,n", [("SIDE", 8), ("SIDE", 2000), ("None", 2000)])
-def test_reserve_leaves_the_scratch_of_a_batch_no_smaller(tmp_path, stream, n):
+def test_reserve_leaves_the_scratch_of_a_batch_no_smaller(stream, n):
     host_double.run("""
     stream, n = %s, %d
     plan = create(512, 3072, 768)
@@ -21,13 +21,13 @@ def test_reserve_leaves_the_scratch_of_a_batch_no_smaller(tmp_path, stream, n):
     D.double_capacity(D.double_in_use())                # nor where there is no memory left
     assert reserve(plan, n, stream) == 0 and inject(plan, n, stream) == 0
     assert scratch_of_last_batch() == held
-    """ % (stream, n), tmp_path)
+    """ % (stream, n))
 
 
 # What only makes a call faster breaks no capture: a reserve no larger than a batch before allocated nothing before there
 # were parts.
 @pytest.mark.parametrize("captures", ["SIDE", "OTHER"])
-def test_reserve_of_what_is_there_under_capture(tmp_path, captures):
+def test_reserve_of_what_is_there_under_capture(captures):
     host_double.run("""
     plan = create(512, 3072, 768)
     inject(plan, 1, OTHER)
@@ -38,10 +38,10 @@ def test_reserve_of_what_is_there_under_capture(tmp_path, captures):
     assert D.double_unsafe_calls() == 0
     assert affected(plan, 2000, SIDE) == 0
     assert parts_used() == %s                           # another stream's capture does not keep it from them
-    """ % (captures, captures == "OTHER"), tmp_path)
+    """ % (captures, captures == "OTHER"))
 
 
-def test_parts_come_with_a_reserve_after_the_batch(tmp_path):
+def test_parts_come_with_a_reserve_after_the_batch():
     host_double.run("""
     plan = create(512, 3072, 768)
     inject(plan, 1, OTHER)
@@ -56,4 +56,44 @@ def test_parts_come_with_a_reserve_after_the_batch(tmp_path):
         assert parts_used(), n
     L.fi_plan_destroy(plan)
     assert D.double_blocks() == 1                       # the plan's own memory, kept for the next
-    """, tmp_path)
+    """)
+
+
+# A reservation's room for the affected-only campaign survives a larger plain batch, wherever it lies.
+@pytest.mark.parametrize("first_stream", [True, False])
+@pytest.mark.parametrize("order", ["reserve", "batch, reserve"])
+def test_a_larger_batch_keeps_the_parts(first_stream, order):
+    host_double.run("""
+    plan = create(512, 3072, 768)
+    stream = %s
+    inject(plan, 1, OTHER if stream else None)
+    if %s:
+        assert inject(plan, 1000, stream) == 0
+    assert reserve(plan, 1000, stream) == 0
+    for n in (1500, 3000, 20000):
+        assert inject(plan, n, stream) == 0
+        for m in (1000, 7):
+            D.double_forget()
+            assert affected(plan, m, stream) == 0
+            assert parts_used(), (n, m)
+    assert reserve(plan, 20000, stream) == 0            # and the larger reservation's are there
+    D.double_forget()
+    assert affected(plan, 4096, stream) == 0
+    assert parts_used()
+    L.fi_plan_destroy(plan)
+    assert D.double_blocks() == 1
+    """ % ("None" if first_stream else "SIDE", order != "reserve"))
+
+
+# No room for the parts: the batch has its scratch all the same.
+def test_a_larger_batch_without_memory_for_the_parts():
+    host_double.run("""
+    plan = create(512, 3072, 768)
+    inject(plan, 1, OTHER)
+    assert reserve(plan, 1000, SIDE) == 0
+    D.double_capacity(D.double_in_use())
+    assert inject(plan, 5000, SIDE) == 0
+    assert all(D.double_is_live(w) for w in scratch_of_last_batch())
+    D.double_forget()
+    assert affected(plan, 1000, SIDE) == 0 and not parts_used()
+    """)
