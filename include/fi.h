@@ -139,7 +139,7 @@ typedef struct fi_plan fi_plan;
  * The plan owns its scratch (C*, sums, maxima; a transposed copy of B for
  * b_layout 1) and gives it up in fi_plan_destroy.  The library keeps up to four such blocks, 256 MB on each GPU
  * together, for the plans that follow; blocks that 16 further plans have no use for, and all of them when the GPU is
- * out of memory for a plan, go back to the runtime.
+ * out of memory for a plan or a stream's scratch, go back to the runtime.  A plan may get a block of up to twice its size.
  * Errors: INVALID_ARG (NULLs, zero dims, K % k_block, k_block % 16, gamma < 1,
  * Inf/NaN operand), UNSUPPORTED (dtype, alignment), OOM, DEVICE, STATE. */
 fi_status fi_plan_create(const fi_plan_desc* desc, const void* d_A, const void* d_B,

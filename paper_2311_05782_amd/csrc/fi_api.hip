@@ -467,6 +467,18 @@ void pool_release(std::vector<PoolBlock>& blocks, size_t keep, uint64_t now) {
   blocks.swap(stay);
 }
 
+// An allocation on the current device; where there is no memory for it the pool's blocks are given back.
+hipError_t device_alloc(int device, void** ptr, size_t bytes) {
+  hipError_t e = hipMalloc(ptr, bytes);
+  if (e == hipErrorOutOfMemory && device >= 0 && device < kMaxDevices) {
+    (void)hipGetLastError();
+    std::lock_guard<std::mutex> lock(g_pool_mu);
+    pool_release(g_pool[device], 0, 0);
+    e = hipMalloc(ptr, bytes);
+  }
+  return e;
+}
+
 // A block of at least `bytes` on the current device, not more than twice as large; *got is its size.
 hipError_t pool_take(int device, size_t bytes, void** ptr, size_t* got) {
   if (device >= 0 && device < kMaxDevices) {
@@ -486,14 +498,7 @@ hipError_t pool_take(int device, size_t bytes, void** ptr, size_t* got) {
     pool_release(blocks, kPoolBytes, now);
   }
   *got = bytes;
-  hipError_t e = hipMalloc(ptr, bytes);
-  if (e == hipErrorOutOfMemory && device >= 0 && device < kMaxDevices) {
-    (void)hipGetLastError();
-    std::lock_guard<std::mutex> lock(g_pool_mu);
-    pool_release(g_pool[device], 0, 0);
-    e = hipMalloc(ptr, bytes);
-  }
-  return e;
+  return device_alloc(device, ptr, bytes);
 }
 
 // Back from a plan on `device`; nothing on it reads or writes the block any more.
@@ -621,6 +626,7 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
       b->parts_cap = p->first_parts;
     }
   }
+  auto alloc = [&](uint32_t** words, size_t n_words) { return device_alloc(p->device, reinterpret_cast<void**>(words), n_words * sizeof(uint32_t)); };
   size_t parts = want_parts ? parts_words(p->d, n) : 0;
   if (b->cap < n) {
     if (b->own) {
@@ -632,7 +638,7 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
     }
     b->words = nullptr; b->cap = 0; b->own = false;
     if (b->parts_cap < parts) {
-      if (hipMalloc(&b->words, (scratch_words(n) + parts) * sizeof(uint32_t)) == hipSuccess) {
+      if (alloc(&b->words, scratch_words(n) + parts) == hipSuccess) {
         if (b->parts_own) (void)hipFree(b->parts);
         b->parts = b->words + scratch_words(n);
         b->parts_cap = parts;
@@ -642,13 +648,13 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
         (void)hipGetLastError();
       }
     }
-    if (!b->words) FI_HIP(hipMalloc(&b->words, scratch_words(n) * sizeof(uint32_t)));
+    if (!b->words) FI_HIP(alloc(&b->words, scratch_words(n)));
     b->cap = n;
     b->own = true;
   } else if (b->parts_cap < parts && !capturing(stream)) {
     const BesideCaptures beside;
     uint32_t* more = nullptr;
-    if (hipMalloc(&more, parts * sizeof(uint32_t)) == hipSuccess) {
+    if (alloc(&more, parts) == hipSuccess) {
       if (b->parts_own) (void)hipFree(b->parts);
       b->parts = more;
       b->parts_cap = parts;

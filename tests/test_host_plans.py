@@ -97,3 +97,18 @@ def test_a_larger_batch_without_memory_for_the_parts():
     D.double_forget()
     assert affected(plan, 1000, SIDE) == 0 and not parts_used()
     """)
+
+
+# Memory of destroyed plans that the library keeps is given back where a stream's scratch finds no other.
+@pytest.mark.parametrize("call", ["reserve(plan, 100000, SIDE)", "inject(plan, 100000, SIDE)", "inject(plan, 100000, None)"])
+def test_scratch_takes_the_memory_of_destroyed_plans(call):
+    host_double.run("""
+    plan, other = create(512, 3072, 768), create(2048, 2048, 64)
+    assert L.fi_plan_destroy(other) == 0
+    kept = D.double_in_use()
+    D.double_capacity(kept + 4096)
+    assert %s == 0, L.fi_last_error()
+    assert D.double_in_use() < kept
+    D.double_capacity(D.double_in_use() + 4096)
+    assert inject(plan, 10000000, SIDE) == fi.OOM       # as before where there is none to give back
+    """ % call)
