@@ -140,11 +140,17 @@ typedef struct fi_plan fi_plan;
  * b_layout 1) and gives it up in fi_plan_destroy.  The library keeps up to four such blocks, 256 MB on each GPU
  * together, for the plans that follow; blocks that 16 further plans have no use for, and all of them when the GPU is
  * out of memory for a plan or a stream's scratch, go back to the runtime.  A plan may get a block of up to twice its size.
+ * fi_release_memory gives them back at once.
  * Errors: INVALID_ARG (NULLs, zero dims, K % k_block, k_block % 16, gamma < 1,
  * Inf/NaN operand), UNSUPPORTED (dtype, alignment), OOM, DEVICE, STATE. */
 fi_status fi_plan_create(const fi_plan_desc* desc, const void* d_A, const void* d_B,
                          void* stream, fi_plan** out);
 fi_status fi_plan_destroy(fi_plan* plan);
+
+/* Gives back what the library keeps beyond its live plans, on all GPUs: the memory of destroyed plans and the pinned
+ * words that fi_plan_create reads back into, while no plan is being created.  For a program that needs the memory itself, and in front of
+ * hipDeviceReset.  Frees, and so belongs outside stream capture.  Errors: DEVICE. */
+fi_status fi_release_memory(void);
 
 /* Device pointers to plan-owned arrays, valid until fi_plan_destroy:
  * which 0: C* [M][N] float, 1: sum_k|a_ik b_kj| [M][N] float,

@@ -453,7 +453,8 @@ std::mutex g_pool_mu;
 std::vector<PoolBlock> g_pool[kMaxDevices];
 uint64_t g_pool_plans[kMaxDevices] = {};
 
-void pool_release(std::vector<PoolBlock>& blocks, size_t keep, uint64_t now) {
+hipError_t pool_release(std::vector<PoolBlock>& blocks, size_t keep, uint64_t now) {
+  hipError_t failed = hipSuccess;
   size_t kept = 0;
   std::vector<PoolBlock> stay;
   for (size_t i = blocks.size(); i-- > 0;) {              // youngest first
@@ -461,10 +462,12 @@ void pool_release(std::vector<PoolBlock>& blocks, size_t keep, uint64_t now) {
       kept += blocks[i].bytes;
       stay.insert(stay.begin(), blocks[i]);
     } else {
-      (void)hipFree(blocks[i].ptr);
+      const hipError_t e = hipFree(blocks[i].ptr);
+      if (e != hipSuccess) failed = e;
     }
   }
   blocks.swap(stay);
+  return failed;
 }
 
 // An allocation on the current device; where there is no memory for it the pool's blocks are given back.
@@ -513,7 +516,7 @@ void pool_give(int device, void* ptr, size_t bytes) {
 }
 
 // Pinned host words into which a plan's creation reads back eight of the device's, in slots of one cache line, made once
-// and held until the process ends (4 KB): into pageable memory the copy is staged, some 8 us.  (A kernel that
+// and held (4 KB): into pageable memory the copy is staged, some 8 us.  (A kernel that
 // writes them and a mark to wait for took 3 us less here and 20 us more in the next synchronisation.)
 constexpr int kHostSlots = 64, kHostSlotWords = 16;
 std::mutex g_host_mu;
@@ -539,6 +542,13 @@ int host_slot_take() {
 void host_slot_give(int slot) {
   std::lock_guard<std::mutex> lock(g_host_mu);
   g_host_used &= ~(1ull << slot);
+}
+hipError_t host_slots_release() {
+  std::lock_guard<std::mutex> lock(g_host_mu);
+  if (!g_host_words || g_host_used != 0) return hipSuccess;
+  uint32_t* const words = g_host_words;
+  g_host_words = nullptr;
+  return hipHostFree(words);
 }
 
 // Eight words of the device, once everything on the stream has run.
@@ -1075,6 +1085,21 @@ fi_status fi_plan_destroy(fi_plan* plan) {
   free_plan_buffers(plan, hipDeviceSynchronize() == hipSuccess);
   if (current != plan->device) (void)hipSetDevice(current);
   delete plan;
+  return FI_OK;
+}
+
+fi_status fi_release_memory(void) {
+  hipError_t failed = hipSuccess;
+  {
+    std::lock_guard<std::mutex> lock(g_pool_mu);
+    for (std::vector<PoolBlock>& blocks : g_pool) {
+      const hipError_t e = pool_release(blocks, 0, 0);
+      if (e != hipSuccess) failed = e;
+    }
+  }
+  const hipError_t e = host_slots_release();
+  if (e != hipSuccess) failed = e;
+  FI_HIP(failed);
   return FI_OK;
 }
 

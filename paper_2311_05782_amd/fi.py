@@ -29,7 +29,7 @@ BUF_C_STAR, BUF_S_ABS, BUF_KRA, BUF_CB = 0, 1, 2, 3
 EXPORTS = ["fi_plan_create", "fi_plan_destroy", "fi_plan_buffer", "fi_plan_tune", "fi_plan_describe",
            "fi_plan_set_product_check", "fi_plan_reserve", "fi_plan_set_clock_sink", "fi_probe_mfma_loop", "fi_deviation_histogram",
            "fi_gemm_inject_batch", "fi_gemm_inject_batch_act", "fi_gemm_inject_batch_noalloc", "fi_gemm_inject_batch_affected", "fi_detect_correct", "fi_classify", "fi_sample_faults",
-           "fi_activation_round", "fi_gemm_propagate_batch", "fi_last_error", "fi_build_info"]
+           "fi_activation_round", "fi_gemm_propagate_batch", "fi_release_memory", "fi_last_error", "fi_build_info"]
 
 FAULT_DTYPE = np.dtype([("kind", "<u4"), ("row", "<u4"), ("col", "<u4"), ("kblock", "<u4"),
                         ("xor_mask", "<u4")])
@@ -88,6 +88,7 @@ def lib():
                               "python paper_2311_05782_amd/build.py" % (LIB_PATH, built[:12], now[:12]))
     L.fi_plan_create.argtypes = [C.POINTER(PlanDesc), vp, vp, vp, C.POINTER(vp)]
     L.fi_plan_destroy.argtypes = [vp]
+    L.fi_release_memory.argtypes = []
     L.fi_plan_buffer.argtypes = [vp, C.c_uint32, C.POINTER(vp)]
     L.fi_plan_tune.argtypes = [vp, C.c_int32, C.c_int32, vp]
     L.fi_plan_describe.argtypes = [vp, C.c_char_p, C.c_uint64]
@@ -151,6 +152,10 @@ def fi_sample_faults(seed, first_trial, n_trials, desc, kind_mode, nbits):
 def fi_probe_mfma_loop(dtype, random_data, iters, n_workgroups, d_sink, d_clocks=None, stream=None):
     _check(lib().fi_probe_mfma_loop(dtype, random_data, iters, n_workgroups, _dptr(d_sink), _dptr(d_clocks),
                                     _stream(stream)))
+
+
+def fi_release_memory():
+    _check(lib().fi_release_memory())
 
 
 def fi_activation_round(dtype, d_c, n, d_h, stream=None):

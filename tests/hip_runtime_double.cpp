@@ -22,6 +22,7 @@ struct Launch { std::string name; uintptr_t stream; std::vector<uint64_t> words;
 std::vector<Launch> launches;
 int device = 0, n_devices = 2, waited[8] = {};
 size_t in_use = 0, capacity = SIZE_MAX;
+int host_blocks = 0;
 long unsafe_calls = 0;                     // allocations, frees and waits that would break a capture
 bool set_device_fails = false, get_device_fails = false, wait_fails = false;
 std::vector<uintptr_t> capturing;          // streams, in the global mode
@@ -37,6 +38,7 @@ extern "C" {
 void double_capacity(uint64_t bytes) { capacity = bytes; }
 uint64_t double_in_use() { return in_use; }
 uint64_t double_blocks() { return live.size(); }
+int double_host_blocks() { return host_blocks; }
 uint64_t double_freed() { return freed.size(); }
 void double_forget() { freed.clear(); launches.clear(); unsafe_calls = 0; memset(waited, 0, sizeof(waited)); }
 int double_is_live(uint64_t ptr) {
@@ -100,8 +102,8 @@ hipError_t hipFree(void* p) {
   free(p);
   return hipSuccess;
 }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { touches(); *p = calloc(1, n); return hipSuccess; }
-hipError_t hipHostFree(void* p) { touches(); free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { touches(); *p = calloc(1, n); ++host_blocks; return hipSuccess; }
+hipError_t hipHostFree(void* p) { touches(); free(p); --host_blocks; return hipSuccess; }
 hipError_t hipMemcpyAsync(void* to, const void* from, size_t n, hipMemcpyKind, hipStream_t) { memcpy(to, from, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { touches(); return hipSuccess; }
 hipError_t hipDeviceSynchronize() { touches(); if (wait_fails) return hipErrorUnknown; ++waited[device]; return hipSuccess; }

@@ -112,6 +112,27 @@ def test_memory_of_destroyed_plans_is_bounded_and_given_back():
     assert before - torch.cuda.mem_get_info()[0] <= 48 * MB
 
 
+def test_memory_of_destroyed_plans_is_given_back_on_demand():
+    import torch
+    plan = _make(300, 700, 64, seed=1)
+    faults = fi.fi_sample_faults(9, 0, 40, plan.desc, fi.KIND_MIX_ACC_A, 1)
+    want = _records(plan, faults)
+    fi.fi_release_memory()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    for m in range(3):
+        _make(2048, 2048 + 1024 * m, 16, seed=m).destroy()             # 34 .. 67 MB
+    torch.cuda.empty_cache()
+    assert before - torch.cuda.mem_get_info()[0] >= 64 << 20           # kept
+    fi.fi_release_memory()
+    assert before - torch.cuda.mem_get_info()[0] <= 8 << 20
+    assert _records(plan, faults) == want                               # the live plan is as it was
+    other = _make(300, 700, 64, seed=1)
+    assert _records(other, faults) == want
+    plan.destroy()
+    other.destroy()
+
+
 # A plan of another device than the current one: destroyed behind work that still reads it, its memory at once a new plan's.
 @pytest.mark.parametrize("rep", range(3))
 def test_plans_of_another_device_than_the_current_one(rep):

@@ -112,3 +112,26 @@ def test_scratch_takes_the_memory_of_destroyed_plans(call):
     D.double_capacity(D.double_in_use() + 4096)
     assert inject(plan, 10000000, SIDE) == fi.OOM       # as before where there is none to give back
     """ % call)
+
+
+# All that the library keeps beyond its plans can be given back, on every GPU, and the next plan starts anew.
+def test_release_memory():
+    host_double.run("""
+    plan = create(300, 700, 64)
+    L.fi_plan_destroy(create(512, 3072, 768))
+    fi_device = C.c_int(1)
+    D.hipSetDevice(fi_device)
+    L.fi_plan_destroy(create(512, 3072, 768))
+    D.hipSetDevice(0)
+    assert D.double_blocks() == 3 and D.double_host_blocks() == 1
+    fi.fi_release_memory()
+    assert D.double_blocks() == 1 and D.double_host_blocks() == 0     # the live plan's
+    assert inject(plan, 40, None) == 0
+    for _ in range(3):
+        L.fi_plan_destroy(create(512, 3072, 768))
+    assert D.double_blocks() == 2
+    L.fi_plan_destroy(plan)
+    fi.fi_release_memory()
+    fi.fi_release_memory()
+    assert D.double_blocks() == 0 and D.double_host_blocks() == 0
+    """)
