@@ -565,8 +565,8 @@ fi_status read_back(const uint32_t* d_words, uint32_t* out, hipStream_t s) {
   return e == hipSuccess ? FI_OK : fail(FI_DEVICE, "plan kernels failed: %s", hipGetErrorString(e));
 }
 
-// idle: the plan's device has been waited for.  Where that failed (a thread captures in the global mode, say) the memory
-// serves no other plan.
+// idle: the plan's device has been waited for.  Where that failed (a thread captures in the global mode, say), or the device
+// could not be selected, the memory serves no other plan.
 void free_plan_buffers(fi_plan* p, bool idle) {
   if (p->memory && idle) pool_give(p->device, p->memory, p->memory_bytes);
   else if (p->memory) (void)hipFree(p->memory);
@@ -1080,10 +1080,12 @@ fi_status fi_plan_destroy(fi_plan* plan) {
   }
   // work that still reads the plan's buffers, on the plan's device, which need not be the current one
   int current = plan->device;
-  (void)hipGetDevice(&current);
-  if (current != plan->device) (void)hipSetDevice(plan->device);
-  free_plan_buffers(plan, hipDeviceSynchronize() == hipSuccess);
-  if (current != plan->device) (void)hipSetDevice(current);
+  bool there = hipGetDevice(&current) == hipSuccess;
+  const bool other = there && current != plan->device;
+  if (other) there = hipSetDevice(plan->device) == hipSuccess;
+  const bool waited = hipDeviceSynchronize() == hipSuccess;
+  free_plan_buffers(plan, there && waited);
+  if (other) (void)hipSetDevice(current);
   delete plan;
   return FI_OK;
 }

@@ -135,3 +135,26 @@ def test_release_memory():
     fi.fi_release_memory()
     assert D.double_blocks() == 0 and D.double_host_blocks() == 0
     """)
+
+
+# A plan's memory serves another plan only once its own device has been waited for; the current device is what it was.
+@pytest.mark.parametrize("failures,kept", [((0, 0, 0), True), ((1, 0, 0), False), ((0, 1, 0), False), ((0, 0, 1), False)])
+@pytest.mark.parametrize("current", [0, 1])
+def test_destroy_waits_for_the_plans_own_device(failures, kept, current):
+    if current == 1 and failures == (1, 0, 0):
+        kept = True                                        # nothing to select
+    host_double.run("""
+    D.hipSetDevice(1)
+    plan = create(512, 3072, 768)
+    assert D.double_blocks() == 1
+    D.hipSetDevice(%d)
+    D.double_forget()
+    D.double_failures(*%r)
+    assert L.fi_plan_destroy(plan) == 0
+    D.double_failures(0, 0, 0)
+    assert D.double_blocks() == %d and D.double_freed() == %d
+    assert D.double_waited(1) == 1 or not %r
+    now = C.c_int(-1)
+    D.hipGetDevice(C.byref(now))
+    assert now.value == %d
+    """ % (current, failures, kept, not kept, kept, current))
