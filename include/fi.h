@@ -185,7 +185,7 @@ fi_status fi_plan_tune(fi_plan* plan, int32_t tile_config, int32_t trial_group, 
 /* Sizes the trial-order scratch `stream` uses for this plan's batches to max_trials, so that
  * fi_gemm_inject_batch with n_trials <= max_trials on that stream neither allocates nor
  * synchronises (a caller about to capture the calls into a HIP graph wants this), and holds room for what the workgroups
- * of fi_gemm_inject_batch_affected count (32 bytes per trial and 128 rows or columns, some 4 MB at most up to 100000
+ * of fi_gemm_inject_batch_affected count (32 bytes per trial and 128 rows or columns, 4.3 MB at most, however many
  * trials), which that call does without where there is none, a little slower, and under capture.  The trial-order scratch
  * itself is replaced only where max_trials is larger than any batch or reservation before on that stream: a graph captured
  * with it may be replayed until then.

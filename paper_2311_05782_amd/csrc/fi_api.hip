@@ -591,8 +591,11 @@ constexpr size_t scratch_words(uint32_t n) { return (kScratchDesc + ((size_t)n +
 // the faults lie along the other, of one to four slots, it costs up to half a microsecond (3072 x 512, 400 trials 15.1 : 15.7).
 constexpr uint32_t kPartSlots = 8;
 // Words of those workgroups' parts, for this number of trials and any smaller one: x_slots <= min(tiles, 2048 / items + 1).
+// It falls below kPartSlots beyond kPartChunks chunks (16384 trials), so that no more are ever used: 4.3 MB.
+constexpr size_t kPartChunks = 2048 / ((kPartSlots - 1) * fi::kRowsSlots);
 size_t parts_words(const fi_plan_desc& d, uint32_t n_trials) {
-  const size_t chunks = ((size_t)n_trials + fi::kRowsChunk - 1) / fi::kRowsChunk;
+  size_t chunks = ((size_t)n_trials + fi::kRowsChunk - 1) / fi::kRowsChunk;
+  if (chunks > kPartChunks) chunks = kPartChunks;
   const size_t tiles = ((size_t)(d.M > d.N ? d.M : d.N) + fi::kRowsX - 1) / fi::kRowsX;
   const size_t bound = 2048 / fi::kRowsSlots + 1 + chunks;   // of chunks * x_slots
   if (tiles < kPartSlots) return 0;

@@ -67,8 +67,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shmem, hip
   *grid = c.grid; *block = c.block; *shmem = c.shmem; *s = c.stream;
   return hipSuccess;
 }
-// The first argument's 64-bit words are kept where it is a structure passed by value; the arguments are told apart by
-// nothing else here, so the test names the kernels that it looks into.
+// What the tests look at among the arguments of a launch is kept, kernel by kernel.
 hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t s) {
   std::lock_guard<std::mutex> lock(mu);
   Launch l{kernels[f], reinterpret_cast<uintptr_t>(s), {}};
@@ -78,6 +77,11 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipSt
       memcpy(&w, args[a], 8);
       l.words.push_back(w);
     }
+  if (l.name.find("affected_element") != std::string::npos) {   // its slots per row or column of tiles
+    int slots;
+    memcpy(&slots, args[2], 4);
+    l.words.push_back((uint64_t)slots);
+  }
   launches.push_back(l);
   return hipSuccess;
 }

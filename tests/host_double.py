@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
 PRELUDE = """
-import ctypes as C, sys
+import ctypes as C, sys, types
 sys.path.insert(0, %(root)r)
 D = C.CDLL(%(double)r, mode=C.RTLD_GLOBAL)          # before the library: its calls to the runtime come here
 for f in ("double_in_use", "double_blocks", "double_freed", "double_launches", "double_launch_word"):
@@ -21,6 +21,7 @@ D.double_unsafe_calls.restype = C.c_int64
 for f, a in (("double_capacity", 1), ("double_is_live", 1), ("double_launch_name", 1), ("double_launch_word", 2)):
     getattr(D, f).argtypes = [C.c_uint64] * a
 D.double_capture.argtypes = [C.c_uint64, C.c_int]
+sys.modules["torch"] = types.SimpleNamespace(_C=None)     # it takes two seconds, and nothing of it is used
 from paper_2311_05782_amd import fi
 L = fi.lib()
 MB, SIDE, OTHER = 1 << 20, 0x5100, 0x5200           # streams are told apart by their handles alone

@@ -158,3 +158,28 @@ def test_destroy_waits_for_the_plans_own_device(failures, kept, current):
     D.hipGetDevice(C.byref(now))
     assert now.value == %d
     """ % (current, failures, kept, not kept, kept, current))
+
+
+# Room for what the largest batch with eight slots per tile row or more counts, 16384 trials, and not for more.
+@pytest.mark.parametrize("M,N", [(512, 3072), (1000, 130), (64, 8192), (4096, 4096), (100000, 16)])
+def test_parts_are_bounded_and_enough(M, N):
+    host_double.run("""
+    plan = create(%d, %d, 16)
+    inject(plan, 1, OTHER)
+    used = []
+    for n in (1, 512, 513, 4000, 8192, 16384, 16385, 1000000):
+        before = D.double_in_use()
+        assert reserve(plan, n, SIDE) == 0
+        used.append((n, D.double_in_use() - before - 24 * n))   # beside the six words of each trial
+        for m in sorted({min(n, 100000), max(1, n // 300), min(n, 5000), min(n, 16384)}):
+            D.double_forget()
+            assert affected(plan, m, SIDE) == 0
+            slots = D.double_launch_word([i for i, s in enumerate(names()) if "affected_element" in s][0], 0)
+            assert parts_used() == (slots >= 8), (n, m, slots)
+            assert slots < 8 or m <= 16384
+        L.fi_plan_destroy(plan)
+        fi.fi_release_memory()
+        plan = create(%d, %d, 16)
+        inject(plan, 1, OTHER)
+    assert max(b for n, b in used) <= 4400000, used
+    """ % (M, N, M, N))
