@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfi_gfx950.so")
-HEADERS = ["gemm_fi.hpp", "gemm_fi_multi.hpp", "gemm_fi_small.hpp", "affected.hpp", "aux_kernels.hpp", "clamped.hpp",
+HEADERS = ["gemm_fi.hpp", "gemm_fi_multi.hpp", "gemm_fi_small.hpp", "affected.hpp", "aux_kernels.hpp", "clamped.hpp", "clear_once.hpp",
            "tile_cfg.hpp"]
 SOURCES = ["fi_api.hip", "gemm_inst.hip"]
 # (family, dtype, cfg): family 0 = one trial per work item, 1 = R trials per work item

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "clear_once.hpp"
 #include "fi.h"
 #include "gemm_fi.hpp"
 
@@ -138,34 +139,26 @@ __global__ void __launch_bounds__(256) detect_correct_kernel(
     float* __restrict__ C, uint32_t batch, uint32_t M, uint32_t N, const float* __restrict__ kra,
     const float* __restrict__ cb, float gamma, int bound_global, float t_global, int policy,
     const float* __restrict__ c_star, uint8_t* __restrict__ flags, uint32_t* __restrict__ n_flagged,
-    const DetectStep step, uint32_t* cleared, uint32_t epoch) {
+    const DetectStep step, uint32_t* clear_word, uint32_t epoch) {
   static_assert(VEC == 4 || (VEC == 1 && !ROW4), "vectors of four or single elements");
   constexpr uint32_t THREADS = 256, WAVES = THREADS / 64, CHUNK = THREADS * VEC * UNROLL;
   // what the waves have flagged, trial by trial: entries 0 .. slots - 1, then what is left at the end
   constexpr uint32_t SLOTS = kDetectSlots<UNROLL>;
   __shared__ uint32_t kept_b[WAVES][SLOTS + 1], kept_n[WAVES][SLOTS + 1], arrived;
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   [[maybe_unused]] uint32_t slots = 0;
   if (threadIdx.x == 0) arrived = 0;
-  // Counters that no launch in front has cleared, as the small campaign kernel's records: the first workgroup to be
-  // dispatched clears them, whoever has flagged something looks whether it has (raw outputs of 3136 x 64 x 576, detector
-  // and hand-over 95.8 -> 94.2 us, two trials of 417 x 842 x 144 21.3 -> 19.0).
-  if (cleared != nullptr && blockIdx.x == 0) {
-    for (uint32_t i = threadIdx.x; i < batch; i += THREADS)
-      __hip_atomic_store(n_flagged + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __builtin_amdgcn_s_waitcnt(0x0F70);                   // vmcnt(0)
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_fetch_max(cleared, epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  // Counters that no launch in front has cleared, as the small campaign kernel's records, see clear_once.hpp (raw outputs of
+  // 3136 x 64 x 576, detector and hand-over 95.8 -> 94.2 us, two trials of 417 x 842 x 144 21.3 -> 19.0).
+  if (clear_word != nullptr && blockIdx.x == 0 && wave == 0 && take_clearing(clear_word, epoch, lane)) {
+    clear_words(n_flagged, batch, lane, 64);
+    clearing_done(clear_word, epoch, lane);
   }
-  bool waited = cleared == nullptr;
+  bool waited = clear_word == nullptr;
   auto wait_cleared = [&]() {                             // by whole waves
     if (waited) return;
-    uint32_t seen;
-    do {
-      seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(cleared, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      __builtin_amdgcn_s_sleep(1);
-    } while (seen < epoch);
-    asm volatile("" ::: "memory");                        // nothing is read that another wave has written
+    uint32_t seen = 0;
+    cleared(n_flagged, batch, clear_word, epoch, seen, lane, 64);
     waited = true;
   };
   const bool together = n_flagged != nullptr && step.together != 0;

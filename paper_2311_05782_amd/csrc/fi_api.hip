@@ -87,7 +87,7 @@ struct fi_plan {
   float* s_abs = nullptr;            // [M][N]
   float* kra = nullptr;              // [pad(M)]
   float* cb = nullptr;               // [pad(N)]
-  float* scratch = nullptr;          // 4 floats + 4 words: maxima, what plan_stats_kernel found, clean flags; GemmArgs::cleared
+  float* scratch = nullptr;          // 4 floats + 4 words: maxima, what plan_stats_kernel found, clean flags; GemmArgs::clear_word
   uint32_t epoch = 0;                // the last value that went into that word, by calls on this stream
   hipStream_t clear_stream = nullptr;
   float t_global = 0.0f;
@@ -476,7 +476,7 @@ hipError_t device_alloc(int device, void** ptr, size_t bytes) {
   if (e == hipErrorOutOfMemory && device >= 0 && device < kMaxDevices) {
     (void)hipGetLastError();
     std::lock_guard<std::mutex> lock(g_pool_mu);
-    pool_release(g_pool[device], 0, 0);
+    (void)pool_release(g_pool[device], 0, 0);
     e = hipMalloc(ptr, bytes);
   }
   return e;
@@ -498,7 +498,7 @@ hipError_t pool_take(int device, size_t bytes, void** ptr, size_t* got) {
       blocks.erase(blocks.begin() + best);
       return hipSuccess;
     }
-    pool_release(blocks, kPoolBytes, now);
+    (void)pool_release(blocks, kPoolBytes, now);
   }
   *got = bytes;
   return device_alloc(device, ptr, bytes);
@@ -512,7 +512,7 @@ void pool_give(int device, void* ptr, size_t bytes) {
   }
   std::lock_guard<std::mutex> lock(g_pool_mu);
   g_pool[device].push_back({ptr, bytes, g_pool_plans[device]});
-  pool_release(g_pool[device], kPoolBytes, g_pool_plans[device]);
+  (void)pool_release(g_pool[device], kPoolBytes, g_pool_plans[device]);
 }
 
 // Pinned host words into which a plan's creation reads back eight of the device's, in slots of one cache line, made once
@@ -694,7 +694,7 @@ constexpr uint32_t kDetectTogether = 1024;
 // The detector / corrector on [batch][M][N] outputs: whole vectors where the outputs (and flags)
 // are aligned for them and a vector spans two rows at most, else element by element.
 hipError_t launch_detect(const fi_plan* p, float* d_c, uint32_t batch, uint32_t policy, uint8_t* d_flags,
-                         uint32_t* d_n_flagged, uint32_t* cleared, uint32_t epoch, hipStream_t s) {
+                         uint32_t* d_n_flagged, uint32_t* clear_word, uint32_t epoch, hipStream_t s) {
   const fi_plan_desc& d = p->d;
   const bool vec = d.N >= 4 && (reinterpret_cast<uintptr_t>(d_c) & 15u) == 0 &&
                    (reinterpret_cast<uintptr_t>(d_flags) & 3u) == 0;
@@ -716,7 +716,7 @@ hipError_t launch_detect(const fi_plan* p, float* d_c, uint32_t batch, uint32_t 
   const int global = d.bound_mode != FI_BOUND_ROWCOL;
 #define FI_DETECT(VEC, ROW4, UNROLL)                                                                               \
   hipLaunchKernelGGL((fi::detect_correct_kernel<VEC, ROW4, UNROLL>), grid, block, 0, s, d_c, batch, d.M, d.N, p->kra, \
-                     p->cb, d.gamma, global, p->t_global, (int)policy, p->c_star, d_flags, d_n_flagged, step, cleared, epoch)
+                     p->cb, d.gamma, global, p->t_global, (int)policy, p->c_star, d_flags, d_n_flagged, step, clear_word, epoch)
   if (!vec) {
     if (deep) FI_DETECT(1, false, 4); else FI_DETECT(1, false, 1);
   } else if (d.N % 4 == 0) {
@@ -829,17 +829,19 @@ fi_status build_plan(fi_plan* p, const void* d_A, const void* d_B, hipStream_t s
 // but what a multi-trial batch cannot do without is kept by it.
 bool shared_handle(hipStream_t s) { return s == hipStreamPerThread; }
 
-// The small kernels clear the records themselves, and the detector its counters, through a word of the plan: on the first stream that a plan's such
-// batch comes on, whose calls follow each other, outside capture (a graph may be replayed beside them, and with the same epoch
-// each time), and up to kClearTrials, which one workgroup clears in half a microsecond.  Else a launch in front does.
+// The small kernels clear the records themselves, and the detector its counters, through a word of the plan (clear_once.hpp): on
+// the first stream that a plan's such batch comes on, whose calls follow each other - for good, as nothing here tells when its last
+// one has run - outside capture (a graph may be replayed beside them, and with the same number each time), and up to
+// kClearTrials, which one workgroup clears in half a microsecond (512 trials on 64 x 64 x 128 by one wave 12.2 us, by four
+// 10.5).  Else a launch in front does.
 constexpr uint32_t kClearTrials = 512;
 bool clear_in_kernel(fi_plan* p, uint32_t n_trials, hipStream_t s, GemmArgs* a) {
-  if (n_trials > kClearTrials || shared_handle(s) || p->epoch == 0xFFFFFFFFu) return false;
+  if (n_trials > kClearTrials || shared_handle(s) || p->epoch >= 0xFFFFFFFEu) return false;
   if (p->epoch != 0 && p->clear_stream != s) return false;
   if (capturing(s)) return false;
-  ++p->epoch;
+  p->epoch += 2;                                          // even, see clear_once.hpp
   p->clear_stream = s;
-  a->cleared = reinterpret_cast<uint32_t*>(p->scratch + 8);
+  a->clear_word = reinterpret_cast<uint32_t*>(p->scratch + 8);
   a->epoch = p->epoch;
   return true;
 }
@@ -1417,7 +1419,7 @@ fi_status fi_detect_correct(fi_plan* plan, float* d_c, uint32_t batch, uint32_t 
                        (size_t)batch, 0u);
     FI_HIP(hipGetLastError());
   }
-  FI_HIP(launch_detect(plan, d_c, batch, policy, d_flags, d_n_flagged, a.cleared, a.epoch, s));
+  FI_HIP(launch_detect(plan, d_c, batch, policy, d_flags, d_n_flagged, a.clear_word, a.epoch, s));
   return FI_OK;
 }
 

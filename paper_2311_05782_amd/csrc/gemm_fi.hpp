@@ -91,10 +91,9 @@ struct GemmArgs {
   // the workgroups of an XCD have taken of its slice of the work list, kQueueStride words per XCD; zero at
   // the start.  The operand-fault launch has a set of its own behind the first.
   uint32_t* queue;
-  // Small kernels, nullable (then the records are clear): workgroup 0 clears them and raises the word `cleared`
-  // to `epoch`, larger than any before; nobody else writes into a record before.  The word only grows, so that every
-  // wait for it ends, whatever else is in flight.
-  uint32_t* cleared;
+  // Small kernels, nullable (then the records are clear): the word through which one of their waves clears the records, and the
+  // number of this launch there (clear_once.hpp).
+  uint32_t* clear_word;
   uint32_t epoch;
   // Measurement aid, nullable: workgroup 0 of the persistent kernel writes the shader-clock
   // counter and the constant-rate (100 MHz) counter when it starts and when it has finished its

@@ -24,6 +24,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "clear_once.hpp"
 #include "fi.h"
 #include "gemm_fi.hpp"
 
@@ -256,30 +257,29 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
   };
   clock(0);
 
-  // ---- records: cleared by workgroup 0 where no launch in front has done it (for a few hundred trials a launch is the larger
-  // part of the time: 24 product-term trials on 300 x 203 x 176, with classes and histogram, 16.3 -> 14.0 us).  The first
-  // workgroup to be dispatched waits for nobody, so every wait for it ends.  A wave that owns a fault looks at the word now
-  // and needs it behind its k-loop, the others (thousands, and one word) only when they have something to write.
+  // ---- records: cleared here where no launch in front has done it (for a few hundred trials a launch is the larger
+  // part of the time: 24 product-term trials on 300 x 203 x 176, with classes and histogram, 16.3 -> 14.0 us), see
+  // clear_once.hpp.  A wave that owns a fault looks at the word now and needs it behind its k-loop, the others (thousands,
+  // and one word) only when they have something to write.
   [[maybe_unused]] uint32_t seen = 0;                     // not looked at
-  const bool clearing = !SUMS && p.cleared != nullptr;    // uniform in the launch
-  if (clearing) {
-    if (blockIdx.x == 0) {
-      uint32_t* const words = reinterpret_cast<uint32_t*>(p.results);
-      for (uint32_t i = threadIdx.x; i < n_trials * (uint32_t)(sizeof(fi_trial_result) / 4); i += 256)
-        __hip_atomic_store(words + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0)
-      __syncthreads();
-      if (threadIdx.x == 0) __hip_atomic_fetch_max(p.cleared, p.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  const bool clearing = !SUMS && p.clear_word != nullptr;    // uniform in the launch
+  uint32_t* const records = reinterpret_cast<uint32_t*>(p.results);
+  const uint32_t record_words = n_trials * (uint32_t)(sizeof(fi_trial_result) / 4);
+  if (clearing && blockIdx.x == 0) {
+    uint32_t* const taken = reinterpret_cast<uint32_t*>(smem);   // nothing is staged yet
+    if (wave == 0) {
+      const bool mine = take_clearing(p.clear_word, p.epoch, lane);
+      if (lane == 0) *taken = mine ? 1u : 0u;
     }
+    __syncthreads();
+    const bool ours = __builtin_amdgcn_readfirstlane((int)*taken) != 0;
+    if (ours) clear_words(records, record_words, threadIdx.x, 256);
+    __syncthreads();
+    if (ours) clearing_done(p.clear_word, p.epoch, threadIdx.x);
   }
   // In front of every write into a record.
   auto wait_cleared = [&]() __attribute__((always_inline)) {
-    if (!clearing) return;
-    while ((uint32_t)__builtin_amdgcn_readfirstlane((int)seen) < p.epoch) {
-      seen = __hip_atomic_load(p.cleared, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_s_sleep(1);
-    }
-    asm volatile("" ::: "memory");                        // nothing is read that another wave has written
+    if (clearing) cleared(records, record_words, p.clear_word, p.epoch, seen, lane, 64);
   };
 
   // ---- this wave's fault
@@ -289,7 +289,7 @@ __global__ void __launch_bounds__(256) gemm_fi_small_kernel(const GemmArgs p) {
   if constexpr (MODE == SMALL_CAMPAIGN) {
     f = decode_fault(p, trial);
     owns = works && f.reaches(m0, n0);
-    if (clearing && owns) seen = __hip_atomic_load(p.cleared, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (clearing && owns) seen = __hip_atomic_load(p.clear_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (owns && f.kind == FI_SITE_PRODUCT) fetch_product_terms<DT>(f, p);
   }
   const int event = owns ? f.event : -1;
