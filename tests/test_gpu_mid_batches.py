@@ -25,12 +25,12 @@ def _faults(plan, n, operand):
 
 # (M, N, K, k-block), trials, every how many-th is an operand fault.  The first part ends 1 .. 8 trials into a group of
 # eight, so that the descriptors' padding holds a group of four or none, and either part may be empty; ragged tiles
-# and k-tiles, an odd number of k-tiles, the shortest K; the longest batch that one step of the partition kernel sees; two items per workgroup, several from the counters, and 64 or more, where
-# workgroups look into other XCDs' slices.
+# and k-tiles, an odd number of k-tiles, the shortest K; the longest batch that one step of the partition kernel sees; two
+# items per workgroup, several from the counters, and 64 or more (99000 trials), where workgroups look into other XCDs' slices.
 @pytest.mark.parametrize("shape,n,operand", [
     ((300, 300, 512, 32), 121, 0), ((300, 300, 512, 32), 124, 1), ((300, 300, 512, 32), 127, 5), ((320, 256, 512, 32), 260, 2),
     ((300, 300, 512, 32), 133, 132), ((129, 515, 464, 16), 205, 3), ((1000, 130, 320, 32), 119, 4),
-    ((250, 1000, 80, 16), 440, 3), ((600, 300, 192, 32), 900, 6), ((300, 300, 512, 32), 1024, 3), ((300, 300, 512, 32), 1025, 4), ((70, 60, 128, 32), 50001, 9),
+    ((250, 1000, 80, 16), 440, 3), ((600, 300, 192, 32), 900, 6), ((300, 300, 512, 32), 1024, 3), ((300, 300, 512, 32), 1025, 4), ((70, 60, 128, 32), 50001, 9), ((70, 60, 128, 32), 99000, 9),
 ])
 def test_mid_batches_equal_the_other_shapes(shape, n, operand):
     import torch
@@ -42,8 +42,10 @@ def test_mid_batches_equal_the_other_shapes(shape, n, operand):
     # SIMD than the small kernel takes
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     tiles = -(-M // 32) * -(-N // 32)
-    assert n * tiles * (K // 16) / (4 * cus) + 15 * (n + 3) // 4 * 4 * tiles / (4 * cus) > 550
+    assert n * tiles * (K // 16) / (4 * cus) + 15 * ((n + 3) // 4 * 4) * tiles / (4 * cus) > 550
     assert -(-M // 64) * -(-N // 64) * -(-n // 8) * -(-K // 64) <= 100 * 2 * cus and K > 64
+    if n == 99000:
+        assert -(-M // 64) * -(-N // 64) * (n // 4) / (3 * (cus // 8 * 8)) >= 64
     faults = _faults(plan, n, operand)
     want = gu.gpu_campaign(eight, faults, wl.CORRECT_RECOMPUTE)
     d_f = fi.to_device(faults)
