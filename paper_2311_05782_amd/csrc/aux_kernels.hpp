@@ -530,7 +530,7 @@ __global__ void __launch_bounds__(1024) partition_trials_kernel(const fi_fault* 
   }
   __syncthreads();
   // exclusive prefix sums of the buckets and of the per-thread counts, one entry per thread:
-  // a shuffle scan inside each wave, then one wave scans the 16 wave totals (three barriers)
+  // a scan inside each wave (wave_prefix), then one wave scans the 16 wave totals (three barriers)
   uint32_t pf = 0;                                       // long batches: fast trials before my chunk
   {
     __shared__ uint32_t wave_tot[16], wave_tot_c[16];

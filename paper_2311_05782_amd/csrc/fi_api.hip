@@ -259,21 +259,24 @@ int pick_prop(const fi_plan* p, uint32_t n_trials) {
 }
 
 // Items of four trials, both parts of the batch in one launch, in the place of the 64 x 64 shape's eight trials and two
-// launches.  Four share less, eight leave more of the chip without work at the end and take a launch
-// more (some 4 us), so four while
-//   rounds of that shape's resident workgroups * k-tiles <= 100.
-// From 2021 random batches of up to 27 rounds, all kinds and outputs, eight : four in the mean - up to one round 1.28, one to
-// four 1.17, K = 640 and eight to twelve rounds 1.04, K >= 2560 and twelve to 27 rounds 0.96 (512 x 3072 x 768, 4096
-// trials, 384 rounds 6.8 : 7.5 ms).  By this line 1.11 over all of them, 2.9 % over 3 % slower; 1.8 % from the better of the
-// two.  512 x 3072 x 768, 8 trials with outputs 43.9 : 34.7 us, 3136 x 64 x 576, 128 trials with outputs 56.4 : 47.9.  Not
+// launches.  Four share less, eight leave more of the chip without work at the end and take a launch more (some 4 us).
+// Stores of outputs are hidden better by three workgroups per CU than by two.  With outputs four while
+//   rounds of that shape's resident workgroups * k-tiles <= 100,
+// without them while there are no more than four rounds as well.  From random batches, all kinds, eight : four in the mean
+// and the share over 3 % slower with four: FP32 outputs (500 batches) 1.21, 1.8 %, 16-bit ones (500) 1.24, 2.4 %; beyond 100,
+// up to 500 (300 each), 1.10, 2.0 %, and 1.14, 2.3 %, not taken.  Without outputs (3326) up to 100: one round 1.21, 5 %; two 1.15,
+// 11 %; four 1.10, 11 %; four to six 1.07, 17 %; six to ten 1.04, 31 %; more 1.00, 44 %, where accumulator and product faults
+// lose 5 % in the mean, 59 x 1012 x 256, 5056 mixed trials 282 : 347 us and 64 x 2327 x 160, 2509 accumulator faults 123 : 136.
+// 512 x 3072 x 768, 8 trials with outputs 43.9 : 34.7 us, 3136 x 64 x 576, 128 trials with outputs 56.4 : 47.9.  Not
 // for K <= 64, whose items are handed out in turn: operand faults, 142 x 167 x 64, 7802 trials 190 : 294.
-constexpr uint64_t kFourWork = 100;
-bool use_four(const fi_plan* p, uint32_t n_trials) {
+constexpr uint64_t kFourWork = 100, kFourRounds = 4;
+bool use_four(const fi_plan* p, uint32_t n_trials, bool outputs) {
   const fi_plan_desc& d = p->d;
   if (!p->auto_cfg || p->mcfg != 3 || d.K <= 64) return false;
   const MultiCfg& m = kMulti[3];
   const uint64_t items = (uint64_t)((d.M + m.bm - 1) / m.bm) * ((d.N + m.bn - 1) / m.bn) * (((uint64_t)n_trials + m.r - 1) / m.r);
-  return items * ((d.K + 63) / 64) <= kFourWork * (uint64_t)m.wgs * (uint64_t)p->n_cus;
+  const uint64_t round = (uint64_t)m.wgs * (uint64_t)p->n_cus;
+  return items * ((d.K + 63) / 64) <= kFourWork * round && (outputs || items <= kFourRounds * round);
 }
 
 // Batches that gemm_fi_trial_kernel serves.
@@ -890,7 +893,7 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
   GemmArgs a = base_args(plan);
   const uint64_t blocks = (uint64_t)a.tiles_m * a.tiles_n * n_trials;
   if (blocks >= (1ull << 31)) return fail(FI_UNSUPPORTED, "tiles x trials exceeds 2^31 workgroups; split the batch");
-  const bool four = use_four(plan, n_trials);
+  const bool four = use_four(plan, n_trials, d_c_out != nullptr || d_h_out != nullptr);
   const MultiCfg mc = four ? fi::kMultiFour : kMulti[plan->mcfg >= 0 ? plan->mcfg : 0];
   GemmArgs m = a;
   uint64_t mblocks = 0;
@@ -1215,13 +1218,13 @@ fi_status fi_plan_describe(const fi_plan* plan, char* h_buf, uint64_t n) {
       snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, one trial per item, %dx%d, %d threads, persistent x%d per CU>%s", dt,
                m.bm, m.bn, m.wm * m.wn * 64, m.wgs, small);
     else {
-      char four[160] = "";
-      if (use_four(plan, 1)) {
-        const uint64_t each = (uint64_t)((plan->d.M + m.bm - 1) / m.bm) * ((plan->d.N + m.bn - 1) / m.bn) * ((plan->d.K + 63) / 64);
-        const uint64_t most = kFourWork * (uint64_t)m.wgs * (uint64_t)plan->n_cus / each * (uint64_t)m.r;
+      char four[192] = "";
+      if (use_four(plan, 1, true)) {
+        const uint64_t tiles = (uint64_t)((plan->d.M + m.bm - 1) / m.bm) * ((plan->d.N + m.bn - 1) / m.bn), round = (uint64_t)m.wgs * (uint64_t)plan->n_cus;
+        const uint64_t with = kFourWork * round / (tiles * ((plan->d.K + 63) / 64)), without = kFourRounds * round / tiles;
         const MultiCfg f = fi::kMultiFour;
-        snprintf(four, sizeof(four), "; at most %llu trials: gemm_fi_four_kernel<R=%d, x%d per CU, operand faults in the same launch>",
-                 (unsigned long long)most, f.r, f.wgs);
+        snprintf(four, sizeof(four), "; at most %llu trials, with outputs %llu: gemm_fi_four_kernel<R=%d, x%d per CU, operand faults in the same launch>",
+                 (unsigned long long)((without < with ? without : with) * (uint64_t)m.r), (unsigned long long)(with * (uint64_t)m.r), f.r, f.wgs);
       }
       snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, R=%d, %dx%d, %d threads, persistent x%d per CU> (a second, "
                "operand-patching instantiation for operand faults)%s%s", dt, m.r, m.bm, m.bn, m.wm * m.wn * 64, m.wgs, four, small);

@@ -1006,7 +1006,7 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) FI_MULTI
     // Deviation counters of the trials whose fault can reach an element this wave holds (rare):
     // the wave owning the element, or the waves holding its output row (A) / column (B).
     // Counts are sums of lane masks (ballot + popcount: no cross-lane traffic); the two maxima
-    // of all trials are reduced together at the end, so the shuffles' latencies overlap.
+    // are reduced at the end, trial by trial (wave_max).
     if (owned == 0) return;
     float mxp[R], mxq[R];                                   // per lane: largest deviation before / after correction
     static_for<R>([&](auto rr) { mxp[rr] = 0.0f; mxq[rr] = 0.0f; });
