@@ -646,7 +646,7 @@ fi_status batch_scratch(fi_plan* p, hipStream_t stream, uint32_t n, BatchScratch
   size_t parts = want_parts ? parts_words(p->d, n) : 0;
   if (b->cap < n) {
     if (b->own) {
-      if (b->parts == b->words + scratch_words(b->cap)) {   // in that allocation: what was reserved stays so
+      if (!b->parts_own && b->parts == b->words + scratch_words(b->cap)) {   // in that allocation: what was reserved stays so
         if (parts < b->parts_cap) parts = b->parts_cap;
         b->parts = nullptr; b->parts_cap = 0;
       }

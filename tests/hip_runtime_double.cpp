@@ -22,6 +22,7 @@ struct Launch { std::string name; uintptr_t stream; std::vector<uint64_t> words;
 std::vector<Launch> launches;
 int device = 0, n_devices = 2, waited[8] = {};
 size_t in_use = 0, capacity = SIZE_MAX;
+char* packed = nullptr;                    // where the next block lies, right behind the last one; blocks of then are never used again
 int host_blocks = 0;
 long unsafe_calls = 0;                     // allocations, frees and waits that would break a capture
 bool set_device_fails = false, get_device_fails = false, wait_fails = false;
@@ -35,6 +36,7 @@ void touches() { if (!capturing.empty() && mode != hipStreamCaptureModeRelaxed) 
 
 extern "C" {
 // ---- for the test
+void double_packed() { packed = static_cast<char*>(aligned_alloc(4096, 64u << 20)); }
 void double_capacity(uint64_t bytes) { capacity = bytes; }
 uint64_t double_in_use() { return in_use; }
 uint64_t double_blocks() { return live.size(); }
@@ -89,7 +91,12 @@ hipError_t hipMalloc(void** p, size_t n) {
   std::lock_guard<std::mutex> lock(mu);
   touches();
   if (in_use + n > capacity) return hipErrorOutOfMemory;
-  *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);
+  if (packed) {
+    *p = packed;
+    packed += (n + 255) / 256 * 256;
+  } else {
+    *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);
+  }
   memset(*p, 0, n);
   live[reinterpret_cast<uintptr_t>(*p)] = {n, device};
   in_use += n;
@@ -103,7 +110,7 @@ hipError_t hipFree(void* p) {
   in_use -= it->second.bytes;
   live.erase(it);
   freed.push_back(reinterpret_cast<uintptr_t>(p));
-  free(p);
+  if (!packed) free(p);
   return hipSuccess;
 }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { touches(); *p = calloc(1, n); ++host_blocks; return hipSuccess; }

@@ -85,6 +85,23 @@ def test_a_larger_batch_keeps_the_parts(first_stream, order):
     """ % ("None" if first_stream else "SIDE", order != "reserve"))
 
 
+# Parts in an allocation of their own that happens to lie right behind the scratch are not taken for a part of it.
+def test_parts_right_behind_the_scratch_are_given_back():
+    host_double.run("""
+    D.double_packed()
+    plan = create(512, 3072, 768)
+    inject(plan, 1, OTHER)
+    assert inject(plan, 1000, SIDE) == 0 and reserve(plan, 1000, SIDE) == 0
+    for n in (1500, 3000):
+        assert inject(plan, n, SIDE) == 0
+        D.double_forget()
+        assert affected(plan, 1000, SIDE) == 0
+        assert parts_used()
+    L.fi_plan_destroy(plan)
+    assert D.double_blocks() == 1
+    """)
+
+
 # No room for the parts: the batch has its scratch all the same.
 def test_a_larger_batch_without_memory_for_the_parts():
     host_double.run("""
