@@ -29,8 +29,10 @@
  *     synchronises, so device-side failures surface at the caller's next
  *     synchronising call.
  *   - A plan may have batches in flight on several streams at once (each
- *     stream has its own scratch; at most 64 streams per plan).  Calls on one
- *     plan are not thread-safe: serialise them on the host.
+ *     stream has its own scratch; at most 64 streams per plan).  Streams are
+ *     told apart by their handles: what a plan's calls have enqueued on one has
+ *     run before it is destroyed, as the next stream may get the same handle.
+ *     Calls on one plan are not thread-safe: serialise them on the host.
  *   - Every function returns an fi_status; on failure output parameters are
  *     untouched and fi_last_error() describes the problem.  Nothing throws or
  *     aborts across this boundary.
