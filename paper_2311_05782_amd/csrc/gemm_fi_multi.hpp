@@ -643,8 +643,9 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) FI_MULTI
       return T;
     };
     // What `detect` compares with.  HAVE_T: a little less than the column's part of the thresholds, where no product on
-    // the way leaves the normal range (then T is at least 1 - 2^-22 times the exact product), else 0, and row factors of
-    // Inf beyond the problem.  Else the smallest row factor of this lane's rows of each tile row.
+    // the way leaves the normal range (then T is at least 1 - 2^-22 times the exact product), else 0.  Else the smallest
+    // row factor of this lane's rows of each tile row, beyond the problem Inf.
+    const bool ordered = (HAVE_T || R > 1) && (p.bound_global || p.normal);   // no threshold is a NaN
     float kra_least[TM], cb_of[TN];
     static_for<TN>([&](auto jj) {
       constexpr int j = jj;
@@ -653,13 +654,7 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) FI_MULTI
     static_for<TM>([&](auto ii) {
       constexpr int i = ii;
       kra_least[i] = 0.0f;
-      if constexpr (HAVE_T) {
-        if (ragged) {
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-            kra4[i][v >> 2][v & 3] = row_base + 32 * i + 8 * (v >> 2) + (v & 3) < p.M ? kra4[i][v >> 2][v & 3] : __builtin_inff();
-        }
-      } else {
+      if constexpr (!HAVE_T) {
         f32x4 least = {__builtin_inff(), __builtin_inff(), __builtin_inff(), __builtin_inff()};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -725,8 +720,11 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) FI_MULTI
         const int col = col_base + 32 * j;
         // Nearly always nothing is flagged, which a comparison with a little less than the thresholds shows: the excess
         // of the largest magnitude of a row's R elements over it in one instruction, of all rows the largest
-        // (v_maximum3_f32 takes two values an instruction, and a NaN outweighs all).  A threshold of 0 or NaN does not
-        // pass.  Without the row factors in registers the three roundings, which are monotonous, of the smallest one.
+        // (v_maximum3_f32 takes two values an instruction, and a NaN outweighs all).  Rows beyond the problem hold zeros
+        // and factors of 0 and pass, as does whatever equals the threshold; where a threshold may be a NaN (a factor of
+        // Inf by one of 0) only what is below it.  (Factors of Inf for those rows and a second look at every tile that does
+        // not pass: 18 x 1241 x 128, 6857 A faults 746 us, now 683; 903 x 36 x 32, 13722 B faults 1187 and 1066.)  Without
+        // the row factors in registers the three roundings, which are monotonous, of the smallest one.
         uint64_t some;
         if (!HAVE_T || p.bound_global) {
           float top = 0.0f;
@@ -736,26 +734,30 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) FI_MULTI
             for (int v = 0; v < 16; ++v) top = __builtin_elementwise_maximum(top, fabsf(acc[r][i][j][v]));
           });
           const float least = p.bound_global ? p.t_global : __fmul_rn(__fmul_rn(kra_least[i], cb_of[j]), p.gamma);
-          some = __ballot(!(top < least));
+          some = ordered ? __ballot(!(top <= least)) : __ballot(!(top < least));
         } else {
           float excess = -__builtin_inff();
 #pragma unroll
           for (int v = 0; v < 16; ++v)
             excess = __builtin_elementwise_maximum(excess, __fmaf_rn(-kra4[i][v >> 2][v & 3], cb_of[j], largest(tt, v)));
-          some = __ballot(!(excess < 0.0f));
+          some = ordered ? __ballot(!(excess <= 0.0f)) : __ballot(!(excess < 0.0f));
         }
         if (!OUT && some == 0) return;
         f32x16 T = {};
         if (some != 0) {
-          // Row by row: the excess of the largest magnitude over T (a difference has the sign that the comparison
-          // says, subnormals being kept), of which again the largest.
           beyond = true;
           T = thresholds(tt);
-          float excess = -__builtin_inff();
+          // A value above that (or a NaN) is nearly always flagged where that is close to the thresholds.  Else row by row: the
+          // excess of the largest magnitude over T (a difference has the sign that the comparison says, subnormals being
+          // kept), of which again the largest.
+          const bool close = R > 1 && (p.bound_global || (HAVE_T && p.normal));
+          if (!close) {
+            float excess = -__builtin_inff();
 #pragma unroll
-          for (int v = 0; v < 16; ++v) excess = __builtin_elementwise_maximum(excess, __fsub_rn(largest(tt, v), T[v]));
-          some = __ballot(!(excess <= 0.0f));
-          if (!OUT && some == 0) return;
+            for (int v = 0; v < 16; ++v) excess = __builtin_elementwise_maximum(excess, __fsub_rn(largest(tt, v), T[v]));
+            some = __ballot(!(excess <= 0.0f));
+            if (!OUT && some == 0) return;
+          }
         }
         static_for<R>([&](auto rr) {
           constexpr int r = rr;
