@@ -175,8 +175,8 @@ fi_status fi_plan_buffer(const fi_plan* plan, uint32_t which, const void** d_ptr
  *         alone and the operand-fault trials; the latter run in a second instantiation that
  *         XORs the faulted word in the fragment registers around the faulted trial's MFMAs.
  * While no tile_config has been chosen, batches of problems below 2^35 multiply-adds that fill the chip a few times run
- * items of four trials of a 64x64 tile, the operand faults in the same launch (K > 64; the numbers of trials,
- * without outputs and with, are in fi_plan_describe), and batches too small to fill the chip run one wave per
+ * items of four trials of a 64x64 tile, the operand faults in the same launch, or of larger batches the operand faults
+ * alone (K > 64; the numbers of trials are in fi_plan_describe), and batches too small to fill the chip run one wave per
  * (trial, 32x32 tile) instead (every fault kind, any K; at most as many trials as fi_plan_describe says, fewer where K is short),
  * and those of the smallest problems one workgroup per trial.
  * trial_group: -1 keep, else how many trials (groups of R trials) of the same

@@ -262,14 +262,17 @@ int pick_prop(const fi_plan* p, uint32_t n_trials) {
 // launches.  Four share less, eight leave more of the chip without work at the end and take a launch more (some 4 us).
 // Stores of outputs are hidden better by three workgroups per CU than by two.  With outputs four while
 //   rounds of that shape's resident workgroups * k-tiles <= 100,
-// without them while there are no more than four rounds as well.  From random batches, all kinds, eight : four in the mean
+// without them while there are no more than six rounds as well.  From random batches, all kinds, eight : four in the mean
 // and the share over 3 % slower with four: FP32 outputs (500 batches) 1.21, 1.8 %, 16-bit ones (500) 1.24, 2.4 %; beyond 100,
 // up to 500 (300 each), 1.10, 2.0 %, and 1.14, 2.3 %, not taken.  Without outputs (3326) up to 100: one round 1.21, 5 %; two 1.15,
-// 11 %; four 1.10, 11 %; four to six 1.07, 17 %; six to ten 1.04, 31 %; more 1.00, 44 %, where accumulator and product faults
-// lose 5 % in the mean, 59 x 1012 x 256, 5056 mixed trials 282 : 347 us and 64 x 2327 x 160, 2509 accumulator faults 123 : 136.
+// 11 %; four 1.10, 11 %.  Further (700) by kind - accumulator and product, A, B faults, mixed: four to six rounds 0.99, 1.04, 1.06,
+// 1.10; six to ten 0.97, 1.04, 1.06, 1.09; ten to twenty 0.96, 1.02, 1.03, 1.03; up to fifty 0.92, 1.06, 1.02, 0.92 (59 x 1012 x 256,
+// 5056 mixed trials 282 : 347 us).  Beyond six rounds, up to 100, the operand faults alone therefore, whose accounting three
+// workgroups per CU hide better as well, the others in eights; against eights for both 1.00, 1.02, 1.03, 1.03 in the mean of
+// these batches.
 // 512 x 3072 x 768, 8 trials with outputs 43.9 : 34.7 us, 3136 x 64 x 576, 128 trials with outputs 56.4 : 47.9.  Not
 // for K <= 64, whose items are handed out in turn: operand faults, 142 x 167 x 64, 7802 trials 190 : 294.
-constexpr uint64_t kFourWork = 100, kFourRounds = 4;
+constexpr uint64_t kFourWork = 100, kFourRounds = 6;
 bool use_four(const fi_plan* p, uint32_t n_trials, bool outputs) {
   const fi_plan_desc& d = p->d;
   if (!p->auto_cfg || p->mcfg != 3 || d.K <= 64) return false;
@@ -278,6 +281,8 @@ bool use_four(const fi_plan* p, uint32_t n_trials, bool outputs) {
   const uint64_t round = (uint64_t)m.wgs * (uint64_t)p->n_cus;
   return items * ((d.K + 63) / 64) <= kFourWork * round && (outputs || items <= kFourRounds * round);
 }
+// The second part alone.
+bool use_four_apart(const fi_plan* p, uint32_t n_trials, bool outputs) { return !use_four(p, n_trials, outputs) && use_four(p, n_trials, true); }
 
 // Batches that gemm_fi_trial_kernel serves.
 bool use_trial(const fi_plan* p, uint32_t n_trials, bool c_out, bool h_out) {
@@ -894,6 +899,7 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
   const uint64_t blocks = (uint64_t)a.tiles_m * a.tiles_n * n_trials;
   if (blocks >= (1ull << 31)) return fail(FI_UNSUPPORTED, "tiles x trials exceeds 2^31 workgroups; split the batch");
   const bool four = use_four(plan, n_trials, d_c_out != nullptr || d_h_out != nullptr);
+  const bool apart = use_four_apart(plan, n_trials, d_c_out != nullptr || d_h_out != nullptr);
   const MultiCfg mc = four ? fi::kMultiFour : kMulti[plan->mcfg >= 0 ? plan->mcfg : 0];
   GemmArgs m = a;
   uint64_t mblocks = 0;
@@ -973,7 +979,13 @@ fi_status inject_batch(fi_plan* plan, const fi_fault* d_faults, uint32_t n_trial
   m.part_counts = ts.counts;
   m.desc = ts.desc;
   if (m.K >= 128) m.queue = ts.queue;
+  m.operands_apart = apart;
   FI_HIP(launch_multi((int)plan->d.dtype, four ? fi::kMultiFourInst : plan->mcfg, m, (int)mblocks, s));
+  if (!apart) return FI_OK;
+  if (m.queue) m.queue += fi::kQueueWords;
+  if (m.clocks) m.clocks += 4;
+  const int fours = plan->n_cus / 8 * 8 * fi::kMultiFour.wgs;
+  FI_HIP(launch_multi((int)plan->d.dtype, fi::kMultiFourInst, m, fours, s));
   return FI_OK;
 }
 
@@ -1218,12 +1230,12 @@ fi_status fi_plan_describe(const fi_plan* plan, char* h_buf, uint64_t n) {
       snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, one trial per item, %dx%d, %d threads, persistent x%d per CU>%s", dt,
                m.bm, m.bn, m.wm * m.wn * 64, m.wgs, small);
     else {
-      char four[192] = "";
+      char four[224] = "";
       if (use_four(plan, 1, true)) {
         const uint64_t tiles = (uint64_t)((plan->d.M + m.bm - 1) / m.bm) * ((plan->d.N + m.bn - 1) / m.bn), round = (uint64_t)m.wgs * (uint64_t)plan->n_cus;
         const uint64_t with = kFourWork * round / (tiles * ((plan->d.K + 63) / 64)), without = kFourRounds * round / tiles;
         const MultiCfg f = fi::kMultiFour;
-        snprintf(four, sizeof(four), "; at most %llu trials, with outputs %llu: gemm_fi_four_kernel<R=%d, x%d per CU, operand faults in the same launch>",
+        snprintf(four, sizeof(four), "; at most %llu trials, operand faults and batches with outputs %llu: gemm_fi_four_kernel<R=%d, x%d per CU>",
                  (unsigned long long)((without < with ? without : with) * (uint64_t)m.r), (unsigned long long)(with * (uint64_t)m.r), f.r, f.wgs);
       }
       snprintf(h_buf, n, "gemm_fi_multi_kernel<%s, R=%d, %dx%d, %d threads, persistent x%d per CU> (a second, "

@@ -86,6 +86,7 @@ struct GemmArgs {
   // part, see gemm_fi_multi.hpp.
   const uint32_t* part_counts;
   const uint32_t* desc;
+  int operands_apart;       // the second part runs in items of four, in a launch of its own, which takes nothing else
   uint64_t a_trial_stride;  // PROPAGATE: trial t reads A + t * a_trial_stride (elements)
   // Multi-trial kernel, nullable (then its workgroups walk their items with the grid as stride): what
   // the workgroups of an XCD have taken of its slice of the work list, kQueueStride words per XCD; zero at

@@ -179,10 +179,11 @@ __global__ void __launch_bounds__(WM* WN * 64, VAR == VAR_BOTH ? 3 : 2) FI_MULTI
 
   // ---- work list: n_tiles x ceil(n_fast / R) items
   // OPS: the second part of the batch; its descriptors follow the first part's, padded to 8.  BOTH: the groups of
-  // that padding hold no trial and are left out.
-  const int n_fast = PROP ? p.n_trials : (int)p.part_counts[OPS && !BOTH ? 1 : 0];
+  // that padding hold no trial and are left out, as is the whole first part where it has a launch of its own.
+  const bool second = OPS && (!BOTH || p.operands_apart != 0);
+  const int n_fast = PROP ? p.n_trials : BOTH && second ? 0 : (int)p.part_counts[second ? 1 : 0];
   const uint32_t* const desc =
-      PROP ? nullptr : p.desc + (OPS && !BOTH ? (size_t)((p.part_counts[0] + 7u) & ~7u) * kMultiDescWords : 0);
+      PROP ? nullptr : p.desc + (second ? (size_t)((p.part_counts[0] + 7u) & ~7u) * kMultiDescWords : 0);
   static_assert(!BOTH || 8 % R == 0, "the second part starts at a group");
   const int n_slow = BOTH ? (int)p.part_counts[1] : 0;
   const int fast_groups = (n_fast + R - 1) / R, n_groups = fast_groups + (n_slow + R - 1) / R;

@@ -52,13 +52,14 @@ hipError_t FI_NAME(launch_multi_d, FI_INST_DT, 6)(const GemmArgs& a, int n_block
 #else
 // Two launches: the plain instantiation on the first part of the batch (no fault, accumulator
 // flips, product-term faults), the operand-patching one on the second part (operand faults).
-// Each finds its trial count on the device and exits at once if it is zero.
+// Each finds its trial count on the device and exits at once if it is zero.  Where the second part runs in fours the caller
+// launches that.
 hipError_t FI_NAME(launch_multi_d, FI_INST_DT, FI_INST_CFG)(const GemmArgs& a, int n_blocks, hipStream_t s) {
   constexpr MultiCfg c = kMulti[FI_INST_CFG];
   hipLaunchKernelGGL((gemm_fi_multi_kernel<FI_INST_DT, c.r, c.bm, c.bn, c.wm, c.wn, VAR_PLAIN>), dim3(n_blocks),
                      dim3(c.wm * c.wn * 64), 0, s, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || a.operands_apart) return e;
   hipLaunchKernelGGL((gemm_fi_multi_kernel<FI_INST_DT, c.r, c.bm, c.bn, c.wm, c.wn, VAR_OPERAND>), dim3(n_blocks),
                      dim3(c.wm * c.wn * 64), 0, s, a);
   return hipGetLastError();

@@ -26,11 +26,12 @@ def _faults(plan, n, operand):
 # (M, N, K, k-block), trials, every how many-th is an operand fault.  The first part ends 1 .. 8 trials into a group of
 # eight, so that the descriptors' padding holds a group of four or none, and either part may be empty; ragged tiles
 # and k-tiles, an odd number of k-tiles, the shortest K; the longest batch that one step of the partition kernel sees; two
-# items per workgroup, several from the counters, and 64 or more (99000 trials), where workgroups look into other XCDs' slices.
+# items per workgroup, several from the counters, more than six rounds of eights, of which only the operand faults (some, none,
+# all) run in fours, and 64 or more (99000 trials), where workgroups look into other XCDs' slices.
 @pytest.mark.parametrize("shape,n,operand", [
     ((300, 300, 512, 32), 121, 0), ((300, 300, 512, 32), 124, 1), ((300, 300, 512, 32), 127, 5), ((320, 256, 512, 32), 260, 2),
     ((300, 300, 512, 32), 133, 132), ((129, 515, 464, 16), 205, 3), ((1000, 130, 320, 32), 119, 4),
-    ((250, 1000, 80, 16), 440, 3), ((600, 300, 192, 32), 900, 6), ((300, 300, 512, 32), 1024, 3), ((300, 300, 512, 32), 1025, 4), ((70, 60, 128, 32), 50001, 9), ((70, 60, 128, 32), 99000, 9),
+    ((250, 1000, 80, 16), 440, 3), ((600, 300, 192, 32), 900, 6), ((600, 300, 192, 32), 901, 0), ((600, 300, 192, 32), 905, 1), ((300, 300, 512, 32), 1024, 3), ((300, 300, 512, 32), 1025, 4), ((70, 60, 128, 32), 50001, 9), ((70, 60, 128, 32), 99000, 9),
 ])
 def test_mid_batches_equal_the_other_shapes(shape, n, operand):
     import torch
@@ -61,7 +62,7 @@ def test_mid_batches_equal_the_other_shapes(shape, n, operand):
             p.fi_gemm_inject_batch_act(d_f, n, wl.CORRECT_ZERO, d_r, d_h)
             outs.append((fi.results_to_host(d_r).tobytes(), d_h))
         assert outs[0][0] == outs[1][0] and torch.equal(outs[0][1], outs[1][1])
-    with_half_outputs()                                   # without outputs the larger batches run eight an item
+    with_half_outputs()                                   # without outputs the larger batches run in two launches
     if n < 1000:
         one = gu.make_plan(Aw, Bw, kb, fmt, cfg=2)
         r1, c1 = gu.gpu_campaign(one, faults, wl.CORRECT_ZERO, want_c=True)
