@@ -27,9 +27,9 @@ MFMA_PEAK_TFLOPS = 2516.6     # 256 CUs x 4096 flop/clk/CU x 2.4 GHz, dense FP16
 # commands.  They describe the kernel sources whose digest is recorded with them and are not
 # reported for any other.
 TRAFFIC = {
-    "sources_sha256": "b2184b6c0534b46d9978eb063376933c3baeb3abf2b4ac7036e5e04bd203ba3a",
-    "fetch_bytes": 2.232028e6 * 2.0 * 1024,
-    "write_bytes": 8430.312 * 1.0 * 1024,
+    "sources_sha256": "50872ca1a0b42407b3ca1b316825b18dd73f7a46a6bf27947c9736252a702861",
+    "fetch_bytes": 2.198885e6 * 2.0 * 1024,
+    "write_bytes": 8393.344 * 1.0 * 1024,
 }
 
 
